@@ -672,6 +672,10 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
       if (x->discarded) HIPCHK(hipStreamWaitEvent(c->ins, x->ev_fetched, 0));
       if (c->resolved_once) HIPCHK(hipStreamWaitEvent(c->ins, c->ev_resolved, 0));
     }
+  } else if (x->discarded && c->side != c->st) {
+    // lookahead 0: a step that was given up without a lookup left nothing on the main stream that
+    // waits for its copies, which may still be reading the lists that this prepare rewrites
+    HIPCHK(hipStreamWaitEvent(s, x->ev_fetched, 0));
   }
   hipStream_t su = c->ins ? c->ins : s;          // stream of the unique passes
   c->t += 1;

@@ -447,3 +447,24 @@ def test_discard_frees_a_step_that_was_only_read():
     assert e.value.code == sfc.SFC_ESTATE
     assert c.verify() == [0, 0, 0, 0]
     p.close()
+
+
+def test_steps_given_up_without_a_lookup_still_bring_their_rows():
+    # lookahead 0, copies on a stream of their own: nothing on the main stream waits for the copies of
+    # a step that is discarded before its lookup, and the next prepare rewrites the lists they read
+    V, D, n = 400_000, 64, 60_000
+    p = Pair(V, D, C=150_000, max_ids=n)
+    c = p.cache
+    ids = [torch.from_numpy(np.random.default_rng(t).permutation(V)[:n]).to(p.dev) for t in range(8)]
+    for t in range(24):
+        c.prepare(ids[t % 8]); c.fetch_misses()
+        if t < 23:
+            c.discard()
+    out = c.lookup()
+    want = p.table.w_t[ids[7].cpu()]
+    assert torch.equal(out.cpu(), want)
+    c.discard()
+    assert c.verify() == [0, 0, 0, 0]
+    c.flush()
+    assert np.array_equal(p.table.w, p.ow) and np.array_equal(p.table.acc, p.oa)
+    p.close()
