@@ -144,6 +144,7 @@ struct sfc_cache {
   int* hslot = nullptr;                         // [max_ids]
   int* vid_hslot = nullptr;                     // [max_ids]
   int* blk_cnt = nullptr;                       // [max_ids / kPosChunk + 1]
+  unsigned char* first = nullptr;               // [max_ids / 8 + ..] bit per position: first appearance of its id
   int *tile_lt = nullptr, *tile_eq = nullptr;   // [C / kPosChunk + 1]
   int* tile_miss = nullptr;                     // [max_ids / kVidTile + 1]
   // positions per virtual id [max_ids] and its copies for the lowest virtual ids [kHotRep, kHotBins]:
@@ -560,6 +561,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     if ((rc = dalloc(c, &c->hslot, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->vid_hslot, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->blk_cnt, c->max_ids / kPosChunk + 2))) goto bad;
+    if ((rc = dalloc(c, &c->first, (c->max_ids / kPosChunk + 1) * (kPosChunk / 8)))) goto bad;
     if ((rc = dalloc(c, &c->tile_lt, c->C / kPosChunk + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_eq, c->C / kPosChunk + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_miss, c->max_ids / kVidTile + 2))) goto bad;
@@ -693,6 +695,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   uint32_t hu = (uint32_t)(2 * n_ids);
   if (hu < 64) hu = 64;                       // the batch table is empty between steps: any size works
   const int nchunk = (n + kPosChunk - 1) / kPosChunk;
+  const SortGeom sg = sort_geom(n);
   if (n > 0) {
     const int nub = (n + kUniqChunk - 1) / kUniqChunk, head = nub < kHeadBlocks ? nub : kHeadBlocks;
     hipLaunchKernelGGL(k_uniq_insert, dim3(head), dim3(256), 0, su, d_ids, n, c->V, c->utab, hu,
@@ -700,11 +703,13 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     if (nub > head)
       hipLaunchKernelGGL(k_uniq_insert, dim3(nub - head), dim3(256), 0, su, d_ids, n, c->V, c->utab,
                          hu, c->hslot, c->n_invalid, head);
-    hipLaunchKernelGGL(k_uniq_count, dim3(nchunk), dim3(256), 0, su, c->hslot, c->utab, n, c->blk_cnt);
-    hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk), dim3(256), 0, su, c->hslot, c->utab, n,
+    hipLaunchKernelGGL(k_uniq_count, dim3(nchunk), dim3(256), 0, su, c->hslot, c->utab, n, c->first, c->blk_cnt);
+    hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk), dim3(256), 0, su, d_ids, c->V, c->hslot, c->first, n,
                        c->blk_cnt, d_unique_ids, c->uvid, c->vid_hslot, cnt, c->n_unique);
-    hipLaunchKernelGGL(k_uniq_inverse, dim3((n + kSortChunk - 1) / kSortChunk), dim3(256), 0, su,
-                       c->hslot, c->uvid, n, d_inverse, cnt, cnt_rep, x->pos_slot);
+    auto inv = sg.threads == 256 ? k_uniq_inverse<kFewBins, 4, 256>
+             : sg.threads == 512 ? k_uniq_inverse<kHotBins, 8, 512> : k_uniq_inverse<kHotBins, 8, 1024>;
+    hipLaunchKernelGGL(inv, dim3(sg.blocks), dim3(sg.threads), 0, su, c->hslot, c->uvid, n, d_inverse, cnt,
+                       cnt_rep, sg.nrep, x->pos_slot);
   } else {
     fill<int>(su, c->n_unique, 1, 0);
   }
@@ -720,10 +725,10 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                        c->n_unique, c->n_invalid, c->index, c->hi, x->t);
     hipLaunchKernelGGL(k_index_refill, dim3(kRebuildGrid), dim3(256), 0, s, c->index, c->hi, c->slot_id, x->ctr);
   }
-  const int gr = grid_for(n, 4 * kVidTile, kResolveGrid);
+  const int gr = grid_for(n, kVidTile, kResolveGrid);
   hipLaunchKernelGGL(k_resolve, dim3(gr), dim3(256), 0, s, d_unique_ids, c->vid_hslot, c->utab,
                      c->index, c->hi, c->dmap, c->stamp, c->hist, x->t, d_slot, c->tile_miss, cnt, cnt_rep,
-                     c->tile_cnt, c->age_hist, x->ctr, c->dmap ? (const Ctr*)prev->ctr : (const Ctr*)nullptr,
+                     sg.bins, sg.nrep, c->tile_cnt, c->age_hist, x->ctr, c->dmap ? (const Ctr*)prev->ctr : (const Ctr*)nullptr,
                      (const int*)c->n_unique, c->n_invalid);
   if (c->ins) { HIPCHK(hipEventRecord(c->ev_resolved, s)); c->resolved_once = true; }
   // (after the resolve: it tallies into the step's counters, which that kernel may have started)
@@ -743,14 +748,17 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     hipLaunchKernelGGL(k_victim_unmap, dim3(gv), dim3(256), 0, s, x->victim_id, c->index, c->hi,
                        x->ctr);
   hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, d_unique_ids, cnt, cnt_rep,
-                     c->cur_rep, c->tile_cnt,
+                     c->cur_rep, sg.bins, sg.nrep, c->tile_cnt,
                      c->grp, x->cold_pay, c->tile_miss, x->victim_slot, d_slot, d_miss_vids, x->miss_row,
                      x->miss_id, x->boff, c->slot_id,
                      c->stamp, c->index, c->hi, c->dmap, x->t, (int)c->C, c->tile_reuse, x->ctr);
-  if (n > 0)
-    hipLaunchKernelGGL(k_scatter, dim3((n + kSortChunk - 1) / kSortChunk), dim3(256), 0, s, d_inverse,
-                       d_offsets ? c->pos2bag : (const int*)nullptr, n, c->grp, (int*)x->cold_pay, c->cur_rep,
-                       x->perm64, d_slot, x->pos_slot, (int)c->C, x->boff, (int)n_bags);
+  if (n > 0) {
+    auto scat = sg.threads == 256 ? k_scatter<4, 256> : sg.threads == 512 ? k_scatter<8, 512> : k_scatter<8, 1024>;
+    hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.threads), 0, s, d_inverse,
+                       d_offsets ? c->pos2bag : (const int*)nullptr, n, c->grp, (int*)x->cold_pay,
+                       (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
+                       (const int*)d_slot, x->pos_slot, (int)c->C, x->boff, (int)n_bags);
+  }
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_PREPARE, s, &ep))) return rc;
   HIPCHK(hipEventRecord(x->ev_prepared, s));

@@ -16,8 +16,6 @@ namespace sfc {
 
 constexpr int kPosChunk = 2048;   // positions (or slots) per block in the scan passes
 constexpr int kVidTile = 256;     // virtual ids per tile in resolve / assign
-constexpr int kSortPer = 16;      // positions per thread in the count / group passes (8 and 32 measured slower)
-constexpr int kSortChunk = 256 * kSortPer;
 
 // ---------------------------------------------------------------------------------------------
 // VSI pass 1: insert every position's id into the batch table (open addressing, linear probing,
@@ -35,8 +33,11 @@ constexpr int kSortChunk = 256 * kSortPer;
 // through the claim / re-read / minimum atomics on one address (thousands in a row, about 10 ns
 // each); after the head of the batch has been inserted the frequent keys are in the table with
 // a smaller position than any later block holds, and the plain load settles them.
-// hslot[p] = HBM table entry of position p; bit 31 marks the one position per (block, key) that
-// can still be the key's first appearance, so the later passes test only those.
+// hslot[p] = HBM table entry of position p; bit 31 marks the positions that can still be their key's
+// first appearance, so the later passes test only those: at most one per (block, key), and only
+// where the block found no smaller position in the table.  (With every block's own first marked the
+// pass behind this one had several random reads for each unique id instead of about one: 14 against
+// 11 us at 65536 x 39 positions, 65 against 31 at 8.9e6 in bags.)
 // ---------------------------------------------------------------------------------------------
 constexpr int kUniqChunk = 512;    // positions per block (2048 with its 53 KB of LDS left 12 wavefronts per compute unit: 20 us slower)
 constexpr int kUniqPer = kUniqChunk / 256;
@@ -167,10 +168,14 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (e[u] < 0) continue;
-      if (m0[u] > pm[u] && m1[u] > pm[u]) atomicMin(&utab[h[u]].minpos, pm[u]);
       lval[e[u]] = (int)h[u];
-      const int q = pm[u] - base;
-      atomicOr(&cand[q >> 5], 1u << (q & 31));
+      // A smaller position is in the table already: this block's is not the key's first appearance
+      // (both words read can be too large, never too small), so the later passes need not look.
+      if (m0[u] > pm[u] && m1[u] > pm[u]) {
+        atomicMin(&utab[h[u]].minpos, pm[u]);
+        const int q = pm[u] - base;
+        atomicOr(&cand[q >> 5], 1u << (q & 31));
+      }
     }
   }
   __syncthreads();
@@ -205,22 +210,23 @@ __device__ __forceinline__ void index_reinsert(IdxEntry* index, uint32_t hi,
   }
 }
 
-// VSI pass 2: per chunk of positions, how many are the first appearance of their id.
+// VSI pass 2: which positions are the first appearance of their id, eight per byte, and how many of
+// them each chunk of positions has.  (The pass behind this one then needs no look at the table of its
+// own: its random reads were half of its time.)
 __global__ __launch_bounds__(256) void k_uniq_count(const int* __restrict__ hslot,
                                                      const UEntry* __restrict__ utab, int n,
+                                                     unsigned char* __restrict__ first,
                                                      int* __restrict__ blk_cnt) {
   __shared__ int smem[20];
   const int base = blockIdx.x * kPosChunk + (int)threadIdx.x * 8;
-  int c = 0;
+  unsigned hs[8], flags = 0;
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int p = base + j;
-    if (p < n) {
-      const unsigned hs = (unsigned)hslot[p];
-      if ((hs & kCandBit) && utab[hs & ~kCandBit].minpos == p) ++c;
-    }
-  }
-  const int tot = block_sum(c, smem);
+  for (int j = 0; j < 8; ++j) hs[j] = base + j < n ? (unsigned)hslot[base + j] : 0u;
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    if ((hs[j] & kCandBit) && utab[hs[j] & ~kCandBit].minpos == base + j) flags |= 1u << j;
+  first[blockIdx.x * 256 + threadIdx.x] = (unsigned char)flags;
+  const int tot = block_sum(__popc(flags), smem);
   if (threadIdx.x == 0) blk_cnt[blockIdx.x] = tot;
 }
 
@@ -267,39 +273,33 @@ __global__ __launch_bounds__(256) void k_index_refill(IdxEntry* index, uint32_t 
 // before it, which every block adds up for itself (a few loads per thread from a list that sits in
 // L2: cheaper than a scan kernel between the two passes).  The last chunk leaves the number of
 // unique ids in *n_unique for k_ctr_init.
-__global__ __launch_bounds__(256) void k_uniq_assign(const int* __restrict__ hslot,
-                                                      const UEntry* __restrict__ utab, int n,
+__global__ __launch_bounds__(256) void k_uniq_assign(const int64_t* __restrict__ ids, int64_t V,
+                                                      const int* __restrict__ hslot,
+                                                      const unsigned char* __restrict__ first, int n,
                                                       const int* __restrict__ blk_cnt,
                                                       int64_t* __restrict__ unique_ids,
                                                       int* __restrict__ uvid,
                                                       int* __restrict__ vid_hslot,
                                                       int* __restrict__ cnt, int* n_unique) {
   __shared__ int smem[20];
+  const unsigned flags = first[blockIdx.x * 256 + threadIdx.x];
   int before = 0;
   for (int i = (int)threadIdx.x; i < (int)blockIdx.x; i += 256) before += blk_cnt[i];
-  before = block_sum(before, smem);
+  // the flagged positions' ids and table entries: on their way while the block adds up its counts
   const int base = blockIdx.x * kPosChunk + (int)threadIdx.x * 8;
   int hs[8];
-  unsigned flags = 0;
-  int c = 0;
+  int64_t id[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const int p = base + j;
-    hs[j] = 0;
-    if (p < n) {
-      const unsigned raw = (unsigned)hslot[p];
-      hs[j] = (int)(raw & ~kCandBit);
-      if ((raw & kCandBit) && utab[hs[j]].minpos == p) { flags |= 1u << j; ++c; }
-    }
-  }
+  for (int j = 0; j < 8; ++j)
+    if (flags & (1u << j)) { hs[j] = (int)((unsigned)hslot[base + j] & ~kCandBit); id[j] = ids[base + j]; }
+  before = block_sum(before, smem);
   int tot;
-  int vid = block_excl_scan(c, tot, smem) + before;
+  int vid = block_excl_scan(__popc(flags), tot, smem) + before;
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *n_unique = before + tot;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     if (flags & (1u << j)) {
-      const int64_t key = utab[hs[j]].key;
-      unique_ids[vid] = key == kNullKey ? (int64_t)-1 : key;
+      unique_ids[vid] = (id[j] < 0 || id[j] >= V) ? (int64_t)-1 : id[j];
       uvid[hs[j]] = vid;
       vid_hslot[vid] = hs[j];
       cnt[vid] = 0;
@@ -308,50 +308,88 @@ __global__ __launch_bounds__(256) void k_uniq_assign(const int* __restrict__ hsl
   }
 }
 
-// VSI pass 4: virtual id of every position, and cnt[v] = number of positions of virtual id v.
-// For the ids outside the LDS range the atomic that counts a position also ranks it inside its
-// group (rank[p]): the grouping pass then needs no atomic of its own for them.
+// VSI pass 4: virtual id of every position, cnt[v] = number of positions of virtual id v, and the
+// place of every position inside its group (rank[p]), so that the grouping pass needs no atomics.
 // Virtual ids are handed out in order of first appearance, so the frequent ids of a power-law
 // batch are (nearly all) among the lowest ones: those are counted in an LDS histogram per block
 // and flushed with one coalesced atomic per bin; the rest go to HBM atomics on distinct words.
+// An atomic that counts also ranks: a cold id's returns the position's place in its group, a hot bin's
+// LDS atomic its place in the block's share and the flush the start of that share.
 // Every block adds its tally of a frequent id to one counter: a thousand atomics in a row on one
-// address (about 10 ns each).  The counters of the hot bins are therefore kept in kHotRep copies,
-// block b using copy b mod kHotRep; resolve folds the copies into cnt, the miss assignment turns
-// them into one group cursor per copy.
+// address (about 10 ns each).  The counters of the hot bins are therefore kept in up to kHotRep
+// copies, block b using copy b mod nrep (SortGeom); resolve folds the copies into cnt, the miss
+// assignment turns them into one group start per copy.
 constexpr int kHotRep = 32;
-constexpr int kFlushPer = 16;     // bins per thread and round when k_scatter flushes its LDS tallies
+constexpr int kFewBins = 2048;
 
-__global__ __launch_bounds__(256) void k_uniq_inverse(const int* __restrict__ hslot,
+// The shape of the counting and grouping passes by batch size (nothing else of a batch is known to
+// the host).  A block's histogram costs its clear and its flush whatever the block counts, and the
+// places of a block's positions in a hot group lie side by side, so big batches take many positions
+// per block (fewer flushes, fewer 128-byte lines that two XCDs write) and all bins; small ones are
+// short of blocks instead, and a few bins hold all that is frequent enough to serialise an atomic.
+// Counting + grouping us, threads x positions per thread: 195e3 positions (2048 bins) 256x4 15.6,
+// 256x16 33; 639e3 256x8 28.6, 512x8 29.0, 256x16 38.7; 2.56e6 512x8 57.0, 256x16 63.3, 1024x8 61.7;
+// 8.9e6 in bags 1024x8 268, 256x16 310, 512x8 302.  Fewer bins than 8192 are slower from 639e3
+// positions on: the counters of the ids just beyond the bins share cache lines (2.56e6, 4096 / 2048 /
+// 1024 bins: 68 / 76 / 105 us).
+struct SortGeom { int bins, threads, per, shift, nrep, blocks; };   // positions per block = threads * per = 1 << shift
+inline SortGeom sort_geom(int64_t n) {
+  SortGeom g;
+  if (n < ((int64_t)1 << 18)) { g.bins = kFewBins; g.threads = 256; g.per = 4; g.shift = 10; }
+  else if (n < ((int64_t)1 << 22)) { g.bins = kHotBins; g.threads = 512; g.per = 8; g.shift = 12; }
+  else { g.bins = kHotBins; g.threads = 1024; g.per = 8; g.shift = 13; }
+  g.blocks = (int)((n + (1 << g.shift) - 1) >> g.shift);
+  g.nrep = 1;
+  while (g.nrep < kHotRep && g.nrep * 16 < g.blocks) g.nrep *= 2;
+  return g;
+}
+
+template <int kBins, int kPer, int kT>
+__global__ __launch_bounds__(kT) void k_uniq_inverse(const int* __restrict__ hslot,
                                                        const int* __restrict__ uvid, int n,
                                                        int* __restrict__ inverse, int* cnt,
-                                                       int* cnt_rep, int* __restrict__ rank) {
-  __shared__ int lh[kHotBins];
-  for (int i = threadIdx.x; i < kHotBins; i += 256) lh[i] = 0;
-  __syncthreads();
-  const int base = blockIdx.x * kSortChunk;
-  int hv[kSortPer], vv[kSortPer];
+                                                       int* cnt_rep, int nrep, int* __restrict__ rank) {
+  __shared__ int lh[kBins];
+  for (int i = threadIdx.x; i < kBins; i += kT) lh[i] = 0;
+  const int base = blockIdx.x * kT * kPer;
+  int hv[kPer], vv[kPer], rr[kPer];
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {          // kSortPer loads in flight per level of indirection
-    const int p = base + j * 256 + (int)threadIdx.x;
+  for (int j = 0; j < kPer; ++j) {              // kPer loads in flight per level of indirection
+    const int p = base + j * kT + (int)threadIdx.x;
     hv[j] = p < n ? (int)((unsigned)hslot[p] & ~kCandBit) : -1;
   }
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) vv[j] = hv[j] >= 0 ? uvid[hv[j]] : -1;
+  for (int j = 0; j < kPer; ++j) vv[j] = hv[j] >= 0 ? uvid[hv[j]] : -1;
+  __syncthreads();
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    const int p = base + j * 256 + (int)threadIdx.x;
+  for (int j = 0; j < kPer; ++j) {
+    const int p = base + j * kT + (int)threadIdx.x;
     const int v = vv[j];
     if (v >= 0) {
       inverse[p] = v;
-      if (v < kHotBins) atomicAdd(&lh[v], 1);
-      else rank[p] = atomicAdd(&cnt[v], 1);      // arrival order inside the group, for k_scatter
+      rr[j] = v < kBins ? atomicAdd(&lh[v], 1) : atomicAdd(&cnt[v], 1);
     }
   }
   __syncthreads();
-  int* mine = cnt_rep + (blockIdx.x & (kHotRep - 1)) * kHotBins;
-  for (int b = threadIdx.x; b < kHotBins; b += 256) {
-    const int c = lh[b];
-    if (c) atomicAdd(&mine[b], c);
+  int* mine = cnt_rep + (blockIdx.x & (nrep - 1)) * kHotBins;
+  // the block's share of each non-empty bin: returning atomics, several in flight per thread (each
+  // round of them is a round trip to the memory side)
+  constexpr int kFlush = kBins / kT < 16 ? kBins / kT : 16;
+  static_assert(kBins % (kT * kFlush) == 0, "flush rounds cover the bins exactly");
+  for (int b0 = threadIdx.x; b0 < kBins; b0 += kT * kFlush) {
+    int c[kFlush], r[kFlush];
+#pragma unroll
+    for (int u = 0; u < kFlush; ++u) c[u] = lh[b0 + u * kT];
+#pragma unroll
+    for (int u = 0; u < kFlush; ++u) r[u] = c[u] ? atomicAdd(&mine[b0 + u * kT], c[u]) : 0;
+#pragma unroll
+    for (int u = 0; u < kFlush; ++u) if (c[u]) lh[b0 + u * kT] = r[u];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int p = base + j * kT + (int)threadIdx.x;
+    if (vv[j] >= 0) rank[p] = vv[j] < kBins ? lh[vv[j]] + rr[j] : rr[j];
   }
 }
 
@@ -379,82 +417,61 @@ __global__ __launch_bounds__(256) void k_pos2bag(const int64_t* __restrict__ off
   }
 }
 
-// Grouping of positions by virtual id (counting sort): perm64[cursor[v]++] = (v << 32) | payload,
-// payload = position (one-hot) or bag index (multi-hot).  cursor[v] starts at the exclusive scan
-// of cnt.  Same LDS treatment of the low virtual ids as above; the others already carry their rank
-// inside the group from the counting pass (rank_slot[p], the array this pass then overwrites with
-// pos_slot[p]).  The order inside a group is the order in which the atomics land.
-// Also writes pos_slot[p] = row of slot[inverse[p]] for the forward gather (a bypass slot C + j
-// lives at row C + boff + j: each step in flight has its own bypass region).
-__global__ __launch_bounds__(256) void k_scatter(const int* __restrict__ inverse,
+// Grouping of positions by virtual id (counting sort): perm64[start of the group + rank] =
+// (v << 32) | payload, payload = position (one-hot) or bag index (multi-hot).  The counting pass has
+// ranked every position inside its group (a hot bin's copy: inside the copy's share, whose start is in
+// cur_rep), so this pass is loads and stores only (65536 x 39 positions: 31 us with a second histogram
+// and its returning atomics here, 22 without, and the counting pass is none the slower for ranking).
+// rank_slot[p] is read as the rank and overwritten with pos_slot[p] = row of slot[inverse[p]] for the
+// forward gather (a bypass slot C + j lives at row C + boff + j: each step in flight has its own
+// bypass region).
+// A block takes the same positions as a block of the counting pass: their places in a hot group lie
+// side by side, and with half the positions per block two XCDs write into the same 128-byte lines
+// (169 against 120 us at 8.9e6 positions in bags).
+template <int kScatPer, int kT>
+__global__ __launch_bounds__(kT) void k_scatter(const int* __restrict__ inverse,
                                                   const int* __restrict__ pos2bag, int n,
                                                   const int64_t* __restrict__ grp,
                                                   int* __restrict__ cold_pay,
-                                                  int* cur_rep,
-                                                  int64_t* __restrict__ perm64,
+                                                  const int* __restrict__ cur_rep, int bins, int shift,
+                                                  int nrep, int64_t* __restrict__ perm64,
                                                   const int* __restrict__ slot,
                                                   int* rank_slot, int C, int boff, int n_bags) {
-  __shared__ int lh[kHotBins];
-  for (int i = threadIdx.x; i < kHotBins; i += 256) lh[i] = 0;
-  __syncthreads();
-  const int base = blockIdx.x * kSortChunk;
-  int vv[kSortPer], rr[kSortPer], sv[kSortPer], cb[kSortPer], pay[kSortPer];
-  unsigned coldm = 0;                       // bit j: position j of this thread belongs to a cold group
-  // two levels of indirection, kSortPer loads in flight at each: position -> vid -> slot / group start
+  const int base = blockIdx.x * kT * kScatPer + (int)threadIdx.x;
+  int vv[kScatPer], rr[kScatPer], sv[kScatPer], pay[kScatPer];
+  int64_t gr[kScatPer];
+  // two levels of indirection, kScatPer loads in flight at each: position -> vid -> slot / group start
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    const int p = base + j * 256 + (int)threadIdx.x;
+  for (int j = 0; j < kScatPer; ++j) {
+    const int p = base + j * kT;
     vv[j] = p < n ? inverse[p] : -1;
-    rr[j] = p < n ? rank_slot[p] : 0;           // meaningful for the ids outside the LDS range only
+    rr[j] = p < n ? rank_slot[p] : 0;
     pay[j] = (p < n && pos2bag) ? pos2bag[p] : p;
     // a position that malformed offsets left uncovered carries a stale bag number
     if (pos2bag && (unsigned)pay[j] >= (unsigned)n_bags) pay[j] = 0;
   }
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    sv[j] = vv[j] >= 0 ? slot[vv[j]] : -1;
-    cb[j] = 0;
-    if (vv[j] >= kHotBins) {
-      const int64_t g = grp[vv[j]];
-      cb[j] = (int)g;
-      if (group_cold(vv[j], g)) coldm |= 1u << j;
+  for (int j = 0; j < kScatPer; ++j) {
+    const int p = base + j * kT;
+    if (vv[j] >= 0) {
+      sv[j] = slot[vv[j]];
+      gr[j] = vv[j] < bins ? (int64_t)cur_rep[((p >> shift) & (nrep - 1)) * kHotBins + vv[j]] : grp[vv[j]];
     }
   }
-  // the hot ids' ranks come from LDS; every group entry is written at the end
 #pragma unroll
-  for (int j = 0; j < kSortPer; ++j) {
-    const int p = base + j * 256 + (int)threadIdx.x;
+  for (int j = 0; j < kScatPer; ++j) {
+    const int p = base + j * kT;
     if (vv[j] < 0) continue;
     rank_slot[p] = sv[j] >= C ? sv[j] + boff : sv[j];   // pos_slot: row index for the forward gather
-    if (vv[j] < kHotBins) rr[j] = atomicAdd(&lh[vv[j]], 1);
-    else {
-      // a cold group's gradient rows also go where the optimizer kernel finds them without
-      // walking the grouping: two words per virtual id, filled in the order of the ranks
-      if ((coldm >> j) & 1u) cold_pay[2 * vv[j] + rr[j]] = pay[j];
-      rr[j] += cb[j];
+    int64_t e = ((int64_t)vv[j] << 32) | (uint32_t)pay[j];
+    // a cold group's gradient rows also go where the optimizer kernel finds them without
+    // walking the grouping: two words per virtual id, filled in the order of the ranks
+    if (vv[j] >= bins && group_cold(gr[j])) {
+      cold_pay[2 * vv[j] + rr[j]] = pay[j];
+      e |= kColdBit;
     }
+    perm64[(int)gr[j] + rr[j]] = e;
   }
-  __syncthreads();
-  int* mine = cur_rep + (blockIdx.x & (kHotRep - 1)) * kHotBins;
-  // the block's share of each non-empty bin's cursor: returning atomics, sixteen in flight per
-  // thread (each round of them is a round trip to the memory side)
-  static_assert(kHotBins % (256 * kFlushPer) == 0, "flush rounds cover the bins exactly");
-  for (int b0 = threadIdx.x; b0 < kHotBins; b0 += 256 * kFlushPer) {
-    int c[kFlushPer], r[kFlushPer];
-#pragma unroll
-    for (int u = 0; u < kFlushPer; ++u) c[u] = lh[b0 + u * 256];
-#pragma unroll
-    for (int u = 0; u < kFlushPer; ++u) r[u] = c[u] ? atomicAdd(&mine[b0 + u * 256], c[u]) : 0;
-#pragma unroll
-    for (int u = 0; u < kFlushPer; ++u) if (c[u]) lh[b0 + u * 256] = r[u];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int j = 0; j < kSortPer; ++j)
-    if (vv[j] >= 0) {
-      const int at = vv[j] < kHotBins ? lh[vv[j]] + rr[j] : rr[j];
-      perm64[at] = ((int64_t)vv[j] << 32) | (uint32_t)pay[j] | ((coldm >> j) & 1u ? kColdBit : (int64_t)0);
-    }
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -547,7 +564,11 @@ __device__ __forceinline__ bool index_insert(IdxEntry* index, uint32_t hi, int64
 // table never needs a per-step clear, and sums cnt per tile for the segment offsets.
 // ---------------------------------------------------------------------------------------------
 constexpr int kAgeBins = 1024;
-constexpr int kResolveGrid = 256;
+// One tile per block and iteration, up to 512 blocks: what hides the chain vid -> id -> index entry ->
+// stamp is more wavefronts, not more tiles per thread.  (us at 10.6e3 / 40e3 / 132e3 / 200e3 / 837e3 /
+// 1.24e6 unique ids: 7.1 / 7.7 / 16 / 17.5 / 48 / 62; four tiles per thread on 256 blocks 16 / 15 / 17 / 25 /
+// 60 / 84; one tile on 256 blocks 7.2 / 7.5 / 15 / 21 / 58 / 81, on 1024 6.8 / 7.7 / 16 / 22.5 / 49 / 59.)
+constexpr int kResolveGrid = 512;
 
 __global__ __launch_bounds__(256) void k_resolve(const int64_t* __restrict__ unique_ids,
                                                   const int* __restrict__ vid_hslot, UEntry* utab,
@@ -557,7 +578,7 @@ __global__ __launch_bounds__(256) void k_resolve(const int64_t* __restrict__ uni
                                                   int* __restrict__ slot_out,
                                                   int* __restrict__ tile_miss,
                                                   int* __restrict__ cnt,
-                                                  const int* __restrict__ cnt_rep,
+                                                  const int* __restrict__ cnt_rep, int bins, int nrep,
                                                   int* __restrict__ tile_cnt,
                                                   int* __restrict__ age_hist, Ctr* ctr,
                                                   const Ctr* prev, const int* n_unique,
@@ -573,79 +594,49 @@ __global__ __launch_bounds__(256) void k_resolve(const int64_t* __restrict__ uni
   const int U = prev ? *n_unique : ctr->U;
   __syncthreads();
   if (prev && blockIdx.x == 0 && threadIdx.x == 0) ctr_start(ctr, prev, n_unique, n_invalid, t);
-  // four tiles per iteration, so that each level of the chain vid -> id -> index entry -> stamp
-  // has four loads in flight per thread
-  for (int tile0 = blockIdx.x * 4; tile0 * kVidTile < U; tile0 += gridDim.x * 4) {
-    int hs[4], cc[4], sl[4], old[4];
-    int64_t id[4];
-    uint32_t hb[4];
-    int4 ent[4];
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int v = (tile0 + k) * kVidTile + (int)threadIdx.x;
-      hs[k] = -1; cc[k] = 0; id[k] = -1;
-      if (v < U) {
-        hs[k] = vid_hslot[v]; id[k] = unique_ids[v];
-        if (v < kHotBins) {                     // fold the copies of a hot bin
-          int c = 0;
-#pragma unroll
-          for (int r = 0; r < kHotRep; ++r) c += cnt_rep[r * kHotBins + v];
-          cnt[v] = c; cc[k] = c;
-        } else {
-          cc[k] = cnt[v];
-        }
+  for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
+    const int v = tile * kVidTile + (int)threadIdx.x;
+    int hs = -1, cc = 0, sl = -1, old = 0;
+    int64_t id = -1;
+    if (v < U) {
+      hs = vid_hslot[v]; id = unique_ids[v];
+      if (v < bins) {                           // fold the copies of a hot bin
+#pragma unroll 8
+        for (int r = 0; r < nrep; ++r) cc += cnt_rep[r * kHotBins + v];
+        cnt[v] = cc;
+      } else {
+        cc = cnt[v];
       }
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (hs[k] >= 0) { UEntry z; z.key = kEmpty; z.minpos = kIntMax; z.pad = 0; utab[hs[k]] = z; }
-      if (id[k] >= 0) {
-        if (dmap) {
-          ent[k].z = dmap[id[k]];
-        } else {
-          hb[k] = bucket_of(id[k], hi);
-          ent[k] = *reinterpret_cast<const int4*>(&index[hb[k]]);
-        }
+    if (hs >= 0) { UEntry z; z.key = kEmpty; z.minpos = kIntMax; z.pad = 0; utab[hs] = z; }
+    if (id >= 0) {
+      if (dmap) {
+        sl = dmap[id];
+      } else {
+        const int4 ent = *reinterpret_cast<const int4*>(&index[bucket_of(id, hi)]);
+        const int64_t k0 = ((int64_t)(uint32_t)ent.y << 32) | (uint32_t)ent.x;
+        if (k0 == id) sl = ent.z;
+        else if (k0 != kEmpty) sl = index_find(index, hi, id, nullptr, ctr);   // walk on
       }
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      sl[k] = -1;
-      if (id[k] >= 0) {
-        if (dmap) {
-          sl[k] = ent[k].z;
-        } else {
-          const int64_t k0 = ((int64_t)(uint32_t)ent[k].y << 32) | (uint32_t)ent[k].x;
-          if (k0 == id[k]) sl[k] = ent[k].z;
-          else if (k0 != kEmpty) sl[k] = index_find(index, hi, id[k], nullptr, ctr);   // walk on
-        }
-      }
+    const bool hit = sl >= 0, miss = id >= 0 && sl < 0;
+    int age = 0;
+    if (v < U) slot_out[v] = hit ? sl : (miss ? kMissMark : -1);
+    if (hit) {
+      old = stamp[sl];
+      stamp[sl] = t;
+      age = t - old;
+      if (age >= kAgeBins) atomicSub(&hist[old], 1);
     }
-#pragma unroll
-    for (int k = 0; k < 4; ++k) old[k] = sl[k] >= 0 ? stamp[sl[k]] : 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int tile = tile0 + k;
-      if (tile * kVidTile >= U) break;               // uniform over the block
-      const int v = tile * kVidTile + (int)threadIdx.x;
-      const bool hit = sl[k] >= 0, miss = id[k] >= 0 && sl[k] < 0;
-      int age = 0;
-      if (v < U) slot_out[v] = hit ? sl[k] : (miss ? kMissMark : -1);
-      if (hit) {
-        stamp[sl[k]] = t;
-        age = t - old[k];
-        if (age >= kAgeBins) atomicSub(&hist[old[k]], 1);
-      }
-      // most hits were last used one step ago: count those per wavefront, the rest one by one
-      const uint64_t m1 = __ballot(hit && age == 1);
-      if (m1 && lane_id() == 0) atomicAdd(&lage[1], __popcll(m1));
-      if (hit && age > 1 && age < kAgeBins) atomicAdd(&lage[age], 1);
-      const uint64_t mh = __ballot(hit);
-      if (mh && lane_id() == 0) atomicAdd(&lage[0], __popcll(mh));
-      const int nmiss = block_sum(miss ? 1 : 0, smem);
-      const int csum = block_sum(cc[k], smem);
-      if (threadIdx.x == 0) { tile_miss[tile] = nmiss; tile_cnt[tile] = csum; }
-    }
+    // most hits were last used one step ago: count those per wavefront, the rest one by one
+    const uint64_t m1 = __ballot(hit && age == 1);
+    if (m1 && lane_id() == 0) atomicAdd(&lage[1], __popcll(m1));
+    if (hit && age > 1 && age < kAgeBins) atomicAdd(&lage[age], 1);
+    const uint64_t mh = __ballot(hit);
+    if (mh && lane_id() == 0) atomicAdd(&lage[0], __popcll(mh));
+    const int nmiss = block_sum(miss ? 1 : 0, smem);
+    const int csum = block_sum(cc, smem);
+    if (threadIdx.x == 0) { tile_miss[tile] = nmiss; tile_cnt[tile] = csum; }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < kAgeBins; i += 256)
@@ -884,7 +875,7 @@ __global__ __launch_bounds__(256) void k_victim_unmap(const int64_t* __restrict_
 __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict__ unique_ids,
                                                         const int* __restrict__ cnt,
                                                         int* __restrict__ cnt_rep,
-                                                        int* __restrict__ cur_rep,
+                                                        int* __restrict__ cur_rep, int bins, int nrep,
                                                         const int* __restrict__ tile_coff,
                                                         int64_t* __restrict__ grp,
                                                         int2* __restrict__ cold_pay,
@@ -927,10 +918,10 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
       grp[v] = ((int64_t)nv << 32) | (uint32_t)off;
       cold_pay[v] = make_int2(-1, -1);          // the grouping pass fills in the cold groups' rows
     }
-    if (v < U && v < kHotBins) {                // one cursor per copy of a hot bin; copies back to zero
+    if (v < U && v < bins) {                    // one group start per copy of a hot bin; copies back to zero
       int at = off;
-#pragma unroll
-      for (int r = 0; r < kHotRep; ++r) {
+#pragma unroll 8
+      for (int r = 0; r < nrep; ++r) {
         const int c = cnt_rep[r * kHotBins + v];
         cur_rep[r * kHotBins + v] = at;
         at += c;

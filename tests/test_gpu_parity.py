@@ -187,6 +187,20 @@ def test_frequent_ids_that_first_appear_late():
     p.finish(); p.close()
 
 
+@pytest.mark.parametrize("n", [1, 255, 257, 1023, 1025, 5121, (1 << 18) - 1, 1 << 18, (1 << 18) + 1,
+                               (1 << 22) - 1, (1 << 22) + 1])
+def test_batch_sizes_where_the_counting_passes_change_shape(n):
+    # the passes that count, rank and group the positions take other block sizes and another number of
+    # LDS bins by batch size, and a ragged last block; ids beyond the bins, ids outside the table
+    V, D = max(8, n // 2), 4
+    p = Pair(V, D, C=max(4, V // 3), max_ids=n)
+    for t in range(2 if n > 1 << 20 else 3):
+        ids = si.zipf_ids(n, 1.1, max(2, V - V % 10), 300 + n % 97, t).numpy()
+        ids[::1001] = V + 5
+        p.step(ids, si.grads(n, D, 300 + n % 97, t).numpy(), check_state=n < 1 << 20)
+    p.finish(); p.close()
+
+
 def test_same_stream_and_separate_host_arrays():
     # copies on the main stream; Host weights and accumulators as two separate arrays
     V, D, n = 4000, 32, 2000
