@@ -362,6 +362,41 @@ int seg_launch(sfc_cache* c, StepCtx* x, const float* d_grad, float* d_common, d
   return SFC_OK;
 }
 
+// The prepare's kernels behind the resolve: bags of the positions, victims' plan and lists, slots of the
+// misses, grouping.  (Called where the resolve has run on c->prep.)
+int plan_and_group(sfc_cache* c, StepCtx* x, const SortGeom& sg, int* cnt, int* cnt_rep) {
+  hipStream_t s = c->prep;
+  const int n = (int)x->n_ids;
+  // (after the resolve: it tallies into the step's counters, which that kernel may have started)
+  if (n > 0 && x->d_offsets)
+    hipLaunchKernelGGL(k_pos2bag, dim3((unsigned)((x->n_bags + 255) / 256)), dim3(256), 0, s,
+                       x->d_offsets, (int)x->n_bags, n, c->pos2bag, x->ctr);
+  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, c->tile_miss, c->tile_cnt, c->age_hist,
+                     c->tile_reuse, c->hist, x->t, c->cfg.lookahead, (int)c->C, c->hi, x->ctr);
+  // a cache that holds the whole table never evicts: there is a free slot for every id that is not resident
+  if (c->C < c->V) {
+    const int gs = grid_for(c->C, kPosChunk, kGridCap);
+    hipLaunchKernelGGL(k_victim_count, dim3(gs), dim3(256), 0, s, c->stamp, c->tile_lt, c->tile_eq, x->ctr);
+    hipLaunchKernelGGL(k_victim_write, dim3(gs), dim3(256), 0, s, c->stamp, c->slot_id, c->tile_lt,
+                       c->tile_eq, x->victim_slot, x->victim_id, x->ctr, c->dmap);
+  }
+  const int gv = grid_for(n, kVidTile, kGridCap);
+  if (!c->dmap && c->C < c->V)
+    hipLaunchKernelGGL(k_victim_unmap, dim3(gv), dim3(256), 0, s, x->victim_id, c->index, c->hi, x->ctr);
+  hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, x->d_unique, cnt, cnt_rep,
+                     c->cur_rep, sg.bins, sg.nrep, c->tile_cnt, c->grp, x->cold_pay, c->tile_miss,
+                     x->victim_slot, x->d_slot, x->d_miss, x->miss_row, x->miss_id, x->boff, c->slot_id,
+                     c->stamp, c->index, c->hi, c->dmap, x->t, (int)c->C, c->tile_reuse, x->ctr);
+  if (n > 0) {
+    auto scat = sg.threads == 256 ? k_scatter<4, 256> : sg.threads == 512 ? k_scatter<8, 512> : k_scatter<8, 1024>;
+    hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.threads), 0, s, x->d_inverse,
+                       x->d_offsets ? c->pos2bag : (const int*)nullptr, n, c->grp, (int*)x->cold_pay,
+                       (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
+                       (const int*)x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags);
+  }
+  return SFC_OK;
+}
+
 int sync_all(sfc_cache* c) {
   HIPCHK(hipStreamSynchronize(c->st));
   if (c->side != c->st) HIPCHK(hipStreamSynchronize(c->side));
@@ -656,6 +691,10 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     return fail(SFC_ESTATE, "every step context holds a step that has not been updated: call "
                             "sfc_backward_update (or sfc_discard) first");
   StepCtx* prev = c->last_prepared >= 0 ? &c->ctx[c->last_prepared] : x;
+  // a small batch is prepared by one block (k_small_prepare), all of it when that block can also choose
+  // the victims
+  const bool small = n_ids > 0 && n_ids <= kSmallIds && n_bags <= kSmallBags;
+  const bool whole = small && c->dmap && (c->C >= c->V || c->C <= kSmallSlots);
   hipStream_t s = c->prep;
   if (s != c->st) {
     // the prepare stream must not overtake what the main stream has been given so far: the
@@ -664,7 +703,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     HIPCHK(hipStreamWaitEvent(s, c->ev_tmp, 0));
     // a context freed by sfc_discard: its copies may still be reading its lists
     if (x->discarded && s != c->side) HIPCHK(hipStreamWaitEvent(s, x->ev_fetched, 0));
-    if (c->ins) {
+    if (c->ins && !small) {
       // The unique passes touch the batch table, the per-position table slots, the tally of
       // invalid ids, this step's set of counts, its context's position array and the caller's
       // buffers of this step: the previous step's prepare has finished with the shared ones once
@@ -679,7 +718,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     // waits for its copies, which may still be reading the lists that this prepare rewrites
     HIPCHK(hipStreamWaitEvent(s, x->ev_fetched, 0));
   }
-  hipStream_t su = c->ins ? c->ins : s;          // stream of the unique passes
+  hipStream_t su = c->ins && !small ? c->ins : s;   // stream of the unique passes
   c->t += 1;
   x->t = c->t; x->state = PREPARED; x->updated = false; x->main_pending = false; x->discarded = false;
   x->n_ids = n_ids; x->n_bags = n_bags; x->d_offsets = d_offsets;
@@ -695,8 +734,10 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   uint32_t hu = (uint32_t)(2 * n_ids);
   if (hu < 64) hu = 64;                       // the batch table is empty between steps: any size works
   const int nchunk = (n + kPosChunk - 1) / kPosChunk;
-  const SortGeom sg = sort_geom(n);
-  if (n > 0) {
+  const SortGeom sg = small ? small_geom(n) : sort_geom(n);
+  if (small) {
+    // its unique passes are part of the kernel below
+  } else if (n > 0) {
     const int nub = (n + kUniqChunk - 1) / kUniqChunk, head = nub < kHeadBlocks ? nub : kHeadBlocks;
     hipLaunchKernelGGL(k_uniq_insert, dim3(head), dim3(256), 0, su, d_ids, n, c->V, c->utab, hu,
                        c->hslot, c->n_invalid, 0);
@@ -725,40 +766,27 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                        c->n_unique, c->n_invalid, c->index, c->hi, x->t);
     hipLaunchKernelGGL(k_index_refill, dim3(kRebuildGrid), dim3(256), 0, s, c->index, c->hi, c->slot_id, x->ctr);
   }
-  const int gr = grid_for(n, kVidTile, kResolveGrid);
-  hipLaunchKernelGGL(k_resolve, dim3(gr), dim3(256), 0, s, d_unique_ids, c->vid_hslot, c->utab,
-                     c->index, c->hi, c->dmap, c->stamp, c->hist, x->t, d_slot, c->tile_miss, cnt, cnt_rep,
-                     sg.bins, sg.nrep, c->tile_cnt, c->age_hist, x->ctr, c->dmap ? (const Ctr*)prev->ctr : (const Ctr*)nullptr,
-                     (const int*)c->n_unique, c->n_invalid);
-  if (c->ins) { HIPCHK(hipEventRecord(c->ev_resolved, s)); c->resolved_once = true; }
-  // (after the resolve: it tallies into the step's counters, which that kernel may have started)
-  if (n > 0 && d_offsets)
-    hipLaunchKernelGGL(k_pos2bag, dim3((unsigned)((n_bags + 255) / 256)), dim3(256), 0, s,
-                       d_offsets, (int)n_bags, n, c->pos2bag, x->ctr);
-  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, c->tile_miss, c->tile_cnt, c->age_hist,
-                     c->tile_reuse,
-                     c->hist, x->t, c->cfg.lookahead, (int)c->C, c->hi, x->ctr);
-  const int gs = grid_for(c->C, kPosChunk, kGridCap);
-  hipLaunchKernelGGL(k_victim_count, dim3(gs), dim3(256), 0, s, c->stamp, c->tile_lt, c->tile_eq,
-                     x->ctr);
-  hipLaunchKernelGGL(k_victim_write, dim3(gs), dim3(256), 0, s, c->stamp, c->slot_id, c->tile_lt,
-                     c->tile_eq, x->victim_slot, x->victim_id, x->ctr, c->dmap);
-  const int gv = grid_for(n, kVidTile, kGridCap);
-  if (!c->dmap)
-    hipLaunchKernelGGL(k_victim_unmap, dim3(gv), dim3(256), 0, s, x->victim_id, c->index, c->hi,
-                       x->ctr);
-  hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, d_unique_ids, cnt, cnt_rep,
-                     c->cur_rep, sg.bins, sg.nrep, c->tile_cnt,
-                     c->grp, x->cold_pay, c->tile_miss, x->victim_slot, d_slot, d_miss_vids, x->miss_row,
-                     x->miss_id, x->boff, c->slot_id,
-                     c->stamp, c->index, c->hi, c->dmap, x->t, (int)c->C, c->tile_reuse, x->ctr);
-  if (n > 0) {
-    auto scat = sg.threads == 256 ? k_scatter<4, 256> : sg.threads == 512 ? k_scatter<8, 512> : k_scatter<8, 1024>;
-    hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.threads), 0, s, d_inverse,
-                       d_offsets ? c->pos2bag : (const int*)nullptr, n, c->grp, (int*)x->cold_pay,
-                       (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
-                       (const int*)d_slot, x->pos_slot, (int)c->C, x->boff, (int)n_bags);
+  if (small) {
+    SmallArgs a;
+    a.ids = d_ids; a.n = n; a.V = c->V; a.offsets = d_offsets; a.n_bags = (int)n_bags;
+    a.unique_ids = d_unique_ids; a.inverse = d_inverse; a.slot = d_slot; a.miss_vids = d_miss_vids;
+    a.index = c->index; a.hi = c->hi; a.dmap = c->dmap;
+    a.stamp = c->stamp; a.slot_id = c->slot_id; a.hist = c->hist;
+    a.t = x->t; a.lookahead = c->cfg.lookahead; a.C = (int)c->C; a.boff = x->boff;
+    a.cnt = cnt; a.tile_miss = c->tile_miss; a.tile_cnt = c->tile_cnt; a.age_hist = c->age_hist;
+    a.grp = c->grp; a.cold_pay = x->cold_pay; a.perm64 = x->perm64; a.pos_slot = x->pos_slot;
+    a.victim_slot = x->victim_slot; a.victim_id = x->victim_id; a.miss_row = x->miss_row; a.miss_id = x->miss_id;
+    a.ctr = x->ctr; a.prev = c->dmap ? prev->ctr : nullptr;
+    hipLaunchKernelGGL(whole ? k_small_prepare<true> : k_small_prepare<false>, dim3(1), dim3(1024), 0, s, a);
+  } else {
+    const int gr = grid_for(n, kVidTile, kResolveGrid);
+    hipLaunchKernelGGL(k_resolve, dim3(gr), dim3(256), 0, s, d_unique_ids, c->vid_hslot, c->utab,
+                       c->index, c->hi, c->dmap, c->stamp, c->hist, x->t, d_slot, c->tile_miss, cnt, cnt_rep,
+                       sg.bins, sg.nrep, c->tile_cnt, c->age_hist, x->ctr,
+                       c->dmap ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid);
   }
+  if (c->ins) { HIPCHK(hipEventRecord(c->ev_resolved, s)); c->resolved_once = true; }
+  if (!whole && (rc = plan_and_group(c, x, sg, cnt, cnt_rep))) return rc;
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_PREPARE, s, &ep))) return rc;
   HIPCHK(hipEventRecord(x->ev_prepared, s));

@@ -344,6 +344,14 @@ inline SortGeom sort_geom(int64_t n) {
   return g;
 }
 
+// A small batch (k_small_prepare): counted and ranked already, no hot bins.
+inline SortGeom small_geom(int64_t n) {
+  SortGeom g;
+  g.bins = 0; g.threads = 256; g.per = 4; g.shift = 10; g.nrep = 1;
+  g.blocks = (int)((n + 1023) >> 10);
+  return g;
+}
+
 template <int kBins, int kPer, int kT>
 __global__ __launch_bounds__(kT) void k_uniq_inverse(const int* __restrict__ hslot,
                                                        const int* __restrict__ uvid, int n,
@@ -644,10 +652,84 @@ __global__ __launch_bounds__(256) void k_resolve(const int64_t* __restrict__ uni
 }
 
 // ---------------------------------------------------------------------------------------------
-// Plan (one block): scan the per-tile miss counts, then decide the victims' stamp threshold from
-// the recency histogram: need = M - free; T is the stamp at which the running count of
-// evictable slots (stamp < limit, oldest first) passes need; r of the slots stamped T go too.
+// The victims' plan, by one block of 1024 threads: need = M - free; T is the stamp at which the
+// running count of evictable slots (stamp < limit, oldest first) passes need; r of the slots stamped T
+// go too; K victims in all.
+// kAtomic: the kernel also updates the recency histogram with atomics, so every access to it is one.
 // ---------------------------------------------------------------------------------------------
+struct Plan { int M, need, T, r, K, f_new, n_bypass, oldest; };
+
+template <bool kAtomic>
+__device__ __forceinline__ void hist_add(int* w, int x) {
+  if (kAtomic) {
+    const int old = atomicAdd(w, x);
+    asm volatile("" :: "v"(old));          // the value has to be back, so the sum has been formed
+  } else {
+    *w += x;
+  }
+}
+
+template <bool kAtomic>
+__device__ __forceinline__ void plan_decide(Plan& pl, int M, int f, int oldest, int* hist, int t,
+                                            int lookahead, int C, int* smem, int* s_found) {
+  const int need = M - (C - f);
+  const int limit = t - lookahead;       // candidates have stamp < limit
+  int T = limit, r = 0, K = 0;
+  if (need > 0) {
+    // running count of candidates from the oldest stamp upwards
+    int cum = 0;           // slots with stamp in [oldest, b)
+    bool done = false;
+    for (int b = oldest; b < limit && !done; b += 1024) {
+      if (threadIdx.x == 0) *s_found = kIntMax;
+      __syncthreads();
+      const int s = b + (int)threadIdx.x;
+      const int x = s < limit ? (kAtomic ? coherent_load(&hist[s]) : hist[s]) : 0;
+      int tot;
+      const int e = block_excl_scan(x, tot, smem);
+      // first stamp whose inclusive count exceeds need
+      if (s < limit && cum + e + x > need) atomicMin(s_found, s);
+      __syncthreads();
+      if (*s_found != kIntMax) {
+        T = *s_found;
+        if (s == T) smem[18] = cum + e;    // candidates strictly older than T
+        __syncthreads();
+        r = need - smem[18];
+        K = need;
+        done = true;
+      } else {
+        cum += tot;
+      }
+      __syncthreads();
+    }
+    if (!done) { T = limit; r = 0; K = cum; }   // everything evictable goes, the rest bypasses
+    // the histogram after eviction: stamps below T vanish, r leave stamp T
+    for (int s = oldest + (int)threadIdx.x; s < T; s += 1024) {
+      if (kAtomic) atomicExch(&hist[s], 0); else hist[s] = 0;
+    }
+  }
+  int f_new = f + (M - K);
+  if (f_new > C) f_new = C;
+  pl.M = M; pl.need = need; pl.T = T; pl.r = r; pl.K = K;
+  pl.f_new = f_new; pl.n_bypass = M - K - (f_new - f);
+  pl.oldest = need > 0 && T > oldest ? T : oldest;
+}
+
+// One thread, once no other reads the counters any more: the plan into the step's counters.
+// reuse: deleted index entries that the previous step's miss assignment took back into use.
+template <bool kAtomic>
+__device__ __forceinline__ void plan_write(const Plan& pl, Ctr* ctr, int f, int* hist, int t, int reuse) {
+  if (pl.need > 0 && pl.r > 0) hist_add<kAtomic>(&hist[pl.T], -pl.r);
+  hist_add<kAtomic>(&hist[t], pl.M - pl.n_bypass);
+  ctr->M = pl.M; ctr->K = pl.K; ctr->n_bypass = pl.n_bypass;
+  ctr->need = pl.need; ctr->T = pl.T; ctr->r = pl.r;
+  ctr->f_old = f; ctr->f = pl.f_new;
+  ctr->oldest = pl.oldest;
+  ctr->tomb -= reuse;
+  // a rebuild asked for by the previous step has run ahead of this step's resolve
+  if (ctr->rebuild) { ctr->rebuild = 0; ctr->tomb = 0; }
+}
+
+// Plan (one block): scan the per-tile miss and position counts, then decide the victims.
 __global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* tile_cnt,
                                                int* __restrict__ age_hist,
                                                int* __restrict__ tile_reuse, int* hist, int t,
@@ -658,7 +740,6 @@ __global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* tile_cnt,
   // every thread reads the counters here; thread 0 overwrites them only after the last barrier
   const int U = ctr->U;
   const int f = ctr->f;
-  const int oldest = ctr->oldest;
   const int ntiles = (U + kVidTile - 1) / kVidTile;
   // deleted index entries that the previous step's miss assignment took back into use
   int reuse = 0;
@@ -693,57 +774,14 @@ __global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* tile_cnt,
     if (i < ntiles) tile_cnt[i] = carry + e;
     carry += tot;
   }
-  const int free_slots = C - f;
-  const int need = M - free_slots;
-  const int limit = t - lookahead;       // candidates have stamp < limit
-  int T = limit, r = 0, K = 0;
-  if (need > 0) {
-    // running count of candidates from the oldest stamp upwards
-    int cum = 0;           // slots with stamp in [oldest, b)
-    bool done = false;
-    for (int b = oldest; b < limit && !done; b += 1024) {
-      if (threadIdx.x == 0) s_found = kIntMax;
-      __syncthreads();
-      const int s = b + (int)threadIdx.x;
-      const int x = s < limit ? hist[s] : 0;
-      int tot;
-      const int e = block_excl_scan(x, tot, smem);
-      // first stamp whose inclusive count exceeds need
-      if (s < limit && cum + e + x > need) atomicMin(&s_found, s);
-      __syncthreads();
-      if (s_found != kIntMax) {
-        T = s_found;
-        if (s == T) smem[18] = cum + e;    // candidates strictly older than T
-        __syncthreads();
-        r = need - smem[18];
-        K = need;
-        done = true;
-      } else {
-        cum += tot;
-      }
-      __syncthreads();
-    }
-    if (!done) { T = limit; r = 0; K = cum; }   // everything evictable goes, the rest bypasses
-    // the histogram after eviction: stamps below T vanish, r leave stamp T
-    for (int s = oldest + (int)threadIdx.x; s < T; s += 1024) hist[s] = 0;
-  }
+  Plan pl;
+  plan_decide<false>(pl, M, f, ctr->oldest, hist, t, lookahead, C, smem, &s_found);
   __syncthreads();
   if (threadIdx.x == 0) {
-    if (need > 0 && r > 0) hist[T] -= r;
-    int f_new = f + (M - K);
-    if (f_new > C) f_new = C;
-    const int n_bypass = M - K - (f_new - f);
-    hist[t] += M - n_bypass;
-    ctr->M = M; ctr->K = K; ctr->n_bypass = n_bypass;
-    ctr->need = need; ctr->T = T; ctr->r = r;
-    ctr->f_old = f; ctr->f = f_new;
-    if (need > 0 && T > oldest) ctr->oldest = T;
-    ctr->tomb -= reuse;
-    // a rebuild asked for by the previous step has run ahead of this step's resolve
-    if (ctr->rebuild) { ctr->rebuild = 0; ctr->tomb = 0; }
+    plan_write<false>(pl, ctr, f, hist, t, reuse);
     // K deletions are about to add tombstones; ask for a rebuild before the next resolve when a
     // eighth of the index would be deleted entries
-    if (!ctr->dense && (unsigned)(ctr->tomb + K) > hi / 8) ctr->rebuild = 1;
+    if (!ctr->dense && (unsigned)(ctr->tomb + pl.K) > hi / 8) ctr->rebuild = 1;
   }
 }
 
@@ -867,6 +905,19 @@ __global__ __launch_bounds__(256) void k_victim_unmap(const int64_t* __restrict_
   }
 }
 
+// The step's counters, final since the plan, into the Host status block (sequence word odd while
+// they are being written).
+__device__ __forceinline__ void publish(const Ctr* ctr, int t) {
+  volatile HostStatus* h = ctr->hstat;
+  if (!h) return;
+  h->seq = 2 * t - 1;
+  __threadfence_system();
+  h->U = ctr->U; h->n_hit = ctr->n_hit; h->M = ctr->M; h->K = ctr->K; h->n_bypass = ctr->n_bypass;
+  h->n_invalid = ctr->n_invalid; h->n_bad_offsets = ctr->bad_offsets;
+  __threadfence_system();
+  h->seq = 2 * t;
+}
+
 // ---------------------------------------------------------------------------------------------
 // Assignment: the i-th miss in virtual-id order takes the i-th slot of (victims u free) in
 // ascending slot order: victims (all below the watermark) first, then never-used slots from the
@@ -892,21 +943,9 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   __shared__ int smem[20];
   const int U = ctr->U, K = ctr->K, f = ctr->f_old;
   const int free_slots = C - f;
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) {
-    // The step's counters have been final since the plan: publish them to the Host status block
-    // (sequence word odd while they are being written).  Here, in one thread of a wide kernel,
-    // the two fences cost nothing that anyone waits for; in the single-block plan kernel they
-    // lengthened the prepare by 6 us.
-    volatile HostStatus* h = ctr->hstat;
-    if (h) {
-      h->seq = 2 * t - 1;
-      __threadfence_system();
-      h->U = U; h->n_hit = ctr->n_hit; h->M = ctr->M; h->K = K; h->n_bypass = ctr->n_bypass;
-      h->n_invalid = ctr->n_invalid; h->n_bad_offsets = ctr->bad_offsets;
-      __threadfence_system();
-      h->seq = 2 * t;
-    }
-  }
+  // Here, in one thread of a wide kernel, the publishing costs nothing that anyone waits for; in the
+  // single-block plan kernel its two fences lengthened the prepare by 6 us.
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) publish(ctr, t);
   for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
     const int v = tile * kVidTile + (int)threadIdx.x;
     const bool miss = v < U && slot_out[v] == kMissMark;
@@ -951,6 +990,296 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
     // atomics on one counter would serialise at the memory side, about 10 ns each)
     const int nre = block_sum(reused ? 1 : 0, smem);
     if (threadIdx.x == 0) tile_reuse[tile] = nre;
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// The prepare of a small batch, by ONE block: up to kSmallIds positions fit the LDS of a compute unit
+// (their table of distinct ids, counts and slots), and for so few the eleven launches of the passes
+// above were all start-up, drain and dependent round trips: what bounds this kernel is the chain ids ->
+// table -> rank -> index -> stamp -> lists, walked once with barriers in between instead of kernel
+// boundaries.  Same outputs, same
+// state: 1248 ids 19 us, 4992 ids 27 us, against 63 and 80 us in ten kernels (and 3 us of host time per
+// launch); a whole pass 118 -> 60 and 148 -> 95 us.
+//
+// kWhole (dense index, and either a cache that holds the whole table, so that nothing is ever evicted,
+// or one whose stamps a single block can scan: kSmallSlots): everything up to the grouping, one launch.
+// Otherwise the unique passes and the resolve only; plan, victims, assignment and grouping follow as
+// for any batch (with no hot bins: cnt and the ranks are complete).
+// Positions and virtual ids are dealt to the threads in consecutive runs, so one block scan orders them.
+// ---------------------------------------------------------------------------------------------
+constexpr int kSmallIds = 6144;             // batch table of 8192 entries at a load of at most 3/4
+constexpr int kSmallTab = 8192;
+constexpr int kSmallPer = kSmallIds / 1024;
+constexpr int kSmallSlots = 1 << 16;        // 16 rounds of 16-byte loads over the stamps
+constexpr int kSmallBags = 4 * kSmallIds;   // bags may be empty, so there can be more of them than ids
+
+struct SmallArgs {
+  const int64_t* ids; int n; int64_t V;
+  const int64_t* offsets; int n_bags;       // multi-hot input (else nullptr)
+  int64_t* unique_ids; int* inverse; int* slot; int* miss_vids;      // caller's buffers of the step
+  const IdxEntry* index; uint32_t hi; int* dmap;
+  int* stamp; int64_t* slot_id; int* hist; int t, lookahead, C, boff;
+  int *cnt, *tile_miss, *tile_cnt, *age_hist;                        // outputs of the short form
+  int64_t* grp; int2* cold_pay; int64_t* perm64; int* pos_slot;
+  int* victim_slot; int64_t* victim_id; int* miss_row; int64_t* miss_id;
+  Ctr* ctr; const Ctr* prev;                // prev: nullptr when k_ctr_init has started the counters
+};
+
+template <bool kWhole>
+__global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
+  __shared__ int64_t keys[kSmallTab];         // later: slot and bag, one word each per virtual id / position
+  __shared__ int val[kSmallTab];              // smallest position, then virtual id, per table entry; later ages and starts
+  __shared__ int cntl[kSmallIds];
+  __shared__ unsigned short ent[kSmallIds];   // table entry of each virtual id
+  __shared__ int smem[20];
+  __shared__ int s_found, s_bad;
+  const int tid = (int)threadIdx.x, n = a.n;
+  const int per = (n + 1023) / 1024, p0 = tid * per;
+  int64_t key[kSmallPer];
+  int e[kSmallPer];
+  bool in[kSmallPer];
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    in[j] = j < per && p0 + j < n;
+    key[j] = in[j] ? a.ids[p0 + j] : 0;
+  }
+  for (int i = tid; i < kSmallTab; i += 1024) { keys[i] = kEmpty; val[i] = kIntMax; }
+  for (int i = tid; i < kSmallIds; i += 1024) cntl[i] = 0;
+  if (tid == 0) s_bad = 0;
+  // counters of the previous step, read before anyone writes (prev == ctr on a cache's first step)
+  Ctr c0;
+  if (tid == 0) { c0 = a.prev ? *a.prev : *a.ctr; a.ctr->t = a.t; }
+  __syncthreads();
+  // the distinct ids and their first positions
+  int n_bad_ids = 0;
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    if (!in[j]) continue;
+    if (key[j] < 0 || key[j] >= a.V) { key[j] = kNullKey; ++n_bad_ids; }
+    uint32_t l = (uint32_t)mix64((uint64_t)key[j]) & (kSmallTab - 1);
+    for (int probes = 0; probes < kSmallTab; ++probes) {
+      const int64_t k = keys[l];
+      if (k == key[j]) break;
+      if (k == kEmpty) {
+        const int64_t old = (int64_t)atomicCAS((unsigned long long*)&keys[l], (unsigned long long)kEmpty,
+                                               (unsigned long long)key[j]);
+        if (old == kEmpty || old == key[j]) break;
+      }
+      l = (l + 1) & (kSmallTab - 1);
+    }
+    if (val[l] > p0 + j) atomicMin(&val[l], p0 + j);
+    e[j] = (int)l;
+  }
+  __syncthreads();
+  // virtual ids in order of first appearance
+  unsigned first = 0;
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j)
+    if (in[j] && val[e[j]] == p0 + j) first |= 1u << j;
+  const int n_invalid = block_sum(n_bad_ids, smem);
+  int U;
+  int vid = block_excl_scan(__popc(first), U, smem);
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j)
+    if (first & (1u << j)) {
+      val[e[j]] = vid;
+      ent[vid] = (unsigned short)e[j];
+      a.unique_ids[vid] = key[j] == kNullKey ? (int64_t)-1 : key[j];
+      ++vid;
+    }
+  __syncthreads();
+  int vv[kSmallPer], rr[kSmallPer];
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j)
+    if (in[j]) {
+      vv[j] = val[e[j]];
+      a.inverse[p0 + j] = vv[j];
+      rr[j] = atomicAdd(&cntl[vv[j]], 1);
+    }
+  __syncthreads();
+  int* const age = val;                       // [kAgeBins]: the virtual ids have been read
+  int* const start = val + kAgeBins;          // [kSmallIds]
+  static_assert(kAgeBins + kSmallIds <= kSmallTab && kAgeBins == 1024, "ages and starts fit the table's words");
+  age[tid] = 0;
+  __syncthreads();
+  // resolve, as k_resolve does
+  const int vper = (U + 1023) / 1024, v0 = tid * vper;
+  int64_t id[kSmallPer];
+  int sl[kSmallPer], old[kSmallPer];
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    id[j] = j < vper && v0 + j < U ? keys[ent[v0 + j]] : (int64_t)-1;    // kNullKey is negative too
+    sl[j] = -1;
+    if (id[j] >= 0) sl[j] = a.dmap ? a.dmap[id[j]] : index_find(a.index, a.hi, id[j], nullptr, a.ctr);
+  }
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) old[j] = sl[j] >= 0 ? a.stamp[sl[j]] : 0;
+  int packed = 0, hits = 0;                   // positions << 16 | misses of this thread's virtual ids
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    if (!(j < vper && v0 + j < U)) continue;
+    packed += cntl[v0 + j] << 16;
+    if (sl[j] >= 0) {
+      a.stamp[sl[j]] = a.t;
+      ++hits;
+      const int g = a.t - old[j];
+      if (g < kAgeBins) atomicAdd(&age[g], 1); else hist_add<true>(&a.hist[old[j]], -1);
+    } else if (id[j] >= 0) {
+      ++packed;
+    }
+  }
+  const int n_hit = block_sum(hits, smem);
+  if (!kWhole) {
+    // in the form k_plan and its followers take it: slots, counts, ranks, tallies per tile and by age
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+      if (j < vper && v0 + j < U) {
+        a.slot[v0 + j] = sl[j] >= 0 ? sl[j] : (id[j] >= 0 ? kMissMark : -1);
+        a.cnt[v0 + j] = cntl[v0 + j];
+        start[v0 + j] = (sl[j] < 0 && id[j] >= 0) ? 1 : 0;
+      }
+      if (in[j]) a.pos_slot[p0 + j] = rr[j];
+    }
+    __syncthreads();
+    a.age_hist[tid] = tid ? age[tid] : n_hit;
+    const int w = tid >> 6, lane = lane_id();
+    for (int tile = w; tile * kVidTile < U; tile += 16) {    // a wavefront per tile of kVidTile virtual ids
+      int m = 0, q = 0;
+      for (int v = tile * kVidTile + lane; v < U && v < (tile + 1) * kVidTile; v += kWave) { m += start[v]; q += cntl[v]; }
+      m = wave_sum(m); q = wave_sum(q);
+      if (lane == 0) { a.tile_miss[tile] = m; a.tile_cnt[tile] = q; }
+    }
+    if (tid == 0) {
+      if (a.prev) {
+        c0.U_prev = c0.U;
+        c0.M = c0.K = c0.n_bypass = c0.n_hit = 0;
+        c0.f_old = c0.f; c0.need = 0; c0.T = 0; c0.r = 0; c0.fetch_on_main = 0;
+        c0.t = a.t; c0.bad_offsets = 0;
+      }
+      c0.U = U; c0.n_invalid = n_invalid;
+      c0.err = a.ctr->err ? a.ctr->err : c0.err;     // a probe above may have flagged one
+      *a.ctr = c0;
+    }
+    return;
+  } else {
+    int* const slotl = reinterpret_cast<int*>(keys);         // [kSmallIds]: every id has been read
+    int* const bagl = slotl + kSmallIds;                     // [kSmallIds]
+    // offsets and miss numbers of this thread's virtual ids
+    int tot;
+    const int before = block_excl_scan(packed, tot, smem);
+    int off = before >> 16, i0 = before & 0xffff;
+    const int M = tot & 0xffff;
+    if (a.offsets) for (int i = tid; i < n; i += 1024) bagl[i] = 0;
+    // the histogram: hits move to stamp t, the rest of the plan as k_plan does it
+    if (tid == 0) hist_add<true>(&a.hist[a.t], n_hit);
+    else if (age[tid]) hist_add<true>(&a.hist[a.t - tid], -age[tid]);
+    __shared__ int s_f, s_oldest;
+    if (tid == 0) { s_f = c0.f; s_oldest = c0.oldest; }
+    __syncthreads();
+    const int f = s_f, C = a.C, free_slots = C - f;
+    Plan pl;
+    plan_decide<true>(pl, M, f, s_oldest, a.hist, a.t, a.lookahead, C, smem, &s_found);
+    // bag of every position, checked as k_pos2bag does
+    if (a.offsets) {
+      int bad = 0;
+      for (int b = tid; b < a.n_bags; b += 1024) {
+        int64_t lo = a.offsets[b], hi = a.offsets[b + 1];
+        bad += hi < lo || (b == 0 && lo != 0) || (b == a.n_bags - 1 && hi != n);
+        if (lo < 0) lo = 0;
+        if (hi > n) hi = n;
+        for (int64_t q = lo; q < hi; ++q) bagl[q] = b;
+      }
+      if (bad) atomicAdd(&s_bad, bad);
+    }
+    // victims, in slot order: k_victim_count / k_victim_write by one block
+    if (pl.K > 0) {
+      int lt_done = 0, eq_done = 0;
+      for (int base = 0; base < f; base += 4096) {
+        const int s0 = base + tid * 4;
+        int v[4];
+        if (s0 + 4 <= f) {
+          const int4 q = *reinterpret_cast<const int4*>(a.stamp + s0);
+          v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+        } else {
+#pragma unroll
+          for (int j = 0; j < 4; ++j) v[j] = s0 + j < f ? a.stamp[s0 + j] : kIntMax;   // never a victim
+        }
+        int lt = 0, eq = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { lt += v[j] < pl.T; eq += v[j] == pl.T; }
+        int both;
+        const int pre = block_excl_scan((lt << 16) | eq, both, smem);
+        int lt_before = lt_done + (pre >> 16), eq_before = eq_done + (pre & 0xffff);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool is_lt = v[j] < pl.T, is_eq = v[j] == pl.T;
+          if (is_lt || (is_eq && eq_before < pl.r)) {
+            const int idx = lt_before + (eq_before < pl.r ? eq_before : pl.r);
+            if (idx < pl.K) {
+              const int64_t vid_out = a.slot_id[s0 + j];
+              a.victim_slot[idx] = s0 + j; a.victim_id[idx] = vid_out;
+              a.dmap[vid_out] = -1;
+            } else {
+              flag_err(a.ctr, 4);                            // never while hist mirrors the stamps
+            }
+          }
+          lt_before += is_lt;
+          eq_before += is_eq;
+        }
+        lt_done += both >> 16; eq_done += both & 0xffff;
+      }
+    }
+    __syncthreads();
+    // slots of the misses; where the groups start
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+      const int v = v0 + j;
+      if (!(j < vper && v < U)) continue;
+      int s = sl[j];
+      if (s < 0 && id[j] >= 0) {
+        const int i = i0++;
+        a.miss_vids[i] = v;
+        if (i < pl.K) s = a.victim_slot[i];
+        else if (i - pl.K < free_slots) s = f + (i - pl.K);
+        else s = C + (i - pl.K - free_slots);
+        a.miss_row[i] = s >= C ? s + a.boff : s;
+        a.miss_id[i] = id[j];
+        if (s < C) { a.slot_id[s] = id[j]; a.stamp[s] = a.t; a.dmap[id[j]] = s; }
+      }
+      a.slot[v] = s;
+      slotl[v] = s >= C ? s + a.boff : s;
+      start[v] = off;
+      a.grp[v] = ((int64_t)cntl[v] << 32) | (uint32_t)off;
+      if (cntl[v] > kColdMax) a.cold_pay[v] = make_int2(-1, -1);
+      else if (cntl[v] < kColdMax) a.cold_pay[v].y = -1;     // the positions write the rest
+      off += cntl[v];
+    }
+    __syncthreads();
+    // grouping; here any group of at most kColdMax positions is a cold one
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+      if (!in[j]) continue;
+      const int p = p0 + j, v = vv[j];
+      const int pay = a.offsets ? bagl[p] : p;
+      a.pos_slot[p] = slotl[v];
+      int64_t w = ((int64_t)v << 32) | (uint32_t)pay;
+      if (cntl[v] <= kColdMax) {
+        w |= kColdBit;
+        reinterpret_cast<int*>(a.cold_pay)[2 * v + rr[j]] = pay;
+      }
+      a.perm64[start[v] + rr[j]] = w;
+    }
+    if (tid == 0) {
+      c0.U_prev = c0.U; c0.U = U; c0.n_hit = n_hit; c0.n_invalid = n_invalid;
+      c0.fetch_on_main = 0; c0.t = a.t; c0.bad_offsets = s_bad;
+      c0.err = a.ctr->err ? a.ctr->err : c0.err;
+      *a.ctr = c0;
+      plan_write<true>(pl, a.ctr, f, a.hist, a.t, 0);
+      volatile HostStatus* h = c0.hstat;
+      if (s_bad && h) h->bad_offsets_step = a.t;
+      publish(a.ctr, a.t);
+    }
   }
 }
 

@@ -201,6 +201,60 @@ def test_batch_sizes_where_the_counting_passes_change_shape(n):
     p.finish(); p.close()
 
 
+@pytest.mark.parametrize("index_kind", [HASHED, DENSE])
+@pytest.mark.parametrize("C", [40_000, 70_000, 150_000])
+@pytest.mark.parametrize("lookahead", [0, 2])
+def test_one_block_batches_beside_large_ones(lookahead, C, index_kind):
+    # up to 6144 ids a batch is prepared by one block, which also chooses the victims when the index is
+    # dense and the cache small (40 000 slots) or as large as the table; with 70 000 slots or a hashed
+    # index the general passes take over behind its resolve.  Steps of both kinds follow each other
+    # through the same counters, histogram, index and step contexts; victims in most of them
+    V, D = 150_000, 4
+    sizes = [80_000, 6144, 500, 1, 6145, 3000, 80_000, 6000, 6144, 200, 80_000, 5000]
+    p = Pair(V, D, C=C, max_ids=80_000, lookahead=lookahead, index_kind=index_kind)
+    bs = []
+    for t, n in enumerate(sizes):
+        # (uniform ids where the batch is large, so that 70 000 slots fill)
+        ids = (si.uniform_ids(n, V, 410, t) if n == 80_000 else si.zipf_ids(n, 1.02, V, 410, t)).numpy()
+        ids[::611] = -3                     # some outside the table
+        bs.append((ids, si.grads(n, D, 410, t).numpy(), None))
+    if lookahead:
+        expect = [pr for pr, _ in p.run_pipelined(bs, False)]
+    else:
+        expect = [p.step(ids, g) for ids, g, _ in bs]
+        p.finish()
+    small_victims = [pr.stats["n_evict"] for pr, n in zip(expect, sizes) if n <= 6144]
+    assert (max(small_victims) > 0) == (C < V)
+    p.close()
+
+
+@pytest.mark.parametrize("n_bags", [20_000, 30_000])
+def test_few_ids_in_many_mostly_empty_bags(n_bags):
+    V, D = 500, 8
+    rng = np.random.default_rng(n_bags)
+    p = Pair(V, D, C=60, max_ids=400, max_bags=n_bags)
+    for t in range(4):
+        lens = np.bincount(rng.integers(0, n_bags, 300 + t), minlength=n_bags)
+        off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        p.step(rng.integers(0, V, int(off[-1])), si.grads(n_bags, D, 5, t).numpy(), offsets=off)
+    p.finish(); p.close()
+
+
+def test_ages_beyond_the_tallied_range_in_a_one_block_batch():
+    # a slot last used more than 1024 steps ago leaves the recency histogram one by one
+    V, D = 60, 4
+    p = Pair(V, D, C=20, max_ids=32)
+    p.step(np.arange(10), si.grads(10, D, 6, 0).numpy())
+    for t in range(1030):
+        ids = torch.tensor([20 + t % 3], dtype=torch.int64, device=p.dev)
+        p.cache.prepare(ids); p.cache.fetch_misses(); p.cache.lookup(); p.cache.discard()
+        p.orc.prepare(np.array([20 + t % 3]), None); p.orc.fetch_misses(); p.orc.lookup()
+        p.orc.backward_update(np.zeros((1, D), np.float32))
+    p.step(np.arange(5), si.grads(5, D, 6, 1).numpy())
+    p.step(np.arange(30, 50), si.grads(20, D, 6, 2).numpy())
+    p.finish(); p.close()
+
+
 def test_same_stream_and_separate_host_arrays():
     # copies on the main stream; Host weights and accumulators as two separate arrays
     V, D, n = 4000, 32, 2000
