@@ -105,6 +105,7 @@ struct StepCtx {
   hipEvent_t ev_fetched = nullptr;    // the side-stream launch of the step's Host copies has run
   bool updated = false;               // backward_update has been enqueued for this step
   bool discarded = false;             // freed by sfc_discard: the step's copies may still be running
+  bool joined = false;                // the main stream is behind the side-stream launch of the step's copies
   // pipelined mode: the second launch of the Host copies, due on the main stream behind the
   // update of step main_after (see k_swap_rows); older1 .. older3 = counters of the older steps
   // that were still in flight when the fetch was issued
@@ -306,14 +307,20 @@ constexpr int kSwapBlocks = 32;
 // published in the status block, which is a step or two old.
 constexpr int kSwapBlocksWide = 128;
 constexpr int64_t kSwapWideBytes = (int64_t)256 << 20;
+// Lookahead 0: steps whose misses (judged as above) are at most this many bytes run their copies on
+// the main stream: the way there and back took 33 us of GPU time and 20 us of host time between the
+// prepare and the lookup, as much as 1 MiB each way takes on the link (a pass of 1024 x 39 ids with 0.88 MB
+// of misses: 193 -> 147 us; of 128 x 39 with none: 95 -> 49).
+constexpr int64_t kSwapMainBytes = (int64_t)1 << 20;
 
 // One launch of the Host<->cache copies of a step on stream s (see k_swap_rows for the two
 // launches of pipelined mode).
 int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   EventPair ep{};
   int rc;
-  // the copies read the step's counters, miss list and victim list: its prepare comes first
-  if (s != c->prep) HIPCHK(hipStreamWaitEvent(s, x->ev_prepared, 0));
+  // the copies read the step's counters, miss list and victim list: its prepare comes first (with
+  // lookahead 0 it is main-stream work, which sfc_fetch_misses has put s behind)
+  if (c->nctx > 1 && s != c->prep) HIPCHK(hipStreamWaitEvent(s, x->ev_prepared, 0));
   if ((rc = prof_begin(c, P_FETCH, s, &ep))) return rc;
   ep.extra = main_variant != 0;          // the second launch of a step: same call
   const int64_t recent_bytes = (int64_t)((const volatile HostStatus*)c->hstat)->M * (c->d4 + c->s4) * 16;
@@ -325,7 +332,15 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_FETCH, s, &ep))) return rc;
   if (main_variant) x->main_pending = false;
-  else HIPCHK(hipEventRecord(x->ev_fetched, s));
+  else if (s != c->st) HIPCHK(hipEventRecord(x->ev_fetched, s));
+  return SFC_OK;
+}
+
+// The main stream behind the side-stream launch of the step's copies (once per step: every
+// cross-stream wait costs the host and the GPU microseconds).
+int join_copies(sfc_cache* c, StepCtx* x) {
+  if (!x->joined) HIPCHK(hipStreamWaitEvent(c->st, x->ev_fetched, 0));
+  x->joined = true;
   return SFC_OK;
 }
 
@@ -333,8 +348,7 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
 int rows_ready(sfc_cache* c, StepCtx* x) {
   int rc;
   if (x->main_pending && (rc = launch_swap(c, x, c->st, 1))) return rc;
-  if (c->side != c->st) HIPCHK(hipStreamWaitEvent(c->st, x->ev_fetched, 0));
-  return SFC_OK;
+  return join_copies(c, x);
 }
 
 // common[v] = segment sum of d_grad over the step's grouping: the stream, then the block-edge partials.
@@ -713,7 +727,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
       if (x->discarded) HIPCHK(hipStreamWaitEvent(c->ins, x->ev_fetched, 0));
       if (c->resolved_once) HIPCHK(hipStreamWaitEvent(c->ins, c->ev_resolved, 0));
     }
-  } else if (x->discarded && c->side != c->st) {
+  } else if (x->discarded && !x->joined) {
     // lookahead 0: a step that was given up without a lookup left nothing on the main stream that
     // waits for its copies, which may still be reading the lists that this prepare rewrites
     HIPCHK(hipStreamWaitEvent(s, x->ev_fetched, 0));
@@ -789,7 +803,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   if (!whole && (rc = plan_and_group(c, x, sg, cnt, cnt_rep))) return rc;
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_PREPARE, s, &ep))) return rc;
-  HIPCHK(hipEventRecord(x->ev_prepared, s));
+  if (c->nctx > 1) HIPCHK(hipEventRecord(x->ev_prepared, s));
   return SFC_OK;
 }
 
@@ -810,13 +824,20 @@ int sfc_fetch_misses(sfc_cache* c) {
     else if (o->t == x->t - 3) x->older3 = o->ctr;
     if (o->t > x->main_after) x->main_after = o->t;
   }
-  if (c->side != c->st) {
+  // With lookahead 0 the copies stand between the prepare and the lookup of the main stream, and the
+  // way to the side stream and back costs about as much as kSwapMainBytes take on the link: a step
+  // that moves less stays on the main stream.
+  const volatile HostStatus* h = c->hstat;
+  const bool on_main = c->side == c->st ||
+                       (c->nctx == 1 && h->seq != 0 && (int64_t)h->M * (c->d4 + c->s4) * 16 <= kSwapMainBytes);
+  if (!on_main) {
     // everything the main stream has been given so far comes first: this step's prepare
     // (lookahead 0), older updates and their second launches
     HIPCHK(hipEventRecord(c->ev_tmp, c->st));
     HIPCHK(hipStreamWaitEvent(c->side, c->ev_tmp, 0));
   }
-  int rc = launch_swap(c, x, c->side, 0);
+  x->joined = on_main;
+  int rc = launch_swap(c, x, on_main ? c->st : c->side, 0);
   if (rc) return rc;
   x->main_pending = x->older1 || x->older2 || x->older3;
   x->state = FETCHED;
@@ -900,7 +921,7 @@ int sfc_segment_sum_static(sfc_cache* c, const float* d_grad, float* d_common_gr
   // could create profiling events
   if (x->main_pending)
     return fail(SFC_ESTATE, "the step's rows are still due on the main stream: call sfc_lookup first");
-  if (c->side != c->st) HIPCHK(hipStreamWaitEvent(c->st, x->ev_fetched, 0));
+  if ((rc = join_copies(c, x))) return rc;
   // every slot that k_seg_finish reads is written by k_seg_stream in the same call: nothing to clear
   double* bp = (double*)base;
   int* bp_vid = (int*)((unsigned char*)base + sums);
