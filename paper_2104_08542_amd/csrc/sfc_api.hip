@@ -141,11 +141,13 @@ struct sfc_cache {
   IdxEntry* index = nullptr; uint32_t hi = 0;   // cache index, hashed kind
   int* dmap = nullptr;                          // cache index, dense kind: [V] slot per id or -1 (else nullptr)
   int* hist = nullptr; int hist_len = 0;        // [max_steps + 2]
-  UEntry* utab = nullptr; int* uvid = nullptr;  // batch table [2*max_ids]: key + first position; vid
+  // batch table [2*max_ids]: id and smallest position, 8 bytes per entry (16: see `wide`); vid per entry
+  uint64_t* utab = nullptr; int* uvid = nullptr;
+  bool wide = false;                            // entries of two words (WideTab)
   int* hslot = nullptr;                         // [max_ids]
   int* vid_hslot = nullptr;                     // [max_ids]
   int* blk_cnt = nullptr;                       // [max_ids / kPosChunk + 1]
-  unsigned char* first = nullptr;               // [max_ids / 8 + ..] bit per position: first appearance of its id
+  unsigned* first = nullptr;                    // [max_ids / 32 + ..] bit per position: first appearance of its id; zero between steps
   int *tile_lt = nullptr, *tile_eq = nullptr;   // [C / kPosChunk + 1]
   int* tile_miss = nullptr;                     // [max_ids / kVidTile + 1]
   // positions per virtual id [max_ids] and its copies for the lowest virtual ids [kHotRep, kHotBins]:
@@ -200,6 +202,13 @@ void fill(hipStream_t s, T* p, int64_t n, T v) {
   int64_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(k_fill<T>, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
+}
+
+// bits that hold any position of a batch of n
+int pos_bits(int64_t n) {
+  int b = 1;
+  while (b < 62 && ((int64_t)1 << b) < n) ++b;
+  return b;
 }
 
 int grid_for(int64_t items, int per_block, int cap) {
@@ -605,12 +614,14 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     if ((rc = dalloc(c, &c->index, (int64_t)c->hi))) goto bad;
     if (dense && (rc = dalloc(c, &c->dmap, c->V))) goto bad;
     if ((rc = dalloc(c, &c->hist, (int64_t)c->hist_len))) goto bad;
-    if ((rc = dalloc(c, &c->utab, hu))) goto bad;
+    // a position of the largest batch and the largest tag (V) side by side in 64 bits, below all ones
+    c->wide = (uint64_t)c->V >= (~0ull >> pos_bits(c->max_ids));
+    if ((rc = dalloc(c, &c->utab, c->wide ? 2 * hu : hu))) goto bad;
     if ((rc = dalloc(c, &c->uvid, hu))) goto bad;
     if ((rc = dalloc(c, &c->hslot, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->vid_hslot, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->blk_cnt, c->max_ids / kPosChunk + 2))) goto bad;
-    if ((rc = dalloc(c, &c->first, (c->max_ids / kPosChunk + 1) * (kPosChunk / 8)))) goto bad;
+    if ((rc = dalloc(c, &c->first, (c->max_ids / kPosChunk + 1) * (kPosChunk / 32)))) goto bad;
     if ((rc = dalloc(c, &c->tile_lt, c->C / kPosChunk + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_eq, c->C / kPosChunk + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_miss, c->max_ids / kVidTile + 2))) goto bad;
@@ -665,7 +676,9 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     fill<int>(s, c->n_unique, 1, 0);
     fill<int>(s, c->tile_reuse, c->max_ids / kVidTile + 2, 0);
     UEntry uempty; uempty.key = kEmpty; uempty.minpos = kIntMax; uempty.pad = 0;
-    fill<UEntry>(s, c->utab, hu, uempty);
+    if (c->wide) fill<UEntry>(s, (UEntry*)c->utab, hu, uempty);
+    else fill<uint64_t>(s, c->utab, hu, ~0ull);
+    fill<unsigned>(s, c->first, (c->max_ids / kPosChunk + 1) * (kPosChunk / 32), 0u);
     Ctr z; memset(&z, 0, sizeof z); z.oldest = 1; z.hstat = c->d_hstat; z.dense = dense ? 1 : 0;
     for (int k = 0; k < c->nctx; ++k)
       if ((e = hipMemcpyAsync(c->ctx[k].ctr, &z, sizeof z, hipMemcpyHostToDevice, s)) != hipSuccess) {
@@ -752,19 +765,30 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   if (small) {
     // its unique passes are part of the kernel below
   } else if (n > 0) {
-    const int nub = (n + kUniqChunk - 1) / kUniqChunk, head = nub < kHeadBlocks ? nub : kHeadBlocks;
-    hipLaunchKernelGGL(k_uniq_insert, dim3(head), dim3(256), 0, su, d_ids, n, c->V, c->utab, hu,
-                       c->hslot, c->n_invalid, 0);
-    if (nub > head)
-      hipLaunchKernelGGL(k_uniq_insert, dim3(nub - head), dim3(256), 0, su, d_ids, n, c->V, c->utab,
-                         hu, c->hslot, c->n_invalid, head);
-    hipLaunchKernelGGL(k_uniq_count, dim3(nchunk), dim3(256), 0, su, c->hslot, c->utab, n, c->first, c->blk_cnt);
-    hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk), dim3(256), 0, su, d_ids, c->V, c->hslot, c->first, n,
-                       c->blk_cnt, d_unique_ids, c->uvid, c->vid_hslot, cnt, c->n_unique);
+    const int nub = (n + kUniqChunk - 1) / kUniqChunk, head = nub <= kHeadMin ? nub : kHeadBlocks;
+    auto insert = [&](int blocks, int block0) {
+      if (c->wide) {
+        WideTab tab{(UEntry*)c->utab, 0, c->V};
+        hipLaunchKernelGGL(k_uniq_insert<WideTab>, dim3(blocks), dim3(256), 0, su, d_ids, n, tab, hu,
+                           c->hslot, c->first, c->n_invalid, block0);
+      } else {
+        PackedTab tab{c->utab, pos_bits(n), c->V};
+        hipLaunchKernelGGL(k_uniq_insert<PackedTab>, dim3(blocks), dim3(256), 0, su, d_ids, n, tab, hu,
+                           c->hslot, c->first, c->n_invalid, block0);
+      }
+    };
+    insert(head, 0);
+    if (nub > head) insert(nub - head, head);
+    const int* const counts = n > kCountMin ? c->blk_cnt : nullptr;
+    if (counts)
+      hipLaunchKernelGGL(k_uniq_count, dim3((nchunk + 3) / 4), dim3(256), 0, su, (const unsigned*)c->first,
+                         nchunk, c->blk_cnt);
+    hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk), dim3(256), 0, su, d_ids, c->V, c->hslot,
+                       (const unsigned*)c->first, n, counts, d_unique_ids, c->uvid, c->vid_hslot, cnt, c->n_unique);
     auto inv = sg.threads == 256 ? k_uniq_inverse<kFewBins, 4, 256>
              : sg.threads == 512 ? k_uniq_inverse<kHotBins, 8, 512> : k_uniq_inverse<kHotBins, 8, 1024>;
     hipLaunchKernelGGL(inv, dim3(sg.blocks), dim3(sg.threads), 0, su, c->hslot, c->uvid, n, d_inverse, cnt,
-                       cnt_rep, sg.nrep, x->pos_slot);
+                       cnt_rep, sg.nrep, x->pos_slot, c->first);
   } else {
     fill<int>(su, c->n_unique, 1, 0);
   }
@@ -795,7 +819,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   } else {
     const int gr = grid_for(n, kVidTile, kResolveGrid);
     hipLaunchKernelGGL(k_resolve, dim3(gr), dim3(256), 0, s, d_unique_ids, c->vid_hslot, c->utab,
-                       c->index, c->hi, c->dmap, c->stamp, c->hist, x->t, d_slot, c->tile_miss, cnt, cnt_rep,
+                       c->wide ? 1 : 0, c->index, c->hi, c->dmap, c->stamp, c->hist, x->t, d_slot, c->tile_miss, cnt, cnt_rep,
                        sg.bins, sg.nrep, c->tile_cnt, c->age_hist, x->ctr,
                        c->dmap ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid);
   }

@@ -78,8 +78,8 @@ __device__ __forceinline__ void flag_err(Ctr* ctr, int code) {
   if (h) { h->err_step = ctr->t; h->err = code; }
 }
 
-// Entry of the per-step batch table: key and the smallest position that carries it, one 16-byte
-// access for both.
+// Entry of the per-step batch table where an id and a position do not fit 64 bits together (WideTab):
+// key and the smallest position that carries it, one 16-byte access for both.
 struct __attribute__((aligned(16))) UEntry {
   int64_t key;    // id, kEmpty or kNullKey
   int32_t minpos; // kIntMax when unset

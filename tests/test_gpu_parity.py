@@ -255,6 +255,40 @@ def test_ages_beyond_the_tallied_range_in_a_one_block_batch():
     p.finish(); p.close()
 
 
+def test_batch_table_whose_entries_take_two_words():
+    # an id and a position share one 64-bit word of the batch table unless the id range is too large for
+    # that: a cache told of 2^61 Host rows (all ids used lie in the rows that exist) gives what one
+    # with the true row count gives
+    import paper_2104_08542_amd as sfc
+    V, D, n = 30_000, 8, 20_011
+    caches = []
+    for rows in (V, 1 << 61):
+        tab = sfc.HostTable(V, D)
+        tab.w_t[:] = si.table_rows(5, 0, V, D)
+        tab.acc[:] = 0.1
+        tab.rows = rows
+        caches.append(sfc.Cache(tab, 9000, n, index_kind=HASHED))
+    for t in range(4):
+        ids = si.zipf_ids(n, 1.1, V, 53, t)
+        ids[::97] = -1
+        d_ids, g = ids.to("cuda:0"), si.grads(n, D, 53, t).to("cuda:0")
+        got = []
+        for c in caches:
+            c.prepare(d_ids); c.fetch_misses()
+            st = c.stats()
+            U = st["n_unique"]
+            got.append((st, c.unique_ids[:U].cpu(), c.inverse[:n].cpu(), c.slot[:U].cpu(), c.lookup().cpu()))
+            c.backward_update(g)
+        assert got[0][0] == got[1][0]
+        for a, b in zip(got[0][1:4], got[1][1:4]):
+            assert torch.equal(a, b)
+        # rows a step later may differ in the last place: the order of a frequent id's fp64 sum is free
+        assert torch.allclose(got[0][4], got[1][4], rtol=1e-6, atol=1e-7)
+    for c in caches:
+        assert c.verify() == [0, 0, 0, 0]
+        c.close(); c.table.free()
+
+
 def test_same_stream_and_separate_host_arrays():
     # copies on the main stream; Host weights and accumulators as two separate arrays
     V, D, n = 4000, 32, 2000
