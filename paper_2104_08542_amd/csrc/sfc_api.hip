@@ -306,12 +306,15 @@ StepCtx* training_ctx(sfc_cache* c) {
   return best;
 }
 
-// The copies are bound by the host link: 32 blocks x 256 lanes x 16 bytes in flight saturate it
-// (measured), and a wider grid only slows the kernels that run beside it on the other streams.
+// The copies are bound by the host link: with other kernels beside them (lookahead > 0) 32 blocks x 256
+// lanes x 16 bytes in flight saturate it well enough, and a wider grid only slows those kernels.
 constexpr int kSwapBlocks = 32;
 // A step that moves hundreds of megabytes over the link (a miss-dominated workload) is bound by
 // the link whatever else runs: there a wider grid is worth its disturbance of the other streams
-// (128 blocks: 16.3 against 18.6 ms per step with 4e6 misses of 128 bytes per step).  The host
+// (128 blocks: 16.3 against 18.6 ms per step with 4e6 misses of 128 bytes per step).  With lookahead 0
+// the copies have the GPU to themselves, and the wider grid is the faster one at every size (128 against
+// 32 blocks: 20.6e3 misses of 960 bytes 532 / 590 us, 52.7e3 of 128 bytes 236 / 256, 58.2e3 of 256
+// 394 / 412, 1.05e6 of 128 3749 / 4130; 64 blocks 541 / 250 / 408 / 3767, 256 blocks as 128).  The host
 // cannot know a step's misses without waiting, so it goes by the latest count the device has
 // published in the status block, which is a step or two old.
 constexpr int kSwapBlocksWide = 128;
@@ -333,7 +336,7 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   if ((rc = prof_begin(c, P_FETCH, s, &ep))) return rc;
   ep.extra = main_variant != 0;          // the second launch of a step: same call
   const int64_t recent_bytes = (int64_t)((const volatile HostStatus*)c->hstat)->M * (c->d4 + c->s4) * 16;
-  const int swap_blocks = recent_bytes > kSwapWideBytes ? kSwapBlocksWide : kSwapBlocks;
+  const int swap_blocks = c->nctx == 1 || recent_bytes > kSwapWideBytes ? kSwapBlocksWide : kSwapBlocks;
   hipLaunchKernelGGL(k_swap_rows, dim3(grid_for(x->n_ids * (c->d4 + c->s4), 256, swap_blocks)),
                      dim3(256), 0, s,
                      x->miss_row, x->miss_id, x->victim_id, (float4*)c->cw, (float4*)c->ca, c->host,
@@ -380,7 +383,7 @@ int seg_launch(sfc_cache* c, StepCtx* x, const float* d_grad, float* d_common, d
                fused ? (int*)x->cold_pay : (int*)nullptr);
   if (n_slots) *n_slots = 2 * nblk;
   if (fused) return SFC_OK;
-  LAUNCH_TIMED(c, P_SEG_FINISH, timed, k_seg_finish, dim3((unsigned)(2 * nblk)), dim3(256), c->st,
+  LAUNCH_TIMED(c, P_SEG_FINISH, timed, k_seg_finish, dim3((unsigned)edge_blocks(2 * nblk, c->d4)), dim3(256), c->st,
                (const double*)bp, (const int*)bp_vid, 2 * nblk, c->d4, (float4*)d_common);
   return SFC_OK;
 }
@@ -931,8 +934,8 @@ int sfc_segment_sum_static(sfc_cache* c, const float* d_grad, float* d_common_gr
   const SegGeom g = seg_geom(c->D, x->n_ids > 0 ? x->n_ids : 1);
   const int64_t nblk = (g.waves + 3) / 4;
   const int64_t sums = 2 * nblk * c->D * (int64_t)sizeof(double);
-  const int64_t need = sums + 2 * nblk * (int64_t)sizeof(int);
-  if (need > (int64_t)SFC_STATIC_SCRATCH_BYTES) {
+  const int64_t need = seg_scratch_limit(c->D, x->n_ids > 0 ? x->n_ids : 1);
+  if (need > (int64_t)SFC_STATIC_SCRATCH_BYTES || sums + 2 * nblk * (int64_t)sizeof(int) > (int64_t)SFC_STATIC_SCRATCH_BYTES) {
     char msg[160];
     snprintf(msg, sizeof msg, "sfc_segment_sum_static: this step needs %lld bytes of scratch, the "
              "fixed array holds %d", (long long)need, (int)SFC_STATIC_SCRATCH_BYTES);

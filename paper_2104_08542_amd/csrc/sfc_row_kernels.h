@@ -326,6 +326,8 @@ constexpr int kSegChunk = SFC_SEG_CHUNK;        // entries per group per loop it
 #endif
 constexpr int kSegTargetWaves = 256 * SFC_SEG_WAVES;
 
+constexpr int kSegMinWaves = 1024;
+
 struct SegGeom { int G, L, waves; };
 // L is chosen so that the stream has about kSegTargetWaves wavefronts.
 inline SegGeom seg_geom(int D, int64_t n) {
@@ -334,14 +336,29 @@ inline SegGeom seg_geom(int D, int64_t n) {
   if (g.G < 1) g.G = 1;
   const int64_t target_waves = kSegTargetWaves;
   int64_t L = (n + g.G * target_waves - 1) / (g.G * target_waves);
-  // never below 32 entries per span, except for batches too small to fill the chip that way
-  // (a 4e4-position batch: 13 against 21 us with spans of 8)
-  const int64_t lmin = n < ((int64_t)1 << 18) ? 8 : 32;
+  // never below 32 entries per span (fewer partial sums, fewer block edges for the kernel behind to
+  // chain), except where that leaves the chip with fewer than kSegMinWaves wavefronts: then 16 or 8.
+  // Stream + optimizer us with spans of 8 / 16 / 32: 40e3 positions of dim 16 21.1 / 21.8 / 22.7, 195e3 of
+  // dim 80 44.3 / 39.5 / 39.0, 213e3 of dim 128 36.0 / 33.7 / 32.4, 639e3 of dim 16 46.6 / 44.9 / 44.4.
+  int64_t lmin = 32;
+  while (lmin > 8 && n < g.G * lmin * kSegMinWaves) lmin /= 2;
   if (L < lmin) L = lmin;
   L = (L + kSegChunk - 1) / kSegChunk * kSegChunk;
   g.L = (int)L;
   g.waves = (int)((n + (int64_t)g.G * L - 1) / ((int64_t)g.G * L));
   return g;
+}
+
+// Bytes of scratch by which sfc_segment_sum_static accepts or refuses a batch: that of spans of 8 entries
+// below 2^18 positions and 32 above (the stream above never takes more where this fits).
+inline int64_t seg_scratch_limit(int D, int64_t n) {
+  const int64_t G = 64 / (D / 4) < 1 ? 1 : 64 / (D / 4);
+  int64_t L = (n + G * kSegTargetWaves - 1) / (G * kSegTargetWaves);
+  const int64_t lmin = n < ((int64_t)1 << 18) ? 8 : 32;
+  if (L < lmin) L = lmin;
+  L = (L + kSegChunk - 1) / kSegChunk * kSegChunk;
+  const int64_t blocks = ((n + G * L - 1) / (G * L) + 3) / 4;
+  return 2 * blocks * (D * (int64_t)sizeof(double) + (int64_t)sizeof(int));
 }
 
 struct D4 { double x, y, z, w; };
@@ -353,40 +370,60 @@ __device__ __forceinline__ float4 d4_round(const D4& a) {
   return make_float4((float)a.x, (float)a.y, (float)a.z, (float)a.w);
 }
 
-// Chains a list of partial slots (even = head of a span, odd = its tail; vid -1 = none).  Runs that
-// begin at an odd slot and end at an even one lie inside the list: they are complete and stored.
-// A run open at the left edge is returned as (bv0, b0), one open at the right edge as (bv1, b1);
-// a run open at both edges returns its sum in b0 and a zero marker in b1.
-__device__ __forceinline__ void chain_slots(int nslots, const int* __restrict__ vids,
+// A list of partial slots (even = head of a span, odd = its tail; vid -1 = none): the sum of the run of
+// equal vids that begins at slot j, four slots per step; end = the slot behind it.
+__device__ __forceinline__ D4 slot_run_sum(int j, int nslots, const int* __restrict__ vids,
+                                           const double* __restrict__ sums, int D, int c4, int& end) {
+  D4 s; d4_zero(s);
+  const int v = vids[j];
+  bool on = true;
+  end = j;
+  for (int k = j; on && k < nslots; k += 4) {
+    int vk[4];
+    D4 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int kk = k + u < nslots ? k + u : nslots - 1;
+      vk[u] = k + u < nslots ? vids[kk] : -1;
+      const double* q = &sums[kk * D + 4 * c4];
+      x[u].x = q[0]; x[u].y = q[1]; x[u].z = q[2]; x[u].w = q[3];
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      on = on && vk[u] == v;
+      if (on) { s.x += x[u].x; s.y += x[u].y; s.z += x[u].z; s.w += x[u].w; ++end; }
+    }
+  }
+  return s;
+}
+
+// Chains such a list of 2 * nspan slots, a lane group per span, all spans at once (one group that walked
+// the whole list, a chain of dependent LDS reads at the end of every wavefront and block, made the stream
+// 64.3 instead of 61.7 us at 2.56e6 positions of dim 32, 24.9 instead of 21.1 at 639e3 of dim 16).  A run begins at a tail,
+// and belongs to the group of that span, or at slot 0, then it belongs to group 0.  A run that begins at
+// a tail and ends at a head lies inside the list: it is complete and stored.  What is open at the left
+// edge is returned as (bv0, b0) in group 0; what is open at the right edge as (bv1, b1) in the group
+// that owns it (own1), if there is any (last_v >= 0); a run open at both edges has its sum in b0 and a
+// zero in b1.
+struct ChainEdges { int bv0, bv1, last_v; bool own1; D4 b0, b1; };
+__device__ __forceinline__ void chain_slots(int span, int nspan, const int* __restrict__ vids,
                                             const double* __restrict__ sums, int D, int d4, int c4,
-                                            float4* __restrict__ common, int& bv0, D4& b0, int& bv1,
-                                            D4& b1) {
-  bv0 = -1; bv1 = -1;
-  d4_zero(b0); d4_zero(b1);
-  D4 run; d4_zero(run);
-  int rv = -1;
-  bool rbegun = false;
-  for (int j = 0; j <= nslots; ++j) {
-    const int v = j < nslots ? vids[j] : -1;
-    if (v != rv) {
-      if (rv >= 0) {
-        const bool ended = ((j - 1) & 1) == 0;      // the run's last slot was a head slot
-        if (rbegun && ended) {
-          common[(int64_t)rv * d4 + c4] = d4_round(run);
-        } else if (!rbegun) {
-          bv0 = rv; b0 = run;
-          if (!ended) bv1 = rv;
-        } else {
-          bv1 = rv; b1 = run;
-        }
-      }
-      rv = v; d4_zero(run);
-      rbegun = (j & 1) == 1;
-    }
-    if (v >= 0) {
-      const double* q = &sums[j * D + 4 * c4];
-      run.x += q[0]; run.y += q[1]; run.z += q[2]; run.w += q[3];
-    }
+                                            float4* __restrict__ common, ChainEdges& e) {
+  e.bv0 = -1; e.bv1 = -1; e.own1 = false;
+  d4_zero(e.b0); d4_zero(e.b1);
+  const int nslots = 2 * nspan;
+  e.last_v = vids[nslots - 1];
+  int end;
+  const int v = vids[2 * span + 1];
+  if (v >= 0 && vids[2 * span] != v) {
+    const D4 s = slot_run_sum(2 * span + 1, nslots, vids, sums, D, c4, end);
+    if (((end - 1) & 1) == 0) common[(int64_t)v * d4 + c4] = d4_round(s);
+    else { e.bv1 = v; e.b1 = s; e.own1 = true; }
+  }
+  if (span == 0 && vids[0] >= 0) {
+    e.bv0 = vids[0];
+    e.b0 = slot_run_sum(0, nslots, vids, sums, D, c4, end);
+    if (((end - 1) & 1) != 0) { e.bv1 = e.bv0; d4_zero(e.b1); e.own1 = true; }
   }
 }
 
@@ -516,113 +553,182 @@ __global__ __launch_bounds__(256) void k_seg_stream(const float4* __restrict__ g
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-  int wbv0 = -1, wbv1 = -1;
-  D4 wb0, wb1;
-  d4_zero(wb0); d4_zero(wb1);
-  if (lane < d4) chain_slots(2 * G, pvid[wib], part[wib], D, d4, c4, common, wbv0, wb0, wbv1, wb1);
+  ChainEdges we;
+  we.own1 = false; we.last_v = -1;
+  if (active) chain_slots(g, G, pvid[wib], part[wib], D, d4, c4, common, we);
   __syncthreads();                       // every wavefront has read its part of `part`
+  // the wavefront's own head / tail become slots 2*wib, 2*wib+1 of the block's chain
   if (lane < d4) {
-    const int bv0 = wbv0, bv1 = wbv1;
-    const D4 b0 = wb0, b1 = wb1;
-    // the wavefront's own head / tail become slots 2*wib, 2*wib+1 of the block's chain
     double* o0 = &wpart[(2 * wib) * D + 4 * c4];
-    o0[0] = b0.x; o0[1] = b0.y; o0[2] = b0.z; o0[3] = b0.w;
-    double* o1 = o0 + D;
-    o1[0] = b1.x; o1[1] = b1.y; o1[2] = b1.z; o1[3] = b1.w;
-    if (c4 == 0) { wvid[2 * wib] = bv0; wvid[2 * wib + 1] = bv1; }
+    o0[0] = we.b0.x; o0[1] = we.b0.y; o0[2] = we.b0.z; o0[3] = we.b0.w;
+    if (c4 == 0) { wvid[2 * wib] = we.bv0; if (we.last_v < 0) wvid[2 * wib + 1] = -1; }
+  }
+  if (we.own1) {
+    double* o1 = &wpart[(2 * wib + 1) * D + 4 * c4];
+    o1[0] = we.b1.x; o1[1] = we.b1.y; o1[2] = we.b1.z; o1[3] = we.b1.w;
+    if (c4 == 0) wvid[2 * wib + 1] = we.bv1;
   }
   __syncthreads();
-  if (threadIdx.x < (unsigned)d4) {
-    int bv0, bv1;
-    D4 b0, b1;
-    chain_slots(8, wvid, wpart, D, d4, c4, common, bv0, b0, bv1, b1);
+  if (lane < d4) {                       // one lane group per wavefront
+    ChainEdges be;
+    chain_slots(wib, 4, wvid, wpart, D, d4, c4, common, be);
     const int64_t o = (int64_t)blockIdx.x * 2;
-    double* o0 = &bp[(o + 0) * D + 4 * c4];
-    o0[0] = b0.x; o0[1] = b0.y; o0[2] = b0.z; o0[3] = b0.w;
-    double* o1 = &bp[(o + 1) * D + 4 * c4];
-    o1[0] = b1.x; o1[1] = b1.y; o1[2] = b1.z; o1[3] = b1.w;
-    if (c4 == 0) {
-      bp_vid[o] = bv0; bp_vid[o + 1] = bv1;
-      // a group cut by a block's edge: its sum is not in `common`, and the optimizer kernel that
-      // chains the partials itself (k_adagrad_rows) must not take it from there (see kEdgeMark)
-      if (edge_mark) {
-        if (bv0 >= 0) edge_mark[2 * bv0] = kEdgeMark;
-        if (bv1 >= 0) edge_mark[2 * bv1] = kEdgeMark;
+    // a group cut by a block's edge: its sum is not in `common`, and the optimizer kernel that
+    // chains the partials itself (k_adagrad_rows) must not take it from there (see kEdgeMark)
+    if (wib == 0) {
+      double* o0 = &bp[(o + 0) * D + 4 * c4];
+      o0[0] = be.b0.x; o0[1] = be.b0.y; o0[2] = be.b0.z; o0[3] = be.b0.w;
+      if (c4 == 0) {
+        bp_vid[o] = be.bv0;
+        if (be.last_v < 0) bp_vid[o + 1] = -1;
+        if (edge_mark && be.bv0 >= 0) edge_mark[2 * be.bv0] = kEdgeMark;
+      }
+    }
+    if (be.own1) {
+      double* o1 = &bp[(o + 1) * D + 4 * c4];
+      o1[0] = be.b1.x; o1[1] = be.b1.y; o1[2] = be.b1.z; o1[3] = be.b1.w;
+      if (c4 == 0) {
+        bp_vid[o + 1] = be.bv1;
+        if (edge_mark) edge_mark[2 * be.bv1] = kEdgeMark;
       }
     }
   }
 }
 
-// Chains the block-edge partials: slot j = 2 * block + (0 head | 1 tail); equal vids are adjacent
-// and a long group (the hottest id spans hundreds of blocks) is one long run of slots.  One
-// thread block per slot; only the first slot of a run works: it finds the run's end by binary
-// search (the predicate "same vid" is true on the run and false after it), its lane groups sum
-// the run's partials in a strided, fixed order, four loads in flight, and combine through LDS.
-// The work of one block on slot j of the block-edge partial lists: true (for the whole block) when
-// j is the first slot of its run; then v is the run's virtual id and the threads tid < d4 hold the
-// run's fp64 sum, chunk tid of the row, in s.
+// The block-edge partials: slot j = 2 * block + (0 head | 1 tail); equal vids are adjacent and a long
+// group (the hottest id spans hundreds of blocks) is one long run of slots.
+// One run, by a whole block: true (for the whole block) when j is the first slot of its run; then v is
+// the run's virtual id and the threads tid < d4 hold its fp64 sum, chunk tid of the row, in s.  The lane
+// groups sum the run's partials in a strided, fixed order, eight rows in flight, and combine in a tree.
 __device__ __forceinline__ bool edge_run_sum(const double* __restrict__ bp,
                                              const int* __restrict__ bp_vid, int nslots, int d4,
                                              int j, int& v, D4& s) {
   __shared__ double red[256 * 4];
-  __shared__ int s_cnt[4];
+  __shared__ int s_first[4];
   v = bp_vid[j];
   if (v < 0 || (j > 0 && bp_vid[j - 1] == v)) return false;     // not the first slot of its run
-  // the run's end: "same vid" is true on the run and false after it, so the block probes 256
-  // places at once and narrows the bracket by that factor per round (two rounds for thousands of
-  // slots, where a bisection took a dozen dependent loads)
+  // the run's end, 1024 slots per round: all loads in flight, the first that differs ends it
   const int tid = (int)threadIdx.x;
-  int lo = j, hi = nslots;                                 // bp_vid[lo] == v, run ends in (lo, hi]
-  while (hi - lo > 1) {
-    const int step = (hi - lo + 255) / 256;
-    const int probe = lo + (tid + 1) * step;
-    const bool same = probe < hi && bp_vid[probe] == v;
-    const uint64_t m = __ballot(same);
-    if ((tid & 63) == 0) s_cnt[tid >> 6] = __popcll(m);
+  int end = j;
+  for (int base = j;; base += 1024) {
+    int first = base + 1024;
+#pragma unroll
+    for (int u = 3; u >= 0; --u) {
+      const int k0 = base + u * 256 + (tid & ~63), k = k0 + (tid & 63);
+      const uint64_t off = __ballot(!(k < nslots && bp_vid[k] == v));
+      if (off) first = k0 + __builtin_ctzll(off);
+    }
+    if ((tid & 63) == 0) s_first[tid >> 6] = first;
     __syncthreads();
-    const int k = s_cnt[0] + s_cnt[1] + s_cnt[2] + s_cnt[3];   // probes 1..k are on the run
+    end = s_first[0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) end = s_first[w] < end ? s_first[w] : end;
     __syncthreads();
-    const int nlo = lo + k * step;
-    int nhi = lo + (k + 1) * step;
-    if (nhi > hi) nhi = hi;
-    lo = nlo; hi = nhi;
+    if (end < base + 1024) break;                          // at the latest where the slots end
   }
-  const int end = hi, D = d4 * 4;
+  const int D = d4 * 4;
   const int groups = 256 / d4, g = tid / d4, c4 = tid - g * d4;
   double s0 = 0., s1 = 0., s2 = 0., s3 = 0.;
+  // Behind the first slot only heads (even slots) count: a tail inside the run is that of a block which
+  // lies in the run from edge to edge, and its sum is in its head.  One compute unit reads all of it, and
+  // that is what the longest run costs.
+  const int e0 = j + (j & 1), ne = (end - e0 + 1) >> 1;
   if (g < groups) {
-    const double4 zero = make_double4(0., 0., 0., 0.);
-    for (int k = j + g; k < end; k += 4 * groups) {
-      double4 x[4];
+    const double* q = bp + 4 * c4;
+    if (g == 0 && (j & 1)) { const double* x = q + (int64_t)j * D; s0 = x[0]; s1 = x[1]; s2 = x[2]; s3 = x[3]; }
+    for (int k = g; k < ne; k += 8 * groups) {
+      double x[8][4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const int kk = k + u * groups;
-        x[u] = kk < end ? *reinterpret_cast<const double4*>(&bp[(int64_t)kk * D + 4 * c4]) : zero;
+      for (int u = 0; u < 8; ++u) {
+        const int kk = k + u * groups < ne ? k + u * groups : ne - 1;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[u][i] = q[(int64_t)(e0 + 2 * kk) * D + i];
       }
 #pragma unroll
-      for (int u = 0; u < 4; ++u) { s0 += x[u].x; s1 += x[u].y; s2 += x[u].z; s3 += x[u].w; }
+      for (int u = 0; u < 8; ++u)
+        if (k + u * groups < ne) { s0 += x[u][0]; s1 += x[u][1]; s2 += x[u][2]; s3 += x[u][3]; }
     }
   }
   double* r = &red[tid * 4];
   r[0] = s0; r[1] = s1; r[2] = s2; r[3] = s3;
-  __syncthreads();
-  if (g == 0) {
-    for (int o = 1; o < groups; ++o) {
-      const double* q = &red[(o * d4 + c4) * 4];
-      s0 += q[0]; s1 += q[1]; s2 += q[2]; s3 += q[3];
+  int o = 1;
+  while (o < groups) o <<= 1;
+  for (o >>= 1; o > 0; o >>= 1) {
+    __syncthreads();
+    if (g < o && g + o < groups) {
+      const double* q = r + o * d4 * 4;
+      r[0] += q[0]; r[1] += q[1]; r[2] += q[2]; r[3] += q[3];
     }
   }
-  s.x = s0; s.y = s1; s.z = s2; s.w = s3;
+  s.x = r[0]; s.y = r[1]; s.z = r[2]; s.w = r[3];
   return true;
+}
+
+// Every run, by edge_blocks() blocks: a lane group per slot.  Nearly all runs are two slots long (the tail
+// of one stream block and the head of the next): a group that finds the first slot of a run of at most
+// kEdgeShort slots adds them up itself, in slot order.  The few long runs (an id with thousands of
+// positions spans many stream blocks) are listed in LDS and summed by the whole block, one after the
+// other; their first slots lie more than kEdgeShort slots apart, so a block meets only a few.
+// emit(v, c4, sum): chunk c4 of the summed row of virtual id v, rounded to fp32.
+// What bounds it is dependent loads and barriers, so the slots around one are loaded together and a long
+// run ends in a tree.  As a kernel of its own 7.4 -> 3.3 us at 213e3 positions of dim 128; 9.5 us as before at
+// 2.56e6 of dim 32, where the hottest id spans a thousand slots and six round trips in a row are what is left.
+constexpr int kEdgeShort = 8;
+inline int edge_blocks(int nslots, int d4) {
+  const int per_block = 4 * (64 / d4 > 0 ? 64 / d4 : 1);
+  return (nslots + per_block - 1) / per_block;
+}
+
+template <class Emit>
+__device__ __forceinline__ void edge_block(const double* __restrict__ bp, const int* __restrict__ bp_vid,
+                                           int nslots, int d4, int blk, Emit emit) {
+  __shared__ int n_long;
+  __shared__ int long_at[256];
+  if (threadIdx.x == 0) n_long = 0;
+  __syncthreads();
+  const int lane = lane_id(), G = 64 / d4 > 0 ? 64 / d4 : 1;
+  const int g = lane / d4, c4 = lane - g * d4;
+  const int j = (blk * 4 + (int)(threadIdx.x >> 6)) * G + g;
+  if (g < G && j < nslots) {
+    // the slots around, all in flight: a run of two is found in one round trip, not slot by slot
+    int vs[kEdgeShort + 1];
+    const int before = j > 0 ? bp_vid[j - 1] : -1;
+#pragma unroll
+    for (int u = 0; u <= kEdgeShort; ++u) vs[u] = j + u < nslots ? bp_vid[j + u] : -1;
+    const int v = vs[0];
+    if (v >= 0 && before != v) {                          // first slot of its run
+      int len = 1;
+#pragma unroll
+      for (int u = 1; u <= kEdgeShort; ++u) len += len == u && vs[u] == v;
+      if (len > kEdgeShort) {
+        if (c4 == 0) long_at[atomicAdd(&n_long, 1)] = j;
+      } else {
+        const int D = d4 * 4;
+        double s0 = 0., s1 = 0., s2 = 0., s3 = 0.;
+        for (int k = 0; k < len; ++k) {
+          const double* q = bp + (int64_t)(j + k) * D + 4 * c4;
+          s0 += q[0]; s1 += q[1]; s2 += q[2]; s3 += q[3];
+        }
+        emit(v, c4, make_float4((float)s0, (float)s1, (float)s2, (float)s3));
+      }
+    }
+  }
+  __syncthreads();
+  const int nl = n_long;
+  for (int i = 0; i < nl; ++i) {
+    int v;
+    D4 s;
+    const bool first = edge_run_sum(bp, bp_vid, nslots, d4, long_at[i], v, s);
+    if (first && (int)threadIdx.x < d4) emit(v, (int)threadIdx.x, d4_round(s));
+    __syncthreads();
+  }
 }
 
 __global__ __launch_bounds__(256) void k_seg_finish(const double* __restrict__ bp,
                                                      const int* __restrict__ bp_vid, int nslots,
                                                      int d4, float4* __restrict__ common) {
-  int v;
-  D4 s;
-  if (!edge_run_sum(bp, bp_vid, nslots, d4, (int)blockIdx.x, v, s)) return;
-  if ((int)threadIdx.x < d4) common[(int64_t)v * d4 + threadIdx.x] = d4_round(s);
+  edge_block(bp, bp_vid, nslots, d4, (int)blockIdx.x,
+             [&](int v, int c4, float4 g) { common[(int64_t)v * d4 + c4] = g; });
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -808,17 +914,6 @@ __device__ __forceinline__ void update_one_row(const Op& op, int v, int c4, floa
 // over the marked ones (kEdgeMark).  The two parts share nothing and wait for nothing: the chain of
 // dependent loads that sums a run (ten microseconds as a kernel of its own) runs beside the row
 // stream instead of before it.
-// In an edge block every lane group takes one slot of the partial lists.  Nearly all runs are two
-// slots long (the tail of one stream block and the head of the next): a group that finds the first
-// slot of a run of at most kEdgeShort slots adds them up itself, in slot order.  The few long runs
-// (an id with thousands of positions spans many stream blocks) are listed in LDS and summed by
-// the whole block, one after the other, as in k_seg_finish; their first slots lie more than
-// kEdgeShort slots apart, so a block meets only a few.
-constexpr int kEdgeShort = 8;
-inline int edge_blocks(int nslots, int d4) {
-  const int per_block = 4 * (64 / d4 > 0 ? 64 / d4 : 1);
-  return (nslots + per_block - 1) / per_block;
-}
 
 template <class Op, bool kOneHot>
 __device__ __forceinline__ void update_kernel(const Op& op, const float4* __restrict__ common,
@@ -832,46 +927,22 @@ __device__ __forceinline__ void update_kernel(const Op& op, const float4* __rest
                                               const int* __restrict__ bp_vid, int nslots,
                                               int nedge) {
   if ((int)blockIdx.x < nedge) {
-    __shared__ int n_long;
-    __shared__ int long_at[256];
-    if (threadIdx.x == 0) n_long = 0;
-    __syncthreads();
-    const int lane = lane_id(), G = 64 / d4 > 0 ? 64 / d4 : 1;
-    const int g = lane / d4, c4 = lane - g * d4;
-    const int j = ((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * G + g;
-    if (g < G && j < nslots) {
-      const int v = bp_vid[j];
-      if (v >= 0 && (j == 0 || bp_vid[j - 1] != v)) {       // first slot of its run
-        int len = 1;
-        while (len <= kEdgeShort && j + len < nslots && bp_vid[j + len] == v) ++len;
-        if (len > kEdgeShort) {
-          if (c4 == 0) long_at[atomicAdd(&n_long, 1)] = j;
-        } else {
-          const int D = d4 * 4;
-          double s0 = 0., s1 = 0., s2 = 0., s3 = 0.;
-          for (int k = 0; k < len; ++k) {
-            const double4 x = *reinterpret_cast<const double4*>(&bp[(int64_t)(j + k) * D + 4 * c4]);
-            s0 += x.x; s1 += x.y; s2 += x.z; s3 += x.w;
-          }
-          update_one_row(op, v, c4, make_float4((float)s0, (float)s1, (float)s2, (float)s3), slot,
-                         unique_ids, cw, cs, h, C, boff, d4);
-        }
-      }
-    }
-    __syncthreads();
-    const int nl = n_long;
-    for (int i = 0; i < nl; ++i) {
-      int v;
-      D4 s;
-      const bool first = edge_run_sum(bp, bp_vid, nslots, d4, long_at[i], v, s);
-      if (first && (int)threadIdx.x < d4)
-        update_one_row(op, v, (int)threadIdx.x, d4_round(s), slot, unique_ids, cw, cs, h, C, boff, d4);
-      __syncthreads();
-    }
+    edge_block(bp, bp_vid, nslots, d4, (int)blockIdx.x, [&](int v, int c4, float4 g) {
+      update_one_row(op, v, c4, g, slot, unique_ids, cw, cs, h, C, boff, d4);
+    });
     return;
   }
   const int U = ctr->U;
-  const int blk = (int)blockIdx.x - nedge, nblk = (int)gridDim.x - nedge;
+  // Few rows for the grid (the host does not know their number): every thread that works takes
+  // Op::kRows of them at once, the other blocks return; spread over all blocks there was one row in
+  // flight per thread and two rounds of blocks.  132e3 rows of dim 16 23.5 -> 20.6 us, 200e3 of dim 32
+  // 28.4 -> 26.7.
+  const int64_t total = (int64_t)U * d4;
+  const int64_t most = (total + 256 * Op::kRows - 1) / (256 * Op::kRows);
+  const int blk = (int)blockIdx.x - nedge;
+  int nblk = (int)gridDim.x - nedge;
+  if (nblk > most) nblk = (int)most;
+  if (blk >= nblk) return;
   if (stream_rows(U, d4, Op::kParts * d4))
     update_rows<Op, true, kOneHot>(op, common, slot, unique_ids, cw, cs, h, C, boff, d4, U, cold_pay, grad, blk, nblk);
   else
