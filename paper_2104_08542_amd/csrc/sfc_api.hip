@@ -105,6 +105,7 @@ struct StepCtx {
   hipEvent_t ev_fetched = nullptr;    // the side-stream launch of the step's Host copies has run
   bool updated = false;               // backward_update has been enqueued for this step
   bool discarded = false;             // freed by sfc_discard: the step's copies may still be running
+  bool copies_on_main = false;        // this step's copies run on the main stream
   bool joined = false;                // the main stream is behind the side-stream launch of the step's copies
   // pipelined mode: the second launch of the Host copies, due on the main stream behind the
   // update of step main_after (see k_swap_rows); older1 .. older3 = counters of the older steps
@@ -330,17 +331,23 @@ constexpr int64_t kSwapMainBytes = (int64_t)1 << 20;
 int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   EventPair ep{};
   int rc;
-  // the copies read the step's counters, miss list and victim list: its prepare comes first (with
-  // lookahead 0 it is main-stream work, which sfc_fetch_misses has put s behind)
-  if (c->nctx > 1 && s != c->prep) HIPCHK(hipStreamWaitEvent(s, x->ev_prepared, 0));
+  // the copies read the step's counters, miss list and victim list: its prepare comes first
+  if (s != c->prep) HIPCHK(hipStreamWaitEvent(s, x->ev_prepared, 0));
   if ((rc = prof_begin(c, P_FETCH, s, &ep))) return rc;
   ep.extra = main_variant != 0;          // the second launch of a step: same call
   const int64_t recent_bytes = (int64_t)((const volatile HostStatus*)c->hstat)->M * (c->d4 + c->s4) * 16;
   const int swap_blocks = c->nctx == 1 || recent_bytes > kSwapWideBytes ? kSwapBlocksWide : kSwapBlocks;
-  hipLaunchKernelGGL(k_swap_rows, dim3(grid_for(x->n_ids * (c->d4 + c->s4), 256, swap_blocks)),
-                     dim3(256), 0, s,
+  int blocks = grid_for(x->n_ids * (c->d4 + c->s4), 256, swap_blocks), staged_at = -1;
+  // where victims are possible, and the copies have the side stream to themselves (see k_stage_victims)
+  if (c->nctx == 1 && !x->copies_on_main && c->C > 0 && c->C < c->V && x->n_ids >= kSplitMin) {
+    staged_at = (int)c->C + x->boff;
+    blocks = kSplitWriters + kSplitReaders;
+    hipLaunchKernelGGL(k_stage_victims, dim3(1024), dim3(256), 0, s, x->victim_slot, (float4*)c->cw,
+                       (float4*)c->ca, (int)c->C, x->boff, c->d4, c->s4, (const Ctr*)x->ctr);
+  }
+  hipLaunchKernelGGL(k_swap_rows, dim3(blocks), dim3(256), 0, s,
                      x->miss_row, x->miss_id, x->victim_id, (float4*)c->cw, (float4*)c->ca, c->host,
-                     c->d4, c->s4, x->ctr, x->older1, x->older2, x->older3, x->chain, main_variant);
+                     c->d4, c->s4, x->ctr, x->older1, x->older2, x->older3, x->chain, main_variant, staged_at);
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_FETCH, s, &ep))) return rc;
   if (main_variant) x->main_pending = false;
@@ -413,6 +420,10 @@ int plan_and_group(sfc_cache* c, StepCtx* x, const SortGeom& sg, int* cnt, int* 
                      c->cur_rep, sg.bins, sg.nrep, c->tile_cnt, c->grp, x->cold_pay, c->tile_miss,
                      x->victim_slot, x->d_slot, x->d_miss, x->miss_row, x->miss_id, x->boff, c->slot_id,
                      c->stamp, c->index, c->hi, c->dmap, x->t, (int)c->C, c->tile_reuse, x->ctr);
+  // The Host copies need nothing of the grouping: with lookahead 0 they are let go here, so that the way
+  // to the side stream (12 us) and the grouping pass, beside the copies' first round trips, cost no time
+  // of their own.  (Pipelined, the grouping is on the path of the next prepare: there it stays first.)
+  if (c->nctx == 1 && !x->copies_on_main) HIPCHK(hipEventRecord(x->ev_prepared, s));
   if (n > 0) {
     auto scat = sg.threads == 256 ? k_scatter<4, 256> : sg.threads == 512 ? k_scatter<8, 512> : k_scatter<8, 1024>;
     hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.threads), 0, s, x->d_inverse,
@@ -420,6 +431,7 @@ int plan_and_group(sfc_cache* c, StepCtx* x, const SortGeom& sg, int* cnt, int* 
                        (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
                        (const int*)x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags);
   }
+  if (c->nctx > 1) HIPCHK(hipEventRecord(x->ev_prepared, s));
   return SFC_OK;
 }
 
@@ -725,6 +737,14 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   // the victims
   const bool small = n_ids > 0 && n_ids <= kSmallIds && n_bags <= kSmallBags;
   const bool whole = small && c->dmap && (c->C >= c->V || c->C <= kSmallSlots);
+  // With lookahead 0 the copies stand between the prepare and the lookup of the main stream, and the
+  // way to the side stream and back costs about as much as kSwapMainBytes take on the link: a step
+  // that moves less stays on the main stream.
+  {
+    const volatile HostStatus* h = c->hstat;
+    x->copies_on_main = c->nctx == 1 && (c->side == c->st || (h->seq != 0 &&
+                        (int64_t)h->M * (c->d4 + c->s4) * 16 <= kSwapMainBytes));
+  }
   hipStream_t s = c->prep;
   if (s != c->st) {
     // the prepare stream must not overtake what the main stream has been given so far: the
@@ -827,11 +847,13 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                        c->dmap ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid);
   }
   if (c->ins) { HIPCHK(hipEventRecord(c->ev_resolved, s)); c->resolved_once = true; }
-  if (!whole && (rc = plan_and_group(c, x, sg, cnt, cnt_rep))) return rc;
+  if (whole) {
+    if (!x->copies_on_main) HIPCHK(hipEventRecord(x->ev_prepared, s));
+  } else if ((rc = plan_and_group(c, x, sg, cnt, cnt_rep))) {
+    return rc;
+  }
   HIPCHK(hipGetLastError());
-  if ((rc = prof_end(c, P_PREPARE, s, &ep))) return rc;
-  if (c->nctx > 1) HIPCHK(hipEventRecord(x->ev_prepared, s));
-  return SFC_OK;
+  return prof_end(c, P_PREPARE, s, &ep);
 }
 
 int sfc_fetch_misses(sfc_cache* c) {
@@ -851,15 +873,10 @@ int sfc_fetch_misses(sfc_cache* c) {
     else if (o->t == x->t - 3) x->older3 = o->ctr;
     if (o->t > x->main_after) x->main_after = o->t;
   }
-  // With lookahead 0 the copies stand between the prepare and the lookup of the main stream, and the
-  // way to the side stream and back costs about as much as kSwapMainBytes take on the link: a step
-  // that moves less stays on the main stream.
-  const volatile HostStatus* h = c->hstat;
-  const bool on_main = c->side == c->st ||
-                       (c->nctx == 1 && h->seq != 0 && (int64_t)h->M * (c->d4 + c->s4) * 16 <= kSwapMainBytes);
-  if (!on_main) {
-    // everything the main stream has been given so far comes first: this step's prepare
-    // (lookahead 0), older updates and their second launches
+  const bool on_main = x->copies_on_main;
+  if (!on_main && c->nctx > 1) {
+    // everything the main stream has been given so far comes first: older updates and their second
+    // launches (with lookahead 0 the prepare is behind those, and the copies are behind the prepare)
     HIPCHK(hipEventRecord(c->ev_tmp, c->st));
     HIPCHK(hipStreamWaitEvent(c->side, c->ev_tmp, 0));
   }

@@ -52,13 +52,81 @@ struct HostRows {
   int64_t has4;   // row stride of a in float4
 };
 
+// Reads and writes of the link in separate blocks.  A lane that does both waits for its read, then writes,
+// and with few rounds per lane the lanes of the whole grid do so in step: the link idles in turn one way
+// and the other.  So with lookahead 0, and where the misses are many enough to matter and few enough
+// that the rounds have not drifted apart (kSplitMin .. kSplitMax of them), the victims' rows are first
+// copied beside the step's bypass rows in HBM (k_stage_victims; the region has a row for every id of the
+// batch, and victims + bypass rows are at most its misses); then kSplitWriters blocks carry them to the Host
+// while the other blocks read the missed rows into their slots.  Copies alone, staging included, against
+// one lane doing both: 52.7e3 misses of 128 bytes 218 against 236 us, 58.2e3 of 256 bytes 372 against 393,
+// 20.6e3 of 960 bytes 507 against 532; 6.9e3 of 256 bytes 67 against 65, 1e6 of 128 bytes 3740 against 3549.
+constexpr int kSplitMin = 1 << 14;
+constexpr int kSplitMax = 1 << 18;
+constexpr int kSplitWriters = 32, kSplitReaders = 128;
+__device__ __forceinline__ bool split_swap(const Ctr* ctr) {
+  return ctr->M >= kSplitMin && ctr->M <= kSplitMax && ctr->K > 0;
+}
+
+__global__ __launch_bounds__(256) void k_stage_victims(const int* __restrict__ victim_slot,
+                                                        float4* __restrict__ cw, float4* __restrict__ ca,
+                                                        int C, int boff, int d4, int s4, const Ctr* ctr) {
+  if (!split_swap(ctr)) return;
+  const unsigned w2 = (unsigned)(d4 + s4), total = (unsigned)ctr->K * w2;    // < 2^18 * 192
+  const int64_t row0 = (int64_t)C + boff + ctr->n_bypass;
+  for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
+    const unsigned k = i / w2;
+    const int c = (int)(i - k * w2);
+    const int64_t from = victim_slot[k], to = row0 + k;
+    if (c < d4) cw[to * d4 + c] = cw[from * d4 + c];
+    else ca[to * s4 + (c - d4)] = ca[from * s4 + (c - d4)];
+  }
+}
+
+// One direction: rows list[k] (k < count) of the Host table and rows row(k) of the cache, four chunks of a
+// lane in flight.
+template <bool kToHost, class Row>
+__device__ __forceinline__ void link_rows(const int64_t* __restrict__ list, Row row, int count, float4* cw,
+                                          float4* ca, const HostRows& h, int d4, int s4, int blk, int nblk) {
+  const unsigned w2 = (unsigned)(d4 + s4), total = (unsigned)count * w2, stride = (unsigned)nblk * 256;
+  for (unsigned i0 = (unsigned)blk * 256 + threadIdx.x; i0 < total; i0 += 4 * stride) {
+    int64_t at[4], hat[4];                  // chunk in the cache array, chunk in the Host array
+    bool on[4], state[4];
+    vf4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const unsigned i = i0 + u * stride;
+      on[u] = i < total;
+      const unsigned k = on[u] ? i / w2 : 0;
+      const int c = on[u] ? (int)(i - k * w2) : 0;
+      state[u] = c >= d4;
+      const int64_t id = list[k], r = row(k);
+      at[u] = state[u] ? r * s4 + (c - d4) : r * d4 + c;
+      hat[u] = state[u] ? id * h.has4 + (c - d4) : id * h.hs4 + c;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (on[u]) {
+        const float4* const from = kToHost ? (state[u] ? ca : cw) : (state[u] ? h.a : h.w);
+        v[u] = *reinterpret_cast<const vf4*>(&from[kToHost ? at[u] : hat[u]]);
+      }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (on[u]) {
+        float4* const to = kToHost ? (state[u] ? h.a : h.w) : (state[u] ? ca : cw);
+        *reinterpret_cast<vf4*>(&to[kToHost ? hat[u] : at[u]]) = v[u];
+      }
+  }
+}
+
 __global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_row,
                                                     const int64_t* __restrict__ miss_id,
                                                     const int64_t* __restrict__ victim_id,
                                                     float4* __restrict__ cw, float4* __restrict__ ca,
                                                     HostRows h, int d4, int s4, Ctr* ctr,
                                                     const Ctr* older1, const Ctr* older2,
-                                                    const Ctr* older3, int chain, int main_variant) {
+                                                    const Ctr* older3, int chain, int main_variant,
+                                                    int staged_at) {
   const bool on_main = (older1 && older1->n_bypass != 0) || (older2 && older2->n_bypass != 0) ||
                        (older3 && older3->n_bypass != 0) ||
                        (chain && older1 && older1->fetch_on_main != 0);
@@ -66,6 +134,17 @@ __global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_
   if (on_main != (main_variant != 0)) return;
   __builtin_amdgcn_s_setprio(3);            // few waves, long round trips: issue ahead of the kernels beside them
   const int K = ctr->K;
+  // staged_at >= 0: k_stage_victims has run, the victims' rows are at staged_at + the bypass rows
+  if (staged_at >= 0 && split_swap(ctr)) {
+    const int64_t row0 = (int64_t)staged_at + ctr->n_bypass;
+    if (blockIdx.x < kSplitWriters)
+      link_rows<true>(victim_id, [&](unsigned k) { return row0 + k; }, K, cw, ca, h, d4, s4, (int)blockIdx.x,
+                      kSplitWriters);
+    else
+      link_rows<false>(miss_id, [&](unsigned k) { return (int64_t)miss_row[k]; }, ctr->M, cw, ca, h, d4, s4,
+                       (int)blockIdx.x - kSplitWriters, (int)gridDim.x - kSplitWriters);
+    return;
+  }
   const int w2 = d4 + s4;                   // chunks of a row and of its optimizer state
   const int64_t total = (int64_t)ctr->M * w2;
   const int64_t stride = (int64_t)gridDim.x * 256;

@@ -289,6 +289,24 @@ def test_batch_table_whose_entries_take_two_words():
         c.close(); c.table.free()
 
 
+@pytest.mark.parametrize("C,n,optimizer", [(60_000, 50_000, "adagrad"), (20_000, 50_000, "adagrad"),
+                                           (60_000, 18_500, "adagrad"), (30_000, 50_000, "adam"),
+                                           (60_000, 50_000, "rowwise_adagrad"), (90_000, 300_000, "adagrad")])
+def test_host_copies_in_separate_blocks(C, n, optimizer):
+    # lookahead 0 and 2^14 to 2^18 misses: the victims' rows are staged beside the step's bypass rows and
+    # one part of the blocks writes them to the Host while the other reads the missed rows; with bypass
+    # rows in front of the staged ones, and with misses around the lower bound
+    V, D = 200_000, 12
+    p = Pair(V, D, C=C, max_ids=n, optimizer=optimizer, init_acc=0.0 if optimizer == "adam" else 0.1)
+    seen = []
+    for t in range(5):
+        m = n if t % 2 == 0 else n - n // 7
+        pr = p.step(si.uniform_ids(m, V, 71, t).numpy(), si.grads(m, D, 71, t).numpy(), check_common=False)
+        seen.append(pr.stats)
+    assert n == 18_500 or any(st["n_miss"] >= 1 << 14 and st["n_evict"] > 0 for st in seen)
+    p.finish(); p.close()
+
+
 def test_same_stream_and_separate_host_arrays():
     # copies on the main stream; Host weights and accumulators as two separate arrays
     V, D, n = 4000, 32, 2000
