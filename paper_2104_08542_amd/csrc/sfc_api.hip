@@ -788,20 +788,16 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   if (small) {
     // its unique passes are part of the kernel below
   } else if (n > 0) {
-    const int nub = (n + kUniqChunk - 1) / kUniqChunk, head = nub <= kHeadMin ? nub : kHeadBlocks;
-    auto insert = [&](int blocks, int block0) {
-      if (c->wide) {
-        WideTab tab{(UEntry*)c->utab, 0, c->V};
-        hipLaunchKernelGGL(k_uniq_insert<WideTab>, dim3(blocks), dim3(256), 0, su, d_ids, n, tab, hu,
-                           c->hslot, c->first, c->n_invalid, block0);
-      } else {
-        PackedTab tab{c->utab, pos_bits(n), c->V};
-        hipLaunchKernelGGL(k_uniq_insert<PackedTab>, dim3(blocks), dim3(256), 0, su, d_ids, n, tab, hu,
-                           c->hslot, c->first, c->n_invalid, block0);
-      }
-    };
-    insert(head, 0);
-    if (nub > head) insert(nub - head, head);
+    const int nub = (n + kUniqChunk - 1) / kUniqChunk;
+    if (c->wide) {
+      WideTab tab{(UEntry*)c->utab, 0, c->V};
+      hipLaunchKernelGGL(k_uniq_insert<WideTab>, dim3(nub), dim3(256), 0, su, d_ids, n, tab, hu, c->hslot,
+                         c->first, c->n_invalid);
+    } else {
+      PackedTab tab{c->utab, pos_bits(n), c->V};
+      hipLaunchKernelGGL(k_uniq_insert<PackedTab>, dim3(nub), dim3(256), 0, su, d_ids, n, tab, hu, c->hslot,
+                         c->first, c->n_invalid);
+    }
     const int* const counts = n > kCountMin ? c->blk_cnt : nullptr;
     if (counts)
       hipLaunchKernelGGL(k_uniq_count, dim3((nchunk + 3) / 4), dim3(256), 0, su, (const unsigned*)c->first,

@@ -25,7 +25,8 @@ constexpr int kVidTile = 256;     // virtual ids per tile in resolve / assign
 // (tag << sh) | smallest position so far (tag = the id, or V for the collapsed out-of-range id; sh = bits of
 // a position of this batch): claiming an entry stores its position with the same compare-and-swap,
 // and a smaller position is one 64-bit minimum.  (Key and position in two words took two atomics for
-// every distinct id and a table twice the size: INSFIG.)
+// every distinct id and a table twice the size: 53 us instead of 46.5 at 65536 x 39 positions, 159 instead
+// of 134 at 8.9e6 in bags, 143 instead of 108 at 1.28e6 uniform ones.)
 // Same-address atomics serialise at the memory side (about 10 ns each on this chip), and the
 // hottest id of a power-law batch owns a fifth of all positions.  So each block first
 // deduplicates its kUniqChunk positions in an LDS table (key -> smallest position in the block) and
@@ -33,11 +34,13 @@ constexpr int kVidTile = 256;     // virtual ids per tile in resolve / assign
 // comes first (the table entry of a key never changes once set, and a stale position can only be too
 // large), and an atomic is issued only when the load has not already seen the key / a small enough
 // position.
-// A large batch launches the kernel twice: the first kHeadBlocks blocks, then the rest.  When all
-// blocks start together they all find the table empty, and every block's copy of a frequent key goes
-// through the claim / re-read / minimum atomics on one address (thousands in a row, about 10 ns
-// each); after the head of the batch has been inserted the frequent keys are in the table with
-// a smaller position than any later block holds, and the plain load settles them.
+// When all blocks of a large batch start together they all find the table empty, and every block's copy
+// of a frequent key goes through the claim / re-read / minimum atomics on one address (thousands in a
+// row, about 10 ns each).  So only the first kHeadBlocks blocks go to the table at once; the others that
+// are resident from the start sleep a few microseconds first, and then their plain loads find the
+// frequent keys in the table with a smaller position than theirs.  (Nothing depends on the sleep being
+// long enough.)  us without the sleep / with the head in a launch of its own / this way: 58 / 35 / 29 at
+// 16384 x 39 positions, 80 / 47 / 42 at 65536 x 39, 30 / 28 / 20 at 5003 x 39, 95 / 109 / 98 at 1.28e6 uniform ones.
 // hslot[p] = HBM table entry of position p.
 // first: one bit per position, set for the positions that hold their entry's smallest position in the
 // end, all zero before.  Whoever places a position in an entry flips its bit, and whoever replaces one
@@ -47,11 +50,10 @@ constexpr int kVidTile = 256;     // virtual ids per tile in resolve / assign
 constexpr int kUniqChunk = 512;    // positions per block (2048 with its 53 KB of LDS left 12 wavefronts per compute unit: 20 us slower)
 constexpr int kUniqPer = kUniqChunk / 256;
 constexpr int kLdsPer = 2 * kUniqChunk / 256;
-constexpr int kHeadBlocks = 64;    // blocks of the first of the two launches
-// batches of at most this many blocks go in one launch: all resident at once, and an atomic per block on
-// one address costs less than a second launch (78 blocks 16 against 25 us, 382 blocks 29.7 against 27.8,
-// 5000 blocks 80 against 46.5)
-constexpr int kHeadMin = 256;
+constexpr int kHeadBlocks = 64;    // blocks that go to the table at once
+constexpr int kHeadMin = 256;      // a grid of at most this many blocks does not sleep: 16 us either way at 78 blocks
+constexpr int kResidentBlocks = 2048;        // eight per compute unit
+constexpr int kHeadSleep = 5;      // times 2048 clocks, 4.3 us (3 / 5 / 7 / 10: 30 / 28.7 / 29 / 31 us at 16384 x 39)
 constexpr int kLdsTab = 2 * kUniqChunk;      // LDS table entries per block
 
 template <typename T>
@@ -111,8 +113,7 @@ struct WideTab {
 template <class Tab>
 __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__ ids, int n, Tab tab,
                                                       uint32_t hu, int* __restrict__ hslot,
-                                                      unsigned* first, int* __restrict__ n_invalid,
-                                                      int block0) {
+                                                      unsigned* first, int* __restrict__ n_invalid) {
   __shared__ int64_t lkey[kLdsTab];
   __shared__ int lval[kLdsTab];               // smallest position of the key in this block; later its HBM entry
   __shared__ unsigned short lst[kUniqChunk];  // occupied LDS entries, compacted
@@ -121,7 +122,7 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
   for (int i = threadIdx.x; i < kLdsTab; i += 256) { lkey[i] = kEmpty; lval[i] = kIntMax; }
   if (threadIdx.x < kUniqChunk / 32) flip[threadIdx.x] = 0;
   const int64_t V = tab.V;
-  const int base = (block0 + (int)blockIdx.x) * kUniqChunk;
+  const int base = (int)blockIdx.x * kUniqChunk;
   int ls[kUniqPer];
   int64_t idv[kUniqPer];
 #pragma unroll
@@ -169,6 +170,8 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
       if (occ & (1u << k)) lst[at++] = (unsigned short)(threadIdx.x * kLdsPer + k);
   }
   __syncthreads();
+  if (gridDim.x > kHeadMin && blockIdx.x >= kHeadBlocks && blockIdx.x < kResidentBlocks)
+    for (int i = 0; i < kHeadSleep; ++i) __builtin_amdgcn_s_sleep(32);
   // distinct keys of the block -> HBM table, kFly per thread in flight
   constexpr int kFly = kUniqPer;
   {
