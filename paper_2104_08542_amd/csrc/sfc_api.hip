@@ -292,6 +292,13 @@ int healthy(sfc_cache* c) {
   return SFC_OK;
 }
 
+// Pipelined, the unique passes of a batch of kTwoStreamMin up to kTwoStreamMax ids run on a stream of their
+// own, beside the rest of the previous step's prepare: small grids that leave most of the GPU idle.
+// Below, the events between the two streams cost more than that gains (213e3 ids, lookahead 1: 213 us a
+// pass on two streams, 197 on one); above, the passes fill the chip themselves (lookahead 2, ms per step
+// on two / one: 639e3 ids 0.284 / 0.299, 2.56e6 0.482 / 0.470, 8.9e6 in bags 2.00 / 1.98; 2.56e6 with three
+// caches taking turns 0.691 / 0.638).
+constexpr int64_t kTwoStreamMin = (int64_t)1 << 18, kTwoStreamMax = (int64_t)1 << 20;
 constexpr int kGridCap = 2048;   // blocks of the grid-stride kernels whose size lives on the device
 constexpr int kRebuildGrid = 2048; // blocks of the two launches that only work when the index is rebuilt
 
@@ -736,6 +743,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   // a small batch is prepared by one block (k_small_prepare), all of it when that block can also choose
   // the victims
   const bool small = n_ids > 0 && n_ids <= kSmallIds && n_bags <= kSmallBags;
+  const bool one_stream = n_ids < kTwoStreamMin || n_ids >= kTwoStreamMax;
   const bool whole = small && c->dmap && (c->C >= c->V || c->C <= kSmallSlots);
   // With lookahead 0 the copies stand between the prepare and the lookup of the main stream, and the
   // way to the side stream and back costs about as much as kSwapMainBytes take on the link: a step
@@ -753,7 +761,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     HIPCHK(hipStreamWaitEvent(s, c->ev_tmp, 0));
     // a context freed by sfc_discard: its copies may still be reading its lists
     if (x->discarded && s != c->side) HIPCHK(hipStreamWaitEvent(s, x->ev_fetched, 0));
-    if (c->ins && !small) {
+    if (c->ins && !one_stream) {
       // The unique passes touch the batch table, the per-position table slots, the tally of
       // invalid ids, this step's set of counts, its context's position array and the caller's
       // buffers of this step: the previous step's prepare has finished with the shared ones once
@@ -768,7 +776,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     // waits for its copies, which may still be reading the lists that this prepare rewrites
     HIPCHK(hipStreamWaitEvent(s, x->ev_fetched, 0));
   }
-  hipStream_t su = c->ins && !small ? c->ins : s;   // stream of the unique passes
+  hipStream_t su = c->ins && !one_stream ? c->ins : s;   // stream of the unique passes
   c->t += 1;
   x->t = c->t; x->state = PREPARED; x->updated = false; x->main_pending = false; x->discarded = false;
   x->n_ids = n_ids; x->n_bags = n_bags; x->d_offsets = d_offsets;
@@ -896,10 +904,12 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
   hipStream_t s = c->st;
   const int64_t total = x->n_bags * c->d4;
   if (total > 0) {
-    // the rows of the batch into the memory-side cache first (returns at once when they are too many)
-    LAUNCH_TIMED_X(c, P_LOOKUP, true, true, k_warm_rows, dim3(grid_for(x->n_ids * c->d4, 2048, kWarmGrid)),
-                   dim3(256), s, (const int*)x->d_slot, (const float4*)c->cw, c->d4, (int)c->C, x->boff,
-                   (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, (int)(x->n_ids / 4));
+    // the rows of the batch into the memory-side cache first (not for a small batch; returns at once when
+    // the rows are too many)
+    if (x->n_ids * c->d4 >= kWarmMinChunks)
+      LAUNCH_TIMED_X(c, P_LOOKUP, true, true, k_warm_rows, dim3(grid_for(x->n_ids * c->d4, 2048, kWarmGrid)),
+                     dim3(256), s, (const int*)x->d_slot, (const float4*)c->cw, c->d4, (int)c->C, x->boff,
+                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, (int)(x->n_ids / 4));
     if (!x->d_offsets) {
       const int d4 = c->d4, sh = (d4 & (d4 - 1)) == 0 ? __builtin_ctz(d4) : -1;
       const int bpb = lookup_rows_per_block(d4);

@@ -233,6 +233,11 @@ inline int lookup_rows_per_block(int d4) {
 // It only pays while the rows fit that cache with room to spare: beyond kWarmMaxBytes of rows
 // (decided on the device from the step's unique count) the kernel returns at once.
 constexpr int64_t kWarmMaxBytes = (int64_t)96 << 20;
+// Below this many 16-byte chunks of output (32 MB) the gather alone is the faster one: its rows come once
+// from HBM whoever asks for them, and it is over before the writes get in their way (a pass with / without
+// the warm kernel: 1248 x 16 floats 25.4 / 22.2 us, 40e3 x 16 123.7 / 119.9, 639e3 x 16 (2.6e6 chunks) 415.9 /
+// 414.7, 213e3 x 128 (6.8e6) 213 / 217.6, 2.56e6 x 32 (2e7) 741 / 768).
+constexpr int64_t kWarmMinChunks = (int64_t)1 << 21;
 constexpr int kWarmGrid = 2048;
 
 __global__ __launch_bounds__(256) void k_warm_rows(const int* __restrict__ slot,

@@ -307,6 +307,18 @@ def test_host_copies_in_separate_blocks(C, n, optimizer):
     p.finish(); p.close()
 
 
+@pytest.mark.parametrize("lookahead", [1, 3])
+def test_pipelined_batches_on_one_and_on_two_prepare_streams(lookahead):
+    # pipelined, the unique passes take a stream of their own between 2^18 and 2^20 ids only: steps of
+    # either kind follow each other, a one-block batch among them
+    V, D = 300_000, 4
+    sizes = [270_000, 250_000, 300_000, 1_100_000, 280_000, 4000, 265_000, 1_100_000, 262_144, 262_143]
+    p = Pair(V, D, C=250_000, max_ids=1_100_000, lookahead=lookahead)
+    p.run_pipelined([(si.zipf_ids(n, 1.05, V, 510, t).numpy(), si.grads(n, D, 510, t).numpy(), None)
+                     for t, n in enumerate(sizes)], False)
+    p.close()
+
+
 def test_same_stream_and_separate_host_arrays():
     # copies on the main stream; Host weights and accumulators as two separate arrays
     V, D, n = 4000, 32, 2000
