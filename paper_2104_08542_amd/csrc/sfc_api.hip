@@ -330,7 +330,7 @@ constexpr int64_t kSwapWideBytes = (int64_t)256 << 20;
 // Lookahead 0: steps whose misses (judged as above) are at most this many bytes run their copies on
 // the main stream: the way there and back took 33 us of GPU time and 20 us of host time between the
 // prepare and the lookup, as much as 1 MiB each way takes on the link (a pass of 1024 x 39 ids with 0.88 MB
-// of misses: 193 -> 147 us; of 128 x 39 with none: 95 -> 49).
+// of misses: 193 -> 147 us).
 constexpr int64_t kSwapMainBytes = (int64_t)1 << 20;
 
 // One launch of the Host<->cache copies of a step on stream s (see k_swap_rows for the two

@@ -751,14 +751,9 @@ __global__ __launch_bounds__(256) void k_resolve(const int64_t* __restrict__ uni
 // ---------------------------------------------------------------------------------------------
 struct Plan { int M, need, T, r, K, f_new, n_bypass, oldest; };
 
-template <bool kAtomic>
 __device__ __forceinline__ void hist_add(int* w, int x) {
-  if (kAtomic) {
-    const int old = atomicAdd(w, x);
-    asm volatile("" :: "v"(old));          // the value has to be back, so the sum has been formed
-  } else {
-    *w += x;
-  }
+  const int old = atomicAdd(w, x);
+  asm volatile("" :: "v"(old));            // the value has to be back, so the sum has been formed
 }
 
 template <bool kAtomic>
@@ -806,19 +801,12 @@ __device__ __forceinline__ void plan_decide(Plan& pl, int M, int f, int oldest, 
   pl.oldest = need > 0 && T > oldest ? T : oldest;
 }
 
-// One thread, once no other reads the counters any more: the plan into the step's counters.
-// reuse: deleted index entries that the previous step's miss assignment took back into use.
-template <bool kAtomic>
-__device__ __forceinline__ void plan_write(const Plan& pl, Ctr* ctr, int f, int* hist, int t, int reuse) {
-  if (pl.need > 0 && pl.r > 0) hist_add<kAtomic>(&hist[pl.T], -pl.r);
-  hist_add<kAtomic>(&hist[t], pl.M - pl.n_bypass);
-  ctr->M = pl.M; ctr->K = pl.K; ctr->n_bypass = pl.n_bypass;
-  ctr->need = pl.need; ctr->T = pl.T; ctr->r = pl.r;
-  ctr->f_old = f; ctr->f = pl.f_new;
-  ctr->oldest = pl.oldest;
-  ctr->tomb -= reuse;
-  // a rebuild asked for by the previous step has run ahead of this step's resolve
-  if (ctr->rebuild) { ctr->rebuild = 0; ctr->tomb = 0; }
+// The plan into the step's counters.
+__device__ __forceinline__ void plan_store(const Plan& pl, Ctr& ctr, int f) {
+  ctr.M = pl.M; ctr.K = pl.K; ctr.n_bypass = pl.n_bypass;
+  ctr.need = pl.need; ctr.T = pl.T; ctr.r = pl.r;
+  ctr.f_old = f; ctr.f = pl.f_new;
+  ctr.oldest = pl.oldest;
 }
 
 // Plan (one block): scan the per-tile miss and position counts, then decide the victims.
@@ -870,7 +858,12 @@ __global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* tile_cnt,
   plan_decide<false>(pl, M, f, ctr->oldest, hist, t, lookahead, C, smem, &s_found);
   __syncthreads();
   if (threadIdx.x == 0) {
-    plan_write<false>(pl, ctr, f, hist, t, reuse);
+    if (pl.need > 0 && pl.r > 0) hist[pl.T] -= pl.r;
+    hist[t] += pl.M - pl.n_bypass;
+    plan_store(pl, *ctr, f);
+    ctr->tomb -= reuse;
+    // a rebuild asked for by the previous step has run ahead of this step's resolve
+    if (ctr->rebuild) { ctr->rebuild = 0; ctr->tomb = 0; }
     // K deletions are about to add tombstones; ask for a rebuild before the next resolve when a
     // eighth of the index would be deleted entries
     if (!ctr->dense && (unsigned)(ctr->tomb + pl.K) > hi / 8) ctr->rebuild = 1;
@@ -998,15 +991,18 @@ __global__ __launch_bounds__(256) void k_victim_unmap(const int64_t* __restrict_
 }
 
 // The step's counters, final since the plan, into the Host status block (sequence word odd while
-// they are being written).
-__device__ __forceinline__ void publish(const Ctr* ctr, int t) {
-  volatile HostStatus* h = ctr->hstat;
+// they are being written).  The block is uncached Host memory that nothing else is published through:
+// what its words need is their order, so each group of stores is waited for (a microsecond) and no
+// cache is written back (a system-scope fence took several).
+__device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+__device__ __forceinline__ void publish(volatile HostStatus* h, int t, int U, int n_hit, int M, int K,
+                                        int n_bypass, int n_invalid, int bad_offsets) {
   if (!h) return;
   h->seq = 2 * t - 1;
-  __threadfence_system();
-  h->U = ctr->U; h->n_hit = ctr->n_hit; h->M = ctr->M; h->K = ctr->K; h->n_bypass = ctr->n_bypass;
-  h->n_invalid = ctr->n_invalid; h->n_bad_offsets = ctr->bad_offsets;
-  __threadfence_system();
+  stores_done();
+  h->U = U; h->n_hit = n_hit; h->M = M; h->K = K; h->n_bypass = n_bypass;
+  h->n_invalid = n_invalid; h->n_bad_offsets = bad_offsets;
+  stores_done();
   h->seq = 2 * t;
 }
 
@@ -1037,7 +1033,8 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   const int free_slots = C - f;
   // Here, in one thread of a wide kernel, the publishing costs nothing that anyone waits for; in the
   // single-block plan kernel its two fences lengthened the prepare by 6 us.
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) publish(ctr, t);
+  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
+    publish(ctr->hstat, t, U, ctr->n_hit, ctr->M, K, ctr->n_bypass, ctr->n_invalid, ctr->bad_offsets);
   for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
     const int v = tile * kVidTile + (int)threadIdx.x;
     const bool miss = v < U && slot_out[v] == kMissMark;
@@ -1091,8 +1088,8 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
 // above were all start-up, drain and dependent round trips: what bounds this kernel is the chain ids ->
 // table -> rank -> index -> stamp -> lists, walked once with barriers in between instead of kernel
 // boundaries.  Same outputs, same
-// state: 1248 ids 19 us, 4992 ids 27 us, against 63 and 80 us in ten kernels (and 3 us of host time per
-// launch); a whole pass 118 -> 60 and 148 -> 95 us.
+// state: 1248 ids 16 us, 4992 ids 25 us, against 63 and 80 us in ten kernels (and 3 us of host time per
+// launch).
 //
 // kWhole (dense index, and either a cache that holds the whole table, so that nothing is ever evicted,
 // or one whose stamps a single block can scan: kSmallSlots): everything up to the grouping, one launch.
@@ -1125,7 +1122,7 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
   __shared__ int cntl[kSmallIds];
   __shared__ unsigned short ent[kSmallIds];   // table entry of each virtual id
   __shared__ int smem[20];
-  __shared__ int s_found, s_bad;
+  __shared__ int s_found, s_bad, s_err;
   const int tid = (int)threadIdx.x, n = a.n;
   const int per = (n + 1023) / 1024, p0 = tid * per;
   int64_t key[kSmallPer];
@@ -1138,7 +1135,7 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
   }
   for (int i = tid; i < kSmallTab; i += 1024) { keys[i] = kEmpty; val[i] = kIntMax; }
   for (int i = tid; i < kSmallIds; i += 1024) cntl[i] = 0;
-  if (tid == 0) s_bad = 0;
+  if (tid == 0) s_bad = s_err = 0;
   // counters of the previous step, read before anyone writes (prev == ctr on a cache's first step)
   Ctr c0;
   if (tid == 0) { c0 = a.prev ? *a.prev : *a.ctr; a.ctr->t = a.t; }
@@ -1216,7 +1213,7 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
       a.stamp[sl[j]] = a.t;
       ++hits;
       const int g = a.t - old[j];
-      if (g < kAgeBins) atomicAdd(&age[g], 1); else hist_add<true>(&a.hist[old[j]], -1);
+      if (g < kAgeBins) atomicAdd(&age[g], 1); else hist_add(&a.hist[old[j]], -1);
     } else if (id[j] >= 0) {
       ++packed;
     }
@@ -1250,7 +1247,8 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
         c0.t = a.t; c0.bad_offsets = 0;
       }
       c0.U = U; c0.n_invalid = n_invalid;
-      c0.err = a.ctr->err ? a.ctr->err : c0.err;     // a probe above may have flagged one
+      const int err = a.ctr->err;
+      if (err) c0.err = err;                         // a probe above may have flagged one
       *a.ctr = c0;
     }
     return;
@@ -1263,13 +1261,18 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
     int off = before >> 16, i0 = before & 0xffff;
     const int M = tot & 0xffff;
     if (a.offsets) for (int i = tid; i < n; i += 1024) bagl[i] = 0;
-    // the histogram: hits move to stamp t, the rest of the plan as k_plan does it
-    if (tid == 0) hist_add<true>(&a.hist[a.t], n_hit);
-    else if (age[tid]) hist_add<true>(&a.hist[a.t - tid], -age[tid]);
+    // the histogram: hits move to stamp t, the rest of the plan as k_plan does it.  Only a search for
+    // victims reads it in here, so only then do the sums have to be back.
     __shared__ int s_f, s_oldest;
-    if (tid == 0) { s_f = c0.f; s_oldest = c0.oldest; }
+    __shared__ HostStatus* s_hstat;
+    if (tid == 0) { s_f = c0.f; s_oldest = c0.oldest; s_hstat = c0.hstat; }
     __syncthreads();
     const int f = s_f, C = a.C, free_slots = C - f;
+    const int moved = tid == 0 ? n_hit : -age[tid];
+    if (moved) {
+      if (M > free_slots) hist_add(&a.hist[a.t - tid], moved);
+      else atomicAdd(&a.hist[a.t - tid], moved);
+    }
     Plan pl;
     plan_decide<true>(pl, M, f, s_oldest, a.hist, a.t, a.lookahead, C, smem, &s_found);
     // bag of every position, checked as k_pos2bag does
@@ -1313,7 +1316,8 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
               a.victim_slot[idx] = s0 + j; a.victim_id[idx] = vid_out;
               a.dmap[vid_out] = -1;
             } else {
-              flag_err(a.ctr, 4);                            // never while hist mirrors the stamps
+              s_err = 4;                                     // never while hist mirrors the stamps
+              flag_err(a.ctr, 4);
             }
           }
           lt_before += is_lt;
@@ -1363,15 +1367,17 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
       a.perm64[start[v] + rr[j]] = w;
     }
     if (tid == 0) {
+      if (pl.need > 0 && pl.r > 0) atomicAdd(&a.hist[pl.T], -pl.r);
+      if (M != pl.n_bypass) atomicAdd(&a.hist[a.t], M - pl.n_bypass);
       c0.U_prev = c0.U; c0.U = U; c0.n_hit = n_hit; c0.n_invalid = n_invalid;
       c0.fetch_on_main = 0; c0.t = a.t; c0.bad_offsets = s_bad;
-      c0.err = a.ctr->err ? a.ctr->err : c0.err;
+      plan_store(pl, c0, f);
+      if (s_err) c0.err = s_err;
       *a.ctr = c0;
-      plan_write<true>(pl, a.ctr, f, a.hist, a.t, 0);
       volatile HostStatus* h = c0.hstat;
       if (s_bad && h) h->bad_offsets_step = a.t;
-      publish(a.ctr, a.t);
     }
+    if (tid == 1023) publish(s_hstat, a.t, U, n_hit, M, pl.K, pl.n_bypass, n_invalid, s_bad);
   }
 }
 
