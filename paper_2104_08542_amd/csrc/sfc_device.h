@@ -32,6 +32,19 @@ __device__ __forceinline__ bool entry_cold(int64_t e) { return (e & kColdBit) !=
 // per virtual id: (positions << 32) | start of its group in perm64
 __device__ __forceinline__ bool group_cold(int64_t grp) { return (int)(grp >> 32) <= kColdMax; }
 
+// Positions [lo, hi) of a bag by its two offsets, whatever these hold: each clamped to [0, n] in 64 bits
+// before it becomes a 32-bit position (an offset below -2^31 narrowed as it is can look like any position).
+// Empty where lo >= hi.
+struct BagRange { int lo, hi; };
+__host__ __device__ __forceinline__ int clamp_offset(int64_t x, int n) { return x < 0 ? 0 : (x > n ? n : (int)x); }
+__host__ __device__ __forceinline__ BagRange bag_range(int64_t lo, int64_t hi, int n) {
+  return BagRange{clamp_offset(lo, n), clamp_offset(hi, n)};
+}
+// Is bag b of n_bags malformed: decreasing, or the first one not at 0, or the last one not ending at n?
+__host__ __device__ __forceinline__ bool bag_malformed(int64_t lo, int64_t hi, int b, int n_bags, int n) {
+  return hi < lo || (b == 0 && lo != 0) || (b == n_bags - 1 && hi != n);
+}
+
 // Status block in pinned, device-mapped Host memory: kernels write it, the host reads it without
 // waiting for any stream (sfc_check, sfc_peek_stats and the first lines of every step call).
 // The published counters are guarded by a sequence word: odd while a kernel is writing them.

@@ -481,14 +481,13 @@ __global__ __launch_bounds__(256) void k_pos2bag(const int64_t* __restrict__ off
   const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
   const int b0 = blockIdx.x * 256 + w * kWave, b = b0 + lane;
   bool bad = false;
-  int64_t lo = n, hi = n;                         // lanes beyond the last bag: empty, at the end
+  BagRange r{n, n};                               // lanes beyond the last bag: empty, at the end
   if (b < n_bags) {
-    lo = offsets[b]; hi = offsets[b + 1];
-    bad = hi < lo || (b == 0 && lo != 0) || (b == n_bags - 1 && hi != n);
-    if (lo < 0) lo = 0;
-    if (hi > n) hi = n;
+    const int64_t lo = offsets[b], hi = offsets[b + 1];
+    bad = bag_malformed(lo, hi, b, n_bags, n);
+    r = bag_range(lo, hi, n);
   }
-  starts[w][lane] = (int)(lo < n ? lo : n);
+  starts[w][lane] = r.lo;
   const uint64_t m = __ballot(bad);
   if (m && lane == 0) {
     atomicAdd(&ctr->bad_offsets, __popcll(m));
@@ -499,12 +498,13 @@ __global__ __launch_bounds__(256) void k_pos2bag(const int64_t* __restrict__ off
   if (b0 >= n_bags) return;
   if (m) {
     if (b < n_bags)
-      for (int64_t q = lo; q < hi; ++q) pos2bag[q] = b;
+      for (int q = r.lo; q < r.hi; ++q) pos2bag[q] = b;
     return;
   }
-  // no violation among these bags: their ranges tile [first start, last end)
+  // No violation among these bags: their offsets do not decrease, so their clamped ranges tile [first start,
+  // last end), also where the offsets lie outside [0, n] (the violation is then another wavefront's).
   const int last = n_bags - b0 < kWave ? n_bags - b0 - 1 : kWave - 1;
-  const int begin = starts[w][0], end = __shfl((int)hi, last, kWave);
+  const int begin = starts[w][0], end = __shfl(r.hi, last, kWave);
   for (int q = begin + lane; q < end; q += kWave) {
     int g = 0;
 #pragma unroll
@@ -1279,11 +1279,10 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
     if (a.offsets) {
       int bad = 0;
       for (int b = tid; b < a.n_bags; b += 1024) {
-        int64_t lo = a.offsets[b], hi = a.offsets[b + 1];
-        bad += hi < lo || (b == 0 && lo != 0) || (b == a.n_bags - 1 && hi != n);
-        if (lo < 0) lo = 0;
-        if (hi > n) hi = n;
-        for (int64_t q = lo; q < hi; ++q) bagl[q] = b;
+        const int64_t lo = a.offsets[b], hi = a.offsets[b + 1];
+        bad += bag_malformed(lo, hi, b, a.n_bags, n);
+        const BagRange r = bag_range(lo, hi, n);
+        for (int q = r.lo; q < r.hi; ++q) bagl[q] = b;
       }
       if (bad) atomicAdd(&s_bad, bad);
     }

@@ -530,6 +530,48 @@ def test_malformed_offsets_are_reported_not_followed():
         p.close()
 
 
+@pytest.mark.parametrize("n_ids,n_bags,index_kind", [(9000, 700, DENSE), (9000, 700, HASHED), (900, 700, HASHED),
+                                                     (900, 25_000, DENSE), (900, 700, DENSE)])
+@pytest.mark.parametrize("where", ["first", "inner", "last"])
+def test_malformed_offsets_at_every_size_and_place(where, n_ids, n_bags, index_kind):
+    # the bags of a batch too large for the one-block prepare, of one that a hashed index or the number of
+    # bags keeps from it, and of one that takes it; the offsets of a whole wavefront's bags and more hold
+    # values far outside, so that some wavefronts see a violation and others, inside the run, none
+    import paper_2104_08542_amd as sfc
+    V, D = 5000, 8
+    rng = np.random.default_rng(n_ids + n_bags)
+    ids = rng.integers(0, V, n_ids)
+    good = np.sort(np.concatenate([[0, n_ids], rng.integers(0, n_ids + 1, n_bags - 1)])).astype(np.int64)
+    a = {"first": 0, "inner": n_bags // 2 - 100, "last": n_bags - 199}[where]
+    for t, x in enumerate([-7, -2 ** 31 - 1, -2 ** 32 + 100, -0x180000001, n_ids + 1, 2 ** 32 + 5, 2 ** 40]):
+        off = good.copy()
+        off[a:a + 200] = x
+        bad = int(np.sum(off[1:] < off[:-1])) + int(off[0] != 0 and off[1] >= off[0])
+        bad += int(off[-1] != n_ids and off[-1] >= off[-2])
+        p = Pair(V, D, C=4000 if n_ids < 4000 else V, max_ids=n_ids, max_bags=n_bags, index_kind=index_kind)
+        c = p.cache
+        c.prepare(torch.from_numpy(ids).to(p.dev), torch.from_numpy(off).to(p.dev))
+        st = c.stats()
+        assert st["n_bad_offsets"] == bad > 0, (x, st, bad)
+        c.fetch_misses()
+        out = c.lookup().cpu().numpy()
+        rows = p.table.w[ids].astype(np.float64)
+        lo, hi = np.clip(off[:-1], 0, n_ids), np.clip(off[1:], 0, n_ids)
+        want = np.stack([rows[i:j].sum(0) for i, j in zip(lo, hi)])
+        size = np.stack([np.abs(rows[i:j]).sum(0) for i, j in zip(lo, hi)])
+        # fp32 additions in a row: each rounds by at most 2^-24 of what has been added up
+        assert np.all(np.abs(out - want) <= 2.0 ** -24 * np.maximum(hi - lo, 1)[:, None] * size + 1e-30), x
+        c.backward_update(torch.zeros(n_bags, D, device=p.dev))
+        torch.cuda.synchronize()
+        with pytest.raises(sfc.SfcError) as e:
+            c.check()
+        assert e.value.code == sfc.SFC_EINVAL and "step 1" in str(e.value)
+        assert c.verify() == [0, 0, 0, 0]
+        c.flush()
+        assert np.array_equal(p.table.w, p.ow)         # a zero gradient changes no weight
+        p.close()
+
+
 def test_status_block_needs_no_waiting():
     # counters and health of the latest planned step, read from pinned memory
     V, D, n = 5000, 8, 3000
