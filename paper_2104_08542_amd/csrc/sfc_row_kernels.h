@@ -328,7 +328,8 @@ __global__ __launch_bounds__(256) void k_lookup_onehot(const int* __restrict__ p
 // is bound by the row traffic (every position reads a full row; only the rows that are hot
 // enough to stay in an XCD's L2 are not fetched again).
 // Malformed offsets are reported by the prepare step; here they only must not lead outside
-// pos_slot, hence the clamp to [0, n_ids].
+// pos_slot, hence the clamp of both ends to [0, n_ids] (a start near 2^63 as it is would wrap round when
+// the unrolled loop adds to it).
 #ifndef SFC_BAG_UNROLL
 #define SFC_BAG_UNROLL 8
 #endif
@@ -343,9 +344,9 @@ __global__ __launch_bounds__(256) void k_lookup_bags(const int64_t* __restrict__
   const int g = lane / d4, c = lane - g * d4;
   const int64_t b = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * G + g;
   if (g >= G || b >= n_bags) return;
-  int64_t q = offsets[b], e = offsets[b + 1];
-  if (q < 0) q = 0;
-  if (e > n_ids) e = n_ids;
+  const BagRange r = bag_range(offsets[b], offsets[b + 1], (int)n_ids);
+  int64_t q = r.lo;
+  const int64_t e = r.hi;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   int sl[kBagUnroll], sn[kBagUnroll];
 #pragma unroll

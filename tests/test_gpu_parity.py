@@ -543,7 +543,7 @@ def test_malformed_offsets_at_every_size_and_place(where, n_ids, n_bags, index_k
     ids = rng.integers(0, V, n_ids)
     good = np.sort(np.concatenate([[0, n_ids], rng.integers(0, n_ids + 1, n_bags - 1)])).astype(np.int64)
     a = {"first": 0, "inner": n_bags // 2 - 100, "last": n_bags - 199}[where]
-    for t, x in enumerate([-7, -2 ** 31 - 1, -2 ** 32 + 100, -0x180000001, n_ids + 1, 2 ** 32 + 5, 2 ** 40]):
+    for x in [-7, -2 ** 31 - 1, -2 ** 32 + 100, -0x180000001, -2 ** 63, n_ids + 1, 2 ** 32 + 5, 2 ** 63 - 4, 2 ** 63 - 1]:
         off = good.copy()
         off[a:a + 200] = x
         bad = int(np.sum(off[1:] < off[:-1])) + int(off[0] != 0 and off[1] >= off[0])
