@@ -101,11 +101,13 @@ struct StepCtx {
   int* miss_row = nullptr;            // [max_ids] cache row of each miss (bypass rows already offset)
   int64_t* miss_id = nullptr;         // [max_ids] id of each miss
   int boff = 0;                       // bypass slot C + j lives at row C + boff + j
-  hipEvent_t ev_prepared = nullptr;   // the step's prepare kernels have run
+  hipEvent_t ev_prepared = nullptr;   // the step's prepare kernels have run (lookahead 0: all but the grouping pass)
   hipEvent_t ev_fetched = nullptr;    // the side-stream launch of the step's Host copies has run
   bool updated = false;               // backward_update has been enqueued for this step
   bool discarded = false;             // freed by sfc_discard: the step's copies may still be running
   bool copies_on_main = false;        // this step's copies run on the main stream
+  bool grouping_due = false;          // lookahead 0: the grouping pass goes out with sfc_fetch_misses
+  SortGeom sg{};                      // shape of the step's counting and grouping passes
   bool joined = false;                // the main stream is behind the side-stream launch of the step's copies
   // pipelined mode: the second launch of the Host copies, due on the main stream behind the
   // update of step main_after (see k_swap_rows); older1 .. older3 = counters of the older steps
@@ -403,10 +405,11 @@ int seg_launch(sfc_cache* c, StepCtx* x, const float* d_grad, float* d_common, d
 }
 
 // The prepare's kernels behind the resolve: bags of the positions, victims' plan and lists, slots of the
-// misses, grouping.  (Called where the resolve has run on c->prep.)
-int plan_and_group(sfc_cache* c, StepCtx* x, const SortGeom& sg, int* cnt, int* cnt_rep) {
+// misses.  (Called where the resolve has run on c->prep; group_positions follows.)
+void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
   hipStream_t s = c->prep;
   const int n = (int)x->n_ids;
+  const SortGeom& sg = x->sg;
   // (after the resolve: it tallies into the step's counters, which that kernel may have started)
   if (n > 0 && x->d_offsets)
     hipLaunchKernelGGL(k_pos2bag, dim3((unsigned)((x->n_bags + 255) / 256)), dim3(256), 0, s,
@@ -427,18 +430,29 @@ int plan_and_group(sfc_cache* c, StepCtx* x, const SortGeom& sg, int* cnt, int* 
                      c->cur_rep, sg.bins, sg.nrep, c->tile_cnt, c->grp, x->cold_pay, c->tile_miss,
                      x->victim_slot, x->d_slot, x->d_miss, x->miss_row, x->miss_id, x->boff, c->slot_id,
                      c->stamp, c->index, c->hi, c->dmap, x->t, (int)c->C, c->tile_reuse, x->ctr);
-  // The Host copies need nothing of the grouping: with lookahead 0 they are let go here, so that the way
-  // to the side stream (12 us) and the grouping pass, beside the copies' first round trips, cost no time
-  // of their own.  (Pipelined, the grouping is on the path of the next prepare: there it stays first.)
-  if (c->nctx == 1 && !x->copies_on_main) HIPCHK(hipEventRecord(x->ev_prepared, s));
-  if (n > 0) {
-    auto scat = sg.threads == 256 ? k_scatter<4, 256> : sg.threads == 512 ? k_scatter<8, 512> : k_scatter<8, 1024>;
-    hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.threads), 0, s, x->d_inverse,
-                       x->d_offsets ? c->pos2bag : (const int*)nullptr, n, c->grp, (int*)x->cold_pay,
-                       (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
-                       (const int*)x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags);
-  }
-  if (c->nctx > 1) HIPCHK(hipEventRecord(x->ev_prepared, s));
+}
+
+// The grouping pass, on c->prep behind the above.  The Host copies need nothing of it: with lookahead 0
+// sfc_fetch_misses launches it behind the event that lets the copies go, so that the way to the side stream
+// (12 us) and this pass, beside the copies' first round trips, cost no time of their own.  (Not in the
+// prepare with the event in front of it: the copies come behind what the caller gives the main stream
+// between the two calls.)  Pipelined, the grouping is on the path of the next prepare and stays in its own.
+int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
+  x->grouping_due = false;
+  const int n = (int)x->n_ids;
+  if (n <= 0) return SFC_OK;
+  hipStream_t s = c->prep;
+  const SortGeom& sg = x->sg;
+  EventPair ep{};
+  int rc;
+  if (extra && (rc = prof_begin(c, P_PREPARE, s, &ep))) return rc;
+  ep.extra = true;
+  auto scat = sg.threads == 256 ? k_scatter<4, 256> : sg.threads == 512 ? k_scatter<8, 512> : k_scatter<8, 1024>;
+  hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.threads), 0, s, x->d_inverse,
+                     x->d_offsets ? c->pos2bag : (const int*)nullptr, n, c->grp, (int*)x->cold_pay,
+                     (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
+                     (const int*)x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags);
+  if (extra) return prof_end(c, P_PREPARE, s, &ep);
   return SFC_OK;
 }
 
@@ -792,7 +806,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   uint32_t hu = (uint32_t)(2 * n_ids);
   if (hu < 64) hu = 64;                       // the batch table is empty between steps: any size works
   const int nchunk = (n + kPosChunk - 1) / kPosChunk;
-  const SortGeom sg = small ? small_geom(n) : sort_geom(n);
+  const SortGeom sg = x->sg = small ? small_geom(n) : sort_geom(n);
   if (small) {
     // its unique passes are part of the kernel below
   } else if (n > 0) {
@@ -851,11 +865,12 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                        c->dmap ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid);
   }
   if (c->ins) { HIPCHK(hipEventRecord(c->ev_resolved, s)); c->resolved_once = true; }
-  if (whole) {
-    if (!x->copies_on_main) HIPCHK(hipEventRecord(x->ev_prepared, s));
-  } else if ((rc = plan_and_group(c, x, sg, cnt, cnt_rep))) {
-    return rc;
+  x->grouping_due = !whole && c->nctx == 1;
+  if (!whole) {
+    plan_and_assign(c, x, cnt, cnt_rep);
+    if (c->nctx > 1 && (rc = group_positions(c, x, false))) return rc;
   }
+  if (c->nctx > 1) HIPCHK(hipEventRecord(x->ev_prepared, s));
   HIPCHK(hipGetLastError());
   return prof_end(c, P_PREPARE, s, &ep);
 }
@@ -877,16 +892,20 @@ int sfc_fetch_misses(sfc_cache* c) {
     else if (o->t == x->t - 3) x->older3 = o->ctr;
     if (o->t > x->main_after) x->main_after = o->t;
   }
+  // everything the main stream has been given so far comes before the copies: older updates and their
+  // second launches, what the caller enqueued behind the prepare (rows it writes into the Host table, say),
+  // with lookahead 0 the prepare itself, which launch_swap then waits for by this event
   const bool on_main = x->copies_on_main;
   if (!on_main && c->nctx > 1) {
-    // everything the main stream has been given so far comes first: older updates and their second
-    // launches (with lookahead 0 the prepare is behind those, and the copies are behind the prepare)
     HIPCHK(hipEventRecord(c->ev_tmp, c->st));
     HIPCHK(hipStreamWaitEvent(c->side, c->ev_tmp, 0));
+  } else if (!on_main) {
+    HIPCHK(hipEventRecord(x->ev_prepared, c->st));
   }
+  int rc;
+  if (x->grouping_due && (rc = group_positions(c, x, true))) return rc;
   x->joined = on_main;
-  int rc = launch_swap(c, x, on_main ? c->st : c->side, 0);
-  if (rc) return rc;
+  if ((rc = launch_swap(c, x, on_main ? c->st : c->side, 0))) return rc;
   x->main_pending = x->older1 || x->older2 || x->older3;
   x->state = FETCHED;
   return SFC_OK;

@@ -1,4 +1,6 @@
 """HIP path vs CPU oracle, element by element (run with -m gpu on an MI355X)."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -641,4 +643,41 @@ def test_steps_given_up_without_a_lookup_still_bring_their_rows():
     assert c.verify() == [0, 0, 0, 0]
     c.flush()
     assert np.array_equal(p.table.w, p.ow) and np.array_equal(p.table.acc, p.oa)
+    p.close()
+
+
+def _copy_on(stream, dst, src, nbytes):
+    """Asynchronous copy between device and pinned Host memory on a stream."""
+    hip = ctypes.CDLL("libamdhip64.so")
+    hip.hipMemcpyAsync.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.c_size_t, ctypes.c_int, ctypes.c_void_p]
+    assert hip.hipMemcpyAsync(dst, src, nbytes, 4, stream.cuda_stream) == 0       # 4: direction by the pointers
+
+
+@pytest.mark.parametrize("lookahead", [0, 1])
+def test_work_between_prepare_and_fetch_comes_before_the_copies(lookahead):
+    # the caller fills the Host rows of a batch's ids on the main stream once the prepare has gone out
+    # (rows that are set up when their id is first seen): the Host copies come behind that work, for steps
+    # of every size, whichever stream their copies take
+    D, sizes = 32, [60_000, 300, 300, 5000, 60_000, 7000, 200]
+    V = sum(sizes)
+    p = Pair(V, D, C=V, max_ids=60_000, lookahead=lookahead, interleaved=False)
+    c, at = p.cache, 0
+    for t, n in enumerate(sizes):
+        ids = at + torch.randperm(n, generator=torch.Generator().manual_seed(t))
+        new = torch.randn(n, D, generator=torch.Generator().manual_seed(100 + t)).to(p.dev)
+        d_ids = ids.to(p.dev)
+        torch.cuda.synchronize()
+        c.prepare(d_ids)
+        torch.cuda._sleep(20_000_000)
+        _copy_on(c.stream, p.table._pw + 4 * D * at, new.data_ptr(), 4 * D * n)
+        filled = torch.cuda.Event()
+        filled.record()
+        c.fetch_misses()
+        assert not filled.query(), "the copies had nothing to wait for"
+        out = c.lookup()
+        assert torch.equal(out, new[d_ids - at]), (t, n)
+        c.backward_update(torch.zeros(n, D, device=p.dev))
+        at += n
+    torch.cuda.synchronize()
+    assert c.verify() == [0, 0, 0, 0]
     p.close()
