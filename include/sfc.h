@@ -10,7 +10,8 @@
  * the caller):
  *
  *     sfc_prepare          lines 3-4   ids -> global_id / virtual_id, hit / miss / victims, slots
- *     sfc_fetch_misses     lines 5-6   victims cache->Host, missed rows Host->cache (side stream)
+ *     sfc_fetch_misses     lines 5-6   victims cache->Host, missed rows Host->cache (side stream,
+ *                                      or `stream` where they are few: see there)
  *     sfc_lookup           lines 9,11  [bags, dim] model input from the cached rows
  *     sfc_backward_update  line 14     segment-sum of the gradients per virtual id + optimizer update
  *
@@ -114,7 +115,8 @@ typedef struct {
                                  prepare buffers. */
   int32_t max_steps;          /* steps this cache may run (sizes the recency histogram); 0 = 1<<20 */
   void* stream;               /* hipStream_t for prepare / lookup / backward_update */
-  void* side_stream;          /* hipStream_t for the Host<->cache copies; may equal stream */
+  void* side_stream;          /* hipStream_t for the Host<->cache copies (see sfc_fetch_misses for
+                                 the few that run on stream); may equal stream */
   int32_t optimizer;          /* SFC_OPT_* */
   int32_t index_kind;         /* SFC_INDEX_AUTO (0), SFC_INDEX_HASHED or SFC_INDEX_DENSE */
   int64_t host_state_stride;  /* floats between consecutive rows of h_acc; 0 = S */
@@ -189,10 +191,15 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                 int32_t* d_miss_vids);
 
 /*
- * Step 2 (Algorithm 1 lines 5-6): on the side stream, after the prepare of this step, write every
- * victim row and its optimizer state back to the Host table and copy every missed row and its
- * state from the Host table into its slot (a victim's row is read before its slot is
- * overwritten).  The main stream is made to wait for it before it touches the step's rows.
+ * Step 2 (Algorithm 1 lines 5-6): write every victim row and its optimizer state back to the Host
+ * table and copy every missed row and its state from the Host table into its slot (a victim's row
+ * is read before its slot is overwritten).  The copies come after all that `stream` and
+ * `side_stream` have been given before this call.  They run on side_stream; with lookahead 0 those
+ * of a step that moves about a megabyte or less run on `stream` instead (side_stream is then not
+ * made to wait for them, which would cost more than they do).  `stream` is made to wait for the
+ * copies by the next call that touches the step's rows: behind sfc_lookup, sfc_segment_sum or
+ * sfc_backward_update of the step `stream` alone tells that they are done, before that only
+ * `stream` and side_stream together.
  * With lookahead > 0 the copies run behind the updates of older steps still in flight whenever
  * one of those had bypass rows (their rows reach the Host table only with the update).
  */

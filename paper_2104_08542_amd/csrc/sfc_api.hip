@@ -330,10 +330,27 @@ constexpr int kSwapBlocks = 32;
 constexpr int kSwapBlocksWide = 128;
 constexpr int64_t kSwapWideBytes = (int64_t)256 << 20;
 // Lookahead 0: steps whose misses (judged as above) are at most this many bytes run their copies on
-// the main stream: the way there and back took 33 us of GPU time and 20 us of host time between the
+// the main stream (see swap_on_main): the way there and back took 33 us of GPU time and 20 us of host time between the
 // prepare and the lookup, as much as 1 MiB each way takes on the link (a pass of 1024 x 39 ids with 0.88 MB
 // of misses: 193 -> 147 us).
 constexpr int64_t kSwapMainBytes = (int64_t)1 << 20;
+
+// Do this step's copies run on the main stream?  With lookahead 0 they stand between the prepare and the
+// lookup of that stream, so a step that moves little stays there (kSwapMainBytes), but only while the side
+// stream has nothing to do: what the caller has given that stream before sfc_fetch_misses comes before the
+// copies.  (Asking takes the host half a microsecond; an event between the two streams in every step took a
+// pass of 32 x 39 ids from 20 to 34 us or more, one of 1024 x 39 from 120 to 144.)
+bool swap_on_main(sfc_cache* c) {
+  if (c->nctx > 1) return false;
+  if (c->side == c->st) return true;
+  const volatile HostStatus* h = c->hstat;
+  if (h->seq == 0 || (int64_t)h->M * (c->d4 + c->s4) * 16 > kSwapMainBytes) return false;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(c->side, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+  if (hipStreamQuery(c->side) == hipSuccess) return true;
+  if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();
+  return false;
+}
 
 // One launch of the Host<->cache copies of a step on stream s (see k_swap_rows for the two
 // launches of pipelined mode).
@@ -759,14 +776,6 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   const bool small = n_ids > 0 && n_ids <= kSmallIds && n_bags <= kSmallBags;
   const bool one_stream = n_ids < kTwoStreamMin || n_ids >= kTwoStreamMax;
   const bool whole = small && c->dmap && (c->C >= c->V || c->C <= kSmallSlots);
-  // With lookahead 0 the copies stand between the prepare and the lookup of the main stream, and the
-  // way to the side stream and back costs about as much as kSwapMainBytes take on the link: a step
-  // that moves less stays on the main stream.
-  {
-    const volatile HostStatus* h = c->hstat;
-    x->copies_on_main = c->nctx == 1 && (c->side == c->st || (h->seq != 0 &&
-                        (int64_t)h->M * (c->d4 + c->s4) * 16 <= kSwapMainBytes));
-  }
   hipStream_t s = c->prep;
   if (s != c->st) {
     // the prepare stream must not overtake what the main stream has been given so far: the
@@ -895,7 +904,7 @@ int sfc_fetch_misses(sfc_cache* c) {
   // everything the main stream has been given so far comes before the copies: older updates and their
   // second launches, what the caller enqueued behind the prepare (rows it writes into the Host table, say),
   // with lookahead 0 the prepare itself, which launch_swap then waits for by this event
-  const bool on_main = x->copies_on_main;
+  const bool on_main = x->copies_on_main = swap_on_main(c);
   if (!on_main && c->nctx > 1) {
     HIPCHK(hipEventRecord(c->ev_tmp, c->st));
     HIPCHK(hipStreamWaitEvent(c->side, c->ev_tmp, 0));

@@ -681,3 +681,54 @@ def test_work_between_prepare_and_fetch_comes_before_the_copies(lookahead):
     torch.cuda.synchronize()
     assert c.verify() == [0, 0, 0, 0]
     p.close()
+
+
+def test_work_on_the_side_stream_comes_before_the_copies():
+    # lookahead 0: what the caller has given the side stream before sfc_fetch_misses comes before the
+    # copies of the step, also of a step so small that its copies would take the main stream
+    D, sizes = 32, [2000, 300, 300, 5000, 200, 40_000, 300, 7000, 100]
+    V = sum(sizes)
+    p = Pair(V, D, C=V, max_ids=40_000, interleaved=False)
+    c, at = p.cache, 0
+    for t, n in enumerate(sizes):
+        ids = at + torch.randperm(n, generator=torch.Generator().manual_seed(t))
+        new = torch.randn(n, D, generator=torch.Generator().manual_seed(200 + t)).to(p.dev)
+        d_ids = ids.to(p.dev)
+        torch.cuda.synchronize()
+        c.prepare(d_ids)
+        if t % 2:                            # (every other step has nothing to wait for)
+            with torch.cuda.stream(c.side):
+                torch.cuda._sleep(20_000_000)
+                _copy_on(c.side, p.table._pw + 4 * D * at, new.data_ptr(), 4 * D * n)
+                filled = torch.cuda.Event()
+                filled.record()
+        c.fetch_misses()
+        out = c.lookup()
+        if t % 2:
+            assert not filled.query(), "the copies had nothing to wait for"
+            assert torch.equal(out, new[d_ids - at]), (t, n)
+        else:
+            assert torch.equal(out.cpu(), p.table.w_t[ids]), (t, n)
+        c.backward_update(torch.zeros(n, D, device=p.dev))
+        at += n
+    torch.cuda.synchronize()
+    assert c.verify() == [0, 0, 0, 0]
+    p.close()
+
+
+@pytest.mark.parametrize("n", [300, 20_000])
+def test_main_stream_behind_the_lookup_tells_that_the_copies_are_done(n):
+    # evicted rows are in the Host table once the main stream has run the step's lookup, whether the
+    # step's copies were few (main stream) or many (side stream)
+    V, D = 10 * n, 32
+    p = Pair(V, D, C=n, max_ids=n)
+    c, ids = p.cache, [torch.arange(t * n, (t + 1) * n, device=p.dev) for t in range(6)]
+    for t in range(6):
+        c.prepare(ids[t]); c.fetch_misses()
+        c.lookup()
+        c.stream.synchronize()
+        if t:                                # the batch before was updated in the cache and then evicted
+            now = p.table.w[(t - 1) * n:t * n]
+            assert not np.any(now == p.ow[(t - 1) * n:t * n])
+        c.backward_update(torch.ones(n, D, device=p.dev))
+    p.close()
