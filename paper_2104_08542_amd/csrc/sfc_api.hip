@@ -18,6 +18,7 @@
 #include <hip/hip_ext.h>
 
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -1137,8 +1138,15 @@ int sfc_peek_stats(sfc_cache* c, sfc_stats* h_out, int64_t* h_step) {
   memset(h_out, 0, sizeof *h_out);
   *h_step = 0;
   // the kernel that publishes makes the sequence word odd, writes, makes it even: take a copy
-  // that has the same even sequence word before and after
-  for (int tries = 0; tries < 1000; ++tries) {
+  // that has the same even sequence word before and after.  Its writes take microseconds on the link,
+  // thousands of reads here, so the limit is a time far beyond that.
+  std::chrono::steady_clock::time_point end{};
+  for (int tries = 1;; ++tries) {
+    if (tries % 1024 == 0) {
+      const auto now = std::chrono::steady_clock::now();
+      if (tries == 1024) end = now + std::chrono::milliseconds(100);
+      else if (now > end) break;
+    }
     const int s1 = h->seq;
     if (s1 & 1) continue;
     std::atomic_thread_fence(std::memory_order_acquire);

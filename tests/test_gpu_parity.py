@@ -1,5 +1,6 @@
 """HIP path vs CPU oracle, element by element (run with -m gpu on an MI355X)."""
 import ctypes
+import time
 
 import numpy as np
 import pytest
@@ -572,6 +573,25 @@ def test_malformed_offsets_at_every_size_and_place(where, n_ids, n_bags, index_k
         c.flush()
         assert np.array_equal(p.table.w, p.ow)         # a zero gradient changes no weight
         p.close()
+
+
+@pytest.mark.parametrize("n", [40, 9000])
+def test_counters_can_be_read_while_the_device_writes_them(n):
+    # polled without a pause from the call on, so that many reads fall into the microseconds in which the
+    # kernel writes the block
+    p = Pair(V=200, D=4, C=200, max_ids=n)
+    c = p.cache
+    ids = torch.arange(n, device=p.dev) % 200
+    for t in range(1, 301):
+        c.prepare(ids)
+        end = time.time() + 20
+        st, step = c.peek_stats()
+        while step != t and time.time() < end:
+            assert step == t - 1
+            st, step = c.peek_stats()
+        assert step == t and st["n_unique"] == min(n, 200) and st["n_miss"] == (min(n, 200) if t == 1 else 0)
+        c.fetch_misses(); c.discard()
+    p.close()
 
 
 def test_status_block_needs_no_waiting():
