@@ -1373,10 +1373,13 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
       plan_store(pl, c0, f);
       if (s_err) c0.err = s_err;
       *a.ctr = c0;
-      volatile HostStatus* h = c0.hstat;
-      if (s_bad && h) h->bad_offsets_step = a.t;
     }
-    if (tid == 1023) publish(s_hstat, a.t, U, n_hit, M, pl.K, pl.n_bypass, n_invalid, s_bad);
+    if (tid == 1023) {
+      // whoever sees the step's counters also sees that its offsets were malformed: first that, and back
+      volatile HostStatus* h = s_hstat;
+      if (s_bad && h) { h->bad_offsets_step = a.t; stores_done(); }
+      publish(s_hstat, a.t, U, n_hit, M, pl.K, pl.n_bypass, n_invalid, s_bad);
+    }
   }
 }
 

@@ -594,6 +594,31 @@ def test_counters_can_be_read_while_the_device_writes_them(n):
     p.close()
 
 
+@pytest.mark.parametrize("n,index_kind", [(40, DENSE), (6000, DENSE), (40, HASHED), (9000, DENSE)])
+def test_malformed_offsets_are_reported_no_later_than_the_counters(n, index_kind):
+    # without waiting for the device: a caller that sees a step's counters has its report as well, for
+    # batches prepared by one block and by the general passes
+    import paper_2104_08542_amd as sfc
+    p = Pair(V=200, D=4, C=200, max_ids=n, max_bags=4, index_kind=index_kind)
+    c = p.cache
+    ids = torch.arange(n, device=p.dev) % 200
+    off = torch.tensor([0, n, 0, n, n - 1], dtype=torch.int64, device=p.dev)
+    torch.cuda.synchronize()
+    for t in range(1, 201):
+        c.prepare(ids, off)
+        end = time.time() + 20
+        st, step = c.peek_stats()
+        while step != t and time.time() < end:
+            st, step = c.peek_stats()
+        assert step == t
+        assert st["n_bad_offsets"] == 2
+        with pytest.raises(sfc.SfcError) as e:
+            c.check()
+        assert e.value.code == sfc.SFC_EINVAL and "step %d " % t in str(e.value)
+        c.fetch_misses(); c.discard()
+    p.close()
+
+
 def test_status_block_needs_no_waiting():
     # counters and health of the latest planned step, read from pinned memory
     V, D, n = 5000, 8, 3000
