@@ -227,9 +227,12 @@ int sfc_segment_sum(sfc_cache* c, const float* d_grad, float* d_common_grad);
  * outputs and result (bit for bit), but the kernels' scratch (the partial sums of runs that cross
  * a thread block's edge) lives in a fixed array inside the library's code object instead of the
  * buffer sfc_cache_create allocated: SFC_STATIC_SCRATCH_BYTES per GPU, held until the process
- * ends.  Returns SFC_ELIMIT when the step needs more (2 * blocks * (8 * dim + 4) bytes, blocks =
- * wavefronts of the stream / 4; the target configuration takes 1.6 MB).  Calls no allocating
- * routine and creates no events.  Every call on one GPU shares the array: calls that overlap on
+ * ends.  Returns SFC_ELIMIT for a batch that counts as more: 2 * blocks * (8 * dim + 4) bytes, blocks
+ * = a quarter of the wavefronts that spans of 8 positions per lane group (below 2^18 ids) or 32 (from
+ * there on; more where that would be over 12288 wavefronts) make.  Rows of up to 128 floats are never
+ * refused, rows of 256 from 65409 ids on.  The count goes by the size of the batch alone; what the
+ * call then uses may be less (2.56e6 ids of dim 32: 1.3 MB).  Calls no allocating routine and
+ * creates no events.  Every call on one GPU shares the array: calls that overlap on
  * one GPU (two caches on two streams) race; nothing needs clearing between calls.
  */
 #define SFC_STATIC_SCRATCH_BYTES (8 << 20)

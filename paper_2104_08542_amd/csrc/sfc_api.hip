@@ -982,15 +982,19 @@ int sfc_segment_sum_static(sfc_cache* c, const float* d_grad, float* d_common_gr
   int dev = -1;
   HIPCHK(hipGetDevice(&dev));
   if (dev != c->device) return fail(SFC_EINVAL, "the cache lives on another device than the current one");
-  // the scratch the step needs: per block of the stream two fp64 rows and two virtual ids
+  // per block of the stream two fp64 rows and two virtual ids
   const SegGeom g = seg_geom(c->D, x->n_ids > 0 ? x->n_ids : 1);
   const int64_t nblk = (g.waves + 3) / 4;
   const int64_t sums = 2 * nblk * c->D * (int64_t)sizeof(double);
-  const int64_t need = seg_scratch_limit(c->D, x->n_ids > 0 ? x->n_ids : 1);
-  if (need > (int64_t)SFC_STATIC_SCRATCH_BYTES || sums + 2 * nblk * (int64_t)sizeof(int) > (int64_t)SFC_STATIC_SCRATCH_BYTES) {
-    char msg[160];
-    snprintf(msg, sizeof msg, "sfc_segment_sum_static: this step needs %lld bytes of scratch, the "
-             "fixed array holds %d", (long long)need, (int)SFC_STATIC_SCRATCH_BYTES);
+  const int64_t used = sums + 2 * nblk * (int64_t)sizeof(int);
+  // what is refused goes by the batch's size alone (see the header), not by the spans that the stream takes;
+  // `used` fits wherever that does
+  const int64_t counted = seg_scratch_count(c->D, x->n_ids > 0 ? x->n_ids : 1);
+  if (counted > (int64_t)SFC_STATIC_SCRATCH_BYTES || used > (int64_t)SFC_STATIC_SCRATCH_BYTES) {
+    char msg[192];
+    snprintf(msg, sizeof msg, "sfc_segment_sum_static: a batch of %lld ids of dim %d counts as %lld bytes of "
+             "scratch, the fixed array holds %d", (long long)x->n_ids, c->D, (long long)counted,
+             (int)SFC_STATIC_SCRATCH_BYTES);
     return fail(SFC_ELIMIT, msg);
   }
   void* base = nullptr;

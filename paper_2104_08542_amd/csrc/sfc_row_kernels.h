@@ -435,8 +435,9 @@ inline SegGeom seg_geom(int D, int64_t n) {
 }
 
 // Bytes of scratch by which sfc_segment_sum_static accepts or refuses a batch: that of spans of 8 entries
-// below 2^18 positions and 32 above (the stream above never takes more where this fits).
-inline int64_t seg_scratch_limit(int D, int64_t n) {
+// below 2^18 positions and 32 above.  The stream above mostly takes less; where it takes more (short rows,
+// at most 233 472 bytes then) both are far from the limit.
+inline int64_t seg_scratch_count(int D, int64_t n) {
   const int64_t G = 64 / (D / 4) < 1 ? 1 : 64 / (D / 4);
   int64_t L = (n + G * kSegTargetWaves - 1) / (G * kSegTargetWaves);
   const int64_t lmin = n < ((int64_t)1 << 18) ? 8 : 32;

@@ -52,3 +52,28 @@ def test_static_scratch_refuses_what_does_not_fit():
     sfc.sfc_segment_sum(c.h, g, out)                  # the allocating entry point still takes it
     c.backward_update(g)
     p.close()
+
+
+@pytest.mark.parametrize("D,n,counts_as", [(256, 65408, 8388576), (256, 65409, 8392680), (256, 200_000, 10260000),
+                                           (256, 262_144, 8404992), (128, 262_143, 5614936), (4, 131_073, 4680)])
+def test_static_scratch_counts_by_size_alone(D, n, counts_as):
+    # refused or taken by the rule of the header, whatever spans the stream takes for the batch, with
+    # that rule's figure in the text
+    import paper_2104_08542_amd as sfc
+    V = 300
+    p = Pair(V, D, C=V, max_ids=n)
+    c = p.cache
+    c.prepare((torch.arange(n, device=p.dev) * 7) % V); c.fetch_misses(); c.lookup()
+    g = torch.ones(n, D, device=p.dev)
+    want, got = torch.empty(n, D, device=p.dev), torch.zeros(n, D, device=p.dev)
+    sfc.sfc_segment_sum(c.h, g, want)
+    if counts_as > 8 << 20:
+        with pytest.raises(sfc.SfcError) as e:
+            sfc.sfc_segment_sum_static(c.h, g, got)
+        assert e.value.code == sfc.SFC_ELIMIT and "counts as %d bytes of scratch" % counts_as in str(e.value)
+        assert not got.any()
+    else:
+        sfc.sfc_segment_sum_static(c.h, g, got)
+        assert torch.equal(got[:V], want[:V])
+        assert torch.equal(got[:V, 0].cpu(), torch.bincount((torch.arange(n) * 7) % V).float()[(torch.arange(V) * 7) % V])
+    p.close()
