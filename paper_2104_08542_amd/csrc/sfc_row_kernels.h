@@ -54,25 +54,30 @@ struct HostRows {
 
 // Reads and writes of the link in separate blocks.  A lane that does both waits for its read, then writes,
 // and with few rounds per lane the lanes of the whole grid do so in step: the link idles in turn one way
-// and the other.  So with lookahead 0, and where the misses are many enough to matter and few enough
-// that the rounds have not drifted apart (kSplitMin .. kSplitMax of them), the victims' rows are first
-// copied beside the step's bypass rows in HBM (k_stage_victims; the region has a row for every id of the
-// batch, and victims + bypass rows are at most its misses); then kSplitWriters blocks carry them to the Host
-// while the other blocks read the missed rows into their slots.  Copies alone, staging included, against
-// one lane doing both: 52.7e3 misses of 128 bytes 218 against 236 us, 58.2e3 of 256 bytes 372 against 393,
-// 20.6e3 of 960 bytes 507 against 532; 6.9e3 of 256 bytes 67 against 65, 1e6 of 128 bytes 3740 against 3549.
+// and the other.  So with lookahead 0, and where the misses are many enough to matter (kSplitMin) and few
+// enough that the rounds have not drifted apart, the victims' rows are first copied beside the step's bypass
+// rows in HBM (k_stage_victims; the region has a row for every id of the batch, and victims + bypass rows are
+// at most its misses); then kSplitWriters blocks carry them to the Host while the other blocks read the
+// missed rows into their slots.  Copies alone, staging included, against one lane doing both, us: 128-byte
+// rows 59e3 240 / 271, 99e3 380 / 407, 137e3 526 / 546, 194e3 732 / 743, 250e3 932 / 932, 377e3 1385 / 1350;
+// 512-byte rows 18e3 234 / 264, 57e3 693 / 695, 93e3 1100 / 1112, 172e3 2005 / 1996, 212e3 2470 / 2457;
+// 960-byte rows 17.5e3 445 / 460, 46e3 1109 / 1120, 86e3 2015 / 2012, 144e3 3354 / 3337; 6.9e3 of 256 bytes
+// 67 / 65.  So the upper end is both a number of rows (kSplitMax) and of bytes (kSplitMaxBytes).
 constexpr int kSplitMin = 1 << 14;
 constexpr int kSplitMax = 1 << 18;
+constexpr unsigned kSplitMaxBytes = 64u << 20;
 constexpr int kSplitWriters = 32, kSplitReaders = 128;
-__device__ __forceinline__ bool split_swap(const Ctr* ctr) {
-  return ctr->M >= kSplitMin && ctr->M <= kSplitMax && ctr->K > 0;
+// w2: 16-byte chunks of a row and its state (at most 192, so the product stays below 2^30)
+__device__ __forceinline__ bool split_swap(const Ctr* ctr, int w2) {
+  return ctr->M >= kSplitMin && ctr->M <= kSplitMax && (unsigned)ctr->M * (unsigned)w2 * 16u <= kSplitMaxBytes &&
+         ctr->K > 0;
 }
 
 __global__ __launch_bounds__(256) void k_stage_victims(const int* __restrict__ victim_slot,
                                                         float4* __restrict__ cw, float4* __restrict__ ca,
                                                         int C, int boff, int d4, int s4, const Ctr* ctr) {
-  if (!split_swap(ctr)) return;
-  const unsigned w2 = (unsigned)(d4 + s4), total = (unsigned)ctr->K * w2;    // < 2^18 * 192
+  if (!split_swap(ctr, d4 + s4)) return;
+  const unsigned w2 = (unsigned)(d4 + s4), total = (unsigned)ctr->K * w2;    // at most kSplitMaxBytes / 16
   const int64_t row0 = (int64_t)C + boff + ctr->n_bypass;
   for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
     const unsigned k = i / w2;
@@ -135,7 +140,7 @@ __global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_
   __builtin_amdgcn_s_setprio(3);            // few waves, long round trips: issue ahead of the kernels beside them
   const int K = ctr->K;
   // staged_at >= 0: k_stage_victims has run, the victims' rows are at staged_at + the bypass rows
-  if (staged_at >= 0 && split_swap(ctr)) {
+  if (staged_at >= 0 && split_swap(ctr, d4 + s4)) {
     const int64_t row0 = (int64_t)staged_at + ctr->n_bypass;
     if (blockIdx.x < kSplitWriters)
       link_rows<true>(victim_id, [&](unsigned k) { return row0 + k; }, K, cw, ca, h, d4, s4, (int)blockIdx.x,
