@@ -933,9 +933,9 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
   hipStream_t s = c->st;
   const int64_t total = x->n_bags * c->d4;
   if (total > 0) {
-    // the rows of the batch into the memory-side cache first (not for a small batch; returns at once when
+    // the rows of the batch into the memory-side cache first (not for a small output; returns at once when
     // the rows are too many)
-    if (x->n_ids * c->d4 >= kWarmMinChunks)
+    if (total >= kWarmMinChunks)
       LAUNCH_TIMED_X(c, P_LOOKUP, true, true, k_warm_rows, dim3(grid_for(x->n_ids * c->d4, 2048, kWarmGrid)),
                      dim3(256), s, (const int*)x->d_slot, (const float4*)c->cw, c->d4, (int)c->C, x->boff,
                      (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, (int)(x->n_ids / 4));

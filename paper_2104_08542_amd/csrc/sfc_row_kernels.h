@@ -238,10 +238,14 @@ inline int lookup_rows_per_block(int d4) {
 // It only pays while the rows fit that cache with room to spare: beyond kWarmMaxBytes of rows
 // (decided on the device from the step's unique count) the kernel returns at once.
 constexpr int64_t kWarmMaxBytes = (int64_t)96 << 20;
-// Below this many 16-byte chunks of output (32 MB) the gather alone is the faster one: its rows come once
-// from HBM whoever asks for them, and it is over before the writes get in their way (a pass with / without
-// the warm kernel: 1248 x 16 floats 25.4 / 22.2 us, 40e3 x 16 123.7 / 119.9, 639e3 x 16 (2.6e6 chunks) 415.9 /
-// 414.7, 213e3 x 128 (6.8e6) 213 / 217.6, 2.56e6 x 32 (2e7) 741 / 768).
+// Below this many 16-byte chunks of output (32 MB) the gather alone is the faster one: it is over before its
+// writes get in the way of its reads.  A pass with / without the warm kernel, us, where other work between the
+// steps has pushed the rows out of the caches (one-hot: millions of chunks = those read = those written):
+// 1.28 260.6 / 259.2, 2.56 288.1 / 286.8 updated and 244.2 / 245.7 looked up only, 5.11 362.6 / 364.9, 6.82
+// 329.1 / 333.0; bags, millions read and written: 9.36, 1.70 295.5 / 290.9; 5.12, 1.70 292.0 / 288.5; 6.82, 3.41
+// 321.5 / 325.3; 13.6, 6.82 423.9 / 434.5; 34.1, 13.6 574.7 / 588.6.  So what is written decides, also for bags.
+// With rows that are still cached, which the host cannot know, the line would lie higher: 2.56 141 / 137,
+// 6.82 173.2 / 168.1, 10.2 320.6 / 329.1; bags 6.82, 3.41 172 / 171; 13.6, 6.82 272 / 282.
 constexpr int64_t kWarmMinChunks = (int64_t)1 << 21;
 constexpr int kWarmGrid = 2048;
 
