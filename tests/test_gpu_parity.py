@@ -637,6 +637,36 @@ def test_malformed_offsets_are_reported_no_later_than_the_counters(n, index_kind
     p.close()
 
 
+@pytest.mark.parametrize("index_kind", [HASHED, DENSE])
+@pytest.mark.parametrize("C", [0, 7000, 20_000])
+def test_degenerate_batches_in_the_general_passes(C, index_kind):
+    # the degenerate batches of the one-block prepare again at sizes that it does not take: one id many
+    # times, only ids outside the table, all distinct and more than the cache holds, n_ids == max_ids
+    V, D, m = 12_000, 4, 9000
+    p = Pair(V, D, C=C, max_ids=m, index_kind=index_kind)
+    g = lambda n, t: si.grads(n, D, 78, t).numpy()
+    p.step(np.zeros(0, np.int64), np.zeros((0, D), np.float32))
+    p.step(np.full(7000, 42), g(7000, 1))
+    p.step(np.resize([-5, V, 10 ** 12, -1], 6145), g(6145, 2))
+    p.step(np.where(np.arange(8000) % 3, np.arange(8000), -1), g(8000, 3))
+    p.step(np.arange(V)[::-1][:m].copy(), g(m, 4))
+    p.step(np.arange(m) % 100, g(m, 5))
+    p.finish(); p.close()
+
+
+def test_ties_in_stamp_break_by_slot_in_the_general_passes():
+    p = Pair(V=40_000, D=4, C=10_000, max_ids=10_000)
+    z = lambda n: np.ones((n, 4), np.float32)
+    p.step(np.arange(10_000), z(10_000))                        # all stamp 1
+    pr = p.step(np.concatenate([np.arange(3000, 10_000), np.arange(20_000, 20_300)]), z(7300))
+    assert pr.evict_slots.tolist() == list(range(300))
+    pr = p.step(np.concatenate([np.arange(4000, 10_000), np.arange(2999, 2499, -1), np.arange(30_000, 32_300)]), z(8800))
+    # slots 300 .. 2499 still carry stamp 1, the other hundred come from stamp 2, lowest slots first; the
+    # list is in slot order
+    assert pr.evict_slots.tolist() == list(range(100)) + list(range(300, 2500))
+    p.finish(); p.close()
+
+
 def test_status_block_needs_no_waiting():
     # counters and health of the latest planned step, read from pinned memory
     V, D, n = 5000, 8, 3000

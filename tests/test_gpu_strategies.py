@@ -13,14 +13,15 @@ STATE0 = {"adam": 0.0}
 
 
 @pytest.mark.parametrize("sync_every_call", [True, False])
-@pytest.mark.parametrize("optimizer", ["adagrad", "adam"])
-def test_prefetch_strategy_is_stale_by_one_step(optimizer, sync_every_call):
+@pytest.mark.parametrize("optimizer,n", [("adagrad", 1500), ("adam", 1500), ("adagrad", 9000), ("adam", 280_000)])
+def test_prefetch_strategy_is_stale_by_one_step(optimizer, n, sync_every_call):
     # the ablation's Prefetch strategy: no cache, the next batch's rows copied before the current
-    # update; Zipf batches share their hot rows, so every step trains stale rows
-    V, D = 3000, 16
-    p = Pair(V, D, C=0, max_ids=2048, lookahead=1, optimizer=optimizer, init_acc=STATE0.get(optimizer, 0.1),
+    # update; Zipf batches share their hot rows, so every step trains stale rows.  Batches prepared by one
+    # block, by the general passes, and of a size whose unique passes take a stream of their own otherwise
+    V, D = 2 * n, 16
+    p = Pair(V, D, C=0, max_ids=n + 548, lookahead=1, optimizer=optimizer, init_acc=STATE0.get(optimizer, 0.1),
              strategy="prefetch")
-    bs = [(si.zipf_ids(1500 + 11 * t, 1.1, V, 71, t).numpy(), si.grads(1500 + 11 * t, D, 71, t).numpy(), None)
+    bs = [(si.zipf_ids(n + 11 * t, 1.1, V, 71, t).numpy(), si.grads(n + 11 * t, D, 71, t).numpy(), None)
           for t in range(9)]
     p.run_pipelined(bs, sync_every_call)
     p.close()
