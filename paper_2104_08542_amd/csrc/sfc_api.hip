@@ -346,8 +346,10 @@ bool swap_on_main(sfc_cache* c) {
   if (c->side == c->st) return true;
   const volatile HostStatus* h = c->hstat;
   if (h->seq == 0 || (int64_t)h->M * (c->d4 + c->s4) * 16 > kSwapMainBytes) return false;
+  // (while the main stream is being captured the copies are recorded as a fork to the side stream: what that
+  // stream is doing now says nothing about the time of the graph's launch)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(c->side, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+  if (hipStreamIsCapturing(c->st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
   if (hipStreamQuery(c->side) == hipSuccess) return true;
   if (hipPeekAtLastError() == hipErrorNotReady) (void)hipGetLastError();
   return false;

@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import sfc_inputs as si
-from gpu_common import Pair
+from gpu_common import Pair, assert_close, same_stats
 
 pytestmark = pytest.mark.gpu
 
@@ -825,3 +825,38 @@ def test_main_stream_behind_the_lookup_tells_that_the_copies_are_done(n):
             assert not np.any(now == p.ow[(t - 1) * n:t * n])
         c.backward_update(torch.ones(n, D, device=p.dev))
     p.close()
+
+
+@pytest.mark.parametrize("n", [300, 7000])
+def test_the_calls_of_a_step_can_be_captured(n):
+    # lookahead 0: recorded into a graph (launched once: the step's number is part of it) the copies fork to
+    # the side stream and join again, for a batch prepared by one block and by the general passes
+    hip = ctypes.CDLL("libamdhip64.so")
+    vp = ctypes.c_void_p
+    V, D = 9000, 8
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        p = Pair(V, D, C=8000, max_ids=n)
+        for t in range(3):
+            p.step(si.zipf_ids(n, 1.05, V, 61, t).numpy(), si.grads(n, D, 61, t).numpy())
+        c, st = p.cache, vp(s.cuda_stream)
+        ids, grad = si.zipf_ids(n, 1.05, V, 61, 3).numpy(), si.grads(n, D, 61, 3).numpy()
+        d_ids, d_grad, out = torch.from_numpy(ids).to(p.dev), torch.from_numpy(grad).to(p.dev), torch.empty(n, D, device=p.dev)
+        torch.cuda.synchronize()
+        graph, run = vp(), vp()
+        assert hip.hipStreamBeginCapture(st, 2) == 0                   # relaxed
+        try:
+            c.prepare(d_ids); c.fetch_misses(); c.lookup(out); c.backward_update(d_grad)
+        finally:
+            rc = hip.hipStreamEndCapture(st, ctypes.byref(graph))
+        assert rc == 0
+        assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)) == 0
+        assert hip.hipGraphLaunch(run, st) == 0
+        torch.cuda.synchronize()
+        pr = p.orc.prepare(ids, None); p.orc.fetch_misses()
+        assert_close(out.cpu().numpy(), p.orc.lookup(), "lookup")
+        p.orc.backward_update(grad)
+        assert same_stats(c.stats(), pr.stats, p.table)
+        hip.hipGraphExecDestroy(run); hip.hipGraphDestroy(graph)
+        p.step(si.zipf_ids(n, 1.05, V, 61, 4).numpy(), si.grads(n, D, 61, 4).numpy())
+        p.finish(); p.close()
