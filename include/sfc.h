@@ -108,8 +108,9 @@ typedef struct {
                                  sfc_fetch_misses of step t+L may be called before
                                  sfc_backward_update of step t; they run on other streams while the
                                  main stream works on step t (the paper's pipeline of Data-Loader,
-                                 Host-Manager and GPU-Worker stages): the prepare on two streams
-                                 the library creates, the Host copies on side_stream.  Each
+                                 Host-Manager and GPU-Worker stages): the prepare on one or (from
+                                 2^18 to 2^20 ids) two streams the library creates, the Host
+                                 copies on side_stream.  Each
                                  further step of lookahead adds a step context, so that a prepare
                                  waits for an older update.  The caller rotates L + 1 sets of
                                  prepare buffers. */
@@ -298,12 +299,14 @@ int sfc_cache_state(sfc_cache* c, int64_t* h_slot_id, int32_t* h_stamp, float* h
 /*
  * Device timing.  level 1: the step calls.  sfc_prepare, sfc_fetch_misses and sfc_backward_update
  * (several kernels each) are bracketed by hipEvents on the stream they run on, so their times
- * include the launch latencies between the events (with lookahead >= 1 the prepare runs on two
- * library streams; its events sit on the one of the cache manager's kernels and include its wait
- * for the unique passes on the other).  sfc_lookup is two kernels (the batch's rows are read into
- * the memory-side cache, then gathered): the start and end of each are recorded by the dispatch
- * itself, i.e. the time is the sum of the two kernels' own durations as a profiler's kernel trace
- * shows them.  level 2: also, the same way, each of the kernels inside sfc_backward_update.
+ * include the launch latencies between the events (with lookahead >= 1 the prepare's events sit on
+ * the library's stream of the cache manager's kernels; where the unique passes take a second
+ * stream, the wait for them is included.  With lookahead 0 the prepare's last kernel, the grouping,
+ * is launched by sfc_fetch_misses; its time is added to the prepare's).  sfc_lookup is one kernel,
+ * or two from 32 MB of output on (the batch's rows are read into the memory-side cache, then
+ * gathered): the start and end of each are recorded by the dispatch itself, i.e. the time is the
+ * sum of the kernels' own durations as a profiler's kernel trace shows them.  level 2: also, the
+ * same way, each of the kernels inside sfc_backward_update.
  * level 0: off.  sfc_profile_read waits for the streams and returns, for which = 0..6 (prepare,
  * fetch_misses, lookup, backward_update, segment-sum stream kernel, segment-sum finish kernel,
  * optimizer kernel), the summed milliseconds and the number of launches since the last read of

@@ -5,9 +5,10 @@
 //
 // A step in flight is a StepCtx: the caller's buffers, the step's device counters, its grouping
 // of positions, its victim list and its bypass region.  lookahead = L has L + 1 contexts.
-// L = 0 runs the prepare on the main stream.  L >= 1 gives the prepare two streams of its own (one
-// for the unique passes, one for the cache manager's kernels) and the Host copies run on the side
-// stream, so that the prepare of step t+L, the copies of the step before it and lookup / update of
+// L = 0 runs the prepare on the main stream and the Host copies on the side stream (few of them on the
+// main stream, see swap_on_main).  L >= 1 gives the prepare a stream of its own, batches of
+// kTwoStreamMin to kTwoStreamMax ids a second one for their unique passes, and the Host copies run on
+// the side stream, so that the prepare of step t+L, the copies of the step before it and lookup / update of
 // step t overlap (the paper's pipeline of Data-Loader, Host-Manager and GPU-Worker stages); a
 // larger L means more contexts, i.e. a prepare need not wait for the most recent update.  The
 // Prefetch comparison strategy keeps its prepare on the side stream, ahead of its copies.
@@ -130,9 +131,9 @@ struct sfc_cache {
   hipStream_t st = nullptr, side = nullptr;     // main stream; stream of the Host copies
   hipStream_t prep = nullptr;                   // stream of the prepare kernels
   bool own_prep = false;                        // prep was created here (lookahead >= 1)
-  // lookahead >= 1: the unique passes of a step (insert, count, scan, assign, inverse) run on a
-  // stream of their own as soon as the previous step's resolve has emptied the batch table,
-  // beside the rest of that step's prepare
+  // lookahead >= 1, batches of kTwoStreamMin to kTwoStreamMax ids: the unique passes of a step (insert,
+  // count, assign, inverse) run on a stream of their own as soon as the previous step's resolve has
+  // emptied the batch table, beside the rest of that step's prepare
   hipStream_t ins = nullptr;
   hipEvent_t ev_resolved = nullptr, ev_inserted = nullptr;
   bool resolved_once = false;                   // ev_resolved has been recorded
@@ -628,7 +629,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
   c->host.a = (float4*)dp;
   c->host.hs4 = (cfg->host_row_stride ? cfg->host_row_stride : cfg->dim) / 4;
   c->host.has4 = (cfg->host_state_stride ? cfg->host_state_stride : S) / 4;
-  // lookahead 0: prepare on the main stream; otherwise on two streams of its own, beside the Host
+  // lookahead 0: prepare on the main stream; otherwise on one or two streams of its own, beside the Host
   // copies of the step before (the Prefetch strategy: on the side stream, ahead of its copies)
   c->prep = cfg->lookahead == 0 ? c->st : c->side;
   if (cfg->lookahead >= 1 && cfg->policy != SFC_POLICY_PREFETCH) {

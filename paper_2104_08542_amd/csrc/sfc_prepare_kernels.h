@@ -1032,7 +1032,7 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   const int U = ctr->U, K = ctr->K, f = ctr->f_old;
   const int free_slots = C - f;
   // Here, in one thread of a wide kernel, the publishing costs nothing that anyone waits for; in the
-  // single-block plan kernel its two fences lengthened the prepare by 6 us.
+  // single-block plan kernel its stores over the link, each waited for, would lengthen the prepare.
   if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
     publish(ctr->hstat, t, U, ctr->n_hit, ctr->M, K, ctr->n_bypass, ctr->n_invalid, ctr->bad_offsets);
   for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
@@ -1084,7 +1084,7 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
 
 // ---------------------------------------------------------------------------------------------
 // The prepare of a small batch, by ONE block: up to kSmallIds positions fit the LDS of a compute unit
-// (their table of distinct ids, counts and slots), and for so few the eleven launches of the passes
+// (their table of distinct ids, counts and slots), and for so few the ten launches of the passes
 // above were all start-up, drain and dependent round trips: what bounds this kernel is the chain ids ->
 // table -> rank -> index -> stamp -> lists, walked once with barriers in between instead of kernel
 // boundaries.  Same outputs, same
