@@ -468,8 +468,9 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
   int rc;
   if (extra && (rc = prof_begin(c, P_PREPARE, s, &ep))) return rc;
   ep.extra = true;
-  auto scat = sg.threads == 256 ? k_scatter<4, 256> : sg.threads == 512 ? k_scatter<8, 512> : k_scatter<8, 1024>;
-  hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.threads), 0, s, x->d_inverse,
+  auto scat = sg.shift == 10 ? k_scatter<4, 256> : sg.shift == 12 ? k_scatter<8, 512> : k_scatter<8, 1024>;
+  const int threads = sg.shift == 10 ? 256 : sg.shift == 12 ? 512 : 1024;
+  hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(threads), 0, s, x->d_inverse,
                      x->d_offsets ? c->pos2bag : (const int*)nullptr, n, c->grp, (int*)x->cold_pay,
                      (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
                      (const int*)x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags);
@@ -839,9 +840,8 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                          nchunk, c->blk_cnt);
     hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk), dim3(256), 0, su, d_ids, c->V, c->hslot,
                        (const unsigned*)c->first, n, counts, d_unique_ids, c->uvid, c->vid_hslot, cnt, c->n_unique);
-    auto inv = sg.threads == 256 ? k_uniq_inverse<kFewBins, 4, 256>
-             : sg.threads == 512 ? k_uniq_inverse<kHotBins, 8, 512> : k_uniq_inverse<kHotBins, 8, 1024>;
-    hipLaunchKernelGGL(inv, dim3(sg.blocks), dim3(sg.threads), 0, su, c->hslot, c->uvid, n, d_inverse, cnt,
+    auto inv = sg.shift == 10 ? k_uniq_inverse<1, 1024> : sg.shift == 12 ? k_uniq_inverse<8, 512> : k_uniq_inverse<8, 1024>;
+    hipLaunchKernelGGL(inv, dim3(sg.blocks), dim3(sg.shift == 12 ? 512 : 1024), 0, su, c->hslot, c->uvid, n, d_inverse, cnt,
                        cnt_rep, sg.nrep, x->pos_slot, c->first);
   } else {
     fill<int>(su, c->n_unique, 1, 0);

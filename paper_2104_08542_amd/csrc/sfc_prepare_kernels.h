@@ -380,24 +380,25 @@ __global__ __launch_bounds__(256) void k_uniq_assign(const int64_t* __restrict__
 // copies, block b using copy b mod nrep (SortGeom); resolve folds the copies into cnt, the miss
 // assignment turns them into one group start per copy.
 constexpr int kHotRep = 32;
-constexpr int kFewBins = 2048;
 
 // The shape of the counting and grouping passes by batch size (nothing else of a batch is known to
 // the host).  A block's histogram costs its clear and its flush whatever the block counts, and the
 // places of a block's positions in a hot group lie side by side, so big batches take many positions
-// per block (fewer flushes, fewer 128-byte lines that two XCDs write) and all bins; small ones are
-// short of blocks instead, and a few bins hold all that is frequent enough to serialise an atomic.
-// Counting + grouping us, threads x positions per thread: 195e3 positions (2048 bins) 256x4 15.6,
-// 256x16 33; 639e3 256x8 28.6, 512x8 29.0, 256x16 38.7; 2.56e6 512x8 57.0, 256x16 63.3, 1024x8 61.7;
-// 8.9e6 in bags 1024x8 268, 256x16 310, 512x8 302.  Fewer bins than 8192 are slower from 639e3
-// positions on: the counters of the ids just beyond the bins share cache lines (2.56e6, 4096 / 2048 /
-// 1024 bins: 68 / 76 / 105 us).
-struct SortGeom { int bins, threads, per, shift, nrep, blocks; };   // positions per block = threads * per = 1 << shift
+// per block (fewer flushes, fewer 128-byte lines that two XCDs write); small ones are short of blocks
+// instead: there a block counts 1024 positions with 1024 threads, which clear and flush eight bins each.
+// Counting + grouping us: 195e3 positions 1024x1 and 256x4 (threads x positions per thread) 13.4, 256x16 both
+// 33; the same shape for both: 639e3 256x8 28.6, 512x8 29.0, 256x16
+// 38.7; 2.56e6 512x8 57.0, 256x16 63.3, 1024x8 61.7; 8.9e6 in bags 1024x8 268, 256x16 310, 512x8 302.
+// All bins at every size: with the 2048 lowest only, small batches were no faster (195e3: 256x4 15.2), and ids beyond the bins that are frequent all the same, in
+// batches that open with thousands of distinct ids, count through one address: 200e3 ids of which 196e3
+// are 3 ids behind 4000 others 1252 us, 70 with 8192 bins; and from 639e3 positions on the counters
+// of the ids just beyond the bins share cache lines (2.56e6, 8192 / 4096 / 2048 bins: 57 / 68 / 76 us).
+// shift: positions per block = 1 << shift, in both passes.
+struct SortGeom { int bins, shift, nrep, blocks; };
 inline SortGeom sort_geom(int64_t n) {
   SortGeom g;
-  if (n < ((int64_t)1 << 18)) { g.bins = kFewBins; g.threads = 256; g.per = 4; g.shift = 10; }
-  else if (n < ((int64_t)1 << 22)) { g.bins = kHotBins; g.threads = 512; g.per = 8; g.shift = 12; }
-  else { g.bins = kHotBins; g.threads = 1024; g.per = 8; g.shift = 13; }
+  g.bins = kHotBins;
+  g.shift = n < ((int64_t)1 << 18) ? 10 : n < ((int64_t)1 << 22) ? 12 : 13;
   g.blocks = (int)((n + (1 << g.shift) - 1) >> g.shift);
   g.nrep = 1;
   while (g.nrep < kHotRep && g.nrep * 16 < g.blocks) g.nrep *= 2;
@@ -407,23 +408,23 @@ inline SortGeom sort_geom(int64_t n) {
 // A small batch (k_small_prepare): counted and ranked already, no hot bins.
 inline SortGeom small_geom(int64_t n) {
   SortGeom g;
-  g.bins = 0; g.threads = 256; g.per = 4; g.shift = 10; g.nrep = 1;
+  g.bins = 0; g.shift = 10; g.nrep = 1;
   g.blocks = (int)((n + 1023) >> 10);
   return g;
 }
 
-template <int kBins, int kPer, int kT>
+template <int kPer, int kT>
 __global__ __launch_bounds__(kT) void k_uniq_inverse(const int* __restrict__ hslot,
                                                        const int* __restrict__ uvid, int n,
                                                        int* __restrict__ inverse, int* cnt,
                                                        int* cnt_rep, int nrep, int* __restrict__ rank,
                                                        unsigned* __restrict__ first) {
-  __shared__ int lh[kBins];
+  __shared__ int lh[kHotBins];
   // the marks of first appearances have been read: all zero again for the next batch
   static_assert(kPer <= 32 && kT * kPer % 32 == 0, "whole words of marks per block");
   if ((int)threadIdx.x < kT * kPer / 32 && (int)(blockIdx.x * kT * kPer + threadIdx.x * 32) < n)
     first[blockIdx.x * (kT * kPer / 32) + threadIdx.x] = 0;
-  for (int i = threadIdx.x; i < kBins; i += kT) lh[i] = 0;
+  for (int i = threadIdx.x; i < kHotBins; i += kT) lh[i] = 0;
   const int base = blockIdx.x * kT * kPer;
   int hv[kPer], vv[kPer], rr[kPer];
 #pragma unroll
@@ -440,16 +441,16 @@ __global__ __launch_bounds__(kT) void k_uniq_inverse(const int* __restrict__ hsl
     const int v = vv[j];
     if (v >= 0) {
       inverse[p] = v;
-      rr[j] = v < kBins ? atomicAdd(&lh[v], 1) : atomicAdd(&cnt[v], 1);
+      rr[j] = v < kHotBins ? atomicAdd(&lh[v], 1) : atomicAdd(&cnt[v], 1);
     }
   }
   __syncthreads();
   int* mine = cnt_rep + (blockIdx.x & (nrep - 1)) * kHotBins;
   // the block's share of each non-empty bin: returning atomics, several in flight per thread (each
   // round of them is a round trip to the memory side)
-  constexpr int kFlush = kBins / kT < 16 ? kBins / kT : 16;
-  static_assert(kBins % (kT * kFlush) == 0, "flush rounds cover the bins exactly");
-  for (int b0 = threadIdx.x; b0 < kBins; b0 += kT * kFlush) {
+  constexpr int kFlush = kHotBins / kT < 16 ? kHotBins / kT : 16;
+  static_assert(kHotBins % (kT * kFlush) == 0, "flush rounds cover the bins exactly");
+  for (int b0 = threadIdx.x; b0 < kHotBins; b0 += kT * kFlush) {
     int c[kFlush], r[kFlush];
 #pragma unroll
     for (int u = 0; u < kFlush; ++u) c[u] = lh[b0 + u * kT];
@@ -462,7 +463,7 @@ __global__ __launch_bounds__(kT) void k_uniq_inverse(const int* __restrict__ hsl
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const int p = base + j * kT + (int)threadIdx.x;
-    if (vv[j] >= 0) rank[p] = vv[j] < kBins ? lh[vv[j]] + rr[j] : rr[j];
+    if (vv[j] >= 0) rank[p] = vv[j] < kHotBins ? lh[vv[j]] + rr[j] : rr[j];
   }
 }
 

@@ -190,6 +190,21 @@ def test_frequent_ids_that_first_appear_late():
     p.finish(); p.close()
 
 
+@pytest.mark.parametrize("n,head", [(6200, 2100), (40_000, 3000), (200_000, 8191), (200_000, 8200)])
+def test_frequent_ids_behind_a_head_of_distinct_ones(n, head):
+    # batches of every shape of the counting pass below 2^18 that open with distinct ids: the frequent ids
+    # get virtual ids in the middle, at the end and just outside the range that is counted in LDS
+    V, D = 30_000, 4
+    rng = np.random.default_rng(n + head)
+    p = Pair(V, D, C=20_000, max_ids=n)
+    for t in range(2):
+        first = rng.permutation(V - 10)[:head]
+        ids = np.concatenate([first, np.where(rng.random(n - head) < 0.9, V - 1 - rng.integers(0, 3, n - head),
+                                              rng.integers(0, V, n - head))])
+        p.step(ids, si.grads(n, D, 24, t).numpy())
+    p.finish(); p.close()
+
+
 @pytest.mark.parametrize("n", [1, 255, 257, 1023, 1025, 5121, (1 << 18) - 1, 1 << 18, (1 << 18) + 1,
                                (1 << 22) - 1, (1 << 22) + 1])
 def test_batch_sizes_where_the_counting_passes_change_shape(n):
