@@ -762,29 +762,35 @@ __device__ __forceinline__ bool edge_run_sum(const double* __restrict__ bp,
 // Every run, by edge_blocks() blocks: a lane group per slot.  Nearly all runs are two slots long (the tail
 // of one stream block and the head of the next): a group that finds the first slot of a run of at most
 // kEdgeShort slots adds them up itself, in slot order.  The few long runs (an id with thousands of
-// positions spans many stream blocks) are listed in LDS and summed by the whole block, one after the
-// other; their first slots lie more than kEdgeShort slots apart, so a block meets only a few.
+// positions spans many stream blocks) are summed by the whole block.  Their first slots lie more than
+// kEdgeShort slots apart, and a block takes no more slots than that, so it meets at most one of them.
 // emit(v, c4, sum): chunk c4 of the summed row of virtual id v, rounded to fp32.
 // What bounds it is dependent loads and barriers, so the slots around one are loaded together and a long
-// run ends in a tree.  As a kernel of its own 7.4 -> 3.3 us at 213e3 positions of dim 128; 9.5 us as before at
-// 2.56e6 of dim 32, where the hottest id spans a thousand slots and six round trips in a row are what is left.
+// run ends in a tree.  As a kernel of its own, us, one block per slot / 4 * (64 / d4) slots per block, their
+// long runs one after the other / this way: 2.56e6 positions of dim 32 9.6 / 9.1 / 7.3, 2e6 of dim 4 9.9 / 27.8 /
+// 5.5, 200e3 of dim 16 4.6 / 11.2 / 5.5, 40e3 of dim 64 4.6 / 6.7 / 5.9, 213e3 of dim 128 18.3 / 6.2 / 6.1.  In front
+// of the optimizer kernel's rows (whole kernel): 19.0 -> 16.8, 33.2 -> 7.3 and 14.1 -> 7.0 for the first three.
 constexpr int kEdgeShort = 8;
+inline __host__ __device__ int edge_slots(int d4) {
+  const int groups = 4 * (64 / d4 > 0 ? 64 / d4 : 1);
+  return groups < kEdgeShort ? groups : kEdgeShort;
+}
 inline int edge_blocks(int nslots, int d4) {
-  const int per_block = 4 * (64 / d4 > 0 ? 64 / d4 : 1);
+  const int per_block = edge_slots(d4);
   return (nslots + per_block - 1) / per_block;
 }
 
 template <class Emit>
 __device__ __forceinline__ void edge_block(const double* __restrict__ bp, const int* __restrict__ bp_vid,
                                            int nslots, int d4, int blk, Emit emit) {
-  __shared__ int n_long;
-  __shared__ int long_at[256];
-  if (threadIdx.x == 0) n_long = 0;
+  __shared__ int long_at;                                  // first slot of the block's long run
+  if (threadIdx.x == 0) long_at = -1;
   __syncthreads();
   const int lane = lane_id(), G = 64 / d4 > 0 ? 64 / d4 : 1;
   const int g = lane / d4, c4 = lane - g * d4;
-  const int j = (blk * 4 + (int)(threadIdx.x >> 6)) * G + g;
-  if (g < G && j < nslots) {
+  const int i = (int)(threadIdx.x >> 6) * G + g, per_block = edge_slots(d4);
+  const int j = blk * per_block + i;
+  if (g < G && i < per_block && j < nslots) {
     // the slots around, all in flight: a run of two is found in one round trip, not slot by slot
     int vs[kEdgeShort + 1];
     const int before = j > 0 ? bp_vid[j - 1] : -1;
@@ -796,7 +802,7 @@ __device__ __forceinline__ void edge_block(const double* __restrict__ bp, const 
 #pragma unroll
       for (int u = 1; u <= kEdgeShort; ++u) len += len == u && vs[u] == v;
       if (len > kEdgeShort) {
-        if (c4 == 0) long_at[atomicAdd(&n_long, 1)] = j;
+        if (c4 == 0) long_at = j;
       } else {
         const int D = d4 * 4;
         double s0 = 0., s1 = 0., s2 = 0., s3 = 0.;
@@ -809,14 +815,11 @@ __device__ __forceinline__ void edge_block(const double* __restrict__ bp, const 
     }
   }
   __syncthreads();
-  const int nl = n_long;
-  for (int i = 0; i < nl; ++i) {
-    int v;
-    D4 s;
-    const bool first = edge_run_sum(bp, bp_vid, nslots, d4, long_at[i], v, s);
-    if (first && (int)threadIdx.x < d4) emit(v, (int)threadIdx.x, d4_round(s));
-    __syncthreads();
-  }
+  if (long_at < 0) return;
+  int v;
+  D4 s;
+  const bool first = edge_run_sum(bp, bp_vid, nslots, d4, long_at, v, s);
+  if (first && (int)threadIdx.x < d4) emit(v, (int)threadIdx.x, d4_round(s));
 }
 
 __global__ __launch_bounds__(256) void k_seg_finish(const double* __restrict__ bp,

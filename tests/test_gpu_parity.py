@@ -164,6 +164,18 @@ def test_groups_cut_by_block_edges_are_updated_once(D, C, optimizer):
     p.finish(); p.close()
 
 
+@pytest.mark.parametrize("D,n,optimizer", [(4, 200_000, "adagrad"), (4, 9000, "rowwise_adagrad"), (16, 40_000, "adam"),
+                                           (32, 7000, "adagrad"), (128, 9000, "rowwise_adagrad"), (252, 12_000, "adagrad")])
+def test_several_long_runs_of_partial_sums_side_by_side(D, n, optimizer):
+    # ten, then forty ids own the batch: each leaves a run of a few to some dozens of block-edge partials,
+    # around the length from which a whole block sums them, and the runs begin close together
+    p = Pair(V=100, D=D, C=100, max_ids=n, optimizer=optimizer)
+    for t, k in enumerate((10, 40, 11)):
+        ids = np.random.default_rng(t).integers(0, k, n - 13 * t)
+        p.step(ids, si.grads(n - 13 * t, D, 25, t).numpy())
+    p.finish(); p.close()
+
+
 def test_frequent_ids_that_first_appear_late():
     # the grouping passes treat the lowest virtual ids (the early, usually frequent ones) in LDS and
     # rank the others with atomics: here the batch opens with 9000 distinct ids, so the frequent ids
