@@ -67,17 +67,18 @@ constexpr int kSplitMin = 1 << 14;
 constexpr int kSplitMax = 1 << 18;
 constexpr unsigned kSplitMaxBytes = 64u << 20;
 constexpr int kSplitWriters = 32, kSplitReaders = 128;
-// w2: 16-byte chunks of a row and its state (at most 192, so the product stays below 2^30)
-__device__ __forceinline__ bool split_swap(const Ctr* ctr, int w2) {
-  return ctr->M >= kSplitMin && ctr->M <= kSplitMax && (unsigned)ctr->M * (unsigned)w2 * 16u <= kSplitMaxBytes &&
-         ctr->K > 0;
+// M misses, K victims, both loaded together (one after the other they cost the copies 2 us); w2: 16-byte chunks
+// of a row and its state
+__device__ __forceinline__ bool split_swap(int M, int K, int w2) {
+  return (M >= kSplitMin) & (M <= kSplitMax) & ((uint64_t)M * (unsigned)w2 <= kSplitMaxBytes / 16) & (K > 0);
 }
 
 __global__ __launch_bounds__(256) void k_stage_victims(const int* __restrict__ victim_slot,
                                                         float4* __restrict__ cw, float4* __restrict__ ca,
                                                         int C, int boff, int d4, int s4, const Ctr* ctr) {
-  if (!split_swap(ctr, d4 + s4)) return;
-  const unsigned w2 = (unsigned)(d4 + s4), total = (unsigned)ctr->K * w2;    // at most kSplitMaxBytes / 16
+  const int M = ctr->M, K = ctr->K;
+  if (!split_swap(M, K, d4 + s4)) return;
+  const unsigned w2 = (unsigned)(d4 + s4), total = (unsigned)K * w2;    // at most kSplitMaxBytes / 16
   const int64_t row0 = (int64_t)C + boff + ctr->n_bypass;
   for (unsigned i = blockIdx.x * 256 + threadIdx.x; i < total; i += gridDim.x * 256) {
     const unsigned k = i / w2;
@@ -138,20 +139,20 @@ __global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_
   if (blockIdx.x == 0 && threadIdx.x == 0) ctr->fetch_on_main = on_main;   // same value from both launches
   if (on_main != (main_variant != 0)) return;
   __builtin_amdgcn_s_setprio(3);            // few waves, long round trips: issue ahead of the kernels beside them
-  const int K = ctr->K;
+  const int M = ctr->M, K = ctr->K;
   // staged_at >= 0: k_stage_victims has run, the victims' rows are at staged_at + the bypass rows
-  if (staged_at >= 0 && split_swap(ctr, d4 + s4)) {
+  if ((staged_at >= 0) & split_swap(M, K, d4 + s4)) {
     const int64_t row0 = (int64_t)staged_at + ctr->n_bypass;
     if (blockIdx.x < kSplitWriters)
       link_rows<true>(victim_id, [&](unsigned k) { return row0 + k; }, K, cw, ca, h, d4, s4, (int)blockIdx.x,
                       kSplitWriters);
     else
-      link_rows<false>(miss_id, [&](unsigned k) { return (int64_t)miss_row[k]; }, ctr->M, cw, ca, h, d4, s4,
+      link_rows<false>(miss_id, [&](unsigned k) { return (int64_t)miss_row[k]; }, M, cw, ca, h, d4, s4,
                        (int)blockIdx.x - kSplitWriters, (int)gridDim.x - kSplitWriters);
     return;
   }
   const int w2 = d4 + s4;                   // chunks of a row and of its optimizer state
-  const int64_t total = (int64_t)ctr->M * w2;
+  const int64_t total = (int64_t)M * w2;
   const int64_t stride = (int64_t)gridDim.x * 256;
   // A thread's chunks are a serial chain, and with few blocks (see the launch) the chain is long:
   // the list entries of the next chunk are fetched while this chunk's Host read is in flight, so
