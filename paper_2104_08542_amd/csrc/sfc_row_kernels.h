@@ -339,7 +339,7 @@ __global__ __launch_bounds__(256) void k_lookup_onehot(const int* __restrict__ p
 // enough to stay in an XCD's L2 are not fetched again).
 // Malformed offsets are reported by the prepare step; here they only must not lead outside
 // pos_slot, hence the clamp of both ends to [0, n_ids] (a start near 2^63 as it is would wrap round when
-// the unrolled loop adds to it).
+// the unrolled loop adds to it).  Positions are 32 bits from there on: with 64 the clamp cost 1 %.
 #ifndef SFC_BAG_UNROLL
 #define SFC_BAG_UNROLL 8
 #endif
@@ -355,8 +355,8 @@ __global__ __launch_bounds__(256) void k_lookup_bags(const int64_t* __restrict__
   const int64_t b = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * G + g;
   if (g >= G || b >= n_bags) return;
   const BagRange r = bag_range(offsets[b], offsets[b + 1], (int)n_ids);
-  int64_t q = r.lo;
-  const int64_t e = r.hi;
+  int q = r.lo;
+  const int e = r.hi;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
   int sl[kBagUnroll], sn[kBagUnroll];
 #pragma unroll
@@ -370,7 +370,7 @@ __global__ __launch_bounds__(256) void k_lookup_bags(const int64_t* __restrict__
     }
 #pragma unroll
     for (int k = 0; k < kBagUnroll; ++k) {
-      const int64_t qn = q + kBagUnroll + k;
+      const int qn = q + kBagUnroll + k;
       sn[k] = qn < e ? pos_slot[qn] : -1;
     }
 #pragma unroll
