@@ -421,7 +421,7 @@ constexpr int kSegChunk = SFC_SEG_CHUNK;        // entries per group per loop it
 #endif
 constexpr int kSegTargetWaves = 256 * SFC_SEG_WAVES;
 
-constexpr int kSegMinWaves = 1024;
+constexpr int kSegMinWaves = 2048;
 
 struct SegGeom { int G, L, waves; };
 // L is chosen so that the stream has about kSegTargetWaves wavefronts.
@@ -433,8 +433,11 @@ inline SegGeom seg_geom(int D, int64_t n) {
   int64_t L = (n + g.G * target_waves - 1) / (g.G * target_waves);
   // never below 32 entries per span (fewer partial sums, fewer block edges for the kernel behind to
   // chain), except where that leaves the chip with fewer than kSegMinWaves wavefronts: then 16 or 8.
-  // Stream + optimizer us with spans of 8 / 16 / 32: 40e3 positions of dim 16 21.1 / 21.8 / 22.7, 195e3 of
-  // dim 80 44.3 / 39.5 / 39.0, 213e3 of dim 128 36.0 / 33.7 / 32.4, 639e3 of dim 16 46.6 / 44.9 / 44.4.
+  // sfc_backward_update us with spans of 8 / 16 / 32, power-law ids: 40e3 positions of dim 16 29.7 / 30.3 / 31.9,
+  // 200e3 of dim 16 34.6 / 34.4 / 38.6, 639e3 of dim 16 (32: 1248 wavefronts) 44.4 / 44.7 / 46.9, 200e3 of dim 64
+  // (1562) 42.3 / 39.1 / 40.4, 195e3 of dim 80 (2031) 47.7 / 43.5 / 43.6, 639e3 of dim 32 (2496) 49.9 / 45.5 /
+  // 46.0, 213e3 of dim 128 (3328) 57.0 / 55.5 / 50.2, 40e3 of dim 256 (1250) 45.3 / 40.5 / 40.6; all ids distinct:
+  // 40e3 of dim 256 56.5 / 57.2 / 61.2, 639e3 of dim 16 45.5 / 47.5 / 51.7, 213e3 of dim 128 115.3 / 112.0 / 112.2.
   int64_t lmin = 32;
   while (lmin > 8 && n < g.G * lmin * kSegMinWaves) lmin /= 2;
   if (L < lmin) L = lmin;
@@ -446,7 +449,7 @@ inline SegGeom seg_geom(int D, int64_t n) {
 
 // Bytes of scratch by which sfc_segment_sum_static accepts or refuses a batch: that of spans of 8 entries
 // below 2^18 positions and 32 above.  The stream above mostly takes less; where it takes more (short rows,
-// at most 233 472 bytes then) both are far from the limit.
+// at most 794 624 bytes then) both are far from the limit.
 inline int64_t seg_scratch_count(int D, int64_t n) {
   const int64_t G = 64 / (D / 4) < 1 ? 1 : 64 / (D / 4);
   int64_t L = (n + G * kSegTargetWaves - 1) / (G * kSegTargetWaves);
