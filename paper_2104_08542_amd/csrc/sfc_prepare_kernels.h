@@ -387,12 +387,13 @@ constexpr int kHotRep = 32;
 // per block (fewer flushes, fewer 128-byte lines that two XCDs write); small ones are short of blocks
 // instead: there a block counts 1024 positions with 1024 threads, which clear and flush eight bins each.
 // Counting + grouping us: 195e3 positions 1024x1 and 256x4 (threads x positions per thread) 13.4, 256x16 both
-// 33; the same shape for both: 639e3 256x8 28.6, 512x8 29.0, 256x16
-// 38.7; 2.56e6 512x8 57.0, 256x16 63.3, 1024x8 61.7; 8.9e6 in bags 1024x8 268, 256x16 310, 512x8 302.
-// All bins at every size: with the 2048 lowest only, small batches were no faster (195e3: 256x4 15.2), and ids beyond the bins that are frequent all the same, in
-// batches that open with thousands of distinct ids, count through one address: 200e3 ids of which 196e3
-// are 3 ids behind 4000 others 1252 us, 70 with 8192 bins; and from 639e3 positions on the counters
-// of the ids just beyond the bins share cache lines (2.56e6, 8192 / 4096 / 2048 bins: 57 / 68 / 76 us).
+// 33; the same shape for both: 639e3 256x8 28.6, 512x8 29.0, 256x16 38.7; 2.56e6 512x8 57.0, 256x16 63.3, 1024x8
+// 61.7; 8.9e6 in bags 1024x8 268, 256x16 310, 512x8 302.
+// All bins at every size: with the 2048 lowest only, small batches were no faster (195e3: 256x4 15.2), and
+// ids beyond the bins that are frequent all the same, in batches that open with thousands of distinct
+// ids, count through one address: 200e3 ids of which 196e3 are 3 ids behind 4000 others 1252 us, 70 with
+// 8192 bins; and from 639e3 positions on the counters of the ids just beyond the bins share cache lines
+// (2.56e6, 8192 / 4096 / 2048 bins: 57 / 68 / 76 us).
 // shift: positions per block = 1 << shift, in both passes.
 struct SortGeom { int bins, shift, nrep, blocks; };
 inline SortGeom sort_geom(int64_t n) {
