@@ -18,7 +18,6 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
-#include <atomic>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -337,6 +336,12 @@ constexpr int64_t kSwapWideBytes = (int64_t)256 << 20;
 // of misses: 193 -> 147 us).
 constexpr int64_t kSwapMainBytes = (int64_t)1 << 20;
 
+// Misses of the latest step whose counters the device has published; -1: none yet.
+int64_t recent_misses(const sfc_cache* c) {
+  const uint64_t w = ((const volatile HostStatus*)c->hstat)->word[kStatMiss];
+  return w ? (int64_t)(uint32_t)w : -1;
+}
+
 // Do this step's copies run on the main stream?  With lookahead 0 they stand between the prepare and the
 // lookup of that stream, so a step that moves little stays there (kSwapMainBytes), but only while the side
 // stream has nothing to do: what the caller has given that stream before sfc_fetch_misses comes before the
@@ -345,8 +350,8 @@ constexpr int64_t kSwapMainBytes = (int64_t)1 << 20;
 bool swap_on_main(sfc_cache* c) {
   if (c->nctx > 1) return false;
   if (c->side == c->st) return true;
-  const volatile HostStatus* h = c->hstat;
-  if (h->seq == 0 || (int64_t)h->M * (c->d4 + c->s4) * 16 > kSwapMainBytes) return false;
+  const int64_t recent = recent_misses(c);
+  if (recent < 0 || recent * (c->d4 + c->s4) * 16 > kSwapMainBytes) return false;
   // (while the main stream is being captured the copies are recorded as a fork to the side stream: what that
   // stream is doing now says nothing about the time of the graph's launch)
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
@@ -365,7 +370,7 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   if (s != c->prep) HIPCHK(hipStreamWaitEvent(s, x->ev_prepared, 0));
   if ((rc = prof_begin(c, P_FETCH, s, &ep))) return rc;
   ep.extra = main_variant != 0;          // the second launch of a step: same call
-  const int64_t recent_bytes = (int64_t)((const volatile HostStatus*)c->hstat)->M * (c->d4 + c->s4) * 16;
+  const int64_t recent_bytes = recent_misses(c) * (c->d4 + c->s4) * 16;
   const int swap_blocks = c->nctx == 1 || recent_bytes > kSwapWideBytes ? kSwapBlocksWide : kSwapBlocks;
   int blocks = grid_for(x->n_ids * (c->d4 + c->s4), 256, swap_blocks), staged_at = -1;
   // where victims are possible, and the copies have the side stream to themselves (see k_stage_victims)
@@ -869,7 +874,10 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     a.grp = c->grp; a.cold_pay = x->cold_pay; a.perm64 = x->perm64; a.pos_slot = x->pos_slot;
     a.victim_slot = x->victim_slot; a.victim_id = x->victim_id; a.miss_row = x->miss_row; a.miss_id = x->miss_id;
     a.ctr = x->ctr; a.prev = c->dmap ? prev->ctr : nullptr;
-    hipLaunchKernelGGL(whole ? k_small_prepare<true> : k_small_prepare<false>, dim3(1), dim3(1024), 0, s, a);
+    auto kern = n <= 2048 ? (whole ? k_small_prepare<true, 2> : k_small_prepare<false, 2>)
+              : n <= 4096 ? (whole ? k_small_prepare<true, 4> : k_small_prepare<false, 4>)
+                          : (whole ? k_small_prepare<true, kSmallPer> : k_small_prepare<false, kSmallPer>);
+    hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, a);
   } else {
     const int gr = grid_for(n, kVidTile, kResolveGrid);
     hipLaunchKernelGGL(k_resolve, dim3(gr), dim3(256), 0, s, d_unique_ids, c->vid_hslot, c->utab,
@@ -1144,9 +1152,8 @@ int sfc_peek_stats(sfc_cache* c, sfc_stats* h_out, int64_t* h_step) {
   const volatile HostStatus* h = c->hstat;
   memset(h_out, 0, sizeof *h_out);
   *h_step = 0;
-  // the kernel that publishes makes the sequence word odd, writes, makes it even: take a copy
-  // that has the same even sequence word before and after.  Its writes take microseconds on the link,
-  // thousands of reads here, so the limit is a time far beyond that.
+  // all words of one step; the kernel that publishes stores them together, microseconds apart at most on the
+  // link, thousands of reads here, so the limit is a time far beyond that
   std::chrono::steady_clock::time_point end{};
   for (int tries = 1;; ++tries) {
     if (tries % 1024 == 0) {
@@ -1154,19 +1161,19 @@ int sfc_peek_stats(sfc_cache* c, sfc_stats* h_out, int64_t* h_step) {
       if (tries == 1024) end = now + std::chrono::milliseconds(100);
       else if (now > end) break;
     }
-    const int s1 = h->seq;
-    if (s1 & 1) continue;
-    std::atomic_thread_fence(std::memory_order_acquire);
-    const int U = h->U, nh = h->n_hit, M = h->M, K = h->K, nb = h->n_bypass, ni = h->n_invalid,
-              bo = h->n_bad_offsets;
-    std::atomic_thread_fence(std::memory_order_acquire);
-    if (h->seq != s1) continue;
+    uint64_t w[kStatWords];
+    for (int i = 0; i < kStatWords; ++i) w[i] = h->word[i];
+    bool whole = true;
+    for (int i = 1; i < kStatWords; ++i) whole = whole && w[i] >> 32 == w[0] >> 32;
+    if (!whole) continue;
+    const auto count = [&](int i) { return (int64_t)(uint32_t)w[i]; };
     const int64_t rowbytes = (int64_t)sizeof(float) * (c->D + c->S);
-    h_out->n_unique = U; h_out->n_hit = nh; h_out->n_miss = M; h_out->n_evict = K;
-    h_out->n_bypass = nb; h_out->n_invalid = ni; h_out->n_bad_offsets = bo;
-    h_out->h2d_bytes = M * rowbytes;
-    h_out->d2h_bytes = ((int64_t)K + nb) * rowbytes;
-    *h_step = s1 / 2;
+    h_out->n_unique = count(kStatU); h_out->n_hit = count(kStatHit); h_out->n_miss = count(kStatMiss);
+    h_out->n_evict = count(kStatEvict); h_out->n_bypass = count(kStatBypass);
+    h_out->n_invalid = count(kStatInvalid); h_out->n_bad_offsets = count(kStatBadOffsets);
+    h_out->h2d_bytes = h_out->n_miss * rowbytes;
+    h_out->d2h_bytes = (h_out->n_evict + h_out->n_bypass) * rowbytes;
+    *h_step = (int64_t)(w[0] >> 32);
     return SFC_OK;
   }
   return fail(SFC_EHIP, "status block kept changing");

@@ -47,14 +47,17 @@ __host__ __device__ __forceinline__ bool bag_malformed(int64_t lo, int64_t hi, i
 
 // Status block in pinned, device-mapped Host memory: kernels write it, the host reads it without
 // waiting for any stream (sfc_check, sfc_peek_stats and the first lines of every step call).
-// The published counters are guarded by a sequence word: odd while a kernel is writing them.
+// A published counter and the step it belongs to share a 64-bit word, step above, and are stored as one: the
+// host has a step's counters when all words carry the same step, and the writer has nothing to order or to
+// wait for.  (A sequence word around plain counters took two waits for the host link, 5 us at the end of
+// the one-block prepare.)
+enum { kStatU, kStatHit, kStatMiss, kStatEvict, kStatBypass, kStatInvalid, kStatBadOffsets, kStatWords };
 struct HostStatus {
   int err;               // first device-side consistency check that fired (0 = none); never cleared
   int err_step;          // step of that check
   int bad_offsets_step;  // most recent step whose bag offsets were malformed (0 = none)
   int pad;
-  int seq;               // 2 * step once that step's counters below are complete
-  int U, n_hit, M, K, n_bypass, n_invalid, n_bad_offsets;
+  uint64_t word[kStatWords];   // step << 32 | counter; step 0 = none yet
 };
 
 // Device counters of one cache.  Written by kernels only; the host reads a copy in get_stats.
@@ -119,38 +122,54 @@ __device__ __forceinline__ uint32_t bucket_of(int64_t key, uint32_t n) {
 
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & (kWave - 1)); }
 
-__device__ __forceinline__ int wave_incl_scan(int x) {
-  const int lane = lane_id();
-#pragma unroll
-  for (int d = 1; d < kWave; d <<= 1) {
-    int y = __shfl_up(x, d, kWave);
-    if (lane >= d) x += y;
-  }
-  return x;
+// Sums across the wavefront in registers (DPP): lanes 1, 2, 4, 8 to the left within a row of 16, then the last
+// lane of a row into the rows behind it.  Six dependent additions; six shuffles through the LDS crossbar took
+// several times as long, and most of the prepare's kernels are a few such scans long.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ int dpp_add(int x) {
+  return x + __builtin_amdgcn_update_dpp(0, x, kCtrl, kRowMask, 0xf, false);
 }
+// inclusive scan over each row of 16 lanes
+__device__ __forceinline__ int row_incl_scan(int x) {
+  x = dpp_add<0x111, 0xf>(x);      // row_shr:1
+  x = dpp_add<0x112, 0xf>(x);      // row_shr:2
+  x = dpp_add<0x114, 0xf>(x);      // row_shr:4
+  return dpp_add<0x118, 0xf>(x);   // row_shr:8
+}
+__device__ __forceinline__ int wave_incl_scan(int x) {
+  x = row_incl_scan(x);
+  x = dpp_add<0x142, 0xa>(x);      // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(x);   // row_bcast:31 into rows 2 and 3
+}
+// (every lane of the wavefront has to be active in these three)
+__device__ __forceinline__ int wave_sum(int x) { return __builtin_amdgcn_readlane(wave_incl_scan(x), kWave - 1); }
 
-__device__ __forceinline__ int wave_sum(int x) {
-#pragma unroll
-  for (int d = kWave / 2; d > 0; d >>= 1) x += __shfl_xor(x, d, kWave);
-  return x;
+// A barrier for what the block shares in LDS alone: accesses to memory stay in flight across it (__syncthreads
+// waits for them, a microsecond or more each time).  What goes through memory from one thread of the block to
+// another needs __syncthreads.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Exclusive scan of one int per thread over the block (blockDim.x multiple of 64, <= 1024).
-// smem: at least 17 ints.  total = sum over the block.  Safe to call repeatedly.
-__device__ __forceinline__ int block_excl_scan(int x, int& total, int* smem) {
-  const int lane = lane_id(), w = (int)(threadIdx.x >> 6), nw = (int)(blockDim.x >> 6);
-  int inc = wave_incl_scan(x);
+// smem: at least 16 ints, which nothing else may touch between this call and the next barrier.
+// total = sum over the block.
+__device__ __forceinline__ int block_excl_scan_once(int x, int& total, int* smem) {
+  const int lane = lane_id(), nw = (int)(blockDim.x >> 6);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int inc = wave_incl_scan(x);
   if (lane == kWave - 1) smem[w] = inc;
   __syncthreads();
-  if (w == 0) {
-    int s = lane < nw ? smem[lane] : 0;
-    int si = wave_incl_scan(s);
-    if (lane < nw) smem[lane] = si - s;   // exclusive prefix of the wave sums
-    if (lane == nw - 1) smem[16] = si;
-  }
-  __syncthreads();
-  int res = inc - x + smem[w];
-  total = smem[16];
+  const int sums = row_incl_scan(lane < nw ? smem[lane] : 0);     // at most 16 wavefronts: one row
+  total = __builtin_amdgcn_readlane(sums, nw - 1);
+  const int before = w > 0 ? __builtin_amdgcn_readlane(sums, w - 1) : 0;
+  return before + inc - x;
+}
+// Safe to call repeatedly with the same smem.
+__device__ __forceinline__ int block_excl_scan(int x, int& total, int* smem) {
+  const int res = block_excl_scan_once(x, total, smem);
   __syncthreads();
   return res;
 }

@@ -992,20 +992,16 @@ __global__ __launch_bounds__(256) void k_victim_unmap(const int64_t* __restrict_
   }
 }
 
-// The step's counters, final since the plan, into the Host status block (sequence word odd while
-// they are being written).  The block is uncached Host memory that nothing else is published through:
-// what its words need is their order, so each group of stores is waited for (a microsecond) and no
-// cache is written back (a system-scope fence took several).
+// The step's counters, final since the plan, into the Host status block: one 64-bit store by each of the
+// first kStatWords lanes of a wavefront (see HostStatus).
 __device__ __forceinline__ void stores_done() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-__device__ __forceinline__ void publish(volatile HostStatus* h, int t, int U, int n_hit, int M, int K,
+__device__ __forceinline__ void publish(HostStatus* h, int lane, int t, int U, int n_hit, int M, int K,
                                         int n_bypass, int n_invalid, int bad_offsets) {
-  if (!h) return;
-  h->seq = 2 * t - 1;
-  stores_done();
-  h->U = U; h->n_hit = n_hit; h->M = M; h->K = K; h->n_bypass = n_bypass;
-  h->n_invalid = n_invalid; h->n_bad_offsets = bad_offsets;
-  stores_done();
-  h->seq = 2 * t;
+  if (!h || lane >= kStatWords) return;
+  const int v = lane == kStatU ? U : lane == kStatHit ? n_hit : lane == kStatMiss ? M : lane == kStatEvict ? K
+              : lane == kStatBypass ? n_bypass : lane == kStatInvalid ? n_invalid : bad_offsets;
+  __hip_atomic_store(&h->word[lane], (uint64_t)(uint32_t)t << 32 | (uint32_t)v, __ATOMIC_RELAXED,
+                     __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1033,10 +1029,8 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   __shared__ int smem[20];
   const int U = ctr->U, K = ctr->K, f = ctr->f_old;
   const int free_slots = C - f;
-  // Here, in one thread of a wide kernel, the publishing costs nothing that anyone waits for; in the
-  // single-block plan kernel its stores over the link, each waited for, would lengthen the prepare.
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0)
-    publish(ctr->hstat, t, U, ctr->n_hit, ctr->M, K, ctr->n_bypass, ctr->n_invalid, ctr->bad_offsets);
+  if (blockIdx.x == gridDim.x - 1)
+    publish(ctr->hstat, (int)threadIdx.x, t, U, ctr->n_hit, ctr->M, K, ctr->n_bypass, ctr->n_invalid, ctr->bad_offsets);
   for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
     const int v = tile * kVidTile + (int)threadIdx.x;
     const bool miss = v < U && slot_out[v] == kMissMark;
@@ -1086,22 +1080,31 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
 
 // ---------------------------------------------------------------------------------------------
 // The prepare of a small batch, by ONE block: up to kSmallIds positions fit the LDS of a compute unit
-// (their table of distinct ids, counts and slots), and for so few the ten launches of the passes
-// above were all start-up, drain and dependent round trips: what bounds this kernel is the chain ids ->
+// (their table of distinct ids, counts and slots), and for so few the launches of the passes above were
+// all start-up, drain and dependent round trips: what bounds this kernel is the chain ids ->
 // table -> rank -> index -> stamp -> lists, walked once with barriers in between instead of kernel
-// boundaries.  Same outputs, same
-// state: 1248 ids 16 us, 4992 ids 25 us, against 63 and 80 us in ten kernels (and 3 us of host time per
-// launch).
+// boundaries, and, from a few thousand positions on, how many scattered accesses one compute unit issues.
+// Same outputs, same state.
+// So nothing in it waits that need not: the index is read for every position as soon as its id is there, beside
+// the table of distinct ids, and the thread that holds an id's first position keeps what it has learned of the
+// id (slot, stamp, number) in registers to the end; one scan numbers the distinct ids and the misses; the
+// counters are published before the last passes; barriers wait for LDS only.  And what goes to memory goes out in
+// order: thread i takes positions i, 1024 + i, ..., virtual ids are numbered by ballots in that order, and the
+// grouping is put together in LDS.  us at 1248 / 4992 positions: the kernel from its first to its last instruction
+// 14.1 / 23.8 with a thread per run of consecutive positions, the index read per virtual id and the counters
+// published last, 5.4 / 14.8 this way (64-bit words in the table of ids 6.3 / 18.7); a pass of 32 x 39 ids looked up
+// 19.8 -> 15.2 (13.4 of it host time), of 128 x 39 trained 43.1 -> 34.3.
 //
 // kWhole (dense index, and either a cache that holds the whole table, so that nothing is ever evicted,
 // or one whose stamps a single block can scan: kSmallSlots): everything up to the grouping, one launch.
 // Otherwise the unique passes and the resolve only; plan, victims, assignment and grouping follow as
 // for any batch (with no hot bins: cnt and the ranks are complete).
-// Positions and virtual ids are dealt to the threads in consecutive runs, so one block scan orders them.
 // ---------------------------------------------------------------------------------------------
-constexpr int kSmallIds = 6144;             // batch table of 8192 entries at a load of at most 3/4
-constexpr int kSmallTab = 8192;
-constexpr int kSmallPer = kSmallIds / 1024;
+constexpr int kSmallIds = 6144;
+constexpr int kSmallPer = kSmallIds / 1024; // positions per thread, at most
+constexpr int kSmallBits = 13;              // bits of a position
+// entries of the LDS table of distinct ids, for kPer positions per thread: 2.7 to 4 times as many as positions
+constexpr int small_tab(int per) { return per <= 2 ? 8192 : 16384; }
 constexpr int kSmallSlots = 1 << 16;        // 16 rounds of 16-byte loads over the stamps
 constexpr int kSmallBags = 4 * kSmallIds;   // bags may be empty, so there can be more of them than ids
 
@@ -1117,131 +1120,234 @@ struct SmallArgs {
   Ctr* ctr; const Ctr* prev;                // prev: nullptr when k_ctr_init has started the counters
 };
 
-template <bool kWhole>
-__global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
-  __shared__ int64_t keys[kSmallTab];         // later: slot and bag, one word each per virtual id / position
-  __shared__ int val[kSmallTab];              // smallest position, then virtual id, per table entry; later ages and starts
-  __shared__ int cntl[kSmallIds];
-  __shared__ unsigned short ent[kSmallIds];   // table entry of each virtual id
-  __shared__ int smem[20];
-  __shared__ int s_found, s_bad, s_err;
-  const int tid = (int)threadIdx.x, n = a.n;
-  const int per = (n + 1023) / 1024, p0 = tid * per;
-  int64_t key[kSmallPer];
-  int e[kSmallPer];
-  bool in[kSmallPer];
+// Exclusive prefix of this wavefront's kSmallPer numbers in the order of the positions (all wavefronts' first
+// numbers, then all second ones, ...).  x: the numbers, the same in every lane; ent: kSmallPer * 16 words of
+// LDS for this call alone.
+template <int kPer>
+__device__ __forceinline__ void small_prefix(const int (&x)[kPer], int (&pre)[kPer], int& total, int* ent) {
+  static_assert(kPer * 16 <= 2 * kWave, "two words per lane");
+  const int lane = lane_id(), w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int mine = 0;
 #pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) {
-    in[j] = j < per && p0 + j < n;
-    key[j] = in[j] ? a.ids[p0 + j] : 0;
+  for (int j = 0; j < kPer; ++j) mine = lane == j ? x[j] : mine;
+  if (lane < kPer) ent[lane * 16 + w] = mine;
+  lds_barrier();
+  const int s0 = wave_incl_scan(lane < kPer * 16 ? ent[lane] : 0);
+  const int half = __builtin_amdgcn_readlane(s0, kWave - 1);
+  const int s1 = half + wave_incl_scan(lane < kPer * 16 - kWave ? ent[kWave + lane] : 0);
+  total = __builtin_amdgcn_readlane(s1, kWave - 1);
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int k = j * 16 + w - 1;
+    pre[j] = k < 0 ? 0 : k < kWave ? __builtin_amdgcn_readlane(s0, k) : __builtin_amdgcn_readlane(s1, k - kWave);
   }
-  for (int i = tid; i < kSmallTab; i += 1024) { keys[i] = kEmpty; val[i] = kIntMax; }
-  for (int i = tid; i < kSmallIds; i += 1024) cntl[i] = 0;
-  if (tid == 0) s_bad = s_err = 0;
-  // counters of the previous step, read before anyone writes (prev == ctr on a cache's first step)
-  Ctr c0;
-  if (tid == 0) { c0 = a.prev ? *a.prev : *a.ctr; a.ctr->t = a.t; }
-  __syncthreads();
-  // the distinct ids and their first positions
+}
+// lanes before this one whose bit is set
+__device__ __forceinline__ int bits_before(uint64_t m) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0));
+}
+
+template <bool kWhole, int kPer>
+__global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
+  constexpr int kIds = kPer * 1024, kTab = small_tab(kPer);
+  // Table of distinct ids: 18 bits of the hash and the smallest position with that id in one word, ~0 = empty.
+  // (32-bit words, because the claims are what the LDS is busy with.)  Once the virtual ids have been handed
+  // out: cache row per virtual id (short form: does it miss) and bag per position.
+  __shared__ __align__(16) unsigned tab[kTab];
+  __shared__ __align__(16) int64_t lkey[kIds];        // id per position; later the grouping, an entry per position
+  __shared__ __align__(16) int cntl[kIds];            // positions per virtual id; later start of the group << 16 | positions
+  __shared__ int age[kAgeBins];
+  __shared__ int smem[20], ent1[kPer * 16], ent2[kPer * 16];
+  __shared__ int s_found, s_bad, s_err, s_inv;
+  static_assert(kTab >= 2 * kIds && kIds <= 1 << kSmallBits && kAgeBins == 1024, "sizes of the tables");
+  int* const slotl = reinterpret_cast<int*>(tab);
+  int* const bagl = slotl + kIds;
+  constexpr unsigned kPos = (1u << kSmallBits) - 1;
+  const int tid = (int)threadIdx.x, n = a.n, lane = lane_id();
+  int64_t key[kPer];
+  int e[kPer], sl[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int p = j * 1024 + tid;
+    key[j] = p < n ? a.ids[p] : (int64_t)-1;
+  }
+  {
+    const uint4 none = make_uint4(~0u, ~0u, ~0u, ~0u);
+#pragma unroll
+    for (int i = 0; i < kTab / 4096; ++i) reinterpret_cast<uint4*>(tab)[i * 1024 + tid] = none;
+    for (int i = tid; i * 4 < n; i += 1024) reinterpret_cast<int4*>(cntl)[i] = make_int4(0, 0, 0, 0);
+    age[tid] = 0;
+    if (tid == 0) s_bad = s_err = s_inv = 0;
+  }
+  // counters of the previous step (on a cache's first step and behind k_ctr_init: of this one, nothing is written
+  // there before it has been read)
+  const Ctr* const was = a.prev ? a.prev : a.ctr;
+  const int f_was = was->f, oldest = was->oldest;
+  HostStatus* const hstat = was->hstat;
+  if (tid == 0) a.ctr->t = a.t;
+  // the dense index by position, on its way while the table is filled (a frequent id's word is one line)
   int n_bad_ids = 0;
 #pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) {
-    if (!in[j]) continue;
-    if (key[j] < 0 || key[j] >= a.V) { key[j] = kNullKey; ++n_bad_ids; }
-    uint32_t l = (uint32_t)mix64((uint64_t)key[j]) & (kSmallTab - 1);
-    for (int probes = 0; probes < kSmallTab; ++probes) {
-      const int64_t k = keys[l];
-      if (k == key[j]) break;
-      if (k == kEmpty) {
-        const int64_t old = (int64_t)atomicCAS((unsigned long long*)&keys[l], (unsigned long long)kEmpty,
-                                               (unsigned long long)key[j]);
-        if (old == kEmpty || old == key[j]) break;
-      }
-      l = (l + 1) & (kSmallTab - 1);
-    }
-    if (val[l] > p0 + j) atomicMin(&val[l], p0 + j);
-    e[j] = (int)l;
+  for (int j = 0; j < kPer; ++j) {
+    const int p = j * 1024 + tid;
+    if (key[j] < 0 || key[j] >= a.V) { key[j] = kNullKey; n_bad_ids += p < n; }
+    lkey[p] = key[j];
+    sl[j] = -1;
+    if ((kWhole || a.dmap) && key[j] >= 0) sl[j] = a.dmap[key[j]];
   }
-  __syncthreads();
-  // virtual ids in order of first appearance
-  unsigned first = 0;
+  lds_barrier();
+  if (n_bad_ids) atomicAdd(&s_inv, n_bad_ids);
+  // the distinct ids and their first positions: an entry is claimed together with its position, a smaller one
+  // is one minimum; the first probes of a thread's positions go side by side, the few that go on do so one by one
+  {
+    constexpr int kShift = 32 - __builtin_ctz(kTab);
+    auto hash = [](int64_t k) {
+      uint32_t h = (uint32_t)k * 0x9e3779b1u + (uint32_t)((uint64_t)k >> 32) * 0x85ebca77u;
+      return h ^ h >> 15;
+    };
+    uint32_t q[kPer], mine[kPer];
+    unsigned open = 0;
 #pragma unroll
-  for (int j = 0; j < kSmallPer; ++j)
-    if (in[j] && val[e[j]] == p0 + j) first |= 1u << j;
-  const int n_invalid = block_sum(n_bad_ids, smem);
-  int U;
-  int vid = block_excl_scan(__popc(first), U, smem);
-#pragma unroll
-  for (int j = 0; j < kSmallPer; ++j)
-    if (first & (1u << j)) {
-      val[e[j]] = vid;
-      ent[vid] = (unsigned short)e[j];
-      a.unique_ids[vid] = key[j] == kNullKey ? (int64_t)-1 : key[j];
-      ++vid;
+    for (int j = 0; j < kPer; ++j) {
+      const uint32_t h = hash(key[j]);
+      e[j] = (int)(h >> kShift);
+      mine[j] = (h & 0x3ffff) << kSmallBits | (uint32_t)(j * 1024 + tid);
+      q[j] = j * 1024 + tid < n ? tab[e[j]] : 0u;
     }
-  __syncthreads();
-  int vv[kSmallPer], rr[kSmallPer];
 #pragma unroll
-  for (int j = 0; j < kSmallPer; ++j)
-    if (in[j]) {
-      vv[j] = val[e[j]];
-      a.inverse[p0 + j] = vv[j];
+    for (int j = 0; j < kPer; ++j)
+      if (q[j] == ~0u) q[j] = atomicCAS(&tab[e[j]], ~0u, mine[j]);
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      if (q[j] == ~0u || j * 1024 + tid >= n) continue;            // claimed
+      if ((q[j] ^ mine[j]) <= kPos && lkey[q[j] & kPos] == key[j]) {
+        if (q[j] > mine[j]) atomicMin(&tab[e[j]], mine[j]);
+      } else {
+        open |= 1u << j;
+      }
+    }
+    uint32_t l = 0, m = 0;
+    int64_t k = 0;
+    bool fresh = true;
+    while (open) {                            // (at most kTab probes per position: the table is never full)
+      const int j = __builtin_ctz(open);
+      if (fresh) {
+        k = lkey[j * 1024 + tid];
+        const uint32_t h = hash(k);
+        l = h >> kShift;
+        m = (h & 0x3ffff) << kSmallBits | (uint32_t)(j * 1024 + tid);
+        fresh = false;
+      }
+      l = (l + 1) & (kTab - 1);
+      uint32_t w = tab[l];
+      if (w == ~0u) w = atomicCAS(&tab[l], ~0u, m);
+      bool done = w == ~0u;
+      if (!done && (w ^ m) <= kPos && lkey[w & kPos] == k) {
+        if (w > m) atomicMin(&tab[l], m);
+        done = true;
+      }
+      if (done) {
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) e[i] = i == j ? (int)l : e[i];
+        open &= open - 1;
+        fresh = true;
+      }
+    }
+  }
+  lds_barrier();
+  // first appearances, which of them are resident, and their stamps
+  unsigned first = 0, hitm = 0, missm = 0;
+  int old[kPer], vid[kPer], mi[kPer], x[kPer], pre[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const int p = j * 1024 + tid;
+    if (p < n && (int)(tab[e[j]] & kPos) == p) first |= 1u << j;
+  }
+  if (!kWhole && !a.dmap) {                   // the hashed index: one probe sequence at a time, of the distinct ids only
+    for (unsigned m = first; m; m &= m - 1) {
+      const int j = __builtin_ctz(m);
+      const int64_t k = lkey[j * 1024 + tid];
+      const int s = k >= 0 ? index_find(a.index, a.hi, k, nullptr, a.ctr) : -1;
+#pragma unroll
+      for (int i = 0; i < kPer; ++i) sl[i] = i == j ? s : sl[i];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const bool is_first = first & (1u << j);
+    bool miss = false;
+    old[j] = 0;
+    if (is_first && key[j] >= 0) {
+      if (sl[j] >= 0) { hitm |= 1u << j; old[j] = a.stamp[sl[j]]; }
+      else { missm |= 1u << j; miss = true; }
+    }
+    const uint64_t bf = __ballot(is_first), bm = __ballot(miss);
+    x[j] = __popcll(bf) << 16 | __popcll(bm);
+    vid[j] = bits_before(bf);
+    mi[j] = bits_before(bm);
+  }
+  int tot;
+  small_prefix(x, pre, tot, ent1);
+  const int U = tot >> 16, M = tot & 0xffff, n_invalid = s_inv, n_hit = U - M - (n_invalid > 0);
+  // virtual ids in order of first appearance, into the table's entries for the other positions (every
+  // position has read its entry: the barrier above)
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    vid[j] += pre[j] >> 16;
+    mi[j] += pre[j] & 0xffff;
+    if (first & (1u << j)) {
+      tab[e[j]] = (unsigned)vid[j];
+      a.unique_ids[vid[j]] = key[j] == kNullKey ? (int64_t)-1 : key[j];
+    }
+  }
+  lds_barrier();
+  int vv[kPer], rr[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) {
+    const bool in = j * 1024 + tid < n;
+    vv[j] = in ? (int)tab[e[j]] : 0;
+    rr[j] = 0;
+    if (in) {
+      a.inverse[j * 1024 + tid] = vv[j];
       rr[j] = atomicAdd(&cntl[vv[j]], 1);
     }
-  __syncthreads();
-  int* const age = val;                       // [kAgeBins]: the virtual ids have been read
-  int* const start = val + kAgeBins;          // [kSmallIds]
-  static_assert(kAgeBins + kSmallIds <= kSmallTab && kAgeBins == 1024, "ages and starts fit the table's words");
-  age[tid] = 0;
-  __syncthreads();
-  // resolve, as k_resolve does
-  const int vper = (U + 1023) / 1024, v0 = tid * vper;
-  int64_t id[kSmallPer];
-  int sl[kSmallPer], old[kSmallPer];
-#pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) {
-    id[j] = j < vper && v0 + j < U ? keys[ent[v0 + j]] : (int64_t)-1;    // kNullKey is negative too
-    sl[j] = -1;
-    if (id[j] >= 0) sl[j] = a.dmap ? a.dmap[id[j]] : index_find(a.index, a.hi, id[j], nullptr, a.ctr);
   }
+  // hits move to the step's stamp; their old ones by age, as k_resolve does it
 #pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) old[j] = sl[j] >= 0 ? a.stamp[sl[j]] : 0;
-  int packed = 0, hits = 0;                   // positions << 16 | misses of this thread's virtual ids
-#pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) {
-    if (!(j < vper && v0 + j < U)) continue;
-    packed += cntl[v0 + j] << 16;
-    if (sl[j] >= 0) {
+  for (int j = 0; j < kPer; ++j) {
+    const bool hit = hitm & (1u << j);
+    const int g = a.t - old[j];
+    const uint64_t m1 = __ballot(hit && g == 1);
+    if (m1 && lane == 0) atomicAdd(&age[1], __popcll(m1));
+    if (hit) {
       a.stamp[sl[j]] = a.t;
-      ++hits;
-      const int g = a.t - old[j];
-      if (g < kAgeBins) atomicAdd(&age[g], 1); else hist_add(&a.hist[old[j]], -1);
-    } else if (id[j] >= 0) {
-      ++packed;
+      if (g >= kAgeBins) hist_add(&a.hist[old[j]], -1);
+      else if (g != 1) atomicAdd(&age[g], 1);
     }
   }
-  const int n_hit = block_sum(hits, smem);
+  lds_barrier();
   if (!kWhole) {
     // in the form k_plan and its followers take it: slots, counts, ranks, tallies per tile and by age
 #pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) {
-      if (j < vper && v0 + j < U) {
-        a.slot[v0 + j] = sl[j] >= 0 ? sl[j] : (id[j] >= 0 ? kMissMark : -1);
-        a.cnt[v0 + j] = cntl[v0 + j];
-        start[v0 + j] = (sl[j] < 0 && id[j] >= 0) ? 1 : 0;
-      }
-      if (in[j]) a.pos_slot[p0 + j] = rr[j];
+    for (int j = 0; j < kPer; ++j) {
+      if (j * 1024 + tid < n) a.pos_slot[j * 1024 + tid] = rr[j];
+      if (!(first & (1u << j))) continue;
+      const bool miss = missm & (1u << j);
+      a.slot[vid[j]] = sl[j] >= 0 ? sl[j] : (miss ? kMissMark : -1);
+      a.cnt[vid[j]] = cntl[vid[j]];
+      slotl[vid[j]] = miss ? 1 : 0;
     }
-    __syncthreads();
+    lds_barrier();
     a.age_hist[tid] = tid ? age[tid] : n_hit;
-    const int w = tid >> 6, lane = lane_id();
+    const int w = tid >> 6;
     for (int tile = w; tile * kVidTile < U; tile += 16) {    // a wavefront per tile of kVidTile virtual ids
       int m = 0, q = 0;
-      for (int v = tile * kVidTile + lane; v < U && v < (tile + 1) * kVidTile; v += kWave) { m += start[v]; q += cntl[v]; }
+      for (int v = tile * kVidTile + lane; v < U && v < (tile + 1) * kVidTile; v += kWave) { m += slotl[v]; q += cntl[v]; }
       m = wave_sum(m); q = wave_sum(q);
       if (lane == 0) { a.tile_miss[tile] = m; a.tile_cnt[tile] = q; }
     }
     if (tid == 0) {
+      Ctr c0 = *was;
       if (a.prev) {
         c0.U_prev = c0.U;
         c0.M = c0.K = c0.n_bypass = c0.n_hit = 0;
@@ -1255,28 +1361,20 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
     }
     return;
   } else {
-    int* const slotl = reinterpret_cast<int*>(keys);         // [kSmallIds]: every id has been read
-    int* const bagl = slotl + kSmallIds;                     // [kSmallIds]
-    // offsets and miss numbers of this thread's virtual ids
-    int tot;
-    const int before = block_excl_scan(packed, tot, smem);
-    int off = before >> 16, i0 = before & 0xffff;
-    const int M = tot & 0xffff;
-    if (a.offsets) for (int i = tid; i < n; i += 1024) bagl[i] = 0;
+    if (a.offsets) {
+      for (int i = tid; i < n; i += 1024) bagl[i] = 0;
+      lds_barrier();
+    }
     // the histogram: hits move to stamp t, the rest of the plan as k_plan does it.  Only a search for
     // victims reads it in here, so only then do the sums have to be back.
-    __shared__ int s_f, s_oldest;
-    __shared__ HostStatus* s_hstat;
-    if (tid == 0) { s_f = c0.f; s_oldest = c0.oldest; s_hstat = c0.hstat; }
-    __syncthreads();
-    const int f = s_f, C = a.C, free_slots = C - f;
+    const int f = f_was, C = a.C, free_slots = C - f;
     const int moved = tid == 0 ? n_hit : -age[tid];
     if (moved) {
       if (M > free_slots) hist_add(&a.hist[a.t - tid], moved);
       else atomicAdd(&a.hist[a.t - tid], moved);
     }
     Plan pl;
-    plan_decide<true>(pl, M, f, s_oldest, a.hist, a.t, a.lookahead, C, smem, &s_found);
+    plan_decide<true>(pl, M, f, oldest, a.hist, a.t, a.lookahead, C, smem, &s_found);
     // bag of every position, checked as k_pos2bag does
     if (a.offsets) {
       int bad = 0;
@@ -1305,8 +1403,8 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) { lt += v[j] < pl.T; eq += v[j] == pl.T; }
         int both;
-        const int pre = block_excl_scan((lt << 16) | eq, both, smem);
-        int lt_before = lt_done + (pre >> 16), eq_before = eq_done + (pre & 0xffff);
+        const int pre2 = block_excl_scan((lt << 16) | eq, both, smem);
+        int lt_before = lt_done + (pre2 >> 16), eq_before = eq_done + (pre2 & 0xffff);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           const bool is_lt = v[j] < pl.T, is_eq = v[j] == pl.T;
@@ -1327,60 +1425,80 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
         lt_done += both >> 16; eq_done += both & 0xffff;
       }
     }
-    __syncthreads();
-    // slots of the misses; where the groups start
+    if (pl.K > 0) __syncthreads();                           // the victims are listed (through memory)
+    // where the groups start
+    int cn[kPer], off[kPer];
 #pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) {
-      const int v = v0 + j;
-      if (!(j < vper && v < U)) continue;
-      int s = sl[j];
-      if (s < 0 && id[j] >= 0) {
-        const int i = i0++;
-        a.miss_vids[i] = v;
-        if (i < pl.K) s = a.victim_slot[i];
-        else if (i - pl.K < free_slots) s = f + (i - pl.K);
-        else s = C + (i - pl.K - free_slots);
-        a.miss_row[i] = s >= C ? s + a.boff : s;
-        a.miss_id[i] = id[j];
-        if (s < C) { a.slot_id[s] = id[j]; a.stamp[s] = a.t; a.dmap[id[j]] = s; }
-      }
-      a.slot[v] = s;
-      slotl[v] = s >= C ? s + a.boff : s;
-      start[v] = off;
-      a.grp[v] = ((int64_t)cntl[v] << 32) | (uint32_t)off;
-      if (cntl[v] > kColdMax) a.cold_pay[v] = make_int2(-1, -1);
-      else if (cntl[v] < kColdMax) a.cold_pay[v].y = -1;     // the positions write the rest
-      off += cntl[v];
+    for (int j = 0; j < kPer; ++j) {
+      cn[j] = first & (1u << j) ? cntl[vid[j]] : 0;
+      off[j] = wave_incl_scan(cn[j]);
+      x[j] = __builtin_amdgcn_readlane(off[j], kWave - 1);
     }
-    __syncthreads();
-    // grouping; here any group of at most kColdMax positions is a cold one
-#pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) {
-      if (!in[j]) continue;
-      const int p = p0 + j, v = vv[j];
-      const int pay = a.offsets ? bagl[p] : p;
-      a.pos_slot[p] = slotl[v];
-      int64_t w = ((int64_t)v << 32) | (uint32_t)pay;
-      if (cntl[v] <= kColdMax) {
-        w |= kColdBit;
-        reinterpret_cast<int*>(a.cold_pay)[2 * v + rr[j]] = pay;
-      }
-      a.perm64[start[v] + rr[j]] = w;
+    small_prefix(x, pre, tot, ent2);                         // (its barrier: the bags are complete)
+    // the counters, on their way while the lists are written
+    if (tid >= 1024 - kWave) {
+      // whoever sees the step's counters also sees that its offsets were malformed: first that, and back
+      volatile HostStatus* h = hstat;
+      if (s_bad && h) { h->bad_offsets_step = a.t; stores_done(); }
+      publish(hstat, lane, a.t, U, n_hit, M, pl.K, pl.n_bypass, n_invalid, s_bad);
     }
     if (tid == 0) {
       if (pl.need > 0 && pl.r > 0) atomicAdd(&a.hist[pl.T], -pl.r);
       if (M != pl.n_bypass) atomicAdd(&a.hist[a.t], M - pl.n_bypass);
+      Ctr c0 = *was;
       c0.U_prev = c0.U; c0.U = U; c0.n_hit = n_hit; c0.n_invalid = n_invalid;
       c0.fetch_on_main = 0; c0.t = a.t; c0.bad_offsets = s_bad;
       plan_store(pl, c0, f);
       if (s_err) c0.err = s_err;
       *a.ctr = c0;
     }
-    if (tid == 1023) {
-      // whoever sees the step's counters also sees that its offsets were malformed: first that, and back
-      volatile HostStatus* h = s_hstat;
-      if (s_bad && h) { h->bad_offsets_step = a.t; stores_done(); }
-      publish(s_hstat, a.t, U, n_hit, M, pl.K, pl.n_bypass, n_invalid, s_bad);
+    // slots of the misses; groups
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      if (!(first & (1u << j))) continue;
+      const int v = vid[j];
+      int s = sl[j];
+      if (missm & (1u << j)) {
+        const int i = mi[j];
+        a.miss_vids[i] = v;
+        if (i < pl.K) s = a.victim_slot[i];
+        else if (i - pl.K < free_slots) s = f + (i - pl.K);
+        else s = C + (i - pl.K - free_slots);
+        a.miss_row[i] = s >= C ? s + a.boff : s;
+        a.miss_id[i] = key[j];
+        if (s < C) { a.slot_id[s] = key[j]; a.stamp[s] = a.t; a.dmap[key[j]] = s; }
+      }
+      off[j] += pre[j] - cn[j];
+      a.slot[v] = s;
+      slotl[v] = s >= C ? s + a.boff : s;
+      cntl[v] = off[j] << 16 | cn[j];
+      a.grp[v] = ((int64_t)cn[j] << 32) | (uint32_t)off[j];
+    }
+    lds_barrier();
+    // grouping, put together in LDS; here any group of at most kColdMax positions is a cold one
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int p = j * 1024 + tid;
+      if (p >= n) continue;
+      const int v = vv[j], sc = cntl[v];
+      a.pos_slot[p] = slotl[v];
+      int64_t w = ((int64_t)v << 32) | (uint32_t)(a.offsets ? bagl[p] : p);
+      if ((sc & 0xffff) <= kColdMax) w |= kColdBit;
+      lkey[(sc >> 16) + rr[j]] = w;
+    }
+    lds_barrier();
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+      const int i = j * 1024 + tid;
+      if (i < n) a.perm64[i] = lkey[i];
+      if (first & (1u << j)) {
+        int2 cp = make_int2(-1, -1);
+        if (cn[j] <= kColdMax) {
+          cp.x = (int)(uint32_t)lkey[off[j]];
+          if (cn[j] == kColdMax) cp.y = (int)(uint32_t)lkey[off[j] + 1];
+        }
+        a.cold_pay[vid[j]] = cp;
+      }
     }
   }
 }

@@ -258,6 +258,30 @@ def test_one_block_batches_beside_large_ones(lookahead, C, index_kind):
     p.close()
 
 
+@pytest.mark.parametrize("index_kind", [HASHED, DENSE])
+@pytest.mark.parametrize("n", [1, 63, 1023, 1025, 2048, 2049, 4096, 4097, 6143, 6144])
+def test_one_block_batches_at_the_edges_of_their_forms(n, index_kind):
+    # sizes where the positions per thread change; ids that meet in the block's table of distinct ids, whose
+    # place there is the top bits of a multiplicative hash: all from a few of its 8192 or 16384 places, so that most
+    # walk on, and the same batch in bags
+    V, D = 200_000, 4
+    h = (np.arange(V, dtype=np.uint64) * 0x9e3779b1) & 0xffffffff
+    h ^= h >> 15
+    near = np.nonzero((h >> (19 if n <= 2048 else 18)) % 97 < 3)[0]
+    rng = np.random.default_rng(n)
+    p = Pair(V, D, C=9000, max_ids=6144, max_bags=6144, index_kind=index_kind)
+    for t in range(4):
+        ids = rng.choice(near[t * 500:t * 500 + 5000], n)
+        ids[rng.random(n) < 0.2] = near[7]
+        ids[rng.random(n) < 0.01] = -1
+        if t % 2:
+            off = np.concatenate([[0], np.sort(rng.integers(0, n + 1, max(n // 3, 1) - 1)), [n]])
+            p.step(ids, si.grads(off.size - 1, D, 93, t).numpy(), off)
+        else:
+            p.step(ids, si.grads(n, D, 93, t).numpy())
+    p.finish(); p.close()
+
+
 @pytest.mark.parametrize("n_bags", [20_000, 30_000])
 def test_few_ids_in_many_mostly_empty_bags(n_bags):
     V, D = 500, 8
