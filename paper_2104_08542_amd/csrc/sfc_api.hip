@@ -430,28 +430,25 @@ int seg_launch(sfc_cache* c, StepCtx* x, const float* d_grad, float* d_common, d
   return SFC_OK;
 }
 
-// The prepare's kernels behind the resolve: bags of the positions, victims' plan and lists, slots of the
-// misses.  (Called where the resolve has run on c->prep; group_positions follows.)
+// The prepare's kernels behind the resolve: victims' plan (and sums and bags of the positions), victims' lists,
+// slots of the misses.  (Called where the resolve has run on c->prep; group_positions follows.)
 void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
   hipStream_t s = c->prep;
   const int n = (int)x->n_ids;
   const SortGeom& sg = x->sg;
-  // (after the resolve: it tallies into the step's counters, which that kernel may have started)
-  if (n > 0 && x->d_offsets)
-    hipLaunchKernelGGL(k_pos2bag, dim3((unsigned)((x->n_bags + 255) / 256)), dim3(256), 0, s,
-                       x->d_offsets, (int)x->n_bags, n, c->pos2bag, x->ctr);
-  hipLaunchKernelGGL(k_plan, dim3(1), dim3(1024), 0, s, c->tile_miss, c->tile_cnt, c->age_hist,
-                     c->tile_reuse, c->hist, x->t, c->cfg.lookahead, (int)c->C, c->hi, x->ctr);
+  const FoldArgs fo{cnt, cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, 4 * kVidTile, kFoldBlocks)};
+  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag};
+  const unsigned bag_blocks = n > 0 && x->d_offsets ? (unsigned)((x->n_bags + 1023) / 1024) : 0u;
+  hipLaunchKernelGGL(k_plan, dim3(1 + fo.folds + bag_blocks), dim3(1024), 0, s, c->tile_miss, c->age_hist,
+                     c->tile_reuse, c->hist, x->t, c->cfg.lookahead, (int)c->C, c->hi, c->dmap ? 1 : 0, x->ctr, fo, bags);
   // a cache that holds the whole table never evicts: there is a free slot for every id that is not resident
   if (c->C < c->V) {
     const int gs = grid_for(c->C, kPosChunk, kGridCap);
     hipLaunchKernelGGL(k_victim_count, dim3(gs), dim3(256), 0, s, c->stamp, c->tile_lt, c->tile_eq, x->ctr);
     hipLaunchKernelGGL(k_victim_write, dim3(gs), dim3(256), 0, s, c->stamp, c->slot_id, c->tile_lt,
-                       c->tile_eq, x->victim_slot, x->victim_id, x->ctr, c->dmap);
+                       c->tile_eq, x->victim_slot, x->victim_id, x->ctr, c->dmap, c->index, c->hi);
   }
   const int gv = grid_for(n, kVidTile, kGridCap);
-  if (!c->dmap && c->C < c->V)
-    hipLaunchKernelGGL(k_victim_unmap, dim3(gv), dim3(256), 0, s, x->victim_id, c->index, c->hi, x->ctr);
   hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, x->d_unique, cnt, cnt_rep,
                      c->cur_rep, sg.bins, sg.nrep, c->tile_cnt, c->grp, x->cold_pay, c->tile_miss,
                      x->victim_slot, x->d_slot, x->d_miss, x->miss_row, x->miss_id, x->boff, c->slot_id,
@@ -826,39 +823,52 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   if (hu < 64) hu = 64;                       // the batch table is empty between steps: any size works
   const int nchunk = (n + kPosChunk - 1) / kPosChunk;
   const SortGeom sg = x->sg = small ? small_geom(n) : sort_geom(n);
-  if (small) {
-    // its unique passes are part of the kernel below
-  } else if (n > 0) {
+  // Hashed index, where everything runs behind the previous step's prepare: its rebuild, when due, by further
+  // blocks of the unique passes
+  const bool rebuild_inside = !c->dmap && !small && n > 0 && su == s;
+  const int extra = rebuild_inside ? kRebuildBlocks : 0;
+  // What the resolve (and with it the start of the step's counters) waits for is done by the time the unique
+  // passes are: a dense index has no rebuild.  Otherwise both are kernels of their own.
+  const bool start_inside = c->dmap || rebuild_inside;
+  if (!small && n > 0) {
     const int nub = (n + kUniqChunk - 1) / kUniqChunk;
     if (c->wide) {
       WideTab tab{(UEntry*)c->utab, 0, c->V};
-      hipLaunchKernelGGL(k_uniq_insert<WideTab>, dim3(nub), dim3(256), 0, su, d_ids, n, tab, hu, c->hslot,
-                         c->first, c->n_invalid);
+      hipLaunchKernelGGL(k_uniq_insert<WideTab>, dim3(nub + extra), dim3(256), 0, su, d_ids, n, tab, hu, c->hslot,
+                         c->first, c->n_invalid, nub, (const Ctr*)prev->ctr, c->index, c->hi);
     } else {
       PackedTab tab{c->utab, pos_bits(n), c->V};
-      hipLaunchKernelGGL(k_uniq_insert<PackedTab>, dim3(nub), dim3(256), 0, su, d_ids, n, tab, hu, c->hslot,
-                         c->first, c->n_invalid);
+      hipLaunchKernelGGL(k_uniq_insert<PackedTab>, dim3(nub + extra), dim3(256), 0, su, d_ids, n, tab, hu, c->hslot,
+                         c->first, c->n_invalid, nub, (const Ctr*)prev->ctr, c->index, c->hi);
     }
     const int* const counts = n > kCountMin ? c->blk_cnt : nullptr;
     if (counts)
       hipLaunchKernelGGL(k_uniq_count, dim3((nchunk + 3) / 4), dim3(256), 0, su, (const unsigned*)c->first,
                          nchunk, c->blk_cnt);
-    hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk), dim3(256), 0, su, d_ids, c->V, c->hslot,
-                       (const unsigned*)c->first, n, counts, d_unique_ids, c->uvid, c->vid_hslot, cnt, c->n_unique);
-    auto inv = sg.shift == 10 ? k_uniq_inverse<1, 1024> : sg.shift == 12 ? k_uniq_inverse<8, 512> : k_uniq_inverse<8, 1024>;
-    hipLaunchKernelGGL(inv, dim3(sg.blocks), dim3(sg.shift == 12 ? 512 : 1024), 0, su, c->hslot, c->uvid, n, d_inverse, cnt,
-                       cnt_rep, sg.nrep, x->pos_slot, c->first);
-  } else {
+    hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk + extra), dim3(256), 0, su, d_ids, c->V, c->hslot,
+                       (const unsigned*)c->first, n, counts, d_unique_ids, c->uvid, c->vid_hslot, cnt, c->n_unique,
+                       nchunk, x->ctr, x->t, (const Ctr*)prev->ctr, c->index, c->hi, (const int64_t*)c->slot_id);
+  } else if (!small) {
     fill<int>(su, c->n_unique, 1, 0);
   }
+  const RankArgs rank{c->hslot, c->uvid, n, d_inverse, cnt, cnt_rep, sg.nrep, x->pos_slot, c->first};
+  const ResolveArgs res{d_unique_ids, c->vid_hslot, c->utab, c->wide ? 1 : 0, c->index, c->hi, c->dmap, c->stamp,
+                        c->hist, x->t, d_slot, c->tile_miss, c->age_hist, x->ctr,
+                        start_inside ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid};
+  auto rank_resolve = sg.shift == 10 ? k_rank_resolve<1, 1024> : sg.shift == 12 ? k_rank_resolve<8, 512>
+                                                                              : k_rank_resolve<8, 1024>;
+  const int rt = sg.shift == 12 ? 512 : 1024, nres = small ? 0 : grid_for(n, rt, kResolveThreads / rt);
+  const int ncount = small || n == 0 ? 0 : sg.blocks;
+  const bool together = su == s && start_inside;
+  if (!together && ncount)
+    hipLaunchKernelGGL(rank_resolve, dim3(ncount), dim3(rt), 0, su, rank, res, 0);
   if (su != s) {
     HIPCHK(hipEventRecord(c->ev_inserted, su));
     HIPCHK(hipStreamWaitEvent(s, c->ev_inserted, 0));
   }
   // from here on behind the whole prepare of the previous step: the step's counters start from
   // that step's, the index is rebuilt if its plan asked for it
-  // (a dense index is never rebuilt: k_resolve starts the counters itself, neither is launched)
-  if (!c->dmap) {
+  if (!start_inside) {
     hipLaunchKernelGGL(k_ctr_init, dim3(kRebuildGrid), dim3(256), 0, s, x->ctr, prev->ctr,
                        c->n_unique, c->n_invalid, c->index, c->hi, x->t);
     hipLaunchKernelGGL(k_index_refill, dim3(kRebuildGrid), dim3(256), 0, s, c->index, c->hi, c->slot_id, x->ctr);
@@ -870,7 +880,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     a.index = c->index; a.hi = c->hi; a.dmap = c->dmap;
     a.stamp = c->stamp; a.slot_id = c->slot_id; a.hist = c->hist;
     a.t = x->t; a.lookahead = c->cfg.lookahead; a.C = (int)c->C; a.boff = x->boff;
-    a.cnt = cnt; a.tile_miss = c->tile_miss; a.tile_cnt = c->tile_cnt; a.age_hist = c->age_hist;
+    a.cnt = cnt; a.tile_miss = c->tile_miss; a.age_hist = c->age_hist;
     a.grp = c->grp; a.cold_pay = x->cold_pay; a.perm64 = x->perm64; a.pos_slot = x->pos_slot;
     a.victim_slot = x->victim_slot; a.victim_id = x->victim_id; a.miss_row = x->miss_row; a.miss_id = x->miss_id;
     a.ctr = x->ctr; a.prev = c->dmap ? prev->ctr : nullptr;
@@ -879,11 +889,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                           : (whole ? k_small_prepare<true, kSmallPer> : k_small_prepare<false, kSmallPer>);
     hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, a);
   } else {
-    const int gr = grid_for(n, kVidTile, kResolveGrid);
-    hipLaunchKernelGGL(k_resolve, dim3(gr), dim3(256), 0, s, d_unique_ids, c->vid_hslot, c->utab,
-                       c->wide ? 1 : 0, c->index, c->hi, c->dmap, c->stamp, c->hist, x->t, d_slot, c->tile_miss, cnt, cnt_rep,
-                       sg.bins, sg.nrep, c->tile_cnt, c->age_hist, x->ctr,
-                       c->dmap ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid);
+    hipLaunchKernelGGL(rank_resolve, dim3(nres + (together ? ncount : 0)), dim3(rt), 0, s, rank, res, nres);
   }
   if (c->ins) { HIPCHK(hipEventRecord(c->ev_resolved, s)); c->resolved_once = true; }
   x->grouping_due = !whole && c->nctx == 1;

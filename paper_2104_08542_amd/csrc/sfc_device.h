@@ -2,6 +2,7 @@
 // hashing, wavefront/block scans and reductions for 64-wide wavefronts, 16-byte row chunks.
 #pragma once
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 namespace sfc {

@@ -6,7 +6,7 @@
 // cache state) is a function of the input sets and slot numbers only: their orders come from
 // prefix scans over positions / virtual ids / slots, and atomics are used only where the result
 // is order-free (min, counters, set insert).  The one thing that does follow the arrival order of
-// atomics is internal: the order of a group's entries in perm64 (k_uniq_inverse ranks the
+// atomics is internal: the order of a group's entries in perm64 (k_rank_resolve ranks the
 // positions of an id by the value its counting atomic returns).  It decides the order of an fp64
 // sum, nothing else; see the segment-sum kernels for what that means for the results.
 #pragma once
@@ -110,10 +110,43 @@ struct WideTab {
   __device__ __forceinline__ int lower(uint32_t h, int64_t, int p) const { return atomicMin(&e[h].minpos, p); }
 };
 
+// Rebuild of the hashed cache index: emptied, then every resident id goes back in, by nblk blocks of 256 threads
+// each, over the occupied slots [0, f).  The previous step's plan asks for it when too many entries are deleted ones;
+// the two halves run between that step's last index update and this step's resolve, as further blocks of the
+// insert and the assign pass (kRebuildBlocks each, which return at once otherwise), or as kernels of their own
+// where those passes do not run behind that step's prepare (k_ctr_init, k_index_refill).
+constexpr int kRebuildBlocks = 256;
+__device__ __forceinline__ void index_clear(IdxEntry* index, uint32_t hi, int blk, int nblk) {
+  IdxEntry e; e.key = kEmpty; e.slot = -1; e.pad = 0;
+  for (uint32_t i = blk * 256 + threadIdx.x; i < hi; i += nblk * 256) index[i] = e;
+}
+__device__ __forceinline__ void index_reinsert(IdxEntry* index, uint32_t hi,
+                                               const int64_t* __restrict__ slot_id, int f, int blk, int nblk) {
+  for (int s = blk * 256 + threadIdx.x; s < f; s += nblk * 256) {
+    const int64_t id = slot_id[s];
+    if (id < 0) continue;
+    uint32_t h = bucket_of(id, hi);
+    for (uint32_t probes = 0; probes < hi; ++probes) {
+      if (index[h].key == kEmpty &&
+          (int64_t)atomicCAS((unsigned long long*)&index[h].key, (unsigned long long)kEmpty,
+                             (unsigned long long)id) == kEmpty) {
+        atomicExch(&index[h].slot, s);
+        break;
+      }
+      h = h + 1 == hi ? 0 : h + 1;
+    }
+  }
+}
+
 template <class Tab>
 __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__ ids, int n, Tab tab,
                                                       uint32_t hu, int* __restrict__ hslot,
-                                                      unsigned* first, int* __restrict__ n_invalid) {
+                                                      unsigned* first, int* __restrict__ n_invalid, int blocks,
+                                                      const Ctr* prev, IdxEntry* index, uint32_t hi) {
+  if ((int)blockIdx.x >= blocks) {            // (only with a hashed index) see index_clear
+    if (prev->rebuild) index_clear(index, hi, (int)blockIdx.x - blocks, (int)gridDim.x - blocks);
+    return;
+  }
   __shared__ int64_t lkey[kLdsTab];
   __shared__ int lval[kLdsTab];               // smallest position of the key in this block; later its HBM entry
   __shared__ unsigned short lst[kUniqChunk];  // occupied LDS entries, compacted
@@ -170,7 +203,7 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
       if (occ & (1u << k)) lst[at++] = (unsigned short)(threadIdx.x * kLdsPer + k);
   }
   __syncthreads();
-  if (gridDim.x > kHeadMin && blockIdx.x >= kHeadBlocks && blockIdx.x < kResidentBlocks)
+  if (blocks > kHeadMin && blockIdx.x >= kHeadBlocks && blockIdx.x < kResidentBlocks)
     for (int i = 0; i < kHeadSleep; ++i) __builtin_amdgcn_s_sleep(32);
   // distinct keys of the block -> HBM table, kFly per thread in flight
   constexpr int kFly = kUniqPer;
@@ -249,26 +282,6 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
   }
 }
 
-// Rebuild of the cache index, second half (the first half empties it): every resident id goes
-// back in.  Grid-stride over the occupied slots [0, f).
-__device__ __forceinline__ void index_reinsert(IdxEntry* index, uint32_t hi,
-                                               const int64_t* __restrict__ slot_id, int f) {
-  for (int s = blockIdx.x * 256 + threadIdx.x; s < f; s += gridDim.x * 256) {
-    const int64_t id = slot_id[s];
-    if (id < 0) continue;
-    uint32_t h = bucket_of(id, hi);
-    for (uint32_t probes = 0; probes < hi; ++probes) {
-      if (index[h].key == kEmpty &&
-          (int64_t)atomicCAS((unsigned long long*)&index[h].key, (unsigned long long)kEmpty,
-                             (unsigned long long)id) == kEmpty) {
-        atomicExch(&index[h].slot, s);
-        break;
-      }
-      h = h + 1 == hi ? 0 : h + 1;
-    }
-  }
-}
-
 // VSI pass 2: how many first appearances each chunk of positions has; a wavefront per chunk.  Up to
 // kCountMin positions the next pass adds up the bits itself (at most 64 KB per block, out of L2) and
 // this one, 5 us of start-up and drain, is not launched.
@@ -286,12 +299,7 @@ __global__ __launch_bounds__(256) void k_uniq_count(const unsigned* __restrict__
 // cache-wide fields (watermark, oldest stamp, tombstones, rebuild flag, error) from the previous
 // step's and start their own tallies at zero.  Steps in flight on the other streams keep reading
 // their own copy.  n_invalid is the insert pass's tally of out-of-range positions, returned to
-// zero here.
-// The same launch empties the cache index when the previous step's plan asked for a rebuild (too
-// many deleted entries); k_index_refill then puts every resident id back.  Both run between the
-// last index update of one step and the resolve of the next.  They read the flag and the
-// watermark from the previous step's counters, which no kernel changes any more (on the very
-// first step prev == cur and both fields are zero before and after).
+// zero here.  (An error, once there, stays in every later step's counters; a probe beside this may be flagging one.)
 __device__ __forceinline__ void ctr_start(Ctr* cur, const Ctr* prev, const int* n_unique,
                                           int* n_invalid, int t) {
   Ctr c = *prev;
@@ -302,29 +310,37 @@ __device__ __forceinline__ void ctr_start(Ctr* cur, const Ctr* prev, const int* 
   *n_invalid = 0;
   c.f_old = c.f; c.need = 0; c.T = 0; c.r = 0; c.fetch_on_main = 0;
   c.t = t; c.bad_offsets = 0;
-  *cur = c;
+  static_assert(offsetof(Ctr, err) == 14 * sizeof(int), "the fields around err");
+  int* const to = reinterpret_cast<int*>(cur);
+  const int* const from = reinterpret_cast<const int*>(&c);
+#pragma unroll
+  for (int i = 0; i < (int)(sizeof(Ctr) / sizeof(int)); ++i)
+    if (i != 14) to[i] = from[i];
+  if (c.err) cur->err = c.err;
 }
 
+// The counters and the index rebuild as kernels of their own: with a hashed index, for batches prepared by one
+// block and where the unique passes have a stream of their own.  They read the flag and the watermark from the
+// previous step's counters, which no kernel changes any more (on the very first step prev == cur and both fields
+// are zero before and after).
 __global__ __launch_bounds__(256) void k_ctr_init(Ctr* cur, const Ctr* prev, const int* n_unique,
                                                   int* n_invalid, IdxEntry* index, uint32_t hi,
                                                   int t) {
   const bool rebuild = prev->rebuild != 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) ctr_start(cur, prev, n_unique, n_invalid, t);
-  if (!rebuild) return;
-  IdxEntry e; e.key = kEmpty; e.slot = -1; e.pad = 0;
-  for (uint32_t i = blockIdx.x * 256 + threadIdx.x; i < hi; i += gridDim.x * 256) index[i] = e;
+  if (rebuild) index_clear(index, hi, (int)blockIdx.x, (int)gridDim.x);
 }
 __global__ __launch_bounds__(256) void k_index_refill(IdxEntry* index, uint32_t hi,
                                                        const int64_t* __restrict__ slot_id,
                                                        const Ctr* ctr) {
-  if (ctr->rebuild) index_reinsert(index, hi, slot_id, ctr->f);
+  if (ctr->rebuild) index_reinsert(index, hi, slot_id, ctr->f, (int)blockIdx.x, (int)gridDim.x);
 }
 
 // VSI pass 3: the first appearances get their virtual ids (rank among all first appearances) and
 // the tables keyed by them.  A chunk's first virtual id is the sum of the counts of the chunks
 // before it, which every block adds up for itself (a few loads per thread from a list that sits in
 // L2: cheaper than a scan kernel between the two passes).  The last chunk leaves the number of
-// unique ids in *n_unique for k_ctr_init.
+// unique ids in *n_unique.
 __global__ __launch_bounds__(256) void k_uniq_assign(const int64_t* __restrict__ ids, int64_t V,
                                                       const int* __restrict__ hslot,
                                                       const unsigned* __restrict__ first, int n,
@@ -332,7 +348,15 @@ __global__ __launch_bounds__(256) void k_uniq_assign(const int64_t* __restrict__
                                                       int64_t* __restrict__ unique_ids,
                                                       int* __restrict__ uvid,
                                                       int* __restrict__ vid_hslot,
-                                                      int* __restrict__ cnt, int* n_unique) {
+                                                      int* __restrict__ cnt, int* n_unique, int chunks,
+                                                      Ctr* ctr, int t, const Ctr* prev, IdxEntry* index, uint32_t hi,
+                                                      const int64_t* __restrict__ slot_id) {
+  if ((int)blockIdx.x >= chunks) {            // (only with a hashed index) see index_clear
+    // the step's number is in its counters before a probe of the resolve can flag an error under it
+    if ((int)blockIdx.x == chunks && threadIdx.x == 0) ctr->t = t;
+    if (prev->rebuild) index_reinsert(index, hi, slot_id, prev->f, (int)blockIdx.x - chunks, (int)gridDim.x - chunks);
+    return;
+  }
   __shared__ int smem[20];
   const unsigned flags = reinterpret_cast<const unsigned char*>(first)[blockIdx.x * 256 + threadIdx.x];
   int before = 0;
@@ -355,7 +379,7 @@ __global__ __launch_bounds__(256) void k_uniq_assign(const int64_t* __restrict__
   before = block_sum(before, smem);
   int tot;
   int vid = block_excl_scan(__popc(flags), tot, smem) + before;
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) *n_unique = before + tot;
+  if ((int)blockIdx.x == chunks - 1 && threadIdx.x == 0) *n_unique = before + tot;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
     if (flags & (1u << j)) {
@@ -415,18 +439,16 @@ inline SortGeom small_geom(int64_t n) {
 }
 
 template <int kPer, int kT>
-__global__ __launch_bounds__(kT) void k_uniq_inverse(const int* __restrict__ hslot,
-                                                       const int* __restrict__ uvid, int n,
-                                                       int* __restrict__ inverse, int* cnt,
-                                                       int* cnt_rep, int nrep, int* __restrict__ rank,
-                                                       unsigned* __restrict__ first) {
-  __shared__ int lh[kHotBins];
+__device__ __forceinline__ void count_positions(const int* __restrict__ hslot, const int* __restrict__ uvid, int n,
+                                                int* __restrict__ inverse, int* cnt, int* cnt_rep, int nrep,
+                                                int* __restrict__ rank, unsigned* __restrict__ first, int blk,
+                                                int* lh) {
   // the marks of first appearances have been read: all zero again for the next batch
   static_assert(kPer <= 32 && kT * kPer % 32 == 0, "whole words of marks per block");
-  if ((int)threadIdx.x < kT * kPer / 32 && (int)(blockIdx.x * kT * kPer + threadIdx.x * 32) < n)
-    first[blockIdx.x * (kT * kPer / 32) + threadIdx.x] = 0;
+  if ((int)threadIdx.x < kT * kPer / 32 && blk * kT * kPer + (int)threadIdx.x * 32 < n)
+    first[blk * (kT * kPer / 32) + threadIdx.x] = 0;
   for (int i = threadIdx.x; i < kHotBins; i += kT) lh[i] = 0;
-  const int base = blockIdx.x * kT * kPer;
+  const int base = blk * kT * kPer;
   int hv[kPer], vv[kPer], rr[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {              // kPer loads in flight per level of indirection
@@ -446,7 +468,7 @@ __global__ __launch_bounds__(kT) void k_uniq_inverse(const int* __restrict__ hsl
     }
   }
   __syncthreads();
-  int* mine = cnt_rep + (blockIdx.x & (nrep - 1)) * kHotBins;
+  int* mine = cnt_rep + (blk & (nrep - 1)) * kHotBins;
   // the block's share of each non-empty bin: returning atomics, several in flight per thread (each
   // round of them is a round trip to the memory side)
   constexpr int kFlush = kHotBins / kT < 16 ? kHotBins / kT : 16;
@@ -477,11 +499,12 @@ __global__ __launch_bounds__(kT) void k_uniq_inverse(const int* __restrict__ hsl
 // one that starts at or before it (six steps of a search in LDS).  With a thread per bag every store
 // touched a line of its own: 38 us for 852e3 bags of 1 to 20 ids, 17 this way.  A wavefront that has seen a
 // violation falls back to a loop per bag.
-__global__ __launch_bounds__(256) void k_pos2bag(const int64_t* __restrict__ offsets, int n_bags,
-                                                  int n, int* __restrict__ pos2bag, Ctr* ctr) {
-  __shared__ int starts[4][kWave];
+// starts: a word of LDS per thread, used within the wavefront alone.
+__device__ __forceinline__ void bags_of_positions(const int64_t* __restrict__ offsets, int n_bags, int n,
+                                                  int* __restrict__ pos2bag, Ctr* ctr, int blk, int* starts_all) {
   const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
-  const int b0 = blockIdx.x * 256 + w * kWave, b = b0 + lane;
+  int* const starts = starts_all + w * kWave;
+  const int b0 = blk * (int)blockDim.x + w * kWave, b = b0 + lane;
   bool bad = false;
   BagRange r{n, n};                               // lanes beyond the last bag: empty, at the end
   if (b < n_bags) {
@@ -489,14 +512,16 @@ __global__ __launch_bounds__(256) void k_pos2bag(const int64_t* __restrict__ off
     bad = bag_malformed(lo, hi, b, n_bags, n);
     r = bag_range(lo, hi, n);
   }
-  starts[w][lane] = r.lo;
+  starts[lane] = r.lo;
   const uint64_t m = __ballot(bad);
   if (m && lane == 0) {
     atomicAdd(&ctr->bad_offsets, __popcll(m));
     volatile HostStatus* h = ctr->hstat;
     if (h) h->bad_offsets_step = ctr->t;
   }
-  __syncthreads();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
   if (b0 >= n_bags) return;
   if (m) {
     if (b < n_bags)
@@ -506,12 +531,12 @@ __global__ __launch_bounds__(256) void k_pos2bag(const int64_t* __restrict__ off
   // No violation among these bags: their offsets do not decrease, so their clamped ranges tile [first start,
   // last end), also where the offsets lie outside [0, n] (the violation is then another wavefront's).
   const int last = n_bags - b0 < kWave ? n_bags - b0 - 1 : kWave - 1;
-  const int begin = starts[w][0], end = __shfl(r.hi, last, kWave);
+  const int begin = starts[0], end = __shfl(r.hi, last, kWave);
   for (int q = begin + lane; q < end; q += kWave) {
     int g = 0;
 #pragma unroll
     for (int step = kWave / 2; step > 0; step >>= 1)
-      if (g + step <= last && starts[w][g + step] <= q) g += step;
+      if (g + step <= last && starts[g + step] <= q) g += step;
     pos2bag[q] = b0 + g;
   }
 }
@@ -660,53 +685,41 @@ __device__ __forceinline__ bool index_insert(IdxEntry* index, uint32_t hi, int64
 // (t - old stamp) in LDS and adds its nonzero bins to age_hist, which the plan kernel applies
 // to hist and returns to zero.  Only ages beyond the LDS range use an atomic on hist.  Bin 0
 // counts the hits.  Also returns the batch-table entries of this step to the empty state, so that
-// table never needs a per-step clear, and sums cnt per tile for the segment offsets.
+// table never needs a per-step clear.
 // ---------------------------------------------------------------------------------------------
 constexpr int kAgeBins = 1024;
 // One tile per block and iteration, up to 512 blocks: what hides the chain vid -> id -> index entry ->
 // stamp is more wavefronts, not more tiles per thread.  (us at 10.6e3 / 40e3 / 132e3 / 200e3 / 837e3 /
 // 1.24e6 unique ids: 7.1 / 7.7 / 16 / 17.5 / 48 / 62; four tiles per thread on 256 blocks 16 / 15 / 17 / 25 /
 // 60 / 84; one tile on 256 blocks 7.2 / 7.5 / 15 / 21 / 58 / 81, on 1024 6.8 / 7.7 / 16 / 22.5 / 49 / 59.)
-constexpr int kResolveGrid = 512;
+constexpr int kResolveThreads = 512 * 256;
 
-__global__ __launch_bounds__(256) void k_resolve(const int64_t* __restrict__ unique_ids,
-                                                  const int* __restrict__ vid_hslot, uint64_t* utab, int wide,
-                                                  const IdxEntry* __restrict__ index, uint32_t hi,
-                                                  const int* __restrict__ dmap,
-                                                  int* stamp, int* hist, int t,
-                                                  int* __restrict__ slot_out,
-                                                  int* __restrict__ tile_miss,
-                                                  int* __restrict__ cnt,
-                                                  const int* __restrict__ cnt_rep, int bins, int nrep,
-                                                  int* __restrict__ tile_cnt,
-                                                  int* __restrict__ age_hist, Ctr* ctr,
-                                                  const Ctr* prev, const int* n_unique,
-                                                  int* n_invalid) {
-  __shared__ int smem[20];
-  __shared__ int lage[kAgeBins];
-  for (int i = threadIdx.x; i < kAgeBins; i += 256) lage[i] = 0;
-  // Dense index (prev != nullptr): nothing has to happen between the previous step's prepare and
-  // this kernel, so it starts the step's counters itself (k_ctr_init is not launched): the first
+template <int kT>
+__device__ __forceinline__ void resolve_ids(const int64_t* __restrict__ unique_ids,
+                                            const int* __restrict__ vid_hslot, uint64_t* utab, int wide,
+                                            const IdxEntry* __restrict__ index, uint32_t hi,
+                                            const int* __restrict__ dmap, int* stamp, int* hist, int t,
+                                            int* __restrict__ slot_out, int* __restrict__ tile_miss,
+                                            int* __restrict__ age_hist, Ctr* ctr, const Ctr* prev,
+                                            const int* n_unique, int* n_invalid, int blk, int nblk, int* lds) {
+  int* const lage = lds;                       // [kAgeBins]
+  int* const wmiss = lds + kAgeBins;           // a word per wavefront
+  for (int i = threadIdx.x; i < kAgeBins; i += kT) lage[i] = 0;
+  // prev != nullptr: nothing has to happen between the previous step's prepare and this kernel (an index
+  // rebuild is done already), so it starts the step's counters itself (k_ctr_init is not launched): the first
   // thread writes them for the kernels that follow, and every block takes the number of unique ids
-  // from where the unique passes left it.  Nothing else of the counters is read in this kernel,
-  // and the dense index has no probe that could flag an error into them meanwhile.
+  // from where the unique passes left it.  Nothing else of the counters is read in this kernel.
   const int U = prev ? *n_unique : ctr->U;
   __syncthreads();
-  if (prev && blockIdx.x == 0 && threadIdx.x == 0) ctr_start(ctr, prev, n_unique, n_invalid, t);
-  for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
-    const int v = tile * kVidTile + (int)threadIdx.x;
-    int hs = -1, cc = 0, sl = -1, old = 0;
+  if (prev && blk == 0 && threadIdx.x == 0) ctr_start(ctr, prev, n_unique, n_invalid, t);
+  constexpr int kTiles = kT / kVidTile;        // tiles side by side
+  const int sub = (int)threadIdx.x / kVidTile;
+  for (int tile0 = blk * kTiles; tile0 * kVidTile < U; tile0 += nblk * kTiles) {
+    const int tile = tile0 + sub;
+    const int v = tile * kVidTile + (int)threadIdx.x % kVidTile;
+    int hs = -1, sl = -1, old = 0;
     int64_t id = -1;
-    if (v < U) {
-      hs = vid_hslot[v]; id = unique_ids[v];
-      if (v < bins) {                           // fold the copies of a hot bin
-#pragma unroll 8
-        for (int r = 0; r < nrep; ++r) cc += cnt_rep[r * kHotBins + v];
-        cnt[v] = cc;
-      } else {
-        cc = cnt[v];
-      }
-    }
+    if (v < U) { hs = vid_hslot[v]; id = unique_ids[v]; }
     if (hs >= 0) {
       if (wide) { UEntry z; z.key = kEmpty; z.minpos = kIntMax; z.pad = 0; reinterpret_cast<UEntry*>(utab)[hs] = z; }
       else utab[hs] = ~0ull;
@@ -731,18 +744,49 @@ __global__ __launch_bounds__(256) void k_resolve(const int64_t* __restrict__ uni
       if (age >= kAgeBins) atomicSub(&hist[old], 1);
     }
     // most hits were last used one step ago: count those per wavefront, the rest one by one
-    const uint64_t m1 = __ballot(hit && age == 1);
-    if (m1 && lane_id() == 0) atomicAdd(&lage[1], __popcll(m1));
+    const uint64_t m1 = __ballot(hit && age == 1), mh = __ballot(hit), mm = __ballot(miss);
+    if (lane_id() == 0) {
+      if (m1) atomicAdd(&lage[1], __popcll(m1));
+      if (mh) atomicAdd(&lage[0], __popcll(mh));
+      wmiss[threadIdx.x >> 6] = __popcll(mm);
+    }
     if (hit && age > 1 && age < kAgeBins) atomicAdd(&lage[age], 1);
-    const uint64_t mh = __ballot(hit);
-    if (mh && lane_id() == 0) atomicAdd(&lage[0], __popcll(mh));
-    const int nmiss = block_sum(miss ? 1 : 0, smem);
-    const int csum = block_sum(cc, smem);
-    if (threadIdx.x == 0) { tile_miss[tile] = nmiss; tile_cnt[tile] = csum; }
+    lds_barrier();
+    if (threadIdx.x % kVidTile == 0 && tile * kVidTile < U) {
+      const int* const q = wmiss + sub * (kVidTile / kWave);
+      tile_miss[tile] = q[0] + q[1] + q[2] + q[3];
+    }
+    lds_barrier();
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < kAgeBins; i += 256)
+  for (int i = threadIdx.x; i < kAgeBins; i += kT)
     if (lage[i]) atomicAdd(&age_hist[i], lage[i]);
+}
+
+// Both read what the assign pass has left and neither what the other writes, so they are one launch: the first
+// nres blocks resolve, the others count.  us one after the other / in one launch: 1024 x 39 positions 5.3 + 6.6 /
+// 5.7, 8192 x 26 with the hashed index 7.5 + 8.5 / 10.1, 16384 x 39 16.3 + 15.6 / 22.1, 65536 x 39 33.3 + 17.6 / 45.8,
+// 1.28e6 uniform ones 26.7 + 60.8 / 77.5, 8.9e6 in bags 146 + 48 / 178: what is saved is start-up and drain, the random
+// accesses of the two add up.  Where the unique passes have a stream of their own, they are launched apart:
+// nres = 0, or a grid of nres blocks.
+struct RankArgs {
+  const int* hslot; const int* uvid; int n; int* inverse; int* cnt; int* cnt_rep; int nrep; int* rank; unsigned* first;
+};
+struct ResolveArgs {
+  const int64_t* unique_ids; const int* vid_hslot; uint64_t* utab; int wide;
+  const IdxEntry* index; uint32_t hi; const int* dmap; int *stamp, *hist; int t;
+  int *slot, *tile_miss, *age_hist; Ctr* ctr; const Ctr* prev; const int* n_unique; int* n_invalid;
+};
+template <int kPer, int kT>
+__global__ __launch_bounds__(kT) void k_rank_resolve(const RankArgs a, const ResolveArgs b, int nres) {
+  __shared__ int lds[kHotBins];
+  static_assert(kHotBins >= kAgeBins + kT / kWave, "the LDS of the counting blocks holds that of the resolving ones");
+  if ((int)blockIdx.x < nres)
+    resolve_ids<kT>(b.unique_ids, b.vid_hslot, b.utab, b.wide, b.index, b.hi, b.dmap, b.stamp, b.hist, b.t, b.slot,
+                    b.tile_miss, b.age_hist, b.ctr, b.prev, b.n_unique, b.n_invalid, (int)blockIdx.x, nres, lds);
+  else
+    count_positions<kPer, kT>(a.hslot, a.uvid, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, a.first,
+                              (int)blockIdx.x - nres, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -811,53 +855,86 @@ __device__ __forceinline__ void plan_store(const Plan& pl, Ctr& ctr, int f) {
   ctr.oldest = pl.oldest;
 }
 
-// Plan (one block): scan the per-tile miss and position counts, then decide the victims.
-__global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* tile_cnt,
-                                               int* __restrict__ age_hist,
+// Plan (the first block): scan the per-tile miss counts, then decide the victims.  It is a chain of a few dependent
+// loads and scans on one compute unit; beside it the next `folds` blocks add up the positions of every virtual id
+// (the copies of a hot bin, see count_positions) and of every tile, and the blocks behind those find the bags of
+// the positions (multi-hot input): neither needs the plan.  us of plan and bags one after the other / this way, 291e3
+// ids in bags 4.6 + 4.8 / 4.8, 8.9e6 12.8 + 17.0 / 18.8; plan alone at 1024 x 39 ids 6.2 / 3.5, 65536 x 39 8.8 / 6.2.
+constexpr int kFoldBlocks = 64;
+struct FoldArgs { int* cnt; const int* cnt_rep; int bins, nrep; int* tile_cnt; int folds; };
+struct BagArgs { const int64_t* offsets; int n_bags, n; int* pos2bag; };
+
+__global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* __restrict__ age_hist,
                                                int* __restrict__ tile_reuse, int* hist, int t,
-                                               int lookahead, int C, uint32_t hi, Ctr* ctr) {
+                                               int lookahead, int C, uint32_t hi, int dense, Ctr* ctr,
+                                               const FoldArgs fo, const BagArgs bags) {
   static_assert(kAgeBins == 1024, "one thread per age bin");
   __shared__ int smem[20];
   __shared__ int s_found;
-  // every thread reads the counters here; thread 0 overwrites them only after the last barrier
+  __shared__ int words[1024];
+  if ((int)blockIdx.x > fo.folds) {
+    bags_of_positions(bags.offsets, bags.n_bags, bags.n, bags.pos2bag, ctr, (int)blockIdx.x - fo.folds - 1, words);
+    return;
+  }
   const int U = ctr->U;
-  const int f = ctr->f;
+  if (blockIdx.x > 0) {
+    constexpr int kTiles = 1024 / kVidTile;
+    const int sub = (int)threadIdx.x / kVidTile;
+    for (int tile0 = ((int)blockIdx.x - 1) * kTiles; tile0 * kVidTile < U; tile0 += fo.folds * kTiles) {
+      const int tile = tile0 + sub, v = tile * kVidTile + (int)threadIdx.x % kVidTile;
+      int c = 0;
+      if (v < U) {
+        if (v < fo.bins) {
+#pragma unroll 8
+          for (int r = 0; r < fo.nrep; ++r) c += fo.cnt_rep[r * kHotBins + v];
+          fo.cnt[v] = c;
+        } else {
+          c = fo.cnt[v];
+        }
+      }
+      c = wave_sum(c);
+      if (lane_id() == 0) words[threadIdx.x >> 6] = c;
+      lds_barrier();
+      if (threadIdx.x % kVidTile == 0 && tile * kVidTile < U) {
+        const int* const q = words + sub * (kVidTile / kWave);
+        fo.tile_cnt[tile] = q[0] + q[1] + q[2] + q[3];
+      }
+      lds_barrier();
+    }
+    return;
+  }
+  // every thread reads the counters here; thread 0 overwrites them only after the last barrier
+  const int f = ctr->f, oldest = ctr->oldest;
   const int ntiles = (U + kVidTile - 1) / kVidTile;
+  const int a = (int)threadIdx.x;
+  const int x0 = a < ntiles ? tile_miss[a] : 0;
+  const int sum = age_hist[a];
   // deleted index entries that the previous step's miss assignment took back into use
   int reuse = 0;
-  const int reuse_tiles = (ctr->U_prev + kVidTile - 1) / kVidTile;
-  for (int i = (int)threadIdx.x; i < reuse_tiles; i += 1024) { reuse += tile_reuse[i]; tile_reuse[i] = 0; }
-  reuse = block_sum(reuse, smem);
+  if (!dense) {
+    const int reuse_tiles = (ctr->U_prev + kVidTile - 1) / kVidTile;
+    for (int i = a; i < reuse_tiles; i += 1024) { reuse += tile_reuse[i]; tile_reuse[i] = 0; }
+    reuse = block_sum(reuse, smem);
+  }
   // hits by age: thread a owns age a.  hist[t] gains the hits, hist[t - a] loses its share.
-  {
-    const int a = (int)threadIdx.x;
-    const int sum = age_hist[a];
+  if (sum) {
     age_hist[a] = 0;
     if (a == 0) { hist[t] += sum; ctr->n_hit = sum; }
-    else if (sum) hist[t - a] -= sum;
+    else hist[t - a] -= sum;
   }
-  __syncthreads();
   int carry = 0;
   for (int b = 0; b < ntiles; b += 1024) {
-    const int i = b + (int)threadIdx.x;
-    const int x = i < ntiles ? tile_miss[i] : 0;
+    const int i = b + a;
+    const int x = b == 0 ? x0 : i < ntiles ? tile_miss[i] : 0;
     int tot;
     const int e = block_excl_scan(x, tot, smem);
     if (i < ntiles) tile_miss[i] = carry + e;
     carry += tot;
   }
   const int M = carry;
-  carry = 0;
-  for (int b = 0; b < ntiles; b += 1024) {
-    const int i = b + (int)threadIdx.x;
-    const int x = i < ntiles ? tile_cnt[i] : 0;
-    int tot;
-    const int e = block_excl_scan(x, tot, smem);
-    if (i < ntiles) tile_cnt[i] = carry + e;
-    carry += tot;
-  }
+  __syncthreads();                             // the histogram's words are written
   Plan pl;
-  plan_decide<false>(pl, M, f, ctr->oldest, hist, t, lookahead, C, smem, &s_found);
+  plan_decide<false>(pl, M, f, oldest, hist, t, lookahead, C, smem, &s_found);
   __syncthreads();
   if (threadIdx.x == 0) {
     if (pl.need > 0 && pl.r > 0) hist[pl.T] -= pl.r;
@@ -908,8 +985,8 @@ __global__ __launch_bounds__(256) void k_victim_write(const int* __restrict__ st
                                                        const int* __restrict__ tile_lt,
                                                        const int* __restrict__ tile_eq,
                                                        int* __restrict__ victim_slot,
-                                                       int64_t* __restrict__ victim_id, Ctr* ctr,
-                                                       int* __restrict__ dmap) {
+                                                       int64_t* victim_id, Ctr* ctr,
+                                                       int* __restrict__ dmap, IdxEntry* index, uint32_t hi) {
   __shared__ int smem[20];
   if (ctr->K == 0) return;
   const int f = ctr->f_old, T = ctr->T, r = ctr->r, K = ctr->K;
@@ -970,26 +1047,28 @@ __global__ __launch_bounds__(256) void k_victim_write(const int* __restrict__ st
         victim_slot[idx[j]] = base + j; victim_id[idx[j]] = vid8[j];
         if (dmap) dmap[vid8[j]] = -1;          // dense index: the victim leaves it here, one store
       }
+    if (!dmap) {
+      // hashed index: the tile's victims stand side by side in the list; a thread per victim looks its id up and
+      // deletes it.  The inserts are in the next kernel and must stay there: with deletions and inserts in one
+      // kernel a resident id went missing from the index about once in a hundred steps at the target
+      // size (plain stores and memory-side atomics on neighbouring entries of one line from different
+      // XCDs); separated, and with every write to the index of a kernel that also uses atomics on it made an
+      // atomic itself, it has not been seen again.
+      const int k0 = pre_lt + (pre_eq < r ? pre_eq : r);
+      const int eq_end = pre_eq + (tot & 0xffff);
+      int k1 = pre_lt + (tot >> 16) + (eq_end < r ? eq_end : r);
+      if (k1 > K) k1 = K;
+      __syncthreads();
+      for (int k = k0 + (int)threadIdx.x; k < k1; k += 256) {
+        uint32_t where;
+        if (index_find(index, hi, victim_id[k], &where, ctr) >= 0)
+          atomicExch((unsigned long long*)&index[where].key, (unsigned long long)kTomb);
+        else
+          flag_err(ctr, 3);
+      }
+    }
   }
-  // hashed index: the victims are deleted by the next pass (k_victim_unmap)
   if (!dmap && blockIdx.x == 0 && threadIdx.x == 0) atomicAdd(&ctr->tomb, ctr->K);
-}
-
-// The victims leave the index: one thread per victim.  A kernel of its own, before the inserts:
-// with deletions and inserts in one kernel a resident id went missing from the index about once in
-// a hundred steps at the target size (plain stores and memory-side atomics on neighbouring
-// entries of one line from different XCDs); separated, and with every write to the index of a
-// kernel that also uses atomics on it made an atomic itself, it has not been seen again.
-__global__ __launch_bounds__(256) void k_victim_unmap(const int64_t* __restrict__ victim_id,
-                                                       IdxEntry* index, uint32_t hi, Ctr* ctr) {
-  const int K = ctr->K;
-  for (int k = blockIdx.x * 256 + (int)threadIdx.x; k < K; k += gridDim.x * 256) {
-    uint32_t where;
-    if (index_find(index, hi, victim_id[k], &where, ctr) >= 0)
-      atomicExch((unsigned long long*)&index[where].key, (unsigned long long)kTomb);
-    else
-      flag_err(ctr, 3);
-  }
 }
 
 // The step's counters, final since the plan, into the Host status block: one 64-bit store by each of the
@@ -1013,7 +1092,7 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
                                                         const int* __restrict__ cnt,
                                                         int* __restrict__ cnt_rep,
                                                         int* __restrict__ cur_rep, int bins, int nrep,
-                                                        const int* __restrict__ tile_coff,
+                                                        const int* __restrict__ tile_cnt,
                                                         int64_t* __restrict__ grp,
                                                         int2* __restrict__ cold_pay,
                                                         const int* __restrict__ tile_moff,
@@ -1031,13 +1110,18 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   const int free_slots = C - f;
   if (blockIdx.x == gridDim.x - 1)
     publish(ctr->hstat, (int)threadIdx.x, t, U, ctr->n_hit, ctr->M, K, ctr->n_bypass, ctr->n_invalid, ctr->bad_offsets);
+  // positions of the tiles before this block's current one, carried on from tile to tile
+  int before = 0, summed = 0;
   for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
     const int v = tile * kVidTile + (int)threadIdx.x;
     const bool miss = v < U && slot_out[v] == kMissMark;
-    int tot;
+    int tot, more = 0;
+    for (int i = summed + (int)threadIdx.x; i < tile; i += 256) more += tile_cnt[i];
+    before += block_sum(more, smem);
+    summed = tile;
     // start of the group of virtual id v in perm64 = exclusive scan of cnt
     const int nv = v < U ? cnt[v] : 0;
-    const int off = block_excl_scan(nv, tot, smem) + tile_coff[tile];
+    const int off = block_excl_scan(nv, tot, smem) + before;
     if (v < U) {
       grp[v] = ((int64_t)nv << 32) | (uint32_t)off;
       cold_pay[v] = make_int2(-1, -1);          // the grouping pass fills in the cold groups' rows
@@ -1114,7 +1198,7 @@ struct SmallArgs {
   int64_t* unique_ids; int* inverse; int* slot; int* miss_vids;      // caller's buffers of the step
   const IdxEntry* index; uint32_t hi; int* dmap;
   int* stamp; int64_t* slot_id; int* hist; int t, lookahead, C, boff;
-  int *cnt, *tile_miss, *tile_cnt, *age_hist;                        // outputs of the short form
+  int *cnt, *tile_miss, *age_hist;                                   // outputs of the short form
   int64_t* grp; int2* cold_pay; int64_t* perm64; int* pos_slot;
   int* victim_slot; int64_t* victim_id; int* miss_row; int64_t* miss_id;
   Ctr* ctr; const Ctr* prev;                // prev: nullptr when k_ctr_init has started the counters
@@ -1312,7 +1396,7 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
       rr[j] = atomicAdd(&cntl[vv[j]], 1);
     }
   }
-  // hits move to the step's stamp; their old ones by age, as k_resolve does it
+  // hits move to the step's stamp; their old ones by age, as resolve_ids does it
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const bool hit = hitm & (1u << j);
@@ -1341,10 +1425,10 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
     a.age_hist[tid] = tid ? age[tid] : n_hit;
     const int w = tid >> 6;
     for (int tile = w; tile * kVidTile < U; tile += 16) {    // a wavefront per tile of kVidTile virtual ids
-      int m = 0, q = 0;
-      for (int v = tile * kVidTile + lane; v < U && v < (tile + 1) * kVidTile; v += kWave) { m += slotl[v]; q += cntl[v]; }
-      m = wave_sum(m); q = wave_sum(q);
-      if (lane == 0) { a.tile_miss[tile] = m; a.tile_cnt[tile] = q; }
+      int m = 0;
+      for (int v = tile * kVidTile + lane; v < U && v < (tile + 1) * kVidTile; v += kWave) m += slotl[v];
+      m = wave_sum(m);
+      if (lane == 0) a.tile_miss[tile] = m;
     }
     if (tid == 0) {
       Ctr c0 = *was;
@@ -1375,7 +1459,7 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
     }
     Plan pl;
     plan_decide<true>(pl, M, f, oldest, a.hist, a.t, a.lookahead, C, smem, &s_found);
-    // bag of every position, checked as k_pos2bag does
+    // bag of every position, checked as bags_of_positions does
     if (a.offsets) {
       int bad = 0;
       for (int b = tid; b < a.n_bags; b += 1024) {
