@@ -63,10 +63,18 @@ struct HostRows {
 // 512-byte rows 18e3 234 / 264, 57e3 693 / 695, 93e3 1100 / 1112, 172e3 2005 / 1996, 212e3 2470 / 2457;
 // 960-byte rows 17.5e3 445 / 460, 46e3 1109 / 1120, 86e3 2015 / 2012, 144e3 3354 / 3337; 6.9e3 of 256 bytes
 // 67 / 65.  So the upper end is both a number of rows (kSplitMax) and of bytes (kSplitMaxBytes).
+// What is in flight on the link decides the rest, and more is not better: a pass of 16384 x 39 / 65536 x 39 / 5003 x
+// 39 with Adam, us, with kSplitFly 1 for the reads 375 / 694 / 648, 2 378 / 698 / 645, 4 382 / 702 / 654, 8 398 / 733 /
+// 690, 2 both ways 377 / 696 / 640; 24 writers 379 / 700 / 643, 40 377 / 697 / 647; 192 readers (4 in flight) 394 /
+// 719 / 668, 256 442 / 813 / 797; all writers on one XCD 457 / 847 / 885, on two 419 / 795 / 803.  A link that reads
+// and writes rows at random at once reaches 70 to 76 GB/s both ways together for 128-byte rows (its reads alone 40),
+// 88 for 256 bytes, 84 for 960, 97 for the copy engines on large blocks; the order of the rows changes nothing.
+// The staging goes beside the grouping pass, not in front of it: copies that start before that pass has ended hold
+// up its writes (37 -> 332 us at 65536 x 39) and are held up (368 -> 422).
 constexpr int kSplitMin = 1 << 14;
 constexpr int kSplitMax = 1 << 18;
 constexpr unsigned kSplitMaxBytes = 64u << 20;
-constexpr int kSplitWriters = 32, kSplitReaders = 128;
+constexpr int kSplitWriters = 32, kSplitReaders = 128, kSplitFly = 2;
 // M misses, K victims, both loaded together (one after the other they cost the copies 2 us); w2: 16-byte chunks
 // of a row and its state
 __device__ __forceinline__ bool split_swap(int M, int K, int w2) {
@@ -89,18 +97,18 @@ __global__ __launch_bounds__(256) void k_stage_victims(const int* __restrict__ v
   }
 }
 
-// One direction: rows list[k] (k < count) of the Host table and rows row(k) of the cache, four chunks of a
-// lane in flight.
+// One direction: rows list[k] (k < count) of the Host table and rows row(k) of the cache, kSplitFly chunks
+// of a lane in flight.
 template <bool kToHost, class Row>
 __device__ __forceinline__ void link_rows(const int64_t* __restrict__ list, Row row, int count, float4* cw,
                                           float4* ca, const HostRows& h, int d4, int s4, int blk, int nblk) {
   const unsigned w2 = (unsigned)(d4 + s4), total = (unsigned)count * w2, stride = (unsigned)nblk * 256;
-  for (unsigned i0 = (unsigned)blk * 256 + threadIdx.x; i0 < total; i0 += 4 * stride) {
-    int64_t at[4], hat[4];                  // chunk in the cache array, chunk in the Host array
-    bool on[4], state[4];
-    vf4 v[4];
+  for (unsigned i0 = (unsigned)blk * 256 + threadIdx.x; i0 < total; i0 += kSplitFly * stride) {
+    int64_t at[kSplitFly], hat[kSplitFly];                  // chunk in the cache array, chunk in the Host array
+    bool on[kSplitFly], state[kSplitFly];
+    vf4 v[kSplitFly];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < kSplitFly; ++u) {
       const unsigned i = i0 + u * stride;
       on[u] = i < total;
       const unsigned k = on[u] ? i / w2 : 0;
@@ -111,13 +119,13 @@ __device__ __forceinline__ void link_rows(const int64_t* __restrict__ list, Row 
       hat[u] = state[u] ? id * h.has4 + (c - d4) : id * h.hs4 + c;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < kSplitFly; ++u)
       if (on[u]) {
         const float4* const from = kToHost ? (state[u] ? ca : cw) : (state[u] ? h.a : h.w);
         v[u] = *reinterpret_cast<const vf4*>(&from[kToHost ? at[u] : hat[u]]);
       }
 #pragma unroll
-    for (int u = 0; u < 4; ++u)
+    for (int u = 0; u < kSplitFly; ++u)
       if (on[u]) {
         float4* const to = kToHost ? (state[u] ? h.a : h.w) : (state[u] ? ca : cw);
         *reinterpret_cast<vf4*>(&to[kToHost ? hat[u] : at[u]]) = v[u];
