@@ -41,6 +41,8 @@ constexpr int kVidTile = 256;     // virtual ids per tile in resolve / assign
 // frequent keys in the table with a smaller position than theirs.  (Nothing depends on the sleep being
 // long enough.)  us without the sleep / with the head in a launch of its own / this way: 58 / 35 / 29 at
 // 16384 x 39 positions, 80 / 47 / 42 at 65536 x 39, 30 / 28 / 20 at 5003 x 39, 95 / 109 / 98 at 1.28e6 uniform ones.
+// Fewer, larger blocks contend less and take as long (512 / 1024 / 2048 positions, 256 / 512 / 1024 threads, us a pass:
+// 5003 x 39 640 / 641 / 637, 16384 x 39 377 / 377 / 378, 65536 x 39 694 / 699 / 705, 8.9e6 in bags 1194 / 1200 / 1217).
 // hslot[p] = HBM table entry of position p.
 // first: one bit per position, set for the positions that hold their entry's smallest position in the
 // end, all zero before.  Whoever places a position in an entry flips its bit, and whoever replaces one
@@ -51,7 +53,7 @@ constexpr int kUniqChunk = 512;    // positions per block (2048 with its 53 KB o
 constexpr int kUniqPer = kUniqChunk / 256;
 constexpr int kLdsPer = 2 * kUniqChunk / 256;
 constexpr int kHeadBlocks = 64;    // blocks that go to the table at once
-constexpr int kHeadMin = 256;      // a grid of at most this many blocks does not sleep: 16 us either way at 78 blocks
+constexpr int kHeadMin = 256;      // a grid of at most this many blocks does not sleep, and claims without a load first (12.5 against 15.3 us at 78)
 constexpr int kResidentBlocks = 2048;        // eight per compute unit
 constexpr int kHeadSleep = 5;      // times 2048 clocks, 4.3 us (3 / 5 / 7 / 10: 30 / 28.7 / 29 / 31 us at 16384 x 39)
 constexpr int kLdsTab = 2 * kUniqChunk;      // LDS table entries per block
@@ -207,12 +209,13 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
     for (int i = 0; i < kHeadSleep; ++i) __builtin_amdgcn_s_sleep(32);
   // distinct keys of the block -> HBM table, kFly per thread in flight
   constexpr int kFly = kUniqPer;
+  const bool all_claim = blocks <= kHeadMin;        // no load first: the table is empty for all of them
   {
     int e[kFly], pm[kFly];
     int64_t key[kFly];
     uint32_t h[kFly];
     typename Tab::Raw r[kFly];
-    bool mine[kFly];
+    bool mine[kFly], fresh[kFly];             // fresh: r has just come from the memory side
 #pragma unroll
     for (int u = 0; u < kFly; ++u) {
       const int i = (int)threadIdx.x + u * 256;
@@ -223,15 +226,17 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
         key[u] = lkey[e[u]];
         pm[u] = lval[e[u]];
         h[u] = bucket_of(key[u], hu);
-        r[u] = tab.load(h[u]);
+        if (!all_claim) r[u] = tab.load(h[u]);
       }
+      fresh[u] = false;
     }
     // first probe: where the plain load saw an empty entry, try to claim it; all in flight
 #pragma unroll
     for (int u = 0; u < kFly; ++u)
-      if (e[u] >= 0 && tab.empty(r[u])) {
+      if (e[u] >= 0 && (all_claim || tab.empty(r[u]))) {
         r[u] = tab.claim(h[u], key[u], pm[u]);
         mine[u] = tab.empty(r[u]);
+        fresh[u] = Tab::kClaimStoresPos;
       }
 #pragma unroll
     for (int u = 0; u < kFly; ++u) {
@@ -240,6 +245,7 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
       for (uint32_t probes = 0; probes < hu; ++probes) {
         h[u] = h[u] + 1 == hu ? 0 : h[u] + 1;
         r[u] = tab.coherent(h[u]);
+        fresh[u] = true;
         if (tab.same(r[u], key[u])) break;
         if (tab.empty(r[u])) {
           r[u] = tab.claim(h[u], key[u], pm[u]);
@@ -248,12 +254,13 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
         }
       }
     }
-    // a plain load may be stale (too large), never too small: ask the memory side before the atomic
+    // a plain load may be stale (too large), never too small: ask the memory side before the atomic, where what is
+    // known did not come from there just now (a claim that failed)
     bool low[kFly];
 #pragma unroll
     for (int u = 0; u < kFly; ++u) {
       low[u] = e[u] >= 0 && (mine[u] ? !Tab::kClaimStoresPos : tab.pos(r[u]) > pm[u]);
-      if (low[u] && !mine[u]) r[u] = tab.coherent(h[u]);
+      if (low[u] && !mine[u] && !fresh[u]) r[u] = tab.coherent(h[u]);
     }
 #pragma unroll
     for (int u = 0; u < kFly; ++u) {
