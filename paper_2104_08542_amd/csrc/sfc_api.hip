@@ -1045,7 +1045,9 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   int n_slots = 0;
   // Adagrad and Adam: the update kernel sums the cold groups and chains the block-edge partials itself
   const bool fused = c->cfg.optimizer == SFC_OPT_ADAGRAD || c->cfg.optimizer == SFC_OPT_ADAM;
-  if ((rc = seg_launch(c, x, d_grad, c->gsum, c->bp, c->bp_vid, true, fused, &n_slots))) return rc;
+  // a small batch in one kernel; the groups of a step are kept until the next prepare only, so not pipelined
+  const bool groups = fused && c->nctx == 1 && small_update(x->n_ids, c->d4);
+  if (!groups && (rc = seg_launch(c, x, d_grad, c->gsum, c->bp, c->bp_vid, true, fused, &n_slots))) return rc;
   if (c->cfg.policy == SFC_POLICY_PREFETCH) {
     // the copies of a newer step issued so far read the Host table before this update writes it
     for (int k = 0; k < c->nctx; ++k) {
@@ -1058,7 +1060,14 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   // the stream above passed over the cold groups and left the block-edge partials unchained:
   // the fused kernels sum both themselves (their first blocks chain the partials, a lane group per slot)
   const int n_edge = edge_blocks(n_slots, c->d4);
-  if (c->cfg.optimizer == SFC_OPT_ADAGRAD) {
+  const dim3 gg(groups ? (unsigned)grid_for(x->n_ids, kGroupShort, 512) : 1u);
+  if (c->cfg.optimizer == SFC_OPT_ADAGRAD && groups) {
+    AdagradOp op;
+    op.lr = c->cfg.lr; op.eps = c->cfg.eps;
+    LAUNCH_TIMED(c, P_ADAGRAD, true, k_update_groups<AdagradOp>, gg, dim3(kGroupThreads), s, op, (const int64_t*)c->grp,
+                 (const int64_t*)x->perm64, (const float4*)d_grad, (const int*)x->d_slot, (const int64_t*)x->d_unique,
+                 (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->d4, (const Ctr*)x->ctr);
+  } else if (c->cfg.optimizer == SFC_OPT_ADAGRAD) {
     auto kern = x->d_offsets ? k_adagrad_rows<false> : k_adagrad_rows<true>;
     LAUNCH_TIMED(c, P_ADAGRAD, true, kern, dim3(ug.x + (unsigned)n_edge), dim3(256), s, (const float4*)c->gsum,
                  (const int*)x->d_slot, (const int64_t*)x->d_unique, (float4*)c->cw, (float4*)c->ca,
@@ -1073,8 +1082,14 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
     k.bc1 = (float)(1.0 - pow(c->cfg.beta1, (double)x->t));
     k.bc2 = (float)(1.0 - pow(c->cfg.beta2, (double)x->t));
     k.lr = c->cfg.lr; k.eps = c->cfg.eps;
+    AdamOp op;
+    op.k = k;
     auto kern = x->d_offsets ? k_adam_rows<false> : k_adam_rows<true>;
-    LAUNCH_TIMED(c, P_ADAGRAD, true, kern, dim3(ug.x + (unsigned)n_edge), dim3(256), s, (const float4*)c->gsum,
+    if (groups)
+      LAUNCH_TIMED(c, P_ADAGRAD, true, k_update_groups<AdamOp>, gg, dim3(kGroupThreads), s, op, (const int64_t*)c->grp,
+                   (const int64_t*)x->perm64, (const float4*)d_grad, (const int*)x->d_slot, (const int64_t*)x->d_unique,
+                   (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->d4, (const Ctr*)x->ctr);
+    else LAUNCH_TIMED(c, P_ADAGRAD, true, kern, dim3(ug.x + (unsigned)n_edge), dim3(256), s, (const float4*)c->gsum,
                  (const int*)x->d_slot, (const int64_t*)x->d_unique, (float4*)c->cw, (float4*)c->ca,
                  c->host, (int)c->C, x->boff, k, c->d4, (const Ctr*)x->ctr,
                  (const int2*)x->cold_pay, (const float4*)d_grad, (const double*)c->bp,

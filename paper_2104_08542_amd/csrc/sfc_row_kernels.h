@@ -1090,6 +1090,136 @@ __global__ __launch_bounds__(256) void k_adam_rows(
 }
 
 // ---------------------------------------------------------------------------------------------
+// The whole update of a small batch (small_update, lookahead 0), one launch: a lane group per virtual id
+// reads the id's group, sums its gradient rows in fp64 in the order of the grouping and updates the row.
+// Nothing here is many bytes; the stream and the row kernel took their time in start-up, chains of
+// partial sums and the dependent loads of two kernels.  An id with more than kGroupShort positions is left to
+// the whole block, its lane groups each a strided share in fixed order, combined in a tree; there is a block per
+// kGroupShort positions, and a block's ids lie as far apart as the grid allows, because the frequent ids of a batch
+// are among its first ones (with a block's worth of lane groups per block, 100 ids of 12 to 50 positions each came
+// to one or two blocks, one after the other: 278 us at 5000 positions of dim 16, 9 this way).
+// One block sums an id however frequent it is, so what bounds a batch of one id alone is the rate at which one
+// compute unit loads gradient rows, 130 GB/s, and the limit on the size is the bytes that take 5 us (and a cap
+// where short rows would make the grid long).  sfc_backward_update us, stream and row kernel / this way, power-law
+// ids, half of the positions one id, all of them one id, all distinct: 2048 positions of dim 16 16.0 / 10.6, 15.7 / 10.6,
+// 14.9 / 10.0, 12.4 / 6.4; 5000 of dim 16 16.0 / 11.2, 15.8 / 12.8, 16.4 / 13.3, 12.7 / 9.2; 5000 of dim 32 16.3 / 12.6,
+// 14.9 / 15.0, 15.2 / 17.5, 12.8 / 9.2; 2048 of dim 80 15.3 / 12.4, 14.4 / 14.8, 14.4 / 18.2, 12.7 / 7.3; 1250 of dim 128
+// 15.1 / 11.9, 13.5 / 13.9, 13.8 / 17.0, 12.8 / 7.1; 16384 of dim 4 27.1 / 15.1, 26.8 / 12.4, 27.6 / 12.8, 13.8 / 9.9; beyond the
+// limit 8192 of dim 32 17.8 / 18.1, 15.2 / 17.8, 15.3 / 26.9, 14.4 / 9.2.
+// ---------------------------------------------------------------------------------------------
+constexpr int64_t kSmallUpdate = 1 << 14, kSmallUpdateChunks = 40 << 10;      // positions; 16-byte chunks of their rows
+inline bool small_update(int64_t n, int d4) { return n > 0 && n <= kSmallUpdate && n * d4 <= kSmallUpdateChunks; }
+constexpr int kGroupShort = 16;
+constexpr int kGroupThreads = 1024;
+inline __host__ __device__ int update_groups(int d4) { return kGroupThreads / 64 * (64 / d4 > 0 ? 64 / d4 : 1); }
+
+template <class Op>
+__global__ __launch_bounds__(kGroupThreads) void k_update_groups(
+    const Op op, const int64_t* __restrict__ grp, const int64_t* __restrict__ perm64,
+    const float4* __restrict__ grad, const int* __restrict__ slot, const int64_t* __restrict__ unique_ids,
+    float4* __restrict__ cw, float4* __restrict__ cs, HostRows h, int C, int boff, int d4, const Ctr* ctr) {
+  constexpr int kP = Op::kParts, kFly = 8;
+  __shared__ double red[kGroupThreads * 4];
+  __shared__ int long_v[kGroupThreads], n_long;
+  if (threadIdx.x == 0) n_long = 0;
+  __syncthreads();
+  const int U = ctr->U, groups = update_groups(d4), G = groups / (kGroupThreads / 64);
+  const int nblk = (int)gridDim.x < U ? (int)gridDim.x : U;        // blocks that have work
+  if ((int)blockIdx.x >= nblk) return;
+  const int lane = lane_id(), g = lane / d4, c4 = lane - g * d4;
+  const int gi = (int)(threadIdx.x >> 6) * G + g;         // this lane group among the block's
+  const bool active = g < G;
+  const int v = (int)blockIdx.x + gi * nblk;
+
+  // the row of virtual id `id` with the sum s: weights and state are on their way before the sum is there
+  auto apply = [&](int id, int sl, float4 w, float4 (&st)[kP], const D4& s) {
+    const int64_t row = sl >= C ? sl + boff : sl;
+    op.apply(w, st, d4_round(s));
+    cw[row * d4 + c4] = w;
+#pragma unroll
+    for (int p = 0; p < kP; ++p) cs[row * (kP * d4) + p * d4 + c4] = st[p];
+    if (sl >= C) {
+      const int64_t host = unique_ids[id];
+      h.w[host * h.hs4 + c4] = w;
+#pragma unroll
+      for (int p = 0; p < kP; ++p) h.a[host * h.has4 + p * d4 + c4] = st[p];
+    }
+  };
+  auto load_row = [&](int sl, float4& w, float4 (&st)[kP]) {
+    const int64_t row = sl >= C ? sl + boff : sl;
+    w = cw[row * d4 + c4];
+#pragma unroll
+    for (int p = 0; p < kP; ++p) st[p] = cs[row * (kP * d4) + p * d4 + c4];
+  };
+  // entries first, first + step, ... below end
+  auto add_rows = [&](D4& s, int first, int end, int step) {
+    int64_t e[kFly];
+#pragma unroll
+    for (int u = 0; u < kFly; ++u) e[u] = first + u * step < end ? perm64[first + u * step] : (int64_t)-1;
+    for (int q = first; q < end; q += kFly * step) {
+      float4 x[kFly];
+      int64_t en[kFly];
+#pragma unroll
+      for (int u = 0; u < kFly; ++u)
+        if (e[u] >= 0) x[u] = grad[(int64_t)(uint32_t)e[u] * d4 + c4];
+#pragma unroll
+      for (int u = 0; u < kFly; ++u) {                    // the next round's entries meanwhile
+        const int qn = q + (kFly + u) * step;
+        en[u] = qn < end ? perm64[qn] : (int64_t)-1;
+      }
+#pragma unroll
+      for (int u = 0; u < kFly; ++u) {
+        if (e[u] >= 0) d4_add(s, x[u]);
+        e[u] = en[u];
+      }
+    }
+  };
+
+  if (active && v < U) {
+    const int64_t gr = grp[v];
+    const int sl = slot[v], cnt = (int)(gr >> 32), start = (int)gr;
+    if (sl >= 0) {
+      if (cnt > kGroupShort) {
+        if (c4 == 0) long_v[atomicAdd(&n_long, 1)] = v;
+      } else {
+        float4 w, st[kP];
+        load_row(sl, w, st);
+        D4 s; d4_zero(s);
+        add_rows(s, start, start + cnt, 1);
+        apply(v, sl, w, st, s);
+      }
+    }
+  }
+  __syncthreads();
+  const int nl = n_long;
+  for (int i = 0; i < nl; ++i) {
+    const int id = long_v[i];
+    const int64_t gr = grp[id];
+    const int sl = slot[id], cnt = (int)(gr >> 32), start = (int)gr;
+    float4 w, st[kP];
+    if (gi == 0 && active) load_row(sl, w, st);
+    D4 s; d4_zero(s);
+    if (active) add_rows(s, start + gi, start + cnt, groups);
+    double* const r = &red[(gi * d4 + c4) * 4];           // (groups * d4 <= kGroupThreads)
+    if (active) { r[0] = s.x; r[1] = s.y; r[2] = s.z; r[3] = s.w; }
+    int o = 1;
+    while (o < groups) o <<= 1;
+    for (o >>= 1; o > 0; o >>= 1) {
+      __syncthreads();
+      if (active && gi < o && gi + o < groups) {
+        const double* q = r + o * d4 * 4;
+        r[0] += q[0]; r[1] += q[1]; r[2] += q[2]; r[3] += q[3];
+      }
+    }
+    if (gi == 0 && active) {
+      s.x = r[0]; s.y = r[1]; s.z = r[2]; s.w = r[3];
+      apply(id, sl, w, st, s);
+    }
+    __syncthreads();
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
 // Row-wise Adagrad: one accumulator per row (first float of a one-chunk state),
 //   acc += mean_j(g_j^2) ; w_j -= lr * g_j / (sqrt(acc) + eps).
 // One thread per 16-byte chunk of a row as above; the d4 lanes of a row add their squares with

@@ -121,6 +121,26 @@ def test_medium_zipf_many_tiles(index_kind):
     p.finish(); p.close()
 
 
+@pytest.mark.parametrize("D,n,optimizer", [(4, 16384, "adagrad"), (4, 16385, "adam"), (16, 10240, "adam"),
+                                           (16, 10241, "adagrad"), (32, 5120, "adagrad"), (80, 2048, "adam"),
+                                           (128, 1280, "adagrad"), (256, 640, "adam"), (256, 641, "adagrad")])
+def test_updates_of_small_batches_up_to_their_limits(D, n, optimizer):
+    # the update of a small batch in one kernel and, one position more, in two: groups of 16 and 17 positions
+    # (one lane group, the whole block), one id alone, ids that are as frequent as each other, bags, bypass rows
+    V = 30_000
+    p = Pair(V, D, C=n // 2, max_ids=n, max_bags=n, optimizer=optimizer)
+    g = lambda m, t: si.grads(m, D, 83, t).numpy()
+    rng = np.random.default_rng(D)
+    p.step(np.resize(np.repeat(np.arange(n // 16), rng.integers(16, 18, n // 16)), n), g(n, 0))
+    p.step(np.full(n, 11), g(n, 1))
+    p.step(rng.integers(0, 100, n) * 7, g(n, 2))
+    p.step(rng.permutation(V)[:n], g(n, 3))                      # more distinct ids than slots
+    off = np.concatenate([[0], np.sort(rng.integers(0, n + 1, n // 5)), [n]])
+    p.step(si.zipf_ids(n, 1.1, V, 83, 4).numpy(), g(off.size - 1, 4), off)
+    p.step(np.where(rng.random(n) < 0.3, -1, rng.integers(0, V, n)), g(n, 5))
+    p.finish(); p.close()
+
+
 @pytest.mark.parametrize("D", [4, 8, 16, 64, 80, 128, 256])
 def test_row_widths(D):
     # every lane-group geometry of the row kernels (D/4 lanes per row, also a D that does not
