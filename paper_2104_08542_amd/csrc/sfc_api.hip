@@ -1064,10 +1064,12 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   EventPair ep{};
   if ((rc = prof_begin(c, P_BACKWARD, s, &ep))) return rc;
   int n_slots = 0;
-  // Adagrad and Adam: the update kernel sums the cold groups and chains the block-edge partials itself
-  const bool fused = c->cfg.optimizer == SFC_OPT_ADAGRAD || c->cfg.optimizer == SFC_OPT_ADAM;
+  // the update kernel sums the cold groups and chains the block-edge partials itself (row-wise Adagrad: where the
+  // lanes of a row share a wavefront)
+  const bool rowwise = c->cfg.optimizer == SFC_OPT_ROWWISE_ADAGRAD;
+  const bool fused = !rowwise || (c->d4 & (c->d4 - 1)) == 0;
   // a small batch in one kernel; the groups of a step are kept until the next prepare only, so not pipelined
-  const bool groups = fused && c->nctx == 1 && small_update(x->n_ids, c->d4);
+  const bool groups = !rowwise && c->nctx == 1 && small_update(x->n_ids, c->d4);
   if (!groups && (rc = seg_launch(c, x, d_grad, c->gsum, c->bp, c->bp_vid, true, fused, &n_slots))) return rc;
   if (c->cfg.policy == SFC_POLICY_PREFETCH) {
     // the copies of a newer step issued so far read the Host table before this update writes it
@@ -1115,12 +1117,18 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
                  c->host, (int)c->C, x->boff, k, c->d4, (const Ctr*)x->ctr,
                  (const int2*)x->cold_pay, (const float4*)d_grad, (const double*)c->bp,
                  (const int*)c->bp_vid, n_slots, n_edge);
+  } else if (fused) {
+    auto kern = x->d_offsets ? k_rowwise_adagrad_rows<false> : k_rowwise_adagrad_rows<true>;
+    LAUNCH_TIMED(c, P_ADAGRAD, true, kern, dim3(ug.x + (unsigned)n_edge), dim3(256), s, (const float4*)c->gsum,
+                 (const int*)x->d_slot, (const int64_t*)x->d_unique, (float4*)c->cw, (float4*)c->ca,
+                 c->host, (int)c->C, x->boff, c->cfg.lr, c->cfg.eps, c->d4, (const Ctr*)x->ctr,
+                 (const int2*)x->cold_pay, (const float4*)d_grad, (const double*)c->bp,
+                 (const int*)c->bp_vid, n_slots, n_edge);
   } else {
-    const int pow2 = (c->d4 & (c->d4 - 1)) == 0;
-    LAUNCH_TIMED(c, P_ADAGRAD, true, k_rowwise_adagrad_rows, ug, dim3(256), s,
+    LAUNCH_TIMED(c, P_ADAGRAD, true, k_rowwise_adagrad_any, ug, dim3(256), s,
                  (const float4*)c->gsum, (const int*)x->d_slot, (const int64_t*)x->d_unique,
                  (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->cfg.lr, c->cfg.eps,
-                 c->d4, pow2, (const Ctr*)x->ctr);
+                 c->d4, (const Ctr*)x->ctr);
   }
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_BACKWARD, s, &ep))) return rc;

@@ -1223,55 +1223,96 @@ __global__ __launch_bounds__(kGroupThreads) void k_update_groups(
 // Row-wise Adagrad: one accumulator per row (first float of a one-chunk state),
 //   acc += mean_j(g_j^2) ; w_j -= lr * g_j / (sqrt(acc) + eps).
 // One thread per 16-byte chunk of a row as above; the d4 lanes of a row add their squares with
-// shuffles when d4 is a power of two (a row then never straddles a wavefront).
+// shuffles when d4 is a power of two (a row then never straddles a wavefront).  Such rows take the path of the
+// element-wise optimizers: the stream passes over the cold groups and leaves its block-edge partials, both are summed
+// here (213e3 power-law positions of dim 128, us: stream 29.8 + finish 6.3 + rows 26.5 before, 22.5 + 21.4 this way; a pass of 8192 x 26 with lookahead 1 136.9 -> 126).
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_rowwise_adagrad_rows(const float4* __restrict__ common,
-                                                               const int* __restrict__ slot,
-                                                               const int64_t* __restrict__ unique_ids,
-                                                               float4* __restrict__ cw,
-                                                               float4* __restrict__ cs, HostRows h,
-                                                               int C, int boff, float lr, float eps,
-                                                               int d4, int pow2, const Ctr* ctr) {
-  const int64_t total = (int64_t)ctr->U * d4;
+__device__ __forceinline__ float sum_squares(float4 g, int d4) {
+  float ss = g.x * g.x + g.y * g.y + g.z * g.z + g.w * g.w;
+  for (int d = 1; d < d4; d <<= 1) ss += __shfl_xor(ss, d, kWave);
+  return ss;
+}
+
+// Widths that are no power of two: one thread per row (the lanes of a row could straddle two wavefronts, and
+// the accumulator must be read by all of them before one writes it), every sum from the common matrix.
+__global__ __launch_bounds__(256) void k_rowwise_adagrad_any(const float4* __restrict__ common,
+                                                              const int* __restrict__ slot,
+                                                              const int64_t* __restrict__ unique_ids,
+                                                              float4* __restrict__ cw,
+                                                              float4* __restrict__ cs, HostRows h,
+                                                              int C, int boff, float lr, float eps,
+                                                              int d4, const Ctr* ctr) {
   const int64_t stride = (int64_t)gridDim.x * 256;
   const float inv_d = 1.0f / (float)(4 * d4);
-  if (!pow2) {
-    // any other width: one thread per row (the lanes of a row could straddle two wavefronts, and
-    // the accumulator must be read by all of them before one writes it)
-    for (int64_t vrow = (int64_t)blockIdx.x * 256 + threadIdx.x; vrow < ctr->U; vrow += stride) {
-      const int sl = slot[vrow];
-      if (sl < 0) continue;
-      float ss = 0.f;
-      for (int j = 0; j < d4; ++j) {
-        const float4 q = common[vrow * d4 + j];
-        ss += q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
-      }
-      const int64_t row = sl >= C ? sl + boff : sl;
-      float4 st = cs[row];
-      st.x = st.x + ss * inv_d;
-      const float den = sqrtf(st.x) + eps;
-      const int64_t id = unique_ids[vrow];
-      for (int j = 0; j < d4; ++j) {
-        const float4 g = common[vrow * d4 + j];
-        float4 w = cw[row * d4 + j];
-        w.x = w.x - lr * g.x / den; w.y = w.y - lr * g.y / den;
-        w.z = w.z - lr * g.z / den; w.w = w.w - lr * g.w / den;
-        cw[row * d4 + j] = w;
-        if (sl >= C) h.w[id * h.hs4 + j] = w;
-      }
-      cs[row] = st;
-      if (sl >= C) h.a[id * h.has4] = st;
+  for (int64_t vrow = (int64_t)blockIdx.x * 256 + threadIdx.x; vrow < ctr->U; vrow += stride) {
+    const int sl = slot[vrow];
+    if (sl < 0) continue;
+    float ss = 0.f;
+    for (int j = 0; j < d4; ++j) {
+      const float4 q = common[vrow * d4 + j];
+      ss += q.x * q.x + q.y * q.y + q.z * q.z + q.w * q.w;
     }
+    const int64_t row = sl >= C ? sl + boff : sl;
+    float4 st = cs[row];
+    st.x = st.x + ss * inv_d;
+    const float den = sqrtf(st.x) + eps;
+    const int64_t id = unique_ids[vrow];
+    for (int j = 0; j < d4; ++j) {
+      const float4 g = common[vrow * d4 + j];
+      float4 w = cw[row * d4 + j];
+      w.x = w.x - lr * g.x / den; w.y = w.y - lr * g.y / den;
+      w.z = w.z - lr * g.z / den; w.w = w.w - lr * g.w / den;
+      cw[row * d4 + j] = w;
+      if (sl >= C) h.w[id * h.hs4 + j] = w;
+    }
+    cs[row] = st;
+    if (sl >= C) h.a[id * h.has4] = st;
+  }
+}
+
+template <bool kOneHot>
+__global__ __launch_bounds__(256) void k_rowwise_adagrad_rows(
+    const float4* __restrict__ common, const int* __restrict__ slot,
+    const int64_t* __restrict__ unique_ids, float4* __restrict__ cw, float4* __restrict__ cs,
+    HostRows h, int C, int boff, float lr, float eps, int d4, const Ctr* ctr,
+    const int2* __restrict__ cold_pay, const float4* __restrict__ grad,
+    const double* __restrict__ bp, const int* __restrict__ bp_vid, int nslots, int nedge) {
+  const float inv_d = 1.0f / (float)(4 * d4);
+  // chunk c of row `row` (bypass rows: of the Host row `id` as well), its gradient and the row's sum of squares
+  auto update = [&](int64_t row, int c, bool bypass, int64_t id, float4 w, float4 st, float4 g, float ss) {
+    const float acc = st.x + ss * inv_d;
+    const float den = sqrtf(acc) + eps;
+    w.x = w.x - lr * g.x / den; w.y = w.y - lr * g.y / den;
+    w.z = w.z - lr * g.z / den; w.w = w.w - lr * g.w / den;
+    cw[row * d4 + c] = w;
+    st.x = acc;
+    if (c == 0) cs[row] = st;
+    if (bypass) {
+      h.w[id * h.hs4 + c] = w;
+      if (c == 0) h.a[id * h.has4] = st;
+    }
+  };
+  if ((int)blockIdx.x < nedge) {
+    edge_block(bp, bp_vid, nslots, d4, (int)blockIdx.x, [&](int v, int c4, float4 g) {
+      const float ss = sum_squares(g, d4);     // the d4 lanes of the row are here together
+      const int sl = slot[v];
+      if (sl < 0) return;
+      const int64_t row = sl >= C ? sl + boff : sl;
+      const float4 st = cs[row];
+      update(row, c4, sl >= C, sl >= C ? unique_ids[v] : 0, cw[row * d4 + c4], st, g, ss);
+    });
     return;
   }
+  const int64_t total = (int64_t)ctr->U * d4;
+  const int64_t stride = (int64_t)((int)gridDim.x - nedge) * 256;
   // every lane of a wavefront runs the same number of iterations: the shuffles stay convergent.
-  // Four rows per thread in flight at each level (slot + gradient, then state + weights).
+  // Four rows per thread in flight at each level (slot and cold rows, then gradient, state and weights).
   const int64_t rounds = (total + 4 * stride - 1) / (4 * stride);
-  int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  int64_t i0 = (int64_t)((int)blockIdx.x - nedge) * 256 + threadIdx.x;
   for (int64_t it = 0; it < rounds; ++it, i0 += 4 * stride) {
     int vrow[4], c[4], sl[4];
-    float4 g[4], st[4], w[4];
-    float ss[4];
+    int2 cp[4];
+    float4 g[4], x1[4], st[4], w[4];
     int64_t row[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
@@ -1280,31 +1321,33 @@ __global__ __launch_bounds__(256) void k_rowwise_adagrad_rows(const float4* __re
       vrow[u] = live ? (int)(i / d4) : 0;
       c[u] = live ? (int)(i % d4) : 0;
       sl[u] = live ? slot[vrow[u]] : -1;
-      g[u] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (live) g[u] = common[i];
+      cp[u] = live ? cold_pay[vrow[u]] : make_int2(-1, -1);
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      ss[u] = g[u].x * g[u].x + g[u].y * g[u].y + g[u].z * g[u].z + g[u].w * g[u].w;
-      for (int d = 1; d < d4; d <<= 1) ss[u] += __shfl_xor(ss[u], d, kWave);
+      g[u] = x1[u] = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (cp[u].x == kEdgeMark) sl[u] = -1;    // updated by the block that chains its partials
       row[u] = sl[u] >= C ? sl[u] + boff : sl[u];
-      if (sl[u] >= 0) { st[u] = cs[row[u]]; w[u] = cw[row[u] * d4 + c[u]]; }
+      if (sl[u] < 0) continue;
+      st[u] = cs[row[u]]; w[u] = cw[row[u] * d4 + c[u]];
+      if (cp[u].x >= 0) {
+        g[u] = ld_row<kOneHot>(&grad[(int64_t)cp[u].x * d4 + c[u]]);
+        if (cp[u].y >= 0) x1[u] = ld_row<kOneHot>(&grad[(int64_t)cp[u].y * d4 + c[u]]);
+      } else {
+        g[u] = common[(int64_t)vrow[u] * d4 + c[u]];
+      }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (sl[u] < 0) continue;
-      const float acc = st[u].x + ss[u] * inv_d;
-      const float den = sqrtf(acc) + eps;
-      w[u].x = w[u].x - lr * g[u].x / den; w[u].y = w[u].y - lr * g[u].y / den;
-      w[u].z = w[u].z - lr * g[u].z / den; w[u].w = w[u].w - lr * g[u].w / den;
-      cw[row[u] * d4 + c[u]] = w[u];
-      st[u].x = acc;
-      if (c[u] == 0) cs[row[u]] = st[u];
-      if (sl[u] >= C) {
-        const int64_t id = unique_ids[vrow[u]];
-        h.w[id * h.hs4 + c[u]] = w[u];
-        if (c[u] == 0) h.a[id * h.has4] = st[u];
+      if (cp[u].x >= 0 && cp[u].y >= 0) {      // (two terms: the same sum in either order)
+        g[u].x = (float)((double)g[u].x + (double)x1[u].x);
+        g[u].y = (float)((double)g[u].y + (double)x1[u].y);
+        g[u].z = (float)((double)g[u].z + (double)x1[u].z);
+        g[u].w = (float)((double)g[u].w + (double)x1[u].w);
       }
+      const float ss = sum_squares(g[u], d4);
+      if (sl[u] >= 0)
+        update(row[u], c[u], sl[u] >= C, sl[u] >= C ? unique_ids[vrow[u]] : 0, w[u], st[u], g[u], ss);
     }
   }
 }
