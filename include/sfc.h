@@ -128,11 +128,12 @@ typedef struct {
   int64_t n_unique;   /* U: distinct ids of the batch (a null entry for out-of-range ids included) */
   int64_t n_hit;      /* unique ids already resident */
   int64_t n_miss;     /* unique ids fetched from Host (bypass rows included) */
-  int64_t n_evict;    /* resident rows written back to Host to make room */
+  int64_t n_evict;    /* resident rows that left the cache to make room (for sfc_fetch_misses to write back) */
   int64_t n_bypass;   /* misses that found no slot and live in a transient row for this step */
   int64_t n_invalid;  /* positions whose id was outside [0, V) */
   int64_t h2d_bytes;  /* Host->cache bytes of this step (rows + optimizer state) */
-  int64_t d2h_bytes;  /* cache->Host bytes of this step (victims + bypass rows) */
+  int64_t d2h_bytes;  /* cache->Host bytes of this step (victims + bypass rows; the victims of a cache that
+                         has never been updated count too, though nothing has to be written for them) */
   int64_t n_bad_offsets; /* violations found in d_offsets (0 for well-formed input) */
 } sfc_stats;
 
@@ -194,7 +195,8 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
 /*
  * Step 2 (Algorithm 1 lines 5-6): write every victim row and its optimizer state back to the Host
  * table and copy every missed row and its state from the Host table into its slot (a victim's row
- * is read before its slot is overwritten).  The copies come after all that `stream` and
+ * is read before its slot is overwritten).  As long as no sfc_backward_update has been called on the cache its rows
+ * are what the Host table holds, and victims are not written.  The copies come after all that `stream` and
  * `side_stream` have been given before this call.  They run on side_stream; with lookahead 0 those
  * of a step that moves about a megabyte or less run on `stream` instead (side_stream is then not
  * made to wait for them, which would cost more than they do).  `stream` is made to wait for the

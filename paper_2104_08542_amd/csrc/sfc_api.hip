@@ -180,6 +180,7 @@ struct sfc_cache {
   // steps
   StepCtx ctx[kMaxCtx];
   int t = 0;                                    // steps prepared so far
+  bool updated_once = false;                    // an update has been enqueued: resident rows may differ from the Host table's
   int last_prepared = -1;                       // context of the most recent sfc_prepare
   // profiling
   int prof = 0;                                 // 0 off, 1 step calls, 2 also the kernels inside them
@@ -374,6 +375,10 @@ bool swap_on_main(sfc_cache* c) {
   return false;
 }
 
+// Have the victims to be written to the Host table?  Not while no update has ever been enqueued on this cache: every
+// resident row is then as it was read.  (A graph may be launched when that has changed: what is recorded writes.)
+bool writes_back(const sfc_cache* c) { return c->updated_once || capturing(c->st); }
+
 // One launch of the Host<->cache copies of a step on stream s (see k_swap_rows for the two
 // launches of pipelined mode).
 int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
@@ -387,7 +392,8 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   const int swap_blocks = c->nctx == 1 || recent_bytes > kSwapWideBytes ? kSwapBlocksWide : kSwapBlocks;
   int blocks = grid_for(x->n_ids * (c->d4 + c->s4), 256, swap_blocks), staged_at = -1;
   // where victims are possible, and the copies have the side stream to themselves (see k_stage_victims)
-  if (c->nctx == 1 && !x->copies_on_main && c->C > 0 && c->C < c->V && x->n_ids >= kSplitMin) {
+  const bool write_back = writes_back(c);
+  if (c->nctx == 1 && !x->copies_on_main && write_back && c->C > 0 && c->C < c->V && x->n_ids >= kSplitMin) {
     staged_at = (int)c->C + x->boff;
     blocks = kSplitWriters + kSplitReaders;
     hipLaunchKernelGGL(k_stage_victims, dim3(1024), dim3(256), 0, s, x->victim_slot, (float4*)c->cw,
@@ -396,7 +402,8 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   const bool tells = !main_variant && s != c->st;
   LAUNCH_THEN(tells && !prof_on(c, P_FETCH) && !capturing(s), x->ev_fetched, k_swap_rows, dim3(blocks), dim3(256), s,
               x->miss_row, x->miss_id, x->victim_id, (float4*)c->cw, (float4*)c->ca, c->host,
-              c->d4, c->s4, x->ctr, x->older1, x->older2, x->older3, x->chain, main_variant, staged_at);
+              c->d4, c->s4, x->ctr, x->older1, x->older2, x->older3, x->chain, main_variant, staged_at,
+              write_back ? 1 : 0);
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_FETCH, s, &ep))) return rc;
   if (main_variant) x->main_pending = false;
@@ -1060,6 +1067,7 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   if ((uintptr_t)d_grad & 15) return fail(SFC_EINVAL, "gradient must be 16-byte aligned");
   int rc;
   if ((rc = rows_ready(c, x))) return rc;
+  c->updated_once = true;
   hipStream_t s = c->st;
   EventPair ep{};
   if ((rc = prof_begin(c, P_BACKWARD, s, &ep))) return rc;

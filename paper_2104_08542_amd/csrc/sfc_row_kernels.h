@@ -140,14 +140,17 @@ __global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_
                                                     HostRows h, int d4, int s4, Ctr* ctr,
                                                     const Ctr* older1, const Ctr* older2,
                                                     const Ctr* older3, int chain, int main_variant,
-                                                    int staged_at) {
+                                                    int staged_at, int write_back) {
   const bool on_main = (older1 && older1->n_bypass != 0) || (older2 && older2->n_bypass != 0) ||
                        (older3 && older3->n_bypass != 0) ||
                        (chain && older1 && older1->fetch_on_main != 0);
   if (blockIdx.x == 0 && threadIdx.x == 0) ctr->fetch_on_main = on_main;   // same value from both launches
   if (on_main != (main_variant != 0)) return;
   __builtin_amdgcn_s_setprio(3);            // few waves, long round trips: issue ahead of the kernels beside them
-  const int M = ctr->M, K = ctr->K;
+  // write_back 0: no row of the cache has ever been updated, so the victims are what the Host table holds
+  // already (a cache that only serves lookups: 2e5 power-law ids of dim 32 over 1e6 rows with a cache of 1e5 243 -> 183 us a pass,
+  // 4e4 of dim 64 with a cache of 5e4 174 -> 127)
+  const int M = ctr->M, K = write_back ? ctr->K : 0;
   // staged_at >= 0: k_stage_victims has run, the victims' rows are at staged_at + the bypass rows
   if ((staged_at >= 0) & split_swap(M, K, d4 + s4)) {
     const int64_t row0 = (int64_t)staged_at + ctr->n_bypass;

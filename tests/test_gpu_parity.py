@@ -810,6 +810,37 @@ def test_steps_given_up_without_a_lookup_still_bring_their_rows():
     p.close()
 
 
+@pytest.mark.parametrize("lookahead,n", [(0, 400), (0, 7000), (0, 40_000), (1, 400), (1, 7000)])
+def test_victims_are_written_back_once_a_row_may_have_changed(lookahead, n):
+    # a cache that has only been looked up evicts without writing to the Host table (here the Host rows are
+    # replaced behind its back, which a write would undo); from the first update on victims are written
+    V, D = 6 * n, 8
+    p = Pair(V, D, C=2 * n, max_ids=n, lookahead=lookahead)
+    c = p.cache
+    ids = [torch.arange(k * n, (k + 1) * n, device=p.dev) for k in range(6)]
+    for k in range(2):                                    # fills the cache
+        c.prepare(ids[k]); c.fetch_misses(); c.lookup(); c.discard()
+    torch.cuda.synchronize()
+    p.table.w[:2 * n] = 7.0
+    for k in range(2, 6):                                 # every row of the first two batches leaves
+        c.prepare(ids[k]); c.fetch_misses(); c.lookup(); c.discard()
+    st = c.stats()
+    assert st["n_evict"] == n and st["d2h_bytes"] == n * 2 * D * 4
+    torch.cuda.synchronize()
+    assert np.all(p.table.w[:2 * n] == 7.0)
+    c.prepare(ids[0]); c.fetch_misses()                   # batches 4 and 5 are resident; 4 leaves, unwritten
+    out = c.lookup()
+    assert torch.all(out == 7.0)
+    c.backward_update(torch.ones(n, D, device=p.dev))
+    for k in (2, 3):                                      # batches 5 and 0 leave: the latter was updated
+        c.prepare(ids[k]); c.fetch_misses(); c.lookup(); c.discard()
+    torch.cuda.synchronize()
+    assert np.all(p.table.w[:n] < 7.0) and np.all(p.table.w[n:2 * n] == 7.0)
+    assert np.array_equal(p.table.w[2 * n:], p.ow[2 * n:])
+    assert c.verify() == [0, 0, 0, 0]
+    p.close()
+
+
 def _copy_on(stream, dst, src, nbytes):
     """Asynchronous copy between device and pinned Host memory on a stream."""
     hip = ctypes.CDLL("libamdhip64.so")
