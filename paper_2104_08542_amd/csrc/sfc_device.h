@@ -175,6 +175,21 @@ __device__ __forceinline__ int block_excl_scan(int x, int& total, int* smem) {
   return res;
 }
 
+// Two such scans (of two sums) at the barriers of one.  smem: at least 32 ints.
+__device__ __forceinline__ void block_excl_scan2(int& x, int& y, int& total_x, int& total_y, int* smem) {
+  const int lane = lane_id(), nw = (int)(blockDim.x >> 6);
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int ix = wave_incl_scan(x), iy = wave_incl_scan(y);
+  if (lane == kWave - 1) { smem[w] = ix; smem[16 + w] = iy; }
+  __syncthreads();
+  const int sx = row_incl_scan(lane < nw ? smem[lane] : 0), sy = row_incl_scan(lane < nw ? smem[16 + lane] : 0);
+  total_x = __builtin_amdgcn_readlane(sx, nw - 1);
+  total_y = __builtin_amdgcn_readlane(sy, nw - 1);
+  x = (w > 0 ? __builtin_amdgcn_readlane(sx, w - 1) : 0) + ix - x;
+  y = (w > 0 ? __builtin_amdgcn_readlane(sy, w - 1) : 0) + iy - y;
+  __syncthreads();
+}
+
 __device__ __forceinline__ int block_sum(int x, int* smem) {
   const int lane = lane_id(), w = (int)(threadIdx.x >> 6), nw = (int)(blockDim.x >> 6);
   x = wave_sum(x);

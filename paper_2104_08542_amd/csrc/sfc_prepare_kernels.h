@@ -994,20 +994,13 @@ __global__ __launch_bounds__(256) void k_victim_write(const int* __restrict__ st
                                                        int* __restrict__ victim_slot,
                                                        int64_t* victim_id, Ctr* ctr,
                                                        int* __restrict__ dmap, IdxEntry* index, uint32_t hi) {
-  __shared__ int smem[20];
+  __shared__ int smem[32];
   if (ctr->K == 0) return;
   const int f = ctr->f_old, T = ctr->T, r = ctr->r, K = ctr->K;
   // victims in the tiles before this block's current one: summed from the per-tile counts, and
   // carried on from tile to tile (each block reads every count at most once)
   int pre_lt = 0, pre_eq = 0, summed = 0;
   for (int tile = blockIdx.x; tile * kPosChunk < f; tile += gridDim.x) {
-    {
-      int a = 0, b = 0;
-      for (int i = summed + (int)threadIdx.x; i < tile; i += 256) { a += tile_lt[i]; b += tile_eq[i]; }
-      pre_lt += block_sum(a, smem);
-      pre_eq += block_sum(b, smem);
-      summed = tile;
-    }
     const int base = tile * kPosChunk + (int)threadIdx.x * 8;
     unsigned mlt = 0, meq = 0;
     int lt = 0, eq = 0;
@@ -1020,14 +1013,19 @@ __global__ __launch_bounds__(256) void k_victim_write(const int* __restrict__ st
 #pragma unroll
       for (int j = 0; j < 8; ++j) v[j] = base + j < f ? stamp[base + j] : kIntMax;   // never a victim
     }
+    int a = 0, b = 0;
+    for (int i = summed + (int)threadIdx.x; i < tile; i += 256) { a += tile_lt[i]; b += tile_eq[i]; }
+    summed = tile;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       if (v[j] < T) { mlt |= 1u << j; ++lt; }
       if (v[j] == T) { meq |= 1u << j; ++eq; }
     }
     // one scan for both counts: a tile has 2048 slots, so each prefix fits in 16 bits
-    int tot;
-    const int both = block_excl_scan((lt << 16) | eq, tot, smem);
+    int tot, both = (lt << 16) | eq, tot_a;
+    block_excl_scan2(both, a, tot, tot_a, smem);
+    pre_lt += tot_a;
+    pre_eq += block_sum(b, smem);
     int lt_before = (both >> 16) + pre_lt;
     int eq_before = (both & 0xffff) + pre_eq;
     // list position of each victim among this thread's eight slots, then the resident ids with all
@@ -1112,7 +1110,7 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
                                                         IdxEntry* index, uint32_t hi,
                                                         int* __restrict__ dmap, int t, int C,
                                                         int* __restrict__ tile_reuse, Ctr* ctr) {
-  __shared__ int smem[20];
+  __shared__ int smem[32];
   const int U = ctr->U, K = ctr->K, f = ctr->f_old;
   const int free_slots = C - f;
   if (blockIdx.x == gridDim.x - 1)
@@ -1122,13 +1120,17 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
     const int v = tile * kVidTile + (int)threadIdx.x;
     const bool miss = v < U && slot_out[v] == kMissMark;
+    const int first_miss = tile_moff[tile];
     int tot, more = 0;
     for (int i = summed + (int)threadIdx.x; i < tile; i += 256) more += tile_cnt[i];
-    before += block_sum(more, smem);
     summed = tile;
     // start of the group of virtual id v in perm64 = exclusive scan of cnt
     const int nv = v < U ? cnt[v] : 0;
-    const int off = block_excl_scan(nv, tot, smem) + before;
+    int off = nv, i = miss ? 1 : 0, tot_i;
+    block_excl_scan2(off, i, tot, tot_i, smem);
+    before += block_sum(more, smem);
+    off += before;
+    i += first_miss;
     if (v < U) {
       grp[v] = ((int64_t)nv << 32) | (uint32_t)off;
       cold_pay[v] = make_int2(-1, -1);          // the grouping pass fills in the cold groups' rows
@@ -1143,7 +1145,6 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
         cnt_rep[r * kHotBins + v] = 0;
       }
     }
-    const int i = block_excl_scan(miss ? 1 : 0, tot, smem) + tile_moff[tile];
     bool reused = false;
     if (miss) {
       miss_vids[i] = v;
@@ -1164,8 +1165,10 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
     }
     // deleted entries taken back into use: tallied per tile for the next plan pass (thousands of
     // atomics on one counter would serialise at the memory side, about 10 ns each)
-    const int nre = block_sum(reused ? 1 : 0, smem);
-    if (threadIdx.x == 0) tile_reuse[tile] = nre;
+    if (!dmap) {
+      const int nre = block_sum(reused ? 1 : 0, smem);
+      if (threadIdx.x == 0) tile_reuse[tile] = nre;
+    }
   }
 }
 

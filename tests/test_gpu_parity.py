@@ -184,6 +184,25 @@ def test_groups_cut_by_block_edges_are_updated_once(D, C, optimizer):
     p.finish(); p.close()
 
 
+@pytest.mark.parametrize("D,C", [(4, 400), (64, 0), (128, 400), (256, 7), (20, 400)])
+def test_rowwise_rows_with_cold_groups_and_cut_groups(D, C):
+    # row-wise Adagrad: groups of one and two positions, groups cut by the stream's block edges and the
+    # common matrix side by side, rows of one lane to a whole wavefront (20: the path for other widths), one-hot and
+    # in bags, rows that bypass the cache
+    V, n = 9000, 60_000
+    rng = np.random.default_rng(300 + D)
+    p = Pair(V, D, C=C, max_ids=n, optimizer="rowwise_adagrad")
+    for t in range(2):
+        r = rng.random(n)
+        ids = np.where(r < 0.4, 3, np.where(r < 0.8, 20 + rng.integers(0, 12, n), -1))
+        cold = rng.permutation(V)[:6000]
+        ids[-8000:] = np.concatenate([cold, cold[:2000]])         # behind 8192 positions: virtual ids beyond the LDS bins too
+        ids[:9000] = rng.permutation(V)
+        off = None if t == 0 else np.concatenate([[0], np.sort(rng.integers(0, n + 1, n // 4)), [n]])
+        p.step(ids, si.grads(n if off is None else off.size - 1, D, 84, t).numpy(), off)
+    p.finish(); p.close()
+
+
 @pytest.mark.parametrize("D,n,optimizer", [(4, 200_000, "adagrad"), (4, 9000, "rowwise_adagrad"), (16, 40_000, "adam"),
                                            (32, 7000, "adagrad"), (128, 9000, "rowwise_adagrad"), (252, 12_000, "adagrad")])
 def test_several_long_runs_of_partial_sums_side_by_side(D, n, optimizer):
@@ -408,6 +427,18 @@ def test_pipelined_batches_on_one_and_on_two_prepare_streams(lookahead):
     p = Pair(V, D, C=250_000, max_ids=1_100_000, lookahead=lookahead)
     p.run_pipelined([(si.zipf_ids(n, 1.05, V, 510, t).numpy(), si.grads(n, D, 510, t).numpy(), None)
                      for t, n in enumerate(sizes)], False)
+    p.close()
+
+
+def test_hashed_index_rebuilt_between_prepares_on_one_and_on_two_streams():
+    # the rebuild of a hashed index runs inside the unique passes of one-stream prepares and as kernels of its own
+    # where those passes have a stream to themselves or the batch is prepared by one block
+    V, D = 600_000, 4
+    sizes = [270_000, 40_000, 265_000, 5000, 270_000, 60_000, 60_000, 4000, 262_144, 262_143, 0, 50_000, 268_000, 300, 270_000]
+    p = Pair(V, D, C=290_000, max_ids=270_000, lookahead=1, index_kind=HASHED)
+    expect = p.run_pipelined([(si.uniform_ids(n, V, 511, t).numpy() if n else np.zeros(0, np.int64), si.grads(n, D, 511, t).numpy(), None)
+                              for t, n in enumerate(sizes)], False)
+    assert sum(pr.stats["n_evict"] for pr, _ in expect) > 4 * (290_000 + 270_000) / 8       # deleted entries for a rebuild
     p.close()
 
 
