@@ -95,6 +95,7 @@ struct StepCtx {
   int32_t *d_inverse = nullptr, *d_slot = nullptr, *d_miss = nullptr;
   Ctr* ctr = nullptr;                 // device counters of this step
   int64_t* perm64 = nullptr;          // [max_ids] positions grouped by virtual id
+  int64_t* grp = nullptr;             // [max_ids] per virtual id: (positions << 32) | start of its group
   int2* cold_pay = nullptr;           // [max_ids] per virtual id: the gradient rows of a cold group (-1 = none)
   int* pos_slot = nullptr;            // [max_ids] cache row of each position
   int* victim_slot = nullptr;         // [max_ids]
@@ -160,7 +161,6 @@ struct sfc_cache {
   // beside the previous step's miss assignment and grouping, which still read that step's counts
   int* cnt2[2] = {nullptr, nullptr};
   int* cnt_rep2[2] = {nullptr, nullptr};
-  int64_t* grp = nullptr;                       // [max_ids] per virtual id: (positions << 32) | start of its group
   int* cur_rep = nullptr;                       // [kHotRep, kHotBins] group cursors of the lowest virtual ids, one per copy
   int* n_unique = nullptr;                      // unique ids of the step whose unique passes ran last
   int* pos2bag = nullptr;                       // [max_ids] multi-hot: bag of each position
@@ -471,7 +471,7 @@ void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
   }
   const int gv = grid_for(n, kVidTile, kGridCap);
   hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, x->d_unique, cnt, cnt_rep,
-                     c->cur_rep, sg.bins, sg.nrep, c->tile_cnt, c->grp, x->cold_pay, c->tile_miss,
+                     c->cur_rep, sg.bins, sg.nrep, c->tile_cnt, x->grp, x->cold_pay, c->tile_miss,
                      x->victim_slot, x->d_slot, x->d_miss, x->miss_row, x->miss_id, x->boff, c->slot_id,
                      c->stamp, c->index, c->hi, c->dmap, x->t, (int)c->C, c->tile_reuse, x->ctr);
 }
@@ -497,7 +497,7 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
   // pipelined it is the last kernel of the prepare
   const bool tells = c->nctx > 1 && !capturing(s);
   LAUNCH_THEN(tells, x->ev_prepared, scat, dim3(sg.blocks), dim3(threads), s, x->d_inverse,
-              x->d_offsets ? c->pos2bag : (const int*)nullptr, n, c->grp, (int*)x->cold_pay,
+              x->d_offsets ? c->pos2bag : (const int*)nullptr, n, x->grp, (int*)x->cold_pay,
               (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
               (const int*)x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags);
   x->told = tells;
@@ -713,7 +713,6 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     if ((rc = dalloc(c, &c->cnt2[0], c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->cnt2[1], c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->n_unique, 1))) goto bad;
-    if ((rc = dalloc(c, &c->grp, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->pos2bag, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->tile_cnt, c->max_ids / kVidTile + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_reuse, c->max_ids / kVidTile + 2))) goto bad;
@@ -734,6 +733,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
       StepCtx* x = &c->ctx[k];
       if ((rc = dalloc(c, &x->ctr, 1))) goto bad;
       if ((rc = dalloc(c, &x->perm64, c->max_ids))) goto bad;
+      if ((rc = dalloc(c, &x->grp, c->max_ids))) goto bad;
       if ((rc = dalloc(c, &x->cold_pay, c->max_ids))) goto bad;
       if ((rc = dalloc(c, &x->pos_slot, c->max_ids))) goto bad;
       if ((rc = dalloc(c, &x->victim_slot, c->max_ids))) goto bad;
@@ -908,7 +908,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     a.stamp = c->stamp; a.slot_id = c->slot_id; a.hist = c->hist;
     a.t = x->t; a.lookahead = c->cfg.lookahead; a.C = (int)c->C; a.boff = x->boff;
     a.cnt = cnt; a.tile_miss = c->tile_miss; a.age_hist = c->age_hist;
-    a.grp = c->grp; a.cold_pay = x->cold_pay; a.perm64 = x->perm64; a.pos_slot = x->pos_slot;
+    a.grp = x->grp; a.cold_pay = x->cold_pay; a.perm64 = x->perm64; a.pos_slot = x->pos_slot;
     a.victim_slot = x->victim_slot; a.victim_id = x->victim_id; a.miss_row = x->miss_row; a.miss_id = x->miss_id;
     a.ctr = x->ctr; a.prev = c->dmap ? prev->ctr : nullptr;
     auto kern = n <= 2048 ? (whole ? k_small_prepare<true, 2> : k_small_prepare<false, 2>)
@@ -1076,8 +1076,8 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   // lanes of a row share a wavefront)
   const bool rowwise = c->cfg.optimizer == SFC_OPT_ROWWISE_ADAGRAD;
   const bool fused = !rowwise || (c->d4 & (c->d4 - 1)) == 0;
-  // a small batch in one kernel; the groups of a step are kept until the next prepare only, so not pipelined
-  const bool groups = !rowwise && c->nctx == 1 && small_update(x->n_ids, c->d4);
+  // a small batch in one kernel
+  const bool groups = !rowwise && small_update(x->n_ids, c->d4);
   if (!groups && (rc = seg_launch(c, x, d_grad, c->gsum, c->bp, c->bp_vid, true, fused, &n_slots))) return rc;
   if (c->cfg.policy == SFC_POLICY_PREFETCH) {
     // the copies of a newer step issued so far read the Host table before this update writes it
@@ -1095,7 +1095,7 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   if (c->cfg.optimizer == SFC_OPT_ADAGRAD && groups) {
     AdagradOp op;
     op.lr = c->cfg.lr; op.eps = c->cfg.eps;
-    LAUNCH_TIMED(c, P_ADAGRAD, true, k_update_groups<AdagradOp>, gg, dim3(kGroupThreads), s, op, (const int64_t*)c->grp,
+    LAUNCH_TIMED(c, P_ADAGRAD, true, k_update_groups<AdagradOp>, gg, dim3(kGroupThreads), s, op, (const int64_t*)x->grp,
                  (const int64_t*)x->perm64, (const float4*)d_grad, (const int*)x->d_slot, (const int64_t*)x->d_unique,
                  (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->d4, (const Ctr*)x->ctr);
   } else if (c->cfg.optimizer == SFC_OPT_ADAGRAD) {
@@ -1117,7 +1117,7 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
     op.k = k;
     auto kern = x->d_offsets ? k_adam_rows<false> : k_adam_rows<true>;
     if (groups)
-      LAUNCH_TIMED(c, P_ADAGRAD, true, k_update_groups<AdamOp>, gg, dim3(kGroupThreads), s, op, (const int64_t*)c->grp,
+      LAUNCH_TIMED(c, P_ADAGRAD, true, k_update_groups<AdamOp>, gg, dim3(kGroupThreads), s, op, (const int64_t*)x->grp,
                    (const int64_t*)x->perm64, (const float4*)d_grad, (const int*)x->d_slot, (const int64_t*)x->d_unique,
                    (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->d4, (const Ctr*)x->ctr);
     else LAUNCH_TIMED(c, P_ADAGRAD, true, kern, dim3(ug.x + (unsigned)n_edge), dim3(256), s, (const float4*)c->gsum,

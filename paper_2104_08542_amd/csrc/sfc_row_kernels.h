@@ -1093,7 +1093,7 @@ __global__ __launch_bounds__(256) void k_adam_rows(
 }
 
 // ---------------------------------------------------------------------------------------------
-// The whole update of a small batch (small_update, lookahead 0), one launch: a lane group per virtual id
+// The whole update of a small batch (small_update), one launch: a lane group per virtual id
 // reads the id's group, sums its gradient rows in fp64 in the order of the grouping and updates the row.
 // Nothing here is many bytes; the stream and the row kernel took their time in start-up, chains of
 // partial sums and the dependent loads of two kernels.  An id with more than kGroupShort positions is left to
