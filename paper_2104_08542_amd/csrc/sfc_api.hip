@@ -113,12 +113,9 @@ struct StepCtx {
   SortGeom sg{};                      // shape of the step's counting and grouping passes
   bool joined = false;                // the main stream is behind the side-stream launch of the step's copies
   // pipelined mode: the second launch of the Host copies, due on the main stream behind the
-  // update of step main_after (see k_swap_rows); older1 .. older3 = counters of the older steps
-  // that were still in flight when the fetch was issued
+  // update of step main_after; bypass_from: see k_swap_rows (kIntMax: no older step was in flight)
   bool main_pending = false;
-  int main_after = 0;
-  const Ctr *older1 = nullptr, *older2 = nullptr, *older3 = nullptr;
-  int chain = 0;
+  int main_after = 0, bypass_from = kIntMax;
 };
 
 constexpr int kMaxCtx = 4;
@@ -402,8 +399,7 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   const bool tells = !main_variant && s != c->st;
   LAUNCH_THEN(tells && !prof_on(c, P_FETCH) && !capturing(s), x->ev_fetched, k_swap_rows, dim3(blocks), dim3(256), s,
               x->miss_row, x->miss_id, x->victim_id, (float4*)c->cw, (float4*)c->ca, c->host,
-              c->d4, c->s4, x->ctr, x->older1, x->older2, x->older3, x->chain, main_variant, staged_at,
-              write_back ? 1 : 0);
+              c->d4, c->s4, (const Ctr*)x->ctr, x->bypass_from, main_variant, staged_at, write_back ? 1 : 0);
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_FETCH, s, &ep))) return rc;
   if (main_variant) x->main_pending = false;
@@ -937,14 +933,13 @@ int sfc_fetch_misses(sfc_cache* c) {
   if (!x || x->state != PREPARED) return fail(SFC_ESTATE, "sfc_fetch_misses needs a preceding sfc_prepare");
   // older steps whose update has not been enqueued yet: their bypass rows are not in the Host
   // table yet (k_swap_rows decides on the device which of its two launches does the work)
-  x->older1 = x->older2 = x->older3 = nullptr;
-  x->chain = 0; x->main_pending = false; x->main_after = 0;
+  x->main_pending = false; x->main_after = 0; x->bypass_from = kIntMax;
   for (int k = 0; k < c->nctx && c->cfg.policy != SFC_POLICY_PREFETCH; ++k) {
     StepCtx* o = &c->ctx[k];
     if (o == x || o->state != FETCHED || o->updated) continue;
-    if (o->t == x->t - 1) { x->older1 = o->ctr; x->chain = o->main_pending ? 1 : 0; }
-    else if (o->t == x->t - 2) x->older2 = o->ctr;
-    else if (o->t == x->t - 3) x->older3 = o->ctr;
+    // (the steps in flight follow one another, so these are all steps from the smallest of the numbers on)
+    const int from = o->t == x->t - 1 && o->main_pending ? o->bypass_from : o->t;
+    if (from < x->bypass_from) x->bypass_from = from;
     if (o->t > x->main_after) x->main_after = o->t;
   }
   // everything the main stream has been given so far comes before the copies: older updates and their
@@ -961,7 +956,7 @@ int sfc_fetch_misses(sfc_cache* c) {
   if (x->grouping_due && (rc = group_positions(c, x, true))) return rc;
   x->joined = on_main;
   if ((rc = launch_swap(c, x, on_main ? c->st : c->side, 0))) return rc;
-  x->main_pending = x->older1 || x->older2 || x->older3;
+  x->main_pending = x->main_after > 0;
   x->state = FETCHED;
   return SFC_OK;
 }

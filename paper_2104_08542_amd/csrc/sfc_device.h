@@ -78,7 +78,7 @@ struct Ctr {
   int tomb;       // deleted entries in the cache index
   int rebuild;    // set when the index must be rebuilt before the next resolve
   int err;        // nonzero: a probe loop ran off its bound
-  int fetch_on_main;  // pipelined mode: this step's Host copies ran behind the older steps' updates
+  int last_bypass;    // the latest step before this one that had bypass rows (0: none)
   int U_prev;     // unique ids of the previous step (its per-tile tallies are still to be read)
   int dense;      // the id -> slot index is a dense map (no hashed entries, no tombstones, no rebuild)
   int t;          // number of the step these counters belong to

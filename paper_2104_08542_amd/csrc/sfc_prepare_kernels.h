@@ -312,10 +312,11 @@ __device__ __forceinline__ void ctr_start(Ctr* cur, const Ctr* prev, const int* 
   Ctr c = *prev;
   c.U_prev = c.U;
   c.U = *n_unique;
+  if (c.n_bypass) c.last_bypass = t - 1;
   c.M = c.K = c.n_bypass = c.n_hit = 0;
   c.n_invalid = *n_invalid;
   *n_invalid = 0;
-  c.f_old = c.f; c.need = 0; c.T = 0; c.r = 0; c.fetch_on_main = 0;
+  c.f_old = c.f; c.need = 0; c.T = 0; c.r = 0;
   c.t = t; c.bad_offsets = 0;
   static_assert(offsetof(Ctr, err) == 14 * sizeof(int), "the fields around err");
   int* const to = reinterpret_cast<int*>(cur);
@@ -1444,8 +1445,9 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
       Ctr c0 = *was;
       if (a.prev) {
         c0.U_prev = c0.U;
+        if (c0.n_bypass) c0.last_bypass = a.t - 1;
         c0.M = c0.K = c0.n_bypass = c0.n_hit = 0;
-        c0.f_old = c0.f; c0.need = 0; c0.T = 0; c0.r = 0; c0.fetch_on_main = 0;
+        c0.f_old = c0.f; c0.need = 0; c0.T = 0; c0.r = 0;
         c0.t = a.t; c0.bad_offsets = 0;
       }
       c0.U = U; c0.n_invalid = n_invalid;
@@ -1541,7 +1543,8 @@ __global__ __launch_bounds__(1024) void k_small_prepare(const SmallArgs a) {
       if (M != pl.n_bypass) atomicAdd(&a.hist[a.t], M - pl.n_bypass);
       Ctr c0 = *was;
       c0.U_prev = c0.U; c0.U = U; c0.n_hit = n_hit; c0.n_invalid = n_invalid;
-      c0.fetch_on_main = 0; c0.t = a.t; c0.bad_offsets = s_bad;
+      if (c0.n_bypass) c0.last_bypass = a.t - 1;
+      c0.t = a.t; c0.bad_offsets = s_bad;
       plan_store(pl, c0, f);
       if (s_err) c0.err = s_err;
       *a.ctr = c0;

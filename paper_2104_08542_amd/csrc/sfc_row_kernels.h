@@ -42,8 +42,10 @@ __device__ __forceinline__ void st_row(float4* p, float4 v) { if (kStream) st_st
 // host cannot know whether that happened without waiting, so it launches the kernel twice: once
 // on the side stream right away and once on the main stream behind the older steps' updates; the
 // device counters decide which of the two launches does the work (on_main below), the other one
-// returns at once.  `chain` extends the rule to "the previous step's copies ran on the main
-// stream and that launch was not yet enqueued when this one was issued".
+// returns at once.  Bypass rows of step `bypass_from` or a later one send the copies to the main launch: the
+// oldest step in flight when they were issued, or, where the previous step's main launch was still due
+// then, that step's own bypass_from (these copies come behind those).  Both launches go by the step's own
+// counters, which its prepare has completed: an older step's context is prepared anew while they are due.
 // ---------------------------------------------------------------------------------------------
 struct HostRows {
   float4* w;      // device view of h_weights
@@ -137,14 +139,10 @@ __global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_
                                                     const int64_t* __restrict__ miss_id,
                                                     const int64_t* __restrict__ victim_id,
                                                     float4* __restrict__ cw, float4* __restrict__ ca,
-                                                    HostRows h, int d4, int s4, Ctr* ctr,
-                                                    const Ctr* older1, const Ctr* older2,
-                                                    const Ctr* older3, int chain, int main_variant,
+                                                    HostRows h, int d4, int s4, const Ctr* ctr,
+                                                    int bypass_from, int main_variant,
                                                     int staged_at, int write_back) {
-  const bool on_main = (older1 && older1->n_bypass != 0) || (older2 && older2->n_bypass != 0) ||
-                       (older3 && older3->n_bypass != 0) ||
-                       (chain && older1 && older1->fetch_on_main != 0);
-  if (blockIdx.x == 0 && threadIdx.x == 0) ctr->fetch_on_main = on_main;   // same value from both launches
+  const bool on_main = ctr->last_bypass >= bypass_from;      // the same in both launches
   if (on_main != (main_variant != 0)) return;
   __builtin_amdgcn_s_setprio(3);            // few waves, long round trips: issue ahead of the kernels beside them
   // write_back 0: no row of the cache has ever been updated, so the victims are what the Host table holds

@@ -548,6 +548,26 @@ def test_pipelined_mixed_bypass_and_none(lookahead):
     p.close()
 
 
+@pytest.mark.parametrize("index_kind", [HASHED, DENSE])
+@pytest.mark.parametrize("scale", [1, 24])
+@pytest.mark.parametrize("lookahead", [1, 2, 3])
+@pytest.mark.parametrize("sync_every_call", [True, False])
+def test_pipelined_first_bypass_behind_steps_that_only_evict(sync_every_call, lookahead, scale, index_kind):
+    # the Host copies of a step are launched twice and exactly one launch may do them, also where the older steps that
+    # were in flight have been updated and their contexts prepared anew, now with bypass rows, before the second
+    # launch runs: steps that write victims back and have no bypass rows, then bypass rows for the first time
+    V, D, C = 20_000 * scale, 8, 1300 * scale
+    p = Pair(V, D, C=C, max_ids=1250 * scale, lookahead=lookahead, index_kind=index_kind)
+    bs = []
+    for t in range(15):
+        n = (1250 if t in (9, 10) else 300) * scale
+        bs.append((np.random.default_rng(9000 + t).permutation(V)[:n], si.grads(n, D, 82, t).numpy(), None))
+    st = [pr.stats for pr, _ in p.run_pipelined(bs, sync_every_call)]
+    assert [s["n_bypass"] > 0 for s in st[:11]] == [False] * 9 + [True] * 2
+    assert min(s["n_evict"] for s in st[5:]) > 0
+    p.close()
+
+
 @pytest.mark.parametrize("lookahead", [1, 2, 3])
 def test_pipelined_degenerate_batches(lookahead):
     # empty batches, a single id, only out-of-range ids and full-size batches in flight together
