@@ -453,15 +453,24 @@ void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
   hipStream_t s = c->prep;
   const int n = (int)x->n_ids;
   const SortGeom& sg = x->sg;
-  const FoldArgs fo{cnt, cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, 4 * kVidTile, kFoldBlocks)};
-  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag};
-  const unsigned bag_blocks = n > 0 && x->d_offsets ? (unsigned)((x->n_bags + 1023) / 1024) : 0u;
-  hipLaunchKernelGGL(k_plan, dim3(1 + fo.folds + bag_blocks), dim3(1024), 0, s, c->tile_miss, c->age_hist,
-                     c->tile_reuse, c->hist, x->t, c->cfg.lookahead, (int)c->C, c->hi, c->dmap ? 1 : 0, x->ctr, fo, bags);
   // a cache that holds the whole table never evicts: there is a free slot for every id that is not resident
-  if (c->C < c->V) {
+  const bool evicts = c->C < c->V;
+  // Pipelined, the kernels of other streams hold the compute units, and blocks of 1024 threads wait for a whole one.
+  // 2.56e6 ids, lookahead 2, ms per step, positions added up by kernels of 256 threads / beside the plan / with the
+  // victims' count: 0.463 / 0.465 / 0.461 (k_plan 16 us and 43 us with the other streams beside it).  Smaller batches
+  // have few such blocks (639e3 ids 0.283 / 0.277 / 0.277, 213e3 with lookahead 1 137 us a pass beside the plan, 139
+  // otherwise); in order 1024 x 39 ids take 102.0 us a pass beside the plan, 102.6 otherwise.
+  const bool beside_plan = !evicts || c->nctx == 1 || n < kTwoStreamMax;
+  const int ft = beside_plan ? 1024 : 256;
+  const FoldArgs fo{cnt, cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, ft, kFoldThreads / ft)};
+  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag};
+  const int riders = fo.folds + (n > 0 && x->d_offsets ? (int)((x->n_bags + ft - 1) / ft) : 0);
+  hipLaunchKernelGGL(k_plan, dim3(1 + (beside_plan ? riders : 0)), dim3(1024), 0, s, c->tile_miss, c->age_hist,
+                     c->tile_reuse, c->hist, x->t, c->cfg.lookahead, (int)c->C, c->hi, c->dmap ? 1 : 0, x->ctr, fo, bags);
+  if (evicts) {
     const int gs = grid_for(c->C, kPosChunk, kGridCap);
-    hipLaunchKernelGGL(k_victim_count, dim3(gs), dim3(256), 0, s, c->stamp, c->tile_lt, c->tile_eq, x->ctr);
+    hipLaunchKernelGGL(k_victim_count, dim3(gs + (beside_plan ? 0 : riders)), dim3(256), 0, s, c->stamp, c->tile_lt,
+                       c->tile_eq, x->ctr, gs, fo, bags);
     hipLaunchKernelGGL(k_victim_write, dim3(gs), dim3(256), 0, s, c->stamp, c->slot_id, c->tile_lt,
                        c->tile_eq, x->victim_slot, x->victim_id, x->ctr, c->dmap, c->index, c->hi);
   }

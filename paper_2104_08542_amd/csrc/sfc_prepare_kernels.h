@@ -863,14 +863,51 @@ __device__ __forceinline__ void plan_store(const Plan& pl, Ctr& ctr, int f) {
   ctr.oldest = pl.oldest;
 }
 
-// Plan (the first block): scan the per-tile miss counts, then decide the victims.  It is a chain of a few dependent
-// loads and scans on one compute unit; beside it the next `folds` blocks add up the positions of every virtual id
-// (the copies of a hot bin, see count_positions) and of every tile, and the blocks behind those find the bags of
-// the positions (multi-hot input): neither needs the plan.  us of plan and bags one after the other / this way, 291e3
-// ids in bags 4.6 + 4.8 / 4.8, 8.9e6 12.8 + 17.0 / 18.8; plan alone at 1024 x 39 ids 6.2 / 3.5, 65536 x 39 8.8 / 6.2.
-constexpr int kFoldBlocks = 64;
+// What the assign pass needs and the plan does not: the positions of every virtual id (the copies of a hot bin, see
+// count_positions) and of every tile, by `folds` blocks, and the bags of the positions (multi-hot input), by the
+// blocks behind those.  Beside the plan, a chain on one compute unit, they cost nothing (us of plan and bags one after
+// the other / this way, 291e3 ids in bags 4.6 + 4.8 / 4.8, 8.9e6 12.8 + 17.0 / 18.8; plan alone, at 1024 x 39 ids,
+// 6.2 / 3.5, 65536 x 39 8.8 / 6.2); but a block of the plan's 1024 threads needs a compute unit with sixteen free
+// wavefronts, so large pipelined batches give them to the launch of the victims' count: see plan_and_assign.
+constexpr int kFoldThreads = 1 << 16;        // of them all, at most
 struct FoldArgs { int* cnt; const int* cnt_rep; int bins, nrep; int* tile_cnt; int folds; };
 struct BagArgs { const int64_t* offsets; int n_bags, n; int* pos2bag; };
+
+// words: a word of LDS per thread
+template <int kT>
+__device__ __forceinline__ void fold_or_bags(const FoldArgs& fo, const BagArgs& bags, Ctr* ctr, int blk, int* words) {
+  if (blk >= fo.folds) {
+    bags_of_positions(bags.offsets, bags.n_bags, bags.n, bags.pos2bag, ctr, blk - fo.folds, words);
+    return;
+  }
+  const int U = ctr->U;
+  constexpr int kTiles = kT / kVidTile;
+  const int sub = (int)threadIdx.x / kVidTile;
+  for (int tile0 = blk * kTiles; tile0 * kVidTile < U; tile0 += fo.folds * kTiles) {
+    const int tile = tile0 + sub, v = tile * kVidTile + (int)threadIdx.x % kVidTile;
+    int c = 0;
+    if (v < U) {
+      if (v < fo.bins) {
+#pragma unroll 8
+        for (int r = 0; r < fo.nrep; ++r) c += fo.cnt_rep[r * kHotBins + v];
+        fo.cnt[v] = c;
+      } else {
+        c = fo.cnt[v];
+      }
+    }
+    c = wave_sum(c);
+    if (lane_id() == 0) words[threadIdx.x >> 6] = c;
+    lds_barrier();
+    if (threadIdx.x % kVidTile == 0 && tile * kVidTile < U) {
+      const int* const q = words + sub * (kVidTile / kWave);
+      fo.tile_cnt[tile] = q[0] + q[1] + q[2] + q[3];
+    }
+    lds_barrier();
+  }
+}
+
+// Plan (the first block): scan the per-tile miss counts, then decide the victims.  It is a chain of a few dependent
+// loads and scans on one compute unit.
 
 __global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* __restrict__ age_hist,
                                                int* __restrict__ tile_reuse, int* hist, int t,
@@ -880,37 +917,11 @@ __global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* __restrict__
   __shared__ int smem[20];
   __shared__ int s_found;
   __shared__ int words[1024];
-  if ((int)blockIdx.x > fo.folds) {
-    bags_of_positions(bags.offsets, bags.n_bags, bags.n, bags.pos2bag, ctr, (int)blockIdx.x - fo.folds - 1, words);
+  if (blockIdx.x > 0) {
+    fold_or_bags<1024>(fo, bags, ctr, (int)blockIdx.x - 1, words);
     return;
   }
   const int U = ctr->U;
-  if (blockIdx.x > 0) {
-    constexpr int kTiles = 1024 / kVidTile;
-    const int sub = (int)threadIdx.x / kVidTile;
-    for (int tile0 = ((int)blockIdx.x - 1) * kTiles; tile0 * kVidTile < U; tile0 += fo.folds * kTiles) {
-      const int tile = tile0 + sub, v = tile * kVidTile + (int)threadIdx.x % kVidTile;
-      int c = 0;
-      if (v < U) {
-        if (v < fo.bins) {
-#pragma unroll 8
-          for (int r = 0; r < fo.nrep; ++r) c += fo.cnt_rep[r * kHotBins + v];
-          fo.cnt[v] = c;
-        } else {
-          c = fo.cnt[v];
-        }
-      }
-      c = wave_sum(c);
-      if (lane_id() == 0) words[threadIdx.x >> 6] = c;
-      lds_barrier();
-      if (threadIdx.x % kVidTile == 0 && tile * kVidTile < U) {
-        const int* const q = words + sub * (kVidTile / kWave);
-        fo.tile_cnt[tile] = q[0] + q[1] + q[2] + q[3];
-      }
-      lds_barrier();
-    }
-    return;
-  }
   // every thread reads the counters here; thread 0 overwrites them only after the last barrier
   const int f = ctr->f, oldest = ctr->oldest;
   const int ntiles = (U + kVidTile - 1) / kVidTile;
@@ -963,11 +974,16 @@ __global__ __launch_bounds__(1024) void k_plan(int* tile_miss, int* __restrict__
 // ---------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_victim_count(const int* __restrict__ stamp,
                                                        int* __restrict__ tile_lt,
-                                                       int* __restrict__ tile_eq, const Ctr* ctr) {
-  __shared__ int smem[20];
+                                                       int* __restrict__ tile_eq, Ctr* ctr, int blocks,
+                                                       const FoldArgs fo, const BagArgs bags) {
+  __shared__ int smem[256];
+  if ((int)blockIdx.x >= blocks) {            // see fold_or_bags
+    fold_or_bags<256>(fo, bags, ctr, (int)blockIdx.x - blocks, smem);
+    return;
+  }
   if (ctr->K == 0) return;
   const int f = ctr->f_old, T = ctr->T;
-  for (int tile = blockIdx.x; tile * kPosChunk < f; tile += gridDim.x) {
+  for (int tile = blockIdx.x; tile * kPosChunk < f; tile += blocks) {
     const int base = tile * kPosChunk + (int)threadIdx.x * 8;
     int lt = 0, eq = 0;
     if (base + 8 <= f) {

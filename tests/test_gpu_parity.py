@@ -430,6 +430,23 @@ def test_pipelined_batches_on_one_and_on_two_prepare_streams(lookahead):
     p.close()
 
 
+def test_large_pipelined_batches_with_bags_and_without():
+    # from 2^20 ids on a pipelined prepare counts positions and finds bags beside the victims' count: one-hot and in
+    # bags, hits, misses and victims in every step, an index of either kind
+    V, D, C = 1_300_000, 4, 800_000
+    for index_kind in (DENSE, HASHED):
+        p = Pair(V, D, C=C, max_ids=(1 << 20) + 77, lookahead=1, index_kind=index_kind)
+        bs = []
+        for t, n in enumerate([(1 << 20) + 77, 1 << 20, (1 << 20) + 5, (1 << 20) - 1, (1 << 20) + 77]):
+            ids, rng = si.zipf_ids(n, 1.02, V, 512, t).numpy(), np.random.default_rng(t)
+            ids[:200_000] = rng.permutation(V)[:200_000]
+            off = None if t % 2 else np.concatenate([[0], np.sort(rng.integers(0, n + 1, n // 7)), [n]])
+            bs.append((ids, si.grads(n if off is None else off.size - 1, D, 512, t).numpy(), off))
+        expect = p.run_pipelined(bs, index_kind == DENSE)
+        assert min(pr.stats["n_evict"] for pr, _ in expect[-2:]) > 0
+        p.close()
+
+
 def test_hashed_index_rebuilt_between_prepares_on_one_and_on_two_streams():
     # the rebuild of a hashed index runs inside the unique passes of one-stream prepares and as kernels of its own
     # where those passes have a stream to themselves or the batch is prepared by one block
