@@ -829,7 +829,10 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
       // grouping passes (small grids that leave most of the GPU idle).
       HIPCHK(hipStreamWaitEvent(c->ins, c->ev_tmp, 0));
       if (x->discarded) HIPCHK(hipStreamWaitEvent(c->ins, x->ev_fetched, 0));
-      // (told only where the previous step's unique passes had that stream as well; otherwise: behind all of its prepare)
+      // (told only where the previous step's unique passes had that stream as well; otherwise: behind all of its
+      // prepare.  When every step tells, batches either side of 2^18 ids in turn are slower, us a step: 200e3 and
+      // 400e3 ids 125 against 110 with lookahead 1, 121 against 97 with 2; 250e3 and 280e3 115 / 108 and 122 / 96;
+      // 600e3 and 200e3 148 / 152 and 151 / 151; 700e3 and 1.1e6 575 / 573 and 577 / 575)
       if (c->resolved_at == c->t && c->t > 0) HIPCHK(hipStreamWaitEvent(c->ins, c->ev_resolved, 0));
       else if (c->t > 0) HIPCHK(hipStreamWaitEvent(c->ins, prev->ev_prepared, 0));
     }
