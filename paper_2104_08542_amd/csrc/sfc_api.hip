@@ -165,7 +165,8 @@ struct sfc_cache {
   int* tile_reuse = nullptr;                    // [max_ids / kVidTile + 1] deleted index entries reused per tile
   int* n_invalid = nullptr;                     // out-of-range positions of the step being prepared
   int* age_hist = nullptr;                      // [kAgeBins] hits of the step by age, zero between steps
-  double* bp = nullptr; int* bp_vid = nullptr;  // [2 * blocks, D] edge partial sums of k_seg_stream
+  double* bp = nullptr; int* bp_vid = nullptr;  // [2 * blocks, D] edge partial sums of k_seg_stream, or the shares of k_update_groups
+  int* share_ticket = nullptr;                  // [kMaxShares] shares that have arrived (k_update_groups), zero between steps
   float* gsum = nullptr;                        // [max_ids, D] common gradients of the step
   float* warm_sink = nullptr;                   // one float that k_warm_rows never writes
   HostRows host{};                              // device view of the Host table
@@ -732,6 +733,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
       if ((rc = dalloc(c, &c->bp, 2 * nwmax * c->D))) goto bad;
       if ((rc = dalloc(c, &c->bp_vid, 2 * nwmax))) goto bad;
     }
+    if ((rc = dalloc(c, &c->share_ticket, (int64_t)kMaxShares))) goto bad;
     if ((rc = dalloc(c, &c->gsum, c->max_ids * c->D))) goto bad;
     if ((rc = dalloc(c, &c->warm_sink, 1))) goto bad;
     for (int k = 0; k < c->nctx; ++k) {
@@ -764,6 +766,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     fill<int>(s, c->cnt_rep2[0], (int64_t)kHotRep * kHotBins, 0);
     fill<int>(s, c->cnt_rep2[1], (int64_t)kHotRep * kHotBins, 0);
     fill<int>(s, c->n_unique, 1, 0);
+    fill<int>(s, c->share_ticket, (int64_t)kMaxShares, 0);
     fill<int>(s, c->tile_reuse, c->max_ids / kVidTile + 2, 0);
     UEntry uempty; uempty.key = kEmpty; uempty.minpos = kIntMax; uempty.pad = 0;
     if (c->wide) fill<UEntry>(s, (UEntry*)c->utab, hu, uempty);
@@ -1098,13 +1101,15 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   // the stream above passed over the cold groups and left the block-edge partials unchained:
   // the fused kernels sum both themselves (their first blocks chain the partials, a lane group per slot)
   const int n_edge = edge_blocks(n_slots, c->d4);
-  const dim3 gg(groups ? (unsigned)grid_for(x->n_ids, kGroupShort, 512) : 1u);
+  const int shares = groups ? update_shares(x->n_ids, c->d4) : 0;
+  const dim3 gg((unsigned)(shares + grid_for(x->n_ids, kGroupShort, kGroupBlocks)));
   if (c->cfg.optimizer == SFC_OPT_ADAGRAD && groups) {
     AdagradOp op;
     op.lr = c->cfg.lr; op.eps = c->cfg.eps;
     LAUNCH_TIMED(c, P_ADAGRAD, true, k_update_groups<AdagradOp>, gg, dim3(kGroupThreads), s, op, (const int64_t*)x->grp,
                  (const int64_t*)x->perm64, (const float4*)d_grad, (const int*)x->d_slot, (const int64_t*)x->d_unique,
-                 (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->d4, (const Ctr*)x->ctr);
+                 (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->d4, (const Ctr*)x->ctr, (int)x->n_ids,
+                 shares, c->bp, c->share_ticket);
   } else if (c->cfg.optimizer == SFC_OPT_ADAGRAD) {
     auto kern = x->d_offsets ? k_adagrad_rows<false> : k_adagrad_rows<true>;
     LAUNCH_TIMED(c, P_ADAGRAD, true, kern, dim3(ug.x + (unsigned)n_edge), dim3(256), s, (const float4*)c->gsum,
@@ -1126,7 +1131,8 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
     if (groups)
       LAUNCH_TIMED(c, P_ADAGRAD, true, k_update_groups<AdamOp>, gg, dim3(kGroupThreads), s, op, (const int64_t*)x->grp,
                    (const int64_t*)x->perm64, (const float4*)d_grad, (const int*)x->d_slot, (const int64_t*)x->d_unique,
-                   (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->d4, (const Ctr*)x->ctr);
+                   (float4*)c->cw, (float4*)c->ca, c->host, (int)c->C, x->boff, c->d4, (const Ctr*)x->ctr, (int)x->n_ids,
+                   shares, c->bp, c->share_ticket);
     else LAUNCH_TIMED(c, P_ADAGRAD, true, kern, dim3(ug.x + (unsigned)n_edge), dim3(256), s, (const float4*)c->gsum,
                  (const int*)x->d_slot, (const int64_t*)x->d_unique, (float4*)c->cw, (float4*)c->ca,
                  c->host, (int)c->C, x->boff, k, c->d4, (const Ctr*)x->ctr,

@@ -1096,41 +1096,50 @@ __global__ __launch_bounds__(256) void k_adam_rows(
 // Nothing here is many bytes; the stream and the row kernel took their time in start-up, chains of
 // partial sums and the dependent loads of two kernels.  An id with more than kGroupShort positions is left to
 // the whole block, its lane groups each a strided share in fixed order, combined in a tree; there is a block per
-// kGroupShort positions, and a block's ids lie as far apart as the grid allows, because the frequent ids of a batch
-// are among its first ones (with a block's worth of lane groups per block, 100 ids of 12 to 50 positions each came
-// to one or two blocks, one after the other: 278 us at 5000 positions of dim 16, 9 this way).
-// One block sums an id however frequent it is, so what bounds a batch of one id alone is the rate at which one
-// compute unit loads gradient rows, 130 GB/s, and the limit on the size is the bytes that take 5 us (and a cap
-// where short rows would make the grid long).  sfc_backward_update us, stream and row kernel / this way, power-law
-// ids, half of the positions one id, all of them one id, all distinct: 2048 positions of dim 16 16.0 / 10.6, 15.7 / 10.6,
-// 14.9 / 10.0, 12.4 / 6.4; 5000 of dim 16 16.0 / 11.2, 15.8 / 12.8, 16.4 / 13.3, 12.7 / 9.2; 5000 of dim 32 16.3 / 12.6,
-// 14.9 / 15.0, 15.2 / 17.5, 12.8 / 9.2; 2048 of dim 80 15.3 / 12.4, 14.4 / 14.8, 14.4 / 18.2, 12.7 / 7.3; 1250 of dim 128
-// 15.1 / 11.9, 13.5 / 13.9, 13.8 / 17.0, 12.8 / 7.1; 16384 of dim 4 27.1 / 15.1, 26.8 / 12.4, 27.6 / 12.8, 13.8 / 9.9; beyond the
-// limit 8192 of dim 32 17.8 / 18.1, 15.2 / 17.8, 15.3 / 26.9, 14.4 / 9.2.
+// kGroupShort positions, at most kGroupBlocks of them, and a block's ids lie as far apart as the grid allows, because the
+// frequent ids of a batch are among its first ones (with a block's worth of lane groups per block, 100 ids of 12 to 50
+// positions each came to one or two blocks, one after the other: 278 us at 5000 positions of dim 16, 9 this way).
+// One compute unit loads gradient rows at 130 GB/s.  So from kSplitChunks on (320 KiB, 2.5 us of one block) a very
+// frequent id is summed by further blocks, a share of the grouping each; the last to arrive adds up their sums in the
+// order of the shares (2 us for the way through memory, so shares of 64 KiB, and an id takes more than two).
+// sfc_backward_update us, stream and row kernel / one block per id / this way, power-law ids, half of the positions one
+// id, all of them one id: 5000 positions of dim 16 (not split) 15.9 / 10.9, 15.6 / 12.6, 16.6 / 12.8; 10240 of dim 16
+// 19.8 / 14.1 / 13.9, 17.8 / 15.5 / 11.9, 16.9 / 18.4 / 12.5; 5000 of dim 32 16.7 / 12.2 / 11.0, 15.1 / 14.7 / 11.7, 15.2 /
+// 17.3 / 12.5; 2048 of dim 80 15.3 / 12.1 / 11.0, 14.5 / 14.4 / 11.3, 14.4 / 18.2 / 13.2; 1250 of dim 128 15.4 / 11.8 / 10.6,
+// 13.8 / 13.9 / 11.0, 14.1 / 17.0 / 13.2; 640 of dim 256 14.9 / 12.0 / 10.4, 13.6 / 14.2 / 10.9, 13.6 / 17.0 / 12.3; 16384 of
+// dim 4 (not split) 27.8 / 14.5, 29.1 / 12.3, 29.0 / 12.4.  All distinct 12.1 to 17 by the stream and the row kernel, 6.2 to 10
+// this way.  Beyond the limit on the size, one block per id, 8192 of dim 32 17.8 / 18.1, 15.2 / 17.8, 15.3 / 26.9.
 // ---------------------------------------------------------------------------------------------
 constexpr int64_t kSmallUpdate = 1 << 14, kSmallUpdateChunks = 40 << 10;      // positions; 16-byte chunks of their rows
 inline bool small_update(int64_t n, int d4) { return n > 0 && n <= kSmallUpdate && n * d4 <= kSmallUpdateChunks; }
 constexpr int kGroupShort = 16;
+constexpr int kGroupBlocks = 512;            // lane groups for kSmallUpdate ids of the narrowest rows
 constexpr int kGroupThreads = 1024;
 inline __host__ __device__ int update_groups(int d4) { return kGroupThreads / 64 * (64 / d4 > 0 ? 64 / d4 : 1); }
+// A split batch: its grouping is cut into shares of update_share(d4) positions, and an id with more than two shares'
+// worth of positions is summed by the blocks of its shares.
+constexpr int kShareChunks = 4096, kSplitChunks = 20 << 10, kMaxShares = 16;
+inline __host__ __device__ int update_share(int d4) { return kShareChunks / d4; }
+inline int update_shares(int64_t n, int d4) {
+  return n * d4 > kSplitChunks ? (int)((n + update_share(d4) - 1) / update_share(d4)) : 0;
+}
 
 template <class Op>
 __global__ __launch_bounds__(kGroupThreads) void k_update_groups(
     const Op op, const int64_t* __restrict__ grp, const int64_t* __restrict__ perm64,
     const float4* __restrict__ grad, const int* __restrict__ slot, const int64_t* __restrict__ unique_ids,
-    float4* __restrict__ cw, float4* __restrict__ cs, HostRows h, int C, int boff, int d4, const Ctr* ctr) {
+    float4* __restrict__ cw, float4* __restrict__ cs, HostRows h, int C, int boff, int d4, const Ctr* ctr,
+    int n, int shares, double* part, int* ticket) {
   constexpr int kP = Op::kParts, kFly = 8;
   __shared__ double red[kGroupThreads * 4];
   __shared__ int long_v[kGroupThreads], n_long;
   if (threadIdx.x == 0) n_long = 0;
   __syncthreads();
   const int U = ctr->U, groups = update_groups(d4), G = groups / (kGroupThreads / 64);
-  const int nblk = (int)gridDim.x < U ? (int)gridDim.x : U;        // blocks that have work
-  if ((int)blockIdx.x >= nblk) return;
   const int lane = lane_id(), g = lane / d4, c4 = lane - g * d4;
   const int gi = (int)(threadIdx.x >> 6) * G + g;         // this lane group among the block's
   const bool active = g < G;
-  const int v = (int)blockIdx.x + gi * nblk;
+  const int share = update_share(d4), split_from = shares > 0 ? 2 * share : kIntMax;
 
   // the row of virtual id `id` with the sum s: weights and state are on their way before the sum is there
   auto apply = [&](int id, int sl, float4 w, float4 (&st)[kP], const D4& s) {
@@ -1176,10 +1185,80 @@ __global__ __launch_bounds__(kGroupThreads) void k_update_groups(
     }
   };
 
+  // the sum of the rows of entries [first, end) by the whole block; the result is the first lane group's
+  auto block_rows = [&](int first, int end) {
+    D4 s; d4_zero(s);
+    if (active) add_rows(s, first + gi, end, groups);
+    double* const r = &red[(gi * d4 + c4) * 4];           // (groups * d4 <= kGroupThreads)
+    if (active) { r[0] = s.x; r[1] = s.y; r[2] = s.z; r[3] = s.w; }
+    int o = 1;
+    while (o < groups) o <<= 1;
+    for (o >>= 1; o > 0; o >>= 1) {
+      __syncthreads();
+      if (active && gi < o && gi + o < groups) {
+        const double* q = r + o * d4 * 4;
+        r[0] += q[0]; r[1] += q[1]; r[2] += q[2]; r[3] += q[3];
+      }
+    }
+    if (active) { s.x = r[0]; s.y = r[1]; s.z = r[2]; s.w = r[3]; }
+    return s;
+  };
+
+  // A share's block: at most the first and the last group of its positions are split ones (a group with more
+  // positions than a share that meets it covers one of its ends).  Whoever brings in the last share of an id adds
+  // the shares up, in order, and updates the row.
+  if ((int)blockIdx.x < shares) {
+    const int lo = (int)blockIdx.x * share, hi = lo + share < n ? lo + share : n;
+    const int v0 = entry_vid(perm64[lo]), v1 = entry_vid(perm64[hi - 1]);
+    for (int which = 0; which < (v0 == v1 ? 1 : 2); ++which) {
+      const int v = which ? v1 : v0, sl = slot[v];
+      const int64_t gr = grp[v];
+      const int cnt = (int)(gr >> 32), start = (int)gr;
+      if (cnt <= split_from || sl < 0) continue;
+      const D4 s = block_rows(start > lo ? start : lo, start + cnt < hi ? start + cnt : hi);
+      if (gi == 0 && active) {
+        double* const p = &part[((2 * (int)blockIdx.x + which) * d4 + c4) * 4];
+        __hip_atomic_store(p, s.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p + 1, s.y, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p + 2, s.z, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(p + 3, s.w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+      }
+      __syncthreads();
+      const int j0 = start / share, nj = (start + cnt - 1) / share - j0 + 1;
+      if (threadIdx.x == 0) {
+        n_long = atomicAdd(&ticket[j0], 1) == nj - 1;
+        if (n_long) atomicExch(&ticket[j0], 0);            // for the next batch
+        __threadfence();
+      }
+      __syncthreads();
+      if (n_long && gi == 0 && active) {
+        float4 w, st[kP];
+        load_row(sl, w, st);
+        D4 sum; d4_zero(sum);
+        for (int j = 0; j < nj; ++j) {
+          const int at = 2 * (j0 + j) + (j == 0 && start != j0 * share ? 1 : 0);
+          double* const p = &part[(at * d4 + c4) * 4];
+          sum.x += __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          sum.y += __hip_atomic_load(p + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          sum.z += __hip_atomic_load(p + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          sum.w += __hip_atomic_load(p + 3, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        apply(v, sl, w, st, sum);
+      }
+      __syncthreads();
+    }
+    return;
+  }
+
+  const int blk = (int)blockIdx.x - shares, blocks = (int)gridDim.x - shares;
+  const int nblk = blocks < U ? blocks : U;                        // blocks that have work
+  if (blk >= nblk) return;
+  const int v = blk + gi * nblk;
   if (active && v < U) {
     const int64_t gr = grp[v];
     const int sl = slot[v], cnt = (int)(gr >> 32), start = (int)gr;
-    if (sl >= 0) {
+    if (sl >= 0 && cnt <= split_from) {
       if (cnt > kGroupShort) {
         if (c4 == 0) long_v[atomicAdd(&n_long, 1)] = v;
       } else {
@@ -1199,23 +1278,8 @@ __global__ __launch_bounds__(kGroupThreads) void k_update_groups(
     const int sl = slot[id], cnt = (int)(gr >> 32), start = (int)gr;
     float4 w, st[kP];
     if (gi == 0 && active) load_row(sl, w, st);
-    D4 s; d4_zero(s);
-    if (active) add_rows(s, start + gi, start + cnt, groups);
-    double* const r = &red[(gi * d4 + c4) * 4];           // (groups * d4 <= kGroupThreads)
-    if (active) { r[0] = s.x; r[1] = s.y; r[2] = s.z; r[3] = s.w; }
-    int o = 1;
-    while (o < groups) o <<= 1;
-    for (o >>= 1; o > 0; o >>= 1) {
-      __syncthreads();
-      if (active && gi < o && gi + o < groups) {
-        const double* q = r + o * d4 * 4;
-        r[0] += q[0]; r[1] += q[1]; r[2] += q[2]; r[3] += q[3];
-      }
-    }
-    if (gi == 0 && active) {
-      s.x = r[0]; s.y = r[1]; s.z = r[2]; s.w = r[3];
-      apply(id, sl, w, st, s);
-    }
+    const D4 s = block_rows(start, start + cnt);
+    if (gi == 0 && active) apply(id, sl, w, st, s);
     __syncthreads();
   }
 }

@@ -141,6 +141,25 @@ def test_updates_of_small_batches_up_to_their_limits(D, n, optimizer):
     p.finish(); p.close()
 
 
+@pytest.mark.parametrize("C", [0, 400])
+@pytest.mark.parametrize("D,n,optimizer", [(8, 16384, "adam"), (20, 8192, "adagrad"), (32, 5000, "adagrad"),
+                                           (128, 1280, "adam"), (256, 640, "adagrad")])
+def test_frequent_ids_of_small_batches_are_summed_in_shares(D, n, optimizer, C):
+    # an id with more positions than two shares of the grouping (16384 / D positions each) is summed by several blocks:
+    # groups of two shares and one position more or less, that begin at, before and behind a share's edge, two of
+    # them that meet inside a share, the null entry, several batches one after the other, rows that bypass the cache
+    V, share = 3000, 4096 // (D // 4)
+    p = Pair(V, D, C=C, max_ids=n, optimizer=optimizer)
+    rng = np.random.default_rng(D)
+    for t, runs in enumerate([[2 * share], [2 * share + 1], [1, 2 * share + 1, 2 * share + 2], [share, 3 * share, 2 * share],
+                              [share - 1, 2 * share + 1, 3 * share], [n], [1, n - 1], [2 * share + 1, -3 * share, 2 * share + 1]]):
+        ids = np.concatenate([np.full(abs(r), -1 if r < 0 else 100 * t + k) for k, r in enumerate(runs)])[:n]
+        ids = np.concatenate([ids, rng.integers(2000, V, n - ids.size)])
+        ids[100:] = rng.permutation(ids[100:])           # groups lie in order of first appearance
+        p.step(ids, si.grads(n, D, 85, t).numpy())
+    p.finish(); p.close()
+
+
 @pytest.mark.parametrize("D", [4, 8, 16, 64, 80, 128, 256])
 def test_row_widths(D):
     # every lane-group geometry of the row kernels (D/4 lanes per row, also a D that does not
