@@ -864,7 +864,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   // Hashed index, where everything runs behind the previous step's prepare: its rebuild, when due, by further
   // blocks of the unique passes
   const bool rebuild_inside = !c->dmap && !small && n > 0 && su == s;
-  const int extra = rebuild_inside ? kRebuildBlocks : 0;
+  const int extra = rebuild_inside ? rebuild_blocks(c->C) : 0;
   // What the resolve (and with it the start of the step's counters) waits for is done by the time the unique
   // passes are: a dense index has no rebuild.  Otherwise both are kernels of their own.
   const bool start_inside = c->dmap || rebuild_inside;

@@ -115,9 +115,12 @@ struct WideTab {
 // Rebuild of the hashed cache index: emptied, then every resident id goes back in, by nblk blocks of 256 threads
 // each, over the occupied slots [0, f).  The previous step's plan asks for it when too many entries are deleted ones;
 // the two halves run between that step's last index update and this step's resolve, as further blocks of the
-// insert and the assign pass (kRebuildBlocks each, which return at once otherwise), or as kernels of their own
+// insert and the assign pass (rebuild_blocks each, which return at once otherwise), or as kernels of their own
 // where those passes do not run behind that step's prepare (k_ctr_init, k_index_refill).
-constexpr int kRebuildBlocks = 256;
+// A thread puts its ids back one after the other, so large caches get more blocks.  What a step with a rebuild takes
+// longer than one without, us, kernels of their own (2048 blocks each) / 256 blocks inside / 2048 inside: 3e5 slots 45 /
+// 26 / 42, 1e6 100 / 82 / 84, 8e6 720 / 820 / 690.
+inline int rebuild_blocks(int64_t C) { return C < (1 << 20) ? 256 : C >= (8 << 20) ? 2048 : (int)(C >> 12); }
 __device__ __forceinline__ void index_clear(IdxEntry* index, uint32_t hi, int blk, int nblk) {
   IdxEntry e; e.key = kEmpty; e.slot = -1; e.pad = 0;
   for (uint32_t i = blk * 256 + threadIdx.x; i < hi; i += nblk * 256) index[i] = e;
