@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import sfc_inputs as si
+from oracle import Oracle
 from gpu_common import Pair, assert_close, same_stats
 
 pytestmark = pytest.mark.gpu
@@ -466,15 +467,70 @@ def test_large_pipelined_batches_with_bags_and_without():
         p.close()
 
 
+class _DeletedEntries:
+    """The manager's rule for rebuilding a hashed index, replayed: the deleted entries of a table of `size` entries with
+    linear probing, an insert taking the first free or deleted entry on its way."""
+
+    def __init__(self, size):
+        self.size, self.live, self.deleted, self.reused, self.due = size, {}, 0, 0, False
+        self.entry = bytearray(size)                  # 0 free, 1 live, 2 deleted
+
+    def _put(self, ids):
+        h = ids.astype(np.uint64)
+        for mul in (0xff51afd7ed558ccd, 0xc4ceb9fe1a85ec53, 1):
+            h ^= h >> np.uint64(33)
+            h *= np.uint64(mul)
+        reused = 0
+        for i, e in zip(ids.tolist(), (((h >> np.uint64(32)) * np.uint64(self.size)) >> np.uint64(32)).tolist()):
+            while self.entry[e] == 1:
+                e = e + 1 if e + 1 < self.size else 0
+            reused += self.entry[e] == 2
+            self.entry[e] = 1
+            self.live[i] = e
+        return reused
+
+    def step(self, victims, inserted):
+        """Returns what the plan compares with an eighth of the table; afterwards `due` says whether the next prepare
+        starts with a rebuild."""
+        self.deleted -= self.reused
+        if self.due:
+            self.entry, ids = bytearray(self.size), np.array(list(self.live), np.int64)
+            self._put(ids)
+            self.deleted = 0
+        level = self.deleted + len(victims)
+        self.due = level > self.size // 8
+        for i in victims.tolist():
+            self.entry[self.live.pop(i)] = 2
+        self.deleted = level
+        self.reused = self._put(inserted)
+        return level
+
+
 def test_hashed_index_rebuilt_between_prepares_on_one_and_on_two_streams():
     # the rebuild of a hashed index runs inside the unique passes of one-stream prepares and as kernels of its own
-    # where those passes have a stream to themselves or the batch is prepared by one block
-    V, D = 600_000, 4
-    sizes = [270_000, 40_000, 265_000, 5000, 270_000, 60_000, 60_000, 4000, 262_144, 262_143, 0, 50_000, 268_000, 300, 270_000]
-    p = Pair(V, D, C=290_000, max_ids=270_000, lookahead=1, index_kind=HASHED)
-    expect = p.run_pipelined([(si.uniform_ids(n, V, 511, t).numpy() if n else np.zeros(0, np.int64), si.grads(n, D, 511, t).numpy(), None)
-                              for t, n in enumerate(sizes)], False)
-    assert sum(pr.stats["n_evict"] for pr, _ in expect) > 4 * (290_000 + 270_000) / 8       # deleted entries for a rebuild
+    # where those passes have a stream to themselves or the batch is prepared by one block (or empty): whenever one
+    # is due, by the rule replayed here, the next batch is of a form that has not had one yet
+    V, D, C, max_ids, U = 1_000_000, 4, 150_000, 270_000, 45_000
+    table = _DeletedEntries(4 * (C + max_ids))
+    orc = Oracle(C, D, np.zeros((V, D), np.float32), np.ones((V, D), np.float32), lookahead=1)
+    rng = np.random.default_rng(512)
+    forms = {"one stream": 60_000, "two streams": 265_000, "one block": 5000, "empty": 0}
+    to_do, had, bs = ["two streams", "one stream", "one block", "empty", "two streams"], [], []
+    while to_do or table.due:
+        form = to_do.pop(0) if table.due else ["one stream", "two streams"][len(bs) % 2]
+        if table.due:
+            had.append(form)
+        n = forms[form]
+        ids = rng.permutation(V)[:min(n, U)]
+        ids = np.concatenate([ids, rng.choice(ids, n - ids.size)]) if n else np.zeros(0, np.int64)
+        bs.append((ids, si.grads(n, D, 512, len(bs)).numpy(), None))
+        pr, _ = orc.step(ids, bs[-1][1])
+        level = table.step(pr.evict_ids, pr.unique_ids[pr.miss_vids[pr.slot[pr.miss_vids] < C]])
+        # (inserts side by side may share out the deleted entries differently)
+        assert abs(level - table.size // 8) > table.size // 8 // 50, (len(bs), level, table.size // 8)
+    assert had == ["two streams", "one stream", "one block", "empty", "two streams"]
+    p = Pair(V, D, C=C, max_ids=max_ids, lookahead=1, index_kind=HASHED)
+    p.run_pipelined(bs, False)
     p.close()
 
 
@@ -1049,3 +1105,38 @@ def test_the_calls_of_a_step_can_be_captured(n):
         hip.hipGraphExecDestroy(run); hip.hipGraphDestroy(graph)
         p.step(si.zipf_ids(n, 1.05, V, 61, 4).numpy(), si.grads(n, D, 61, 4).numpy())
         p.finish(); p.close()
+
+
+@pytest.mark.parametrize("n", [400, 40_000])
+def test_what_is_recorded_writes_victims_back(n):
+    # a graph may be launched when rows have been updated, so it writes victims also where the cache had never been
+    # updated when it was recorded (the Host rows are replaced behind the cache's back to see it)
+    hip = ctypes.CDLL("libamdhip64.so")
+    vp = ctypes.c_void_p
+    V, D = 3 * n, 8
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        p = Pair(V, D, C=2 * n, max_ids=n)
+        c, st = p.cache, vp(s.cuda_stream)
+        ids = [torch.arange(k * n, (k + 1) * n, device=p.dev) for k in range(3)]
+        out = torch.empty(n, D, device=p.dev)
+        for k in range(2):
+            c.prepare(ids[k]); c.fetch_misses(); c.lookup(out); c.discard()
+        torch.cuda.synchronize()
+        p.table.w[:2 * n] = 7.0
+        graph, run = vp(), vp()
+        assert hip.hipStreamBeginCapture(st, 2) == 0                   # relaxed
+        try:
+            c.prepare(ids[2]); c.fetch_misses(); c.lookup(out)
+        finally:
+            rc = hip.hipStreamEndCapture(st, ctypes.byref(graph))
+        assert rc == 0
+        assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)) == 0
+        assert hip.hipGraphLaunch(run, st) == 0
+        torch.cuda.synchronize()
+        c.discard()
+        assert c.stats()["n_evict"] == n and np.array_equal(out.cpu().numpy(), p.ow[2 * n:])
+        assert np.array_equal(p.table.w[:n], p.ow[:n]) and np.all(p.table.w[n:2 * n] == 7.0)
+        assert c.verify() == [0, 0, 0, 0]
+        hip.hipGraphExecDestroy(run); hip.hipGraphDestroy(graph)
+        p.close()
