@@ -112,8 +112,9 @@ typedef struct {
                                  2^18 to 2^20 ids) two streams the library creates, the Host
                                  copies on side_stream.  Each
                                  further step of lookahead adds a step context, so that a prepare
-                                 waits for an older update.  The caller rotates L + 1 sets of
-                                 prepare buffers. */
+                                 waits for an older update; it takes a bypass row with its state
+                                 and 52 bytes of lists per id of max_ids_per_batch.  The caller
+                                 rotates L + 1 sets of prepare buffers. */
   int32_t max_steps;          /* steps this cache may run (sizes the recency histogram); 0 = 1<<20 */
   void* stream;               /* hipStream_t for prepare / lookup / backward_update */
   void* side_stream;          /* hipStream_t for the Host<->cache copies (see sfc_fetch_misses for

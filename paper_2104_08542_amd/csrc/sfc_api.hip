@@ -458,9 +458,10 @@ void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
   const bool evicts = c->C < c->V;
   // Pipelined, the kernels of other streams hold the compute units, and blocks of 1024 threads wait for a whole one.
   // 2.56e6 ids, lookahead 2, ms per step, positions added up by kernels of 256 threads / beside the plan / with the
-  // victims' count: 0.463 / 0.465 / 0.461 (k_plan 16 us and 43 us with the other streams beside it).  Smaller batches
-  // have few such blocks (639e3 ids 0.283 / 0.277 / 0.277, 213e3 with lookahead 1 137 us a pass beside the plan, 139
-  // otherwise); in order 1024 x 39 ids take 102.0 us a pass beside the plan, 102.6 otherwise.
+  // victims' count: 0.463 / 0.465 / 0.461 (k_plan and k_victim_count among the other streams' kernels 43 + 19 us beside
+  // the plan, 18 + 30 otherwise).  Smaller batches have few such blocks (639e3 ids 0.283 / 0.277 / 0.277, 213e3 with
+  // lookahead 1 137 us a pass beside the plan, 139 otherwise); in order 1024 x 39 ids take 102.0 us a pass beside the
+  // plan, 102.6 otherwise.
   const bool beside_plan = !evicts || c->nctx == 1 || n < kTwoStreamMax;
   const int ft = beside_plan ? 1024 : 256;
   const FoldArgs fo{cnt, cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, ft, kFoldThreads / ft)};

@@ -30,7 +30,7 @@ constexpr int kVidTile = 256;     // virtual ids per tile in resolve / assign
 // Same-address atomics serialise at the memory side (about 10 ns each on this chip), and the
 // hottest id of a power-law batch owns a fifth of all positions.  So each block first
 // deduplicates its kUniqChunk positions in an LDS table (key -> smallest position in the block) and
-// only the distinct keys of the block go to HBM, up to four per thread in flight.  There a plain load
+// only the distinct keys of the block go to HBM, two per thread in flight.  There a plain load
 // comes first (the table entry of a key never changes once set, and a stale position can only be too
 // large), and an atomic is issued only when the load has not already seen the key / a small enough
 // position.

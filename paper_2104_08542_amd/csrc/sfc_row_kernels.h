@@ -1290,7 +1290,7 @@ __global__ __launch_bounds__(kGroupThreads) void k_update_groups(
 // One thread per 16-byte chunk of a row as above; the d4 lanes of a row add their squares with
 // shuffles when d4 is a power of two (a row then never straddles a wavefront).  Such rows take the path of the
 // element-wise optimizers: the stream passes over the cold groups and leaves its block-edge partials, both are summed
-// here (213e3 power-law positions of dim 128, us: stream 29.8 + finish 6.3 + rows 26.5 before, 22.5 + 21.4 this way; a pass of 8192 x 26 with lookahead 1 136.9 -> 126).
+// here (213e3 power-law positions of dim 128, us: stream 29.8 + finish 6.3 + rows 26.5 before, 22.5 + 21.4 this way).
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ float sum_squares(float4 g, int d4) {
   float ss = g.x * g.x + g.y * g.y + g.z * g.z + g.w * g.w;
