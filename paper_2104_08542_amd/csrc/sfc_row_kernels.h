@@ -1108,7 +1108,10 @@ __global__ __launch_bounds__(256) void k_adam_rows(
 // 17.3 / 12.5; 2048 of dim 80 15.3 / 12.1 / 11.0, 14.5 / 14.4 / 11.3, 14.4 / 18.2 / 13.2; 1250 of dim 128 15.4 / 11.8 / 10.6,
 // 13.8 / 13.9 / 11.0, 14.1 / 17.0 / 13.2; 640 of dim 256 14.9 / 12.0 / 10.4, 13.6 / 14.2 / 10.9, 13.6 / 17.0 / 12.3; 16384 of
 // dim 4 (not split) 27.8 / 14.5, 29.1 / 12.3, 29.0 / 12.4.  All distinct 12.1 to 17 by the stream and the row kernel, 6.2 to 10
-// this way.  Beyond the limit on the size, one block per id, 8192 of dim 32 17.8 / 18.1, 15.2 / 17.8, 15.3 / 26.9.
+// this way.  The limit on the size lies where a batch of one id stops being faster on wide rows; beyond it, the same three
+// inputs, two kernels / this way: 1536 of dim 128 14.8 / 11.2, 13.7 / 11.9, 13.7 / 13.7; 2048 of dim 128 15.3 / 11.3, 13.9 /
+// 12.6, 13.9 / 14.8; 3276 of dim 80 15.9 / 11.8, 14.6 / 12.7, 14.4 / 15.1; 1000 of dim 256 13.9 / 11.2, 13.6 / 12.0, 13.5 / 14.5;
+// 8192 of dim 32 17.2 / 13.7, 15.8 / 12.9, 15.5 / 14.1.
 // ---------------------------------------------------------------------------------------------
 constexpr int64_t kSmallUpdate = 1 << 14, kSmallUpdateChunks = 40 << 10;      // positions; 16-byte chunks of their rows
 inline bool small_update(int64_t n, int d4) { return n > 0 && n <= kSmallUpdate && n * d4 <= kSmallUpdateChunks; }
