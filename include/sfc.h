@@ -108,9 +108,8 @@ typedef struct {
                                  sfc_fetch_misses of step t+L may be called before
                                  sfc_backward_update of step t; they run on other streams while the
                                  main stream works on step t (the paper's pipeline of Data-Loader,
-                                 Host-Manager and GPU-Worker stages): the prepare on one or (from
-                                 2^18 to 2^20 ids) two streams the library creates, the Host
-                                 copies on side_stream.  Each
+                                 Host-Manager and GPU-Worker stages): the prepare on a stream that
+                                 the library creates, the Host copies on side_stream.  Each
                                  further step of lookahead adds a step context, so that a prepare
                                  waits for an older update; it takes a bypass row with its state
                                  and 52 bytes of lists per id of max_ids_per_batch.  The caller
@@ -162,8 +161,8 @@ void sfc_cache_destroy(sfc_cache* c);
  * Step 1 (Algorithm 1 lines 3-4; Data-Loader section, Host-Manager section).
  *  d_ids       [n_ids] int64 raw feature ids, row-major [batch, fields] or the concatenated bags.
  *              Produced on `stream` before this call (or already complete): with lookahead > 0 the
- *              prepare runs on other streams (streams the library creates; side_stream for
- *              SFC_POLICY_PREFETCH), which first wait for what `stream` has been given so far.
+ *              prepare runs on another stream (one the library creates; side_stream for
+ *              SFC_POLICY_PREFETCH), which first waits for what `stream` has been given so far.
  *  d_offsets   NULL for one-hot input (then n_bags must equal n_ids), else [n_bags+1] int64 CSR
  *              offsets with d_offsets[0] = 0 and d_offsets[n_bags] = n_ids, non-decreasing.
  *  outputs (each sized for n_ids entries by the caller):
@@ -303,8 +302,7 @@ int sfc_cache_state(sfc_cache* c, int64_t* h_slot_id, int32_t* h_stamp, float* h
  * Device timing.  level 1: the step calls.  sfc_prepare, sfc_fetch_misses and sfc_backward_update
  * (several kernels each) are bracketed by hipEvents on the stream they run on, so their times
  * include the launch latencies between the events (with lookahead >= 1 the prepare's events sit on
- * the library's stream of the cache manager's kernels; where the unique passes take a second
- * stream, the wait for them is included.  With lookahead 0 the prepare's last kernel, the grouping,
+ * the library's stream.  With lookahead 0 the prepare's last kernel, the grouping,
  * is launched by sfc_fetch_misses; its time is added to the prepare's).  sfc_lookup is one kernel,
  * or two from 32 MB of output on (the batch's rows are read into the memory-side cache, then
  * gathered): the start and end of each are recorded by the dispatch itself, i.e. the time is the

@@ -6,8 +6,7 @@
 // A step in flight is a StepCtx: the caller's buffers, the step's device counters, its grouping
 // of positions, its victim list and its bypass region.  lookahead = L has L + 1 contexts.
 // L = 0 runs the prepare on the main stream and the Host copies on the side stream (few of them on the
-// main stream, see swap_on_main).  L >= 1 gives the prepare a stream of its own, batches of
-// kTwoStreamMin to kTwoStreamMax ids a second one for their unique passes, and the Host copies run on
+// main stream, see swap_on_main).  L >= 1 gives the prepare a stream of its own and the Host copies run on
 // the side stream, so that the prepare of step t+L, the copies of the step before it and lookup / update of
 // step t overlap (the paper's pipeline of Data-Loader, Host-Manager and GPU-Worker stages); a
 // larger L means more contexts, i.e. a prepare need not wait for the most recent update.  The
@@ -129,12 +128,6 @@ struct sfc_cache {
   hipStream_t st = nullptr, side = nullptr;     // main stream; stream of the Host copies
   hipStream_t prep = nullptr;                   // stream of the prepare kernels
   bool own_prep = false;                        // prep was created here (lookahead >= 1)
-  // lookahead >= 1, batches of kTwoStreamMin to kTwoStreamMax ids: the unique passes of a step (insert,
-  // count, assign, inverse) run on a stream of their own as soon as the previous step's resolve has
-  // emptied the batch table, beside the rest of that step's prepare
-  hipStream_t ins = nullptr;
-  hipEvent_t ev_resolved = nullptr, ev_inserted = nullptr;
-  int resolved_at = 0;                          // step for which ev_resolved was recorded last
   hipEvent_t ev_tmp = nullptr;                  // cross-stream ordering inside one call
   // device memory
   float *cw = nullptr, *ca = nullptr;           // rows [(C + nctx * max_ids), D] and their optimizer state [.., S]
@@ -308,13 +301,7 @@ int healthy(sfc_cache* c) {
   return SFC_OK;
 }
 
-// Pipelined, the unique passes of a batch of kTwoStreamMin up to kTwoStreamMax ids run on a stream of their
-// own, beside the rest of the previous step's prepare: small grids that leave most of the GPU idle.
-// Below, the events between the two streams cost more than that gains (213e3 ids, lookahead 1: 213 us a
-// pass on two streams, 197 on one); above, the passes fill the chip themselves (lookahead 2, ms per step
-// on two / one: 639e3 ids 0.284 / 0.299, 2.56e6 0.482 / 0.470, 8.9e6 in bags 2.00 / 1.98; 2.56e6 with three
-// caches taking turns 0.691 / 0.638).
-constexpr int64_t kTwoStreamMin = (int64_t)1 << 18, kTwoStreamMax = (int64_t)1 << 20;
+constexpr int64_t kBesidePlanMax = (int64_t)1 << 20;   // see plan_and_assign
 constexpr int kGridCap = 2048;   // blocks of the grid-stride kernels whose size lives on the device
 constexpr int kRebuildGrid = 2048; // blocks of the two launches that only work when the index is rebuilt
 
@@ -462,7 +449,7 @@ void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
   // the plan, 18 + 30 otherwise).  Smaller batches have few such blocks (639e3 ids 0.283 / 0.277 / 0.277, 213e3 with
   // lookahead 1 137 us a pass beside the plan, 139 otherwise); in order 1024 x 39 ids take 102.0 us a pass beside the
   // plan, 102.6 otherwise.
-  const bool beside_plan = !evicts || c->nctx == 1 || n < kTwoStreamMax;
+  const bool beside_plan = !evicts || c->nctx == 1 || n < kBesidePlanMax;
   const int ft = beside_plan ? 1024 : 256;
   const FoldArgs fo{cnt, cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, ft, kFoldThreads / ft)};
   const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag};
@@ -516,7 +503,6 @@ int sync_all(sfc_cache* c) {
   HIPCHK(hipStreamSynchronize(c->st));
   if (c->side != c->st) HIPCHK(hipStreamSynchronize(c->side));
   if (c->prep != c->st && c->prep != c->side) HIPCHK(hipStreamSynchronize(c->prep));
-  if (c->ins) HIPCHK(hipStreamSynchronize(c->ins));
   return SFC_OK;
 }
 
@@ -574,7 +560,6 @@ void sfc_cache_destroy(sfc_cache* c) {
   (void)hipStreamSynchronize(c->st);
   if (c->side != c->st) (void)hipStreamSynchronize(c->side);
   if (c->own_prep && c->prep) (void)hipStreamSynchronize(c->prep);
-  if (c->ins) (void)hipStreamSynchronize(c->ins);
   for (int w = 0; w < P_N; ++w)
     for (EventPair& ep : c->pending[w]) { (void)hipEventDestroy(ep.a); (void)hipEventDestroy(ep.b); }
   for (EventPair& ep : c->spare) { (void)hipEventDestroy(ep.a); (void)hipEventDestroy(ep.b); }
@@ -584,9 +569,6 @@ void sfc_cache_destroy(sfc_cache* c) {
     if (c->ctx[k].ev_fetched) (void)hipEventDestroy(c->ctx[k].ev_fetched);
   }
   if (c->own_prep && c->prep) (void)hipStreamDestroy(c->prep);
-  if (c->ins) (void)hipStreamDestroy(c->ins);
-  if (c->ev_resolved) (void)hipEventDestroy(c->ev_resolved);
-  if (c->ev_inserted) (void)hipEventDestroy(c->ev_inserted);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->hstat) (void)hipHostFree(c->hstat);
   delete c;
@@ -664,8 +646,13 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
   c->host.a = (float4*)dp;
   c->host.hs4 = (cfg->host_row_stride ? cfg->host_row_stride : cfg->dim) / 4;
   c->host.has4 = (cfg->host_state_stride ? cfg->host_state_stride : S) / 4;
-  // lookahead 0: prepare on the main stream; otherwise on one or two streams of its own, beside the Host
-  // copies of the step before (the Prefetch strategy: on the side stream, ahead of its copies)
+  // lookahead 0: prepare on the main stream; otherwise on a stream of its own, beside the Host copies of the step
+  // before (the Prefetch strategy: on the side stream, ahead of its copies).  One stream and no more: the streams of
+  // a process share four hardware queues, and what stands behind a step's copies in one of them waits for hundreds
+  // of microseconds.  A second stream, for the unique passes of 2^18 to 2^20 ids beside the rest of the previous prepare,
+  // against this one, us a step of one cache / of three in turn: 300e3 ids of dim 16 with lookahead 1 135 -> 114 / 137 -> 108, 639e3
+  // 335 -> 313 / 347 -> 325, with lookahead 2 272 -> 272 / 346 -> 326, hashed 277 -> 286 / 365 -> 341, 950e3 398 -> 404 / 466 -> 460;
+  // 700e3 in bags of dim 32 145 -> 123 / 128 -> 129.
   c->prep = cfg->lookahead == 0 ? c->st : c->side;
   if (cfg->lookahead >= 1 && cfg->policy != SFC_POLICY_PREFETCH) {
     if ((e = hipStreamCreateWithFlags(&c->prep, hipStreamNonBlocking)) != hipSuccess) {
@@ -673,14 +660,6 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
       rc = fail(SFC_EHIP, "hipStreamCreate", e); goto bad;
     }
     c->own_prep = true;
-    if ((e = hipStreamCreateWithFlags(&c->ins, hipStreamNonBlocking)) != hipSuccess) {
-      c->ins = nullptr;
-      rc = fail(SFC_EHIP, "hipStreamCreate", e); goto bad;
-    }
-    if ((e = hipEventCreateWithFlags(&c->ev_resolved, hipEventDisableTiming)) != hipSuccess ||
-        (e = hipEventCreateWithFlags(&c->ev_inserted, hipEventDisableTiming)) != hipSuccess) {
-      rc = fail(SFC_EHIP, "hipEventCreate", e); goto bad;
-    }
   }
 
   {
@@ -815,7 +794,6 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   // a small batch is prepared by one block (k_small_prepare), all of it when that block can also choose
   // the victims
   const bool small = n_ids > 0 && n_ids <= kSmallIds && n_bags <= kSmallBags;
-  const bool one_stream = n_ids < kTwoStreamMin || n_ids >= kTwoStreamMax;
   const bool whole = small && c->dmap && (c->C >= c->V || c->C <= kSmallSlots);
   hipStream_t s = c->prep;
   if (s != c->st) {
@@ -825,27 +803,11 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     HIPCHK(hipStreamWaitEvent(s, c->ev_tmp, 0));
     // a context freed by sfc_discard: its copies may still be reading its lists
     if (x->discarded && s != c->side) HIPCHK(hipStreamWaitEvent(s, x->ev_fetched, 0));
-    if (c->ins && !one_stream) {
-      // The unique passes touch the batch table, the per-position table slots, the tally of
-      // invalid ids, this step's set of counts, its context's position array and the caller's
-      // buffers of this step: the previous step's prepare has finished with the shared ones once
-      // its resolve has run, so they need not wait for that step's victim, assignment and
-      // grouping passes (small grids that leave most of the GPU idle).
-      HIPCHK(hipStreamWaitEvent(c->ins, c->ev_tmp, 0));
-      if (x->discarded) HIPCHK(hipStreamWaitEvent(c->ins, x->ev_fetched, 0));
-      // (told only where the previous step's unique passes had that stream as well; otherwise: behind all of its
-      // prepare.  When every step tells, batches either side of 2^18 ids in turn are slower, us a step: 200e3 and
-      // 400e3 ids 125 against 110 with lookahead 1, 121 against 97 with 2; 250e3 and 280e3 115 / 108 and 122 / 96;
-      // 600e3 and 200e3 148 / 152 and 151 / 151; 700e3 and 1.1e6 575 / 573 and 577 / 575)
-      if (c->resolved_at == c->t && c->t > 0) HIPCHK(hipStreamWaitEvent(c->ins, c->ev_resolved, 0));
-      else if (c->t > 0) HIPCHK(hipStreamWaitEvent(c->ins, prev->ev_prepared, 0));
-    }
   } else if (x->discarded && !x->joined) {
     // lookahead 0: a step that was given up without a lookup left nothing on the main stream that
     // waits for its copies, which may still be reading the lists that this prepare rewrites
     HIPCHK(hipStreamWaitEvent(s, x->ev_fetched, 0));
   }
-  hipStream_t su = c->ins && !one_stream ? c->ins : s;   // stream of the unique passes
   c->t += 1;
   x->t = c->t; x->state = PREPARED; x->updated = false; x->main_pending = false; x->discarded = false;
   x->n_ids = n_ids; x->n_bags = n_bags; x->d_offsets = d_offsets;
@@ -862,9 +824,8 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   if (hu < 64) hu = 64;                       // the batch table is empty between steps: any size works
   const int nchunk = (n + kPosChunk - 1) / kPosChunk;
   const SortGeom sg = x->sg = small ? small_geom(n) : sort_geom(n);
-  // Hashed index, where everything runs behind the previous step's prepare: its rebuild, when due, by further
-  // blocks of the unique passes
-  const bool rebuild_inside = !c->dmap && !small && n > 0 && su == s;
+  // Hashed index: its rebuild, when due, by further blocks of the unique passes
+  const bool rebuild_inside = !c->dmap && !small && n > 0;
   const int extra = rebuild_inside ? rebuild_blocks(c->C) : 0;
   // What the resolve (and with it the start of the step's counters) waits for is done by the time the unique
   // passes are: a dense index has no rebuild.  Otherwise both are kernels of their own.
@@ -873,22 +834,22 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     const int nub = (n + kUniqChunk - 1) / kUniqChunk;
     if (c->wide) {
       WideTab tab{(UEntry*)c->utab, 0, c->V};
-      hipLaunchKernelGGL(k_uniq_insert<WideTab>, dim3(nub + extra), dim3(256), 0, su, d_ids, n, tab, hu, c->hslot,
+      hipLaunchKernelGGL(k_uniq_insert<WideTab>, dim3(nub + extra), dim3(256), 0, s, d_ids, n, tab, hu, c->hslot,
                          c->first, c->n_invalid, nub, (const Ctr*)prev->ctr, c->index, c->hi);
     } else {
       PackedTab tab{c->utab, pos_bits(n), c->V};
-      hipLaunchKernelGGL(k_uniq_insert<PackedTab>, dim3(nub + extra), dim3(256), 0, su, d_ids, n, tab, hu, c->hslot,
+      hipLaunchKernelGGL(k_uniq_insert<PackedTab>, dim3(nub + extra), dim3(256), 0, s, d_ids, n, tab, hu, c->hslot,
                          c->first, c->n_invalid, nub, (const Ctr*)prev->ctr, c->index, c->hi);
     }
     const int* const counts = n > kCountMin ? c->blk_cnt : nullptr;
     if (counts)
-      hipLaunchKernelGGL(k_uniq_count, dim3((nchunk + 3) / 4), dim3(256), 0, su, (const unsigned*)c->first,
+      hipLaunchKernelGGL(k_uniq_count, dim3((nchunk + 3) / 4), dim3(256), 0, s, (const unsigned*)c->first,
                          nchunk, c->blk_cnt);
-    hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk + extra), dim3(256), 0, su, d_ids, c->V, c->hslot,
+    hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk + extra), dim3(256), 0, s, d_ids, c->V, c->hslot,
                        (const unsigned*)c->first, n, counts, d_unique_ids, c->uvid, c->vid_hslot, cnt, c->n_unique,
                        nchunk, x->ctr, x->t, (const Ctr*)prev->ctr, c->index, c->hi, (const int64_t*)c->slot_id);
   } else if (!small) {
-    fill<int>(su, c->n_unique, 1, 0);
+    fill<int>(s, c->n_unique, 1, 0);
   }
   const RankArgs rank{c->hslot, c->uvid, n, d_inverse, cnt, cnt_rep, sg.nrep, x->pos_slot, c->first};
   const ResolveArgs res{d_unique_ids, c->vid_hslot, c->utab, c->wide ? 1 : 0, c->index, c->hi, c->dmap, c->stamp,
@@ -898,13 +859,6 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                                                                               : k_rank_resolve<8, 1024>;
   const int rt = sg.shift == 12 ? 512 : 1024, nres = small ? 0 : grid_for(n, rt, kResolveThreads / rt);
   const int ncount = small || n == 0 ? 0 : sg.blocks;
-  const bool together = su == s && start_inside;
-  if (!together && ncount)
-    hipLaunchKernelGGL(rank_resolve, dim3(ncount), dim3(rt), 0, su, rank, res, 0);
-  if (su != s) {
-    HIPCHK(hipEventRecord(c->ev_inserted, su));
-    HIPCHK(hipStreamWaitEvent(s, c->ev_inserted, 0));
-  }
   // from here on behind the whole prepare of the previous step: the step's counters start from
   // that step's, the index is rebuilt if its plan asked for it
   if (!start_inside) {
@@ -928,9 +882,8 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
                           : (whole ? k_small_prepare<true, kSmallPer> : k_small_prepare<false, kSmallPer>);
     hipLaunchKernelGGL(kern, dim3(1), dim3(1024), 0, s, a);
   } else {
-    hipLaunchKernelGGL(rank_resolve, dim3(nres + (together ? ncount : 0)), dim3(rt), 0, s, rank, res, nres);
+    hipLaunchKernelGGL(rank_resolve, dim3(nres + ncount), dim3(rt), 0, s, rank, res, nres);
   }
-  if (su != s) { HIPCHK(hipEventRecord(c->ev_resolved, s)); c->resolved_at = x->t; }
   x->grouping_due = !whole && c->nctx == 1;
   x->told = false;
   if (!whole) {

@@ -116,7 +116,7 @@ struct WideTab {
 // each, over the occupied slots [0, f).  The previous step's plan asks for it when too many entries are deleted ones;
 // the two halves run between that step's last index update and this step's resolve, as further blocks of the
 // insert and the assign pass (rebuild_blocks each, which return at once otherwise), or as kernels of their own
-// where those passes do not run behind that step's prepare (k_ctr_init, k_index_refill).
+// where those passes are not launched (k_ctr_init, k_index_refill).
 // A thread puts its ids back one after the other, so large caches get more blocks.  What a step with a rebuild takes
 // longer than one without, us, kernels of their own (2048 blocks each) / 256 blocks inside / 2048 inside: 3e5 slots 45 /
 // 26 / 42, 1e6 100 / 82 / 84, 8e6 720 / 820 / 690.
@@ -331,9 +331,8 @@ __device__ __forceinline__ void ctr_start(Ctr* cur, const Ctr* prev, const int* 
 }
 
 // The counters and the index rebuild as kernels of their own: with a hashed index, for batches prepared by one
-// block and where the unique passes have a stream of their own.  They read the flag and the watermark from the
-// previous step's counters, which no kernel changes any more (on the very first step prev == cur and both fields
-// are zero before and after).
+// block and empty ones.  They read the flag and the watermark from the previous step's counters, which no kernel
+// changes any more (on the very first step prev == cur and both fields are zero before and after).
 __global__ __launch_bounds__(256) void k_ctr_init(Ctr* cur, const Ctr* prev, const int* n_unique,
                                                   int* n_invalid, IdxEntry* index, uint32_t hi,
                                                   int t) {
@@ -778,8 +777,7 @@ __device__ __forceinline__ void resolve_ids(const int64_t* __restrict__ unique_i
 // nres blocks resolve, the others count.  us one after the other / in one launch: 1024 x 39 positions 5.3 + 6.6 /
 // 5.7, 8192 x 26 with the hashed index 7.5 + 8.5 / 10.1, 16384 x 39 16.3 + 15.6 / 22.1, 65536 x 39 33.3 + 17.6 / 45.8,
 // 1.28e6 uniform ones 26.7 + 60.8 / 77.5, 8.9e6 in bags 146 + 48 / 178: what is saved is start-up and drain, the random
-// accesses of the two add up.  Where the unique passes have a stream of their own, they are launched apart:
-// nres = 0, or a grid of nres blocks.
+// accesses of the two add up.
 struct RankArgs {
   const int* hslot; const int* uvid; int n; int* inverse; int* cnt; int* cnt_rep; int nrep; int* rank; unsigned* first;
 };
