@@ -109,6 +109,7 @@ struct StepCtx {
   bool copies_on_main = false;        // this step's copies run on the main stream
   bool told = false;                  // ev_prepared was completed by the grouping pass's own dispatch
   bool grouping_due = false;          // lookahead 0: the grouping pass goes out with sfc_fetch_misses
+  bool ungrouped = false;             // prepared without its grouping (see group_now)
   SortGeom sg{};                      // shape of the step's counting and grouping passes
   bool joined = false;                // the main stream is behind the side-stream launch of the step's copies
   // pipelined mode: the second launch of the Host copies, due on the main stream behind the
@@ -146,11 +147,8 @@ struct sfc_cache {
   unsigned* first = nullptr;                    // [max_ids / 32 + ..] bit per position: first appearance of its id; zero between steps
   int *tile_lt = nullptr, *tile_eq = nullptr;   // [C / kPosChunk + 1]
   int* tile_miss = nullptr;                     // [max_ids / kVidTile + 1]
-  // positions per virtual id [max_ids] and its copies for the lowest virtual ids [kHotRep, kHotBins]:
-  // two sets, used by steps of even / odd number, so that the unique passes of a step can run
-  // beside the previous step's miss assignment and grouping, which still read that step's counts
-  int* cnt2[2] = {nullptr, nullptr};
-  int* cnt_rep2[2] = {nullptr, nullptr};
+  // positions per virtual id [max_ids] and its copies for the lowest virtual ids [kHotRep, kHotBins] (zero between steps)
+  int *cnt = nullptr, *cnt_rep = nullptr;
   int* cur_rep = nullptr;                       // [kHotRep, kHotBins] group cursors of the lowest virtual ids, one per copy
   int* n_unique = nullptr;                      // unique ids of the step whose unique passes ran last
   int* pos2bag = nullptr;                       // [max_ids] multi-hot: bag of each position
@@ -173,6 +171,7 @@ struct sfc_cache {
   int t = 0;                                    // steps prepared so far
   bool updated_once = false;                    // an update has been enqueued: resident rows may differ from the Host table's
   int last_prepared = -1;                       // context of the most recent sfc_prepare
+  int served = 0;                               // steps given up since a gradient came last, up to kServing
   // profiling
   int prof = 0;                                 // 0 off, 1 step calls, 2 also the kernels inside them
   std::vector<EventPair> pending[P_N], spare;
@@ -435,9 +434,14 @@ int seg_launch(sfc_cache* c, StepCtx* x, const float* d_grad, float* d_common, d
   return SFC_OK;
 }
 
+GroupArgs group_args(const sfc_cache* c, const StepCtx* x) {
+  return GroupArgs{x->ungrouped ? nullptr : c->cnt, c->cnt_rep, c->cur_rep, x->sg.bins, x->sg.nrep, c->tile_cnt, x->grp,
+                   x->cold_pay};
+}
+
 // The prepare's kernels behind the resolve: victims' plan (and sums and bags of the positions), victims' lists,
 // slots of the misses.  (Called where the resolve has run on c->prep; group_positions follows.)
-void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
+void plan_and_assign(sfc_cache* c, StepCtx* x) {
   hipStream_t s = c->prep;
   const int n = (int)x->n_ids;
   const SortGeom& sg = x->sg;
@@ -451,8 +455,8 @@ void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
   // plan, 102.6 otherwise.
   const bool beside_plan = !evicts || c->nctx == 1 || n < kBesidePlanMax;
   const int ft = beside_plan ? 1024 : 256;
-  const FoldArgs fo{cnt, cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, ft, kFoldThreads / ft)};
-  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag};
+  const FoldArgs fo{c->cnt, c->cnt_rep, sg.bins, sg.nrep, c->tile_cnt, x->ungrouped ? 0 : grid_for(n, ft, kFoldThreads / ft)};
+  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, x->ungrouped ? nullptr : c->pos2bag, 1};
   const int riders = fo.folds + (n > 0 && x->d_offsets ? (int)((x->n_bags + ft - 1) / ft) : 0);
   hipLaunchKernelGGL(k_plan, dim3(1 + (beside_plan ? riders : 0)), dim3(1024), 0, s, c->tile_miss, c->age_hist,
                      c->tile_reuse, c->hist, x->t, c->cfg.lookahead, (int)c->C, c->hi, c->dmap ? 1 : 0, x->ctr, fo, bags);
@@ -464,8 +468,7 @@ void plan_and_assign(sfc_cache* c, StepCtx* x, int* cnt, int* cnt_rep) {
                        c->tile_eq, x->victim_slot, x->victim_id, x->ctr, c->dmap, c->index, c->hi);
   }
   const int gv = grid_for(n, kVidTile, kGridCap);
-  hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, x->d_unique, cnt, cnt_rep,
-                     c->cur_rep, sg.bins, sg.nrep, c->tile_cnt, x->grp, x->cold_pay, c->tile_miss,
+  hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, x->d_unique, group_args(c, x), c->tile_miss,
                      x->victim_slot, x->d_slot, x->d_miss, x->miss_row, x->miss_id, x->boff, c->slot_id,
                      c->stamp, c->index, c->hi, c->dmap, x->t, (int)c->C, c->tile_reuse, x->ctr);
 }
@@ -497,6 +500,38 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
   x->told = tells;
   if (extra) return prof_end(c, P_PREPARE, s, &ep);
   return SFC_OK;
+}
+
+// Lookahead 0: a cache that has given up this many steps in a row without a gradient in between serves lookups, and
+// its batches beyond the one-block prepare are prepared without the grouping of their positions, which the backward
+// half alone reads: counts and ranks, sums, bags, starts of the groups and the grouping pass.  The
+// gather then goes from a position by its virtual id to the slot.  A gradient that comes all the same (sfc_segment_sum,
+// sfc_backward_update) has its step grouped first (group_now), and the following ones are grouped by their prepares again.
+// (Not after the first step that is given up: programs look at a few batches before they train.  Not while the
+// stream is captured: what is recorded may be launched at any time.)  us a pass looked up and given up, every row
+// resident, grouped / not: 53e3 bags of 1 to 10 ids, dim 128, 81.3 / 68.7; 852e3 of dim 16 316 / 217; 400e3 of 1 to 20 of dim 32 297 / 229;
+// one-hot 8e3 of dim 16 37 / 32, 639e3 of dim 16 88 / 65.5, 2.56e6 of dim 32 233 / 172; 53e3 ids in bags, hashed, a third
+// resident, 49 / 42.  One step that is grouped late costs its prepare's saving and two launches more.
+constexpr int kServing = 64;
+
+int group_now(sfc_cache* c, StepCtx* x) {
+  c->served = 0;
+  if (!x->ungrouped) return SFC_OK;
+  x->ungrouped = false;
+  hipStream_t s = c->st;                        // (lookahead 0: the prepares run here as well)
+  const int n = (int)x->n_ids;
+  const SortGeom& sg = x->sg;
+  fill<int>(s, c->cnt, n, 0);
+  const RankArgs rank{nullptr, nullptr, n, x->d_inverse, c->cnt, c->cnt_rep, sg.nrep, x->pos_slot, nullptr};
+  auto count = sg.shift == 10 ? k_count_late<1, 1024> : sg.shift == 12 ? k_count_late<8, 512> : k_count_late<8, 1024>;
+  hipLaunchKernelGGL(count, dim3(sg.blocks), dim3(sg.shift == 12 ? 512 : 1024), 0, s, rank);
+  const FoldArgs fo{c->cnt, c->cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, 256, kFoldThreads / 256)};
+  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag, 0};
+  hipLaunchKernelGGL(k_fold_late, dim3(fo.folds + (x->d_offsets ? (unsigned)((x->n_bags + 255) / 256) : 0u)), dim3(256), 0, s,
+                     x->ctr, fo, bags);
+  hipLaunchKernelGGL(k_starts_late, dim3(grid_for(n, kVidTile, kGridCap)), dim3(256), 0, s, group_args(c, x),
+                     (const Ctr*)x->ctr);
+  return group_positions(c, x, false);
 }
 
 int sync_all(sfc_cache* c) {
@@ -696,16 +731,14 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     if ((rc = dalloc(c, &c->tile_lt, c->C / kPosChunk + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_eq, c->C / kPosChunk + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_miss, c->max_ids / kVidTile + 2))) goto bad;
-    if ((rc = dalloc(c, &c->cnt2[0], c->max_ids))) goto bad;
-    if ((rc = dalloc(c, &c->cnt2[1], c->max_ids))) goto bad;
+    if ((rc = dalloc(c, &c->cnt, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->n_unique, 1))) goto bad;
     if ((rc = dalloc(c, &c->pos2bag, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->tile_cnt, c->max_ids / kVidTile + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_reuse, c->max_ids / kVidTile + 2))) goto bad;
     if ((rc = dalloc(c, &c->age_hist, (int64_t)kAgeBins))) goto bad;
     if ((rc = dalloc(c, &c->n_invalid, 1))) goto bad;
-    if ((rc = dalloc(c, &c->cnt_rep2[0], (int64_t)kHotRep * kHotBins))) goto bad;
-    if ((rc = dalloc(c, &c->cnt_rep2[1], (int64_t)kHotRep * kHotBins))) goto bad;
+    if ((rc = dalloc(c, &c->cnt_rep, (int64_t)kHotRep * kHotBins))) goto bad;
     if ((rc = dalloc(c, &c->cur_rep, (int64_t)kHotRep * kHotBins))) goto bad;
     {
       const int64_t nw = seg_geom(c->D, c->max_ids).waves + 8;
@@ -743,8 +776,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     fill<int>(s, c->hist, (int64_t)c->hist_len, 0);
     fill<int>(s, c->age_hist, (int64_t)kAgeBins, 0);
     fill<int>(s, c->n_invalid, 1, 0);
-    fill<int>(s, c->cnt_rep2[0], (int64_t)kHotRep * kHotBins, 0);
-    fill<int>(s, c->cnt_rep2[1], (int64_t)kHotRep * kHotBins, 0);
+    fill<int>(s, c->cnt_rep, (int64_t)kHotRep * kHotBins, 0);
     fill<int>(s, c->n_unique, 1, 0);
     fill<int>(s, c->share_ticket, (int64_t)kMaxShares, 0);
     fill<int>(s, c->tile_reuse, c->max_ids / kVidTile + 2, 0);
@@ -813,8 +845,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   x->n_ids = n_ids; x->n_bags = n_bags; x->d_offsets = d_offsets;
   x->d_unique = d_unique_ids; x->d_inverse = d_inverse; x->d_slot = d_slot; x->d_miss = d_miss_vids;
   c->last_prepared = (int)(x - c->ctx);
-  int* const cnt = c->cnt2[x->t & 1];
-  int* const cnt_rep = c->cnt_rep2[x->t & 1];
+  x->ungrouped = c->nctx == 1 && !small && n_ids > 0 && c->served >= kServing && !capturing(s);
 
   EventPair ep{};
   int rc;
@@ -846,12 +877,12 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
       hipLaunchKernelGGL(k_uniq_count, dim3((nchunk + 3) / 4), dim3(256), 0, s, (const unsigned*)c->first,
                          nchunk, c->blk_cnt);
     hipLaunchKernelGGL(k_uniq_assign, dim3(nchunk + extra), dim3(256), 0, s, d_ids, c->V, c->hslot,
-                       (const unsigned*)c->first, n, counts, d_unique_ids, c->uvid, c->vid_hslot, cnt, c->n_unique,
+                       (const unsigned*)c->first, n, counts, d_unique_ids, c->uvid, c->vid_hslot, c->cnt, c->n_unique,
                        nchunk, x->ctr, x->t, (const Ctr*)prev->ctr, c->index, c->hi, (const int64_t*)c->slot_id);
   } else if (!small) {
     fill<int>(s, c->n_unique, 1, 0);
   }
-  const RankArgs rank{c->hslot, c->uvid, n, d_inverse, cnt, cnt_rep, sg.nrep, x->pos_slot, c->first};
+  const RankArgs rank{c->hslot, c->uvid, n, d_inverse, x->ungrouped ? nullptr : c->cnt, c->cnt_rep, sg.nrep, x->pos_slot, c->first};
   const ResolveArgs res{d_unique_ids, c->vid_hslot, c->utab, c->wide ? 1 : 0, c->index, c->hi, c->dmap, c->stamp,
                         c->hist, x->t, d_slot, c->tile_miss, c->age_hist, x->ctr,
                         start_inside ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid};
@@ -873,7 +904,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
     a.index = c->index; a.hi = c->hi; a.dmap = c->dmap;
     a.stamp = c->stamp; a.slot_id = c->slot_id; a.hist = c->hist;
     a.t = x->t; a.lookahead = c->cfg.lookahead; a.C = (int)c->C; a.boff = x->boff;
-    a.cnt = cnt; a.tile_miss = c->tile_miss; a.age_hist = c->age_hist;
+    a.cnt = c->cnt; a.tile_miss = c->tile_miss; a.age_hist = c->age_hist;
     a.grp = x->grp; a.cold_pay = x->cold_pay; a.perm64 = x->perm64; a.pos_slot = x->pos_slot;
     a.victim_slot = x->victim_slot; a.victim_id = x->victim_id; a.miss_row = x->miss_row; a.miss_id = x->miss_id;
     a.ctr = x->ctr; a.prev = c->dmap ? prev->ctr : nullptr;
@@ -884,10 +915,10 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   } else {
     hipLaunchKernelGGL(rank_resolve, dim3(nres + ncount), dim3(rt), 0, s, rank, res, nres);
   }
-  x->grouping_due = !whole && c->nctx == 1;
+  x->grouping_due = !whole && c->nctx == 1 && !x->ungrouped;
   x->told = false;
   if (!whole) {
-    plan_and_assign(c, x, cnt, cnt_rep);
+    plan_and_assign(c, x);
     if (c->nctx > 1 && (rc = group_positions(c, x, false))) return rc;
   }
   if (c->nctx > 1 && !x->told) HIPCHK(hipEventRecord(x->ev_prepared, s));
@@ -947,20 +978,22 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
     if (total >= kWarmMinChunks)
       LAUNCH_TIMED_X(c, P_LOOKUP, true, true, k_warm_rows, dim3(grid_for(x->n_ids * c->d4, 2048, kWarmGrid)),
                      dim3(256), s, (const int*)x->d_slot, (const float4*)c->cw, c->d4, (int)c->C, x->boff,
-                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, (int)(x->n_ids / 4));
+                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, x->ungrouped ? 0 : (int)(x->n_ids / 4));
+    const int* const row_of_pos = x->ungrouped ? x->d_inverse : x->pos_slot;
     if (!x->d_offsets) {
       const int d4 = c->d4, sh = (d4 & (d4 - 1)) == 0 ? __builtin_ctz(d4) : -1;
       const int bpb = lookup_rows_per_block(d4);
-      LAUNCH_TIMED(c, P_LOOKUP, true, k_lookup_onehot,
-                   dim3((unsigned)((x->n_bags + bpb - 1) / bpb)), dim3(256), s,
-                   (const int*)x->pos_slot, (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, d4, sh, bpb);
+      auto kern = x->ungrouped ? k_lookup_onehot<true> : k_lookup_onehot<false>;
+      LAUNCH_TIMED(c, P_LOOKUP, true, kern, dim3((unsigned)((x->n_bags + bpb - 1) / bpb)), dim3(256), s, row_of_pos,
+                   (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, d4, sh, bpb, (const int*)x->d_slot, (int)c->C,
+                   x->boff);
     } else {
       const int G = 64 / c->d4 > 0 ? 64 / c->d4 : 1;          // bags per wavefront
       const int64_t per_block = 4 * (int64_t)G;
-      LAUNCH_TIMED(c, P_LOOKUP, true, k_lookup_bags,
-                   dim3((unsigned)((x->n_bags + per_block - 1) / per_block)), dim3(256), s,
-                   x->d_offsets, (const int*)x->pos_slot, (const float4*)c->cw, (float4*)d_out,
-                   (int)x->n_bags, c->d4, G, x->n_ids);
+      auto kern = x->ungrouped ? k_lookup_bags<true> : k_lookup_bags<false>;
+      LAUNCH_TIMED(c, P_LOOKUP, true, kern, dim3((unsigned)((x->n_bags + per_block - 1) / per_block)), dim3(256), s,
+                   x->d_offsets, row_of_pos, (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, c->d4, G, x->n_ids,
+                   (const int*)x->d_slot, (int)c->C, x->boff);
     }
   }
   HIPCHK(hipGetLastError());
@@ -975,7 +1008,7 @@ int sfc_segment_sum(sfc_cache* c, const float* d_grad, float* d_common_grad) {
   if ((x->n_bags > 0 && !d_grad) || !d_common_grad) return fail(SFC_EINVAL, "null buffer");
   if (((uintptr_t)d_grad | (uintptr_t)d_common_grad) & 15) return fail(SFC_EINVAL, "buffers must be 16-byte aligned");
   int rc;
-  if ((rc = rows_ready(c, x))) return rc;
+  if ((rc = rows_ready(c, x)) || (rc = group_now(c, x))) return rc;
   if ((rc = seg_launch(c, x, d_grad, d_common_grad, c->bp, c->bp_vid, true, false, nullptr))) return rc;
   HIPCHK(hipGetLastError());
   return SFC_OK;
@@ -1013,7 +1046,7 @@ int sfc_segment_sum_static(sfc_cache* c, const float* d_grad, float* d_common_gr
   // could create profiling events
   if (x->main_pending)
     return fail(SFC_ESTATE, "the step's rows are still due on the main stream: call sfc_lookup first");
-  if ((rc = join_copies(c, x))) return rc;
+  if ((rc = join_copies(c, x)) || (rc = group_now(c, x))) return rc;
   // every slot that k_seg_finish reads is written by k_seg_stream in the same call: nothing to clear
   double* bp = (double*)base;
   int* bp_vid = (int*)((unsigned char*)base + sums);
@@ -1030,7 +1063,7 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   if (x->n_bags > 0 && !d_grad) return fail(SFC_EINVAL, "null gradient");
   if ((uintptr_t)d_grad & 15) return fail(SFC_EINVAL, "gradient must be 16-byte aligned");
   int rc;
-  if ((rc = rows_ready(c, x))) return rc;
+  if ((rc = rows_ready(c, x)) || (rc = group_now(c, x))) return rc;
   c->updated_once = true;
   hipStream_t s = c->st;
   EventPair ep{};
@@ -1212,6 +1245,7 @@ int sfc_discard(sfc_cache* c) {
     return fail(SFC_ESTATE, "the step's copies wait for an older update: it cannot be given up yet");
   x->state = FREE;
   x->discarded = true;
+  if (c->served < kServing) ++c->served;
   return SFC_OK;
 }
 

@@ -448,6 +448,7 @@ inline SortGeom small_geom(int64_t n) {
   return g;
 }
 
+// hslot == nullptr: `inverse` is there already (k_count_late).  cnt == nullptr: that is all (see group_now in the host code).
 template <int kPer, int kT>
 __device__ __forceinline__ void count_positions(const int* __restrict__ hslot, const int* __restrict__ uvid, int n,
                                                 int* __restrict__ inverse, int* cnt, int* cnt_rep, int nrep,
@@ -455,25 +456,30 @@ __device__ __forceinline__ void count_positions(const int* __restrict__ hslot, c
                                                 int* lh) {
   // the marks of first appearances have been read: all zero again for the next batch
   static_assert(kPer <= 32 && kT * kPer % 32 == 0, "whole words of marks per block");
-  if ((int)threadIdx.x < kT * kPer / 32 && blk * kT * kPer + (int)threadIdx.x * 32 < n)
+  if (hslot && (int)threadIdx.x < kT * kPer / 32 && blk * kT * kPer + (int)threadIdx.x * 32 < n)
     first[blk * (kT * kPer / 32) + threadIdx.x] = 0;
-  for (int i = threadIdx.x; i < kHotBins; i += kT) lh[i] = 0;
+  if (cnt)
+    for (int i = threadIdx.x; i < kHotBins; i += kT) lh[i] = 0;
   const int base = blk * kT * kPer;
   int hv[kPer], vv[kPer], rr[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {              // kPer loads in flight per level of indirection
     const int p = base + j * kT + (int)threadIdx.x;
-    hv[j] = p < n ? hslot[p] : -1;
+    hv[j] = p < n ? (hslot ? hslot[p] : inverse[p]) : -1;
   }
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) vv[j] = hv[j] >= 0 ? uvid[hv[j]] : -1;
+  for (int j = 0; j < kPer; ++j) vv[j] = hslot && hv[j] >= 0 ? uvid[hv[j]] : hv[j];
+  if (hslot) {
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+      if (vv[j] >= 0) inverse[base + j * kT + (int)threadIdx.x] = vv[j];
+  }
+  if (!cnt) return;
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
-    const int p = base + j * kT + (int)threadIdx.x;
     const int v = vv[j];
     if (v >= 0) {
-      inverse[p] = v;
       rr[j] = v < kHotBins ? atomicAdd(&lh[v], 1) : atomicAdd(&cnt[v], 1);
     }
   }
@@ -509,7 +515,8 @@ __device__ __forceinline__ void count_positions(const int* __restrict__ hslot, c
 // one that starts at or before it (six steps of a search in LDS).  With a thread per bag every store
 // touched a line of its own: 38 us for 852e3 bags of 1 to 20 ids, 17 this way.  A wavefront that has seen a
 // violation falls back to a loop per bag.
-// starts: a word of LDS per thread, used within the wavefront alone.
+// starts: a word of LDS per thread, used within the wavefront alone.  pos2bag == nullptr: the check alone; ctr ==
+// nullptr: without the check's tally (it has been made).
 __device__ __forceinline__ void bags_of_positions(const int64_t* __restrict__ offsets, int n_bags, int n,
                                                   int* __restrict__ pos2bag, Ctr* ctr, int blk, int* starts_all) {
   const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
@@ -524,11 +531,12 @@ __device__ __forceinline__ void bags_of_positions(const int64_t* __restrict__ of
   }
   starts[lane] = r.lo;
   const uint64_t m = __ballot(bad);
-  if (m && lane == 0) {
+  if (m && lane == 0 && ctr) {
     atomicAdd(&ctr->bad_offsets, __popcll(m));
     volatile HostStatus* h = ctr->hstat;
     if (h) h->bad_offsets_step = ctr->t;
   }
+  if (!pos2bag) return;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -872,13 +880,13 @@ __device__ __forceinline__ void plan_store(const Plan& pl, Ctr& ctr, int f) {
 // wavefronts, so large pipelined batches give them to the launch of the victims' count: see plan_and_assign.
 constexpr int kFoldThreads = 1 << 16;        // of them all, at most
 struct FoldArgs { int* cnt; const int* cnt_rep; int bins, nrep; int* tile_cnt; int folds; };
-struct BagArgs { const int64_t* offsets; int n_bags, n; int* pos2bag; };
+struct BagArgs { const int64_t* offsets; int n_bags, n; int* pos2bag; int tally; };
 
 // words: a word of LDS per thread
 template <int kT>
 __device__ __forceinline__ void fold_or_bags(const FoldArgs& fo, const BagArgs& bags, Ctr* ctr, int blk, int* words) {
   if (blk >= fo.folds) {
-    bags_of_positions(bags.offsets, bags.n_bags, bags.n, bags.pos2bag, ctr, blk - fo.folds, words);
+    bags_of_positions(bags.offsets, bags.n_bags, bags.n, bags.pos2bag, bags.tally ? ctr : nullptr, blk - fo.folds, words);
     return;
   }
   const int U = ctr->U;
@@ -1111,13 +1119,27 @@ __device__ __forceinline__ void publish(HostStatus* h, int lane, int t, int U, i
 // ascending slot order: victims (all below the watermark) first, then never-used slots from the
 // watermark up, then transient bypass rows C + j.
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict__ unique_ids,
-                                                        const int* __restrict__ cnt,
-                                                        int* __restrict__ cnt_rep,
-                                                        int* __restrict__ cur_rep, int bins, int nrep,
-                                                        const int* __restrict__ tile_cnt,
-                                                        int64_t* __restrict__ grp,
-                                                        int2* __restrict__ cold_pay,
+// The groups of the positions: cnt == nullptr where the batch is not grouped (see group_now in the host code).
+struct GroupArgs {
+  const int* cnt; int* cnt_rep; int* cur_rep; int bins, nrep; const int* tile_cnt; int64_t* grp; int2* cold_pay;
+};
+// Virtual id v (below U) has nv positions, which start at off: where its group and the copies of a hot bin start.
+__device__ __forceinline__ void group_start(const GroupArgs& g, int v, int nv, int off) {
+  g.grp[v] = ((int64_t)nv << 32) | (uint32_t)off;
+  g.cold_pay[v] = make_int2(-1, -1);            // the grouping pass fills in the cold groups' rows
+  if (v < g.bins) {                             // one group start per copy of a hot bin; copies back to zero
+    int at = off;
+#pragma unroll 8
+    for (int r = 0; r < g.nrep; ++r) {
+      const int c = g.cnt_rep[r * kHotBins + v];
+      g.cur_rep[r * kHotBins + v] = at;
+      at += c;
+      g.cnt_rep[r * kHotBins + v] = 0;
+    }
+  }
+}
+
+__global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict__ unique_ids, const GroupArgs gr,
                                                         const int* __restrict__ tile_moff,
                                                         const int* __restrict__ victim_slot,
                                                         int* __restrict__ slot_out,
@@ -1140,29 +1162,20 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
     const bool miss = v < U && slot_out[v] == kMissMark;
     const int first_miss = tile_moff[tile];
     int tot, more = 0;
-    for (int i = summed + (int)threadIdx.x; i < tile; i += 256) more += tile_cnt[i];
-    summed = tile;
-    // start of the group of virtual id v in perm64 = exclusive scan of cnt
-    const int nv = v < U ? cnt[v] : 0;
-    int off = nv, i = miss ? 1 : 0, tot_i;
-    block_excl_scan2(off, i, tot, tot_i, smem);
-    before += block_sum(more, smem);
-    off += before;
+    int i = miss ? 1 : 0, tot_i;
+    if (gr.cnt) {
+      for (int j = summed + (int)threadIdx.x; j < tile; j += 256) more += gr.tile_cnt[j];
+      summed = tile;
+      // start of the group of virtual id v in perm64 = exclusive scan of cnt
+      const int nv = v < U ? gr.cnt[v] : 0;
+      int off = nv;
+      block_excl_scan2(off, i, tot, tot_i, smem);
+      before += block_sum(more, smem);
+      if (v < U) group_start(gr, v, nv, before + off);
+    } else {
+      i = block_excl_scan(i, tot_i, smem);
+    }
     i += first_miss;
-    if (v < U) {
-      grp[v] = ((int64_t)nv << 32) | (uint32_t)off;
-      cold_pay[v] = make_int2(-1, -1);          // the grouping pass fills in the cold groups' rows
-    }
-    if (v < U && v < bins) {                    // one group start per copy of a hot bin; copies back to zero
-      int at = off;
-#pragma unroll 8
-      for (int r = 0; r < nrep; ++r) {
-        const int c = cnt_rep[r * kHotBins + v];
-        cur_rep[r * kHotBins + v] = at;
-        at += c;
-        cnt_rep[r * kHotBins + v] = 0;
-      }
-    }
     bool reused = false;
     if (miss) {
       miss_vids[i] = v;
@@ -1187,6 +1200,34 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
       const int nre = block_sum(reused ? 1 : 0, smem);
       if (threadIdx.x == 0) tile_reuse[tile] = nre;
     }
+  }
+}
+
+// The grouping of a batch that was prepared without it, when its gradient comes all the same: positions counted and
+// ranked, sums and bags, starts of the groups; the grouping pass follows.
+template <int kPer, int kT>
+__global__ __launch_bounds__(kT) void k_count_late(const RankArgs a) {
+  __shared__ int lds[kHotBins];
+  count_positions<kPer, kT>(nullptr, nullptr, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, nullptr,
+                            (int)blockIdx.x, lds);
+}
+__global__ __launch_bounds__(256) void k_fold_late(Ctr* ctr, const FoldArgs fo, const BagArgs bags) {
+  __shared__ int words[256];
+  fold_or_bags<256>(fo, bags, ctr, (int)blockIdx.x, words);
+}
+__global__ __launch_bounds__(256) void k_starts_late(const GroupArgs gr, const Ctr* ctr) {
+  __shared__ int smem[20];
+  const int U = ctr->U;
+  int before = 0, summed = 0;
+  for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
+    const int v = tile * kVidTile + (int)threadIdx.x;
+    int tot, more = 0;
+    for (int j = summed + (int)threadIdx.x; j < tile; j += 256) more += gr.tile_cnt[j];
+    summed = tile;
+    const int nv = v < U ? gr.cnt[v] : 0;
+    const int off = block_excl_scan(nv, tot, smem);
+    before += block_sum(more, smem);
+    if (v < U) group_start(gr, v, nv, before + off);
   }
 }
 

@@ -1140,3 +1140,55 @@ def test_what_is_recorded_writes_victims_back(n):
         assert c.verify() == [0, 0, 0, 0]
         hip.hipGraphExecDestroy(run); hip.hipGraphDestroy(graph)
         p.close()
+
+
+@pytest.mark.parametrize("n,bags,C,index_kind", [(6145, 0, 20_000, 0), (7000, 1500, 20_000, 2), (9001, 0, 9000, 1),
+                                                 (30_000, 4000, 12_000, 1), (270_000, 40_000, 20_000, 0)])
+def test_batches_of_a_cache_that_serves_lookups(n, bags, C, index_kind):
+    # 64 steps given up in a row: later batches are prepared without their grouping (ids through the virtual id to the
+    # slot in the gather, with and without evictions and bypass rows); a gradient has the step grouped after all
+    V, D = 20_000, 20
+    p = Pair(V, D, C=C, max_ids=n, max_bags=max(n, bags), index_kind=index_kind)
+    for t in range(64):
+        p.step(si.zipf_ids(40, 1.05, V, 77, t).numpy(), np.zeros((40, D), np.float32), update=False, check_state=False)
+
+    def batch(t):
+        ids = si.zipf_ids(n, 1.05, V, 78, t).numpy().copy()
+        ids[::997] = V + 5
+        off = None
+        if bags:
+            ends = np.sort(np.random.default_rng(t).integers(0, n + 1, bags - 1))
+            off = np.concatenate([[0], ends, [n]])
+        return ids, si.grads(bags or n, D, 78, t).numpy(), off
+
+    for t in range(2):
+        ids, grad, off = batch(t)
+        p.step(ids, grad, off, update=False)
+    if bags:
+        ids, grad, off = batch(2)
+        off[1] = -3
+        p.cache.prepare(torch.from_numpy(ids).cuda(), torch.from_numpy(off).cuda())
+        assert p.cache.stats()["n_bad_offsets"] == 1
+        with pytest.raises(p.sfc.SfcError):
+            p.cache.check()
+        p.cache.fetch_misses(); p.cache.discard()
+        p.orc.prepare(ids, np.maximum(off, 0)); p.orc.fetch_misses()
+    for t in range(3, 6):                     # (the first of them is grouped when its gradient comes)
+        ids, grad, off = batch(t)
+        p.step(ids, grad, off)
+    # once more, with the sum that takes its scratch from the library
+    for t in range(64):
+        p.step(si.zipf_ids(40, 1.05, V, 79, t).numpy(), np.zeros((40, D), np.float32), update=False, check_state=False)
+    ids, grad, off = batch(6)
+    c = p.cache
+    c.prepare(torch.from_numpy(ids).cuda(), None if off is None else torch.from_numpy(off).cuda())
+    p.orc.prepare(ids, off)
+    c.fetch_misses(); p.orc.fetch_misses()
+    out = torch.zeros(n, D, device="cuda")
+    d_grad = torch.from_numpy(grad).cuda()
+    p.sfc.sfc_segment_sum_static(c.h, d_grad, out)
+    assert_close(c.lookup().cpu().numpy(), p.orc.lookup(), "lookup behind the sum")
+    expect = p.orc.backward_update(grad, want_common_grad=True)
+    assert_close(out[:expect.shape[0]].cpu().numpy(), expect, "common gradient")
+    c.backward_update(d_grad)
+    p.finish(); p.close()
