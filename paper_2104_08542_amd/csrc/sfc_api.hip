@@ -363,6 +363,11 @@ bool swap_on_main(sfc_cache* c) {
 // resident row is then as it was read.  (A graph may be launched when that has changed: what is recorded writes.)
 bool writes_back(const sfc_cache* c) { return c->updated_once || capturing(c->st); }
 
+ScatterArgs scatter_args(const sfc_cache* c, const StepCtx* x) {
+  return ScatterArgs{x->d_inverse, x->d_offsets ? c->pos2bag : nullptr, (int)x->n_ids, x->grp, (int*)x->cold_pay, c->cur_rep,
+                     x->sg.bins, x->sg.shift, x->sg.nrep, x->perm64, x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags};
+}
+
 // One launch of the Host<->cache copies of a step on stream s (see k_swap_rows for the two
 // launches of pipelined mode).
 int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
@@ -384,9 +389,14 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
                        (float4*)c->ca, (int)c->C, x->boff, c->d4, c->s4, (const Ctr*)x->ctr);
   }
   const bool tells = !main_variant && s != c->st;
-  LAUNCH_THEN(tells && !prof_on(c, P_FETCH) && !capturing(s), x->ev_fetched, k_swap_rows, dim3(blocks), dim3(256), s,
-              x->miss_row, x->miss_id, x->victim_id, (float4*)c->cw, (float4*)c->ca, c->host,
-              c->d4, c->s4, (const Ctr*)x->ctr, x->bypass_from, main_variant, staged_at, write_back ? 1 : 0);
+  const SwapArgs args{x->miss_row, x->miss_id, x->victim_id, (float4*)c->cw, (float4*)c->ca, c->host, c->d4, c->s4,
+                      (const Ctr*)x->ctr, x->bypass_from, main_variant, staged_at, write_back ? 1 : 0};
+  if (x->grouping_due) {                      // (copies on the main stream: see sfc_fetch_misses)
+    x->grouping_due = false;
+    hipLaunchKernelGGL(k_swap_scatter, dim3(blocks + x->sg.blocks), dim3(256), 0, s, args, blocks, scatter_args(c, x));
+  } else {
+    LAUNCH_THEN(tells && !prof_on(c, P_FETCH) && !capturing(s), x->ev_fetched, k_swap_rows, dim3(blocks), dim3(256), s, args);
+  }
   HIPCHK(hipGetLastError());
   if ((rc = prof_end(c, P_FETCH, s, &ep))) return rc;
   if (main_variant) x->main_pending = false;
@@ -493,10 +503,7 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
   const int threads = sg.shift == 10 ? 256 : sg.shift == 12 ? 512 : 1024;
   // pipelined it is the last kernel of the prepare
   const bool tells = c->nctx > 1 && !capturing(s);
-  LAUNCH_THEN(tells, x->ev_prepared, scat, dim3(sg.blocks), dim3(threads), s, x->d_inverse,
-              x->d_offsets ? c->pos2bag : (const int*)nullptr, n, x->grp, (int*)x->cold_pay,
-              (const int*)c->cur_rep, sg.bins, sg.shift, sg.nrep, x->perm64,
-              (const int*)x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags);
+  LAUNCH_THEN(tells, x->ev_prepared, scat, dim3(sg.blocks), dim3(threads), s, scatter_args(c, x));
   x->told = tells;
   if (extra) return prof_end(c, P_PREPARE, s, &ep);
   return SFC_OK;
@@ -953,7 +960,9 @@ int sfc_fetch_misses(sfc_cache* c) {
     HIPCHK(hipEventRecord(x->ev_prepared, c->st));
   }
   int rc;
-  if (x->grouping_due && (rc = group_positions(c, x, true))) return rc;
+  // (on the main stream the grouping pass of a small batch goes out with the copies)
+  const bool with_copies = on_main && x->n_ids > 0 && x->sg.shift == 10 && !prof_on(c, P_PREPARE);
+  if (x->grouping_due && !with_copies && (rc = group_positions(c, x, true))) return rc;
   x->joined = on_main;
   if ((rc = launch_swap(c, x, on_main ? c->st : c->side, 0))) return rc;
   x->main_pending = x->main_after > 0;

@@ -570,16 +570,17 @@ __device__ __forceinline__ void bags_of_positions(const int64_t* __restrict__ of
 // A block takes the same positions as a block of the counting pass: their places in a hot group lie
 // side by side, and with half the positions per block two XCDs write into the same 128-byte lines
 // (169 against 120 us at 8.9e6 positions in bags).
+struct ScatterArgs {
+  const int *inverse, *pos2bag; int n; const int64_t* grp; int* cold_pay; const int* cur_rep; int bins, shift, nrep;
+  int64_t* perm64; const int* slot; int* rank_slot; int C, boff, n_bags;
+};
 template <int kScatPer, int kT>
-__global__ __launch_bounds__(kT) void k_scatter(const int* __restrict__ inverse,
-                                                  const int* __restrict__ pos2bag, int n,
-                                                  const int64_t* __restrict__ grp,
-                                                  int* __restrict__ cold_pay,
-                                                  const int* __restrict__ cur_rep, int bins, int shift,
-                                                  int nrep, int64_t* __restrict__ perm64,
-                                                  const int* __restrict__ slot,
-                                                  int* rank_slot, int C, int boff, int n_bags) {
-  const int base = blockIdx.x * kT * kScatPer + (int)threadIdx.x;
+__device__ __forceinline__ void scatter_positions(const int* __restrict__ inverse, const int* __restrict__ pos2bag, int n,
+                                                  const int64_t* __restrict__ grp, int* __restrict__ cold_pay,
+                                                  const int* __restrict__ cur_rep, int bins, int shift, int nrep,
+                                                  int64_t* __restrict__ perm64, const int* __restrict__ slot,
+                                                  int* rank_slot, int C, int boff, int n_bags, int blk) {
+  const int base = blk * kT * kScatPer + (int)threadIdx.x;
   int vv[kScatPer], rr[kScatPer], sv[kScatPer], pay[kScatPer];
   int64_t gr[kScatPer];
   // two levels of indirection, kScatPer loads in flight at each: position -> vid -> slot / group start
@@ -614,6 +615,15 @@ __global__ __launch_bounds__(kT) void k_scatter(const int* __restrict__ inverse,
     }
     perm64[(int)gr[j] + rr[j]] = e;
   }
+}
+template <int kScatPer, int kT>
+__device__ __forceinline__ void scatter_positions(const ScatterArgs& a, int blk) {
+  scatter_positions<kScatPer, kT>(a.inverse, a.pos2bag, a.n, a.grp, a.cold_pay, a.cur_rep, a.bins, a.shift, a.nrep, a.perm64,
+                                  a.slot, a.rank_slot, a.C, a.boff, a.n_bags, blk);
+}
+template <int kScatPer, int kT>
+__global__ __launch_bounds__(kT) void k_scatter(const ScatterArgs a) {
+  scatter_positions<kScatPer, kT>(a, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -4,6 +4,7 @@
 // 128-byte row (D = 32) is one request of 8 lanes.
 #pragma once
 #include "sfc_device.h"
+#include "sfc_prepare_kernels.h"
 
 namespace sfc {
 
@@ -135,13 +136,10 @@ __device__ __forceinline__ void link_rows(const int64_t* __restrict__ list, Row 
   }
 }
 
-__global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_row,
-                                                    const int64_t* __restrict__ miss_id,
-                                                    const int64_t* __restrict__ victim_id,
-                                                    float4* __restrict__ cw, float4* __restrict__ ca,
-                                                    HostRows h, int d4, int s4, const Ctr* ctr,
-                                                    int bypass_from, int main_variant,
-                                                    int staged_at, int write_back) {
+__device__ __forceinline__ void swap_rows(const int* __restrict__ miss_row, const int64_t* __restrict__ miss_id,
+                                          const int64_t* __restrict__ victim_id, float4* __restrict__ cw,
+                                          float4* __restrict__ ca, const HostRows& h, int d4, int s4, const Ctr* ctr,
+                                          int bypass_from, int main_variant, int staged_at, int write_back, int blocks) {
   const bool on_main = ctr->last_bypass >= bypass_from;      // the same in both launches
   if (on_main != (main_variant != 0)) return;
   __builtin_amdgcn_s_setprio(3);            // few waves, long round trips: issue ahead of the kernels beside them
@@ -157,12 +155,12 @@ __global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_
                       kSplitWriters);
     else
       link_rows<false>(miss_id, [&](unsigned k) { return (int64_t)miss_row[k]; }, M, cw, ca, h, d4, s4,
-                       (int)blockIdx.x - kSplitWriters, (int)gridDim.x - kSplitWriters);
+                       (int)blockIdx.x - kSplitWriters, blocks - kSplitWriters);
     return;
   }
   const int w2 = d4 + s4;                   // chunks of a row and of its optimizer state
   const int64_t total = (int64_t)M * w2;
-  const int64_t stride = (int64_t)gridDim.x * 256;
+  const int64_t stride = (int64_t)blocks * 256;
   // A thread's chunks are a serial chain, and with few blocks (see the launch) the chain is long:
   // the list entries of the next chunk are fetched while this chunk's Host read is in flight, so
   // that the chain is one Host round trip per chunk and nothing that waits on HBM.
@@ -194,6 +192,23 @@ __global__ __launch_bounds__(256) void k_swap_rows(const int* __restrict__ miss_
     cb[dst] = nv;
     i = inext;
   }
+}
+struct SwapArgs {
+  const int* miss_row; const int64_t *miss_id, *victim_id; float4 *cw, *ca; HostRows h; int d4, s4; const Ctr* ctr;
+  int bypass_from, main_variant, staged_at, write_back;
+};
+__device__ __forceinline__ void swap_rows(const SwapArgs& a, int blocks) {
+  swap_rows(a.miss_row, a.miss_id, a.victim_id, a.cw, a.ca, a.h, a.d4, a.s4, a.ctr, a.bypass_from, a.main_variant,
+            a.staged_at, a.write_back, blocks);
+}
+__global__ __launch_bounds__(256) void k_swap_rows(const SwapArgs a) { swap_rows(a, (int)gridDim.x); }
+
+// Copies on the main stream: the grouping pass of a batch below 2^18 ids, which they do not need, is further blocks of their
+// launch (few misses: what both take is start-up and dependent round trips, 5.8 us of grouping and 35 of copies at 1024 x 39
+// ids with bypass rows; a pass of those 102.0 -> 96.4 us).  From 2^18 ids on the grouping takes larger blocks.
+__global__ __launch_bounds__(256) void k_swap_scatter(const SwapArgs a, int swap_blocks, const ScatterArgs b) {
+  if ((int)blockIdx.x < swap_blocks) swap_rows(a, swap_blocks);
+  else scatter_positions<4, 256>(b, (int)blockIdx.x - swap_blocks);
 }
 
 __global__ __launch_bounds__(256) void k_flush(const int64_t* __restrict__ slot_id,
