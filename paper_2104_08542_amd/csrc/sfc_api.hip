@@ -75,6 +75,35 @@ int static_scratch(int device, void** out) {
   return SFC_OK;
 }
 
+// Streams of the pipelined prepares, one per GPU and main stream: the caches of a program that works on several tables from one
+// stream share it (their prepares all wait for that stream anyway, and while it is captured they all are).  A stream for each
+// cache puts more streams on the four hardware queues of a process, and more often a prepare or the main stream behind some
+// cache's copies.  Three caches in turn, us a step, a stream each / one: 65536 x 39 ids of dim 32 with lookahead 2 565 / 456 and,
+// created behind other caches, 564 / 596; 16384 x 39 of dim 16 326 / 348, 500e3 of dim 80 with Adam 837 / 867; draws of small
+// and middle sizes 151 / 138, 59 / 53, 37 / 31.  (The copies of one cache behind those of the other, by events: 456 -> 499.)
+struct PrepStream { hipStream_t s; int users; };
+std::mutex g_prep_mu;
+std::map<std::pair<int, hipStream_t>, PrepStream> g_prep;
+
+hipError_t prep_acquire(int device, hipStream_t main, hipStream_t* out) {
+  std::lock_guard<std::mutex> lk(g_prep_mu);
+  PrepStream& p = g_prep[std::make_pair(device, main)];       // (a new one: no users)
+  if (!p.users) {
+    const hipError_t e = hipStreamCreateWithFlags(&p.s, hipStreamNonBlocking);
+    if (e != hipSuccess) { g_prep.erase(std::make_pair(device, main)); return e; }
+  }
+  ++p.users;
+  *out = p.s;
+  return hipSuccess;
+}
+void prep_release(int device, hipStream_t main) {
+  std::lock_guard<std::mutex> lk(g_prep_mu);
+  auto it = g_prep.find(std::make_pair(device, main));
+  if (it == g_prep.end() || --it->second.users > 0) return;
+  (void)hipStreamDestroy(it->second.s);
+  g_prep.erase(it);
+}
+
 // life of a step context
 enum State { FREE = 0, PREPARED = 1, FETCHED = 2 };
 enum { P_PREPARE = 0, P_FETCH = 1, P_LOOKUP = 2, P_BACKWARD = 3, P_SEG_STREAM = 4, P_SEG_FINISH = 5,
@@ -128,7 +157,7 @@ struct sfc_cache {
   int D = 0, d4 = 0, nctx = 1;
   hipStream_t st = nullptr, side = nullptr;     // main stream; stream of the Host copies
   hipStream_t prep = nullptr;                   // stream of the prepare kernels
-  bool own_prep = false;                        // prep was created here (lookahead >= 1)
+  bool own_prep = false;                        // prep is one of g_prep (lookahead >= 1)
   hipEvent_t ev_tmp = nullptr;                  // cross-stream ordering inside one call
   // device memory
   float *cw = nullptr, *ca = nullptr;           // rows [(C + nctx * max_ids), D] and their optimizer state [.., S]
@@ -610,7 +639,7 @@ void sfc_cache_destroy(sfc_cache* c) {
     if (c->ctx[k].ev_prepared) (void)hipEventDestroy(c->ctx[k].ev_prepared);
     if (c->ctx[k].ev_fetched) (void)hipEventDestroy(c->ctx[k].ev_fetched);
   }
-  if (c->own_prep && c->prep) (void)hipStreamDestroy(c->prep);
+  if (c->own_prep && c->prep) prep_release(c->device, c->st);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->hstat) (void)hipHostFree(c->hstat);
   delete c;
@@ -697,7 +726,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
   // 700e3 in bags of dim 32 145 -> 123 / 128 -> 129.
   c->prep = cfg->lookahead == 0 ? c->st : c->side;
   if (cfg->lookahead >= 1 && cfg->policy != SFC_POLICY_PREFETCH) {
-    if ((e = hipStreamCreateWithFlags(&c->prep, hipStreamNonBlocking)) != hipSuccess) {
+    if ((e = prep_acquire(c->device, c->st, &c->prep)) != hipSuccess) {
       c->prep = nullptr;
       rc = fail(SFC_EHIP, "hipStreamCreate", e); goto bad;
     }

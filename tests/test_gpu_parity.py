@@ -1192,3 +1192,55 @@ def test_batches_of_a_cache_that_serves_lookups(n, bags, C, index_kind):
     assert_close(out[:expect.shape[0]].cpu().numpy(), expect, "common gradient")
     c.backward_update(d_grad)
     p.finish(); p.close()
+
+
+@pytest.mark.parametrize("lookahead", [1, 2])
+def test_pipelined_caches_of_one_stream_in_turn(lookahead):
+    # they share the stream of their prepares; one of them is closed on the way and another one created
+    V, D, n = 40_000, 8, 20_000
+    sizes = [n, 3000, 12_000, n, 7000, 16_000, n, 2000]
+
+    class Run:
+        def __init__(self, k):
+            self.p = Pair(V, D, C=9000, max_ids=n, lookahead=lookahead, seed=5 + k)
+            self.batches = [(si.zipf_ids(m, 1.05, V, 90 + k, t), si.grads(m, D, 90 + k, t)) for t, m in enumerate(sizes)]
+            self.dev = [(i.to("cuda:0"), g.to("cuda:0")) for i, g in self.batches]
+            self.expect, self.outs, self.t = [], [], 0
+            for ids, grad in self.batches:
+                o = self.p.orc
+                o.prepare(ids.numpy()); o.fetch_misses()
+                self.expect.append(o.lookup()); o.backward_update(grad.numpy())
+            for t in range(lookahead):
+                self.load(t)
+
+        def load(self, t):
+            if t < len(sizes):
+                self.p.cache.prepare(self.dev[t][0]); self.p.cache.fetch_misses()
+
+        def step(self):
+            self.outs.append(self.p.cache.lookup())
+            self.load(self.t + lookahead)
+            self.p.cache.backward_update(self.dev[self.t][1])
+            self.t += 1
+
+        def end(self):
+            while self.t < len(sizes):
+                self.step()
+            torch.cuda.synchronize()
+            for t, out in enumerate(self.outs):
+                assert_close(out.cpu().numpy(), self.expect[t], "lookup of step %d" % t)
+            self.p.finish(); self.p.close()
+
+    torch.cuda.synchronize()
+    runs = [Run(k) for k in range(3)]
+    torch.cuda.synchronize()
+    for t in range(4):
+        for r in runs:
+            r.step()
+    runs.pop(1).end()
+    runs.append(Run(3))
+    for t in range(3):
+        for r in runs:
+            r.step()
+    for r in runs:
+        r.end()
