@@ -898,14 +898,17 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   // passes are: a dense index has no rebuild.  Otherwise both are kernels of their own.
   const bool start_inside = c->dmap || rebuild_inside;
   if (!small && n > 0) {
-    const int nub = (n + kUniqChunk - 1) / kUniqChunk;
+    const bool big = n >= kUniqBigFrom;
+    const int chunk = big ? kUniqChunkBig : kUniqChunk, nub = (n + chunk - 1) / chunk;
     if (c->wide) {
       WideTab tab{(UEntry*)c->utab, 0, c->V};
-      hipLaunchKernelGGL(k_uniq_insert<WideTab>, dim3(nub + extra), dim3(256), 0, s, d_ids, n, tab, hu, c->hslot,
+      auto insert = big ? k_uniq_insert<WideTab, kUniqChunkBig> : k_uniq_insert<WideTab, kUniqChunk>;
+      hipLaunchKernelGGL(insert, dim3(nub + extra), dim3(256), 0, s, d_ids, n, tab, hu, c->hslot,
                          c->first, c->n_invalid, nub, (const Ctr*)prev->ctr, c->index, c->hi);
     } else {
       PackedTab tab{c->utab, pos_bits(n), c->V};
-      hipLaunchKernelGGL(k_uniq_insert<PackedTab>, dim3(nub + extra), dim3(256), 0, s, d_ids, n, tab, hu, c->hslot,
+      auto insert = big ? k_uniq_insert<PackedTab, kUniqChunkBig> : k_uniq_insert<PackedTab, kUniqChunk>;
+      hipLaunchKernelGGL(insert, dim3(nub + extra), dim3(256), 0, s, d_ids, n, tab, hu, c->hslot,
                          c->first, c->n_invalid, nub, (const Ctr*)prev->ctr, c->index, c->hi);
     }
     const int* const counts = n > kCountMin ? c->blk_cnt : nullptr;

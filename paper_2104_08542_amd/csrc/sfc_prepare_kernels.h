@@ -29,8 +29,8 @@ constexpr int kVidTile = 256;     // virtual ids per tile in resolve / assign
 // of 134 at 8.9e6 in bags, 143 instead of 108 at 1.28e6 uniform ones.)
 // Same-address atomics serialise at the memory side (about 10 ns each on this chip), and the
 // hottest id of a power-law batch owns a fifth of all positions.  So each block first
-// deduplicates its kUniqChunk positions in an LDS table (key -> smallest position in the block) and
-// only the distinct keys of the block go to HBM, two per thread in flight.  There a plain load
+// deduplicates its positions in an LDS table (key -> smallest position in the block) and
+// only the distinct keys of the block go to HBM, all in flight.  There a plain load
 // comes first (the table entry of a key never changes once set, and a stale position can only be too
 // large), and an atomic is issued only when the load has not already seen the key / a small enough
 // position.
@@ -40,23 +40,25 @@ constexpr int kVidTile = 256;     // virtual ids per tile in resolve / assign
 // are resident from the start sleep a few microseconds first, and then their plain loads find the
 // frequent keys in the table with a smaller position than theirs.  (Nothing depends on the sleep being
 // long enough.)  us without the sleep / with the head in a launch of its own / this way: 58 / 35 / 29 at
-// 16384 x 39 positions, 80 / 47 / 42 at 65536 x 39, 30 / 28 / 20 at 5003 x 39, 95 / 109 / 98 at 1.28e6 uniform ones.
-// Fewer, larger blocks contend less and take as long (512 / 1024 / 2048 positions, 256 / 512 / 1024 threads, us a pass:
-// 5003 x 39 640 / 641 / 637, 16384 x 39 377 / 377 / 378, 65536 x 39 694 / 699 / 705, 8.9e6 in bags 1194 / 1200 / 1217).
+// 16384 x 39 positions, 80 / 47 / 42 at 65536 x 39, 30 / 28 / 20 at 5003 x 39, 95 / 109 / 98 at 1.28e6 uniform ones
+// (blocks of 512 positions).
 // hslot[p] = HBM table entry of position p.
 // first: one bit per position, set for the positions that hold their entry's smallest position in the
 // end, all zero before.  Whoever places a position in an entry flips its bit, and whoever replaces one
 // flips the bit of the position that was there too; flips commute, so the bits are right whatever the
 // order of the blocks.  A block's own flips go out as one atomic per 32 positions.
 // ---------------------------------------------------------------------------------------------
-constexpr int kUniqChunk = 512;    // positions per block (2048 with its 53 KB of LDS left 12 wavefronts per compute unit: 20 us slower)
-constexpr int kUniqPer = kUniqChunk / 256;
-constexpr int kLdsPer = 2 * kUniqChunk / 256;
-constexpr int kHeadBlocks = 64;    // blocks that go to the table at once
-constexpr int kHeadMin = 256;      // a grid of at most this many blocks does not sleep, and claims without a load first (12.5 against 15.3 us at 78)
+// Positions per block: 256, a key per thread, and from 2^22 positions on, where the grid is twenty rounds of resident
+// blocks, 512, whose blocks bring fewer copies of an id to the table.  The kernel alone, us, 512 / 256 positions (512 with a
+// sleep of five): 7000 13.5 / 9.1, 40e3 12.2 / 9.3, 100e3 14.9 / 12.5, 195e3 18.6 / 13.8, 291e3 20.5 / 15.6, 639e3 26.3 / 24.0, 1.28e6
+// uniform ones 98.8 / 87.6, 2.56e6 34.8 / 34.6 and (s = 1.05) 57.6 / 52.4, 5e6 73.6 / 73.9, 8.9e6 116 / 125.  128 positions, a grid of
+// twice as many blocks: 40e3 10.0, 291e3 17.8, 2.56e6 37.2.
+constexpr int kUniqChunk = 256, kUniqChunkBig = 512;
+constexpr int64_t kUniqBigFrom = (int64_t)1 << 22;
+constexpr int kHeadBlocks = 64;    // blocks that go to the table at once (128: the same; 256 21.1 against 15.8 us at 291e3)
+constexpr int kHeadMin = 512;      // a grid of at most this many blocks does not sleep, and claims without a load first (100e3 positions: 14.4 / 12.0)
 constexpr int kResidentBlocks = 2048;        // eight per compute unit
-constexpr int kHeadSleep = 5;      // times 2048 clocks, 4.3 us (3 / 5 / 7 / 10: 30 / 28.7 / 29 / 31 us at 16384 x 39)
-constexpr int kLdsTab = 2 * kUniqChunk;      // LDS table entries per block
+constexpr int kHeadSleep = 3;      // times 2048 clocks, 2.6 us (2 / 3 / 4 / 5: 15.5 / 15.6 / 16.3 / 16.9 us at 291e3, 25.0 / 24.0 / 24.7 / 26.0 at 639e3)
 
 template <typename T>
 __device__ __forceinline__ T coherent_load(const T* p) {
@@ -143,7 +145,7 @@ __device__ __forceinline__ void index_reinsert(IdxEntry* index, uint32_t hi,
   }
 }
 
-template <class Tab>
+template <class Tab, int kChunk>
 __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__ ids, int n, Tab tab,
                                                       uint32_t hu, int* __restrict__ hslot,
                                                       unsigned* first, int* __restrict__ n_invalid, int blocks,
@@ -152,15 +154,16 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
     if (prev->rebuild) index_clear(index, hi, (int)blockIdx.x - blocks, (int)gridDim.x - blocks);
     return;
   }
+  constexpr int kUniqPer = kChunk / 256, kLdsTab = 2 * kChunk, kLdsPer = kLdsTab / 256;
   __shared__ int64_t lkey[kLdsTab];
   __shared__ int lval[kLdsTab];               // smallest position of the key in this block; later its HBM entry
-  __shared__ unsigned short lst[kUniqChunk];  // occupied LDS entries, compacted
-  __shared__ unsigned flip[kUniqChunk / 32];  // bit per position of the block: placed in an entry by this block
+  __shared__ unsigned short lst[kChunk];      // occupied LDS entries, compacted
+  __shared__ unsigned flip[kChunk / 32];      // bit per position of the block: placed in an entry by this block
   __shared__ int smem[20];
   for (int i = threadIdx.x; i < kLdsTab; i += 256) { lkey[i] = kEmpty; lval[i] = kIntMax; }
-  if (threadIdx.x < kUniqChunk / 32) flip[threadIdx.x] = 0;
+  if (threadIdx.x < kChunk / 32) flip[threadIdx.x] = 0;
   const int64_t V = tab.V;
-  const int base = (int)blockIdx.x * kUniqChunk;
+  const int base = (int)blockIdx.x * kChunk;
   int ls[kUniqPer];
   int64_t idv[kUniqPer];
 #pragma unroll
@@ -283,7 +286,7 @@ __global__ __launch_bounds__(256) void k_uniq_insert(const int64_t* __restrict__
     }
   }
   __syncthreads();
-  if (threadIdx.x < kUniqChunk / 32 && flip[threadIdx.x])
+  if (threadIdx.x < kChunk / 32 && flip[threadIdx.x])
     atomicXor(&first[base / 32 + (int)threadIdx.x], flip[threadIdx.x]);
 #pragma unroll
   for (int j = 0; j < kUniqPer; ++j) {

@@ -1244,3 +1244,31 @@ def test_pipelined_caches_of_one_stream_in_turn(lookahead):
             r.step()
     for r in runs:
         r.end()
+
+
+@pytest.mark.parametrize("n", [6145, 131_072, 131_073, (1 << 22) - 1, 1 << 22, (1 << 22) + 300])
+def test_distinct_ids_where_the_insert_pass_changes_shape(n):
+    # blocks of 256 or 512 positions, grids that claim without a load first or let the head of the batch go ahead;
+    # ids of a power law, so that frequent ones meet in every block, and a batch of all distinct ones behind it
+    V = 5_000_000
+    import paper_2104_08542_amd as sfc
+    tab = sfc.HostTable(V, 4)
+    c = sfc.Cache(tab, V, n)
+    order = torch.randperm(V, device="cuda:0")[:n]
+    for ids in (si.zipf_ids(n, 1.05, V, 61, 0, "cuda:0"), order):
+        ids = ids.clone()
+        ids[n // 3] = V + 1
+        c.prepare(ids); c.fetch_misses()
+        st = c.stats()
+        x = torch.where(ids < V, ids, -1)
+        u, inv = torch.unique(x, return_inverse=True)
+        at = torch.full((u.numel(),), n, device="cuda:0").scatter_reduce(0, inv, torch.arange(n, device="cuda:0"), "amin")
+        rank = torch.empty_like(at)
+        by = torch.argsort(at)
+        rank[by] = torch.arange(u.numel(), device="cuda:0")
+        assert st["n_unique"] == u.numel() and st["n_invalid"] == 1
+        assert torch.equal(c.unique_ids[:u.numel()], u[by])
+        assert torch.equal(c.inverse[:n].long(), rank[inv])
+        c.discard()
+    assert c.verify() == [0, 0, 0, 0]
+    c.close(); tab.free()
