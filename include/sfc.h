@@ -109,8 +109,7 @@ typedef struct {
                                  sfc_backward_update of step t; they run on other streams while the
                                  main stream works on step t (the paper's pipeline of Data-Loader,
                                  Host-Manager and GPU-Worker stages): the prepare on a stream that
-                                 the library creates (one for all caches with the same `stream`),
-                                 the Host copies on side_stream.  Each
+                                 the library creates, the Host copies on side_stream.  Each
                                  further step of lookahead adds a step context, so that a prepare
                                  waits for an older update; it takes a bypass row with its state
                                  and 52 bytes of lists per id of max_ids_per_batch.  The caller

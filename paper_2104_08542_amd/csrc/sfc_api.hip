@@ -75,33 +75,61 @@ int static_scratch(int device, void** out) {
   return SFC_OK;
 }
 
-// Streams of the pipelined prepares, one per GPU and main stream: the caches of a program that works on several tables from one
-// stream share it (their prepares all wait for that stream anyway, and while it is captured they all are).  A stream for each
-// cache puts more streams on the four hardware queues of a process, and more often a prepare or the main stream behind some
-// cache's copies.  Three caches in turn, us a step, a stream each / one: 65536 x 39 ids of dim 32 with lookahead 2 565 / 456 and,
-// created behind other caches, 564 / 596; 16384 x 39 of dim 16 326 / 348, 500e3 of dim 80 with Adam 837 / 867; draws of small
-// and middle sizes 151 / 138, 59 / 53, 37 / 31.  (The copies of one cache behind those of the other, by events: 456 -> 499.)
-struct PrepStream { hipStream_t s; int users; };
-std::mutex g_prep_mu;
-std::map<std::pair<int, hipStream_t>, PrepStream> g_prep;
-
-hipError_t prep_acquire(int device, hipStream_t main, hipStream_t* out) {
-  std::lock_guard<std::mutex> lk(g_prep_mu);
-  PrepStream& p = g_prep[std::make_pair(device, main)];       // (a new one: no users)
-  if (!p.users) {
-    const hipError_t e = hipStreamCreateWithFlags(&p.s, hipStreamNonBlocking);
-    if (e != hipSuccess) { g_prep.erase(std::make_pair(device, main)); return e; }
-  }
-  ++p.users;
-  *out = p.s;
-  return hipSuccess;
+// The stream of a pipelined cache's prepares.  HIP puts the streams of a process on four hardware queues, and what stands
+// behind a step's Host copies in a queue waits for hundreds of microseconds: with the prepares in the queue of the main or the
+// side stream a step takes half as long again.  No call tells a stream's queue, so a few candidates are tried when the cache
+// is created: a kernel that waits for a moment on the one stream, an empty one on the other.  us a step of one cache that
+// is created behind other streams, four times, the first stream that comes / this way: 65536 x 39 ids of dim 32 with lookahead
+// 2 495, 738, 756, 495 / 491, 494, 494, 739 (there the caller's own two streams share a queue), 16384 x 39 of dim 16 458, 461, 319,
+// 353 / 277, 274, 273, 274, 8192 x 26 of dim 128 119, 170, 168, 124 / 116, 116, 117, 117.  (One stream for all caches of a main
+// stream: three caches in turn 456 to 704 us at 65536 x 39, 589 to 655 this way.)
+__global__ void k_hold(long long ticks) {
+  const long long t0 = wall_clock64();
+  for (int i = 0; i < (1 << 16) && wall_clock64() - t0 < ticks; ++i) __builtin_amdgcn_s_sleep(8);
 }
-void prep_release(int device, hipStream_t main) {
-  std::lock_guard<std::mutex> lk(g_prep_mu);
-  auto it = g_prep.find(std::make_pair(device, main));
-  if (it == g_prep.end() || --it->second.users > 0) return;
-  (void)hipStreamDestroy(it->second.s);
-  g_prep.erase(it);
+constexpr int kPrepTries = 4;                   // as many as there are hardware queues
+
+// Does work of stream b run while stream a is busy?  (Both have nothing to do.)
+bool side_by_side(hipStream_t a, hipStream_t b, hipEvent_t ea, hipEvent_t eb) {
+  bool yes = false;
+  for (int i = 0; i < 2 && !yes; ++i) {         // (the host may have been held up)
+    hipLaunchKernelGGL(k_hold, dim3(1), dim3(64), 0, a, 6000LL);          // 60 us of a clock of 100 MHz
+    if (hipEventRecord(ea, a) != hipSuccess) break;
+    hipLaunchKernelGGL(k_hold, dim3(1), dim3(64), 0, b, 0LL);
+    if (hipEventRecord(eb, b) != hipSuccess || hipEventSynchronize(eb) != hipSuccess) break;
+    yes = hipEventQuery(ea) == hipErrorNotReady;
+    if (hipEventSynchronize(ea) != hipSuccess) break;
+  }
+  (void)hipGetLastError();
+  return yes;
+}
+
+hipError_t choose_prep_stream(hipStream_t main, hipStream_t side, hipStream_t* out) {
+  hipStream_t s[kPrepTries] = {};
+  hipEvent_t ea = nullptr, eb = nullptr;
+  int n = 0, best = -1, most = -1;
+  hipError_t e = hipEventCreateWithFlags(&ea, hipEventDisableTiming);
+  if (e == hipSuccess) e = hipEventCreateWithFlags(&eb, hipEventDisableTiming);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_hold, dim3(1), dim3(64), 0, main, 0LL);          // its code is loaded
+    e = hipStreamSynchronize(main);
+  }
+  // (a side stream that the caller has given work is left alone)
+  const bool ask_side = e == hipSuccess && hipStreamQuery(side) == hipSuccess;
+  (void)hipGetLastError();
+  while (e == hipSuccess && n < kPrepTries && most < 3) {
+    if ((e = hipStreamCreateWithFlags(&s[n], hipStreamNonBlocking)) != hipSuccess) break;
+    const int clear = 2 * side_by_side(main, s[n], ea, eb) + (!ask_side || side_by_side(side, s[n], ea, eb));
+    if (clear > most) { most = clear; best = n; }
+    ++n;
+  }
+  for (int i = 0; i < n; ++i)
+    if (i != best) (void)hipStreamDestroy(s[i]);
+  if (ea) (void)hipEventDestroy(ea);
+  if (eb) (void)hipEventDestroy(eb);
+  if (best < 0) return e;
+  *out = s[best];
+  return hipSuccess;
 }
 
 // life of a step context
@@ -157,7 +185,7 @@ struct sfc_cache {
   int D = 0, d4 = 0, nctx = 1;
   hipStream_t st = nullptr, side = nullptr;     // main stream; stream of the Host copies
   hipStream_t prep = nullptr;                   // stream of the prepare kernels
-  bool own_prep = false;                        // prep is one of g_prep (lookahead >= 1)
+  bool own_prep = false;                        // prep was created here (lookahead >= 1)
   hipEvent_t ev_tmp = nullptr;                  // cross-stream ordering inside one call
   // device memory
   float *cw = nullptr, *ca = nullptr;           // rows [(C + nctx * max_ids), D] and their optimizer state [.., S]
@@ -639,7 +667,7 @@ void sfc_cache_destroy(sfc_cache* c) {
     if (c->ctx[k].ev_prepared) (void)hipEventDestroy(c->ctx[k].ev_prepared);
     if (c->ctx[k].ev_fetched) (void)hipEventDestroy(c->ctx[k].ev_fetched);
   }
-  if (c->own_prep && c->prep) prep_release(c->device, c->st);
+  if (c->own_prep && c->prep) (void)hipStreamDestroy(c->prep);
   for (void* p : c->allocs) (void)hipFree(p);
   if (c->hstat) (void)hipHostFree(c->hstat);
   delete c;
@@ -726,7 +754,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
   // 700e3 in bags of dim 32 145 -> 123 / 128 -> 129.
   c->prep = cfg->lookahead == 0 ? c->st : c->side;
   if (cfg->lookahead >= 1 && cfg->policy != SFC_POLICY_PREFETCH) {
-    if ((e = prep_acquire(c->device, c->st, &c->prep)) != hipSuccess) {
+    if ((e = choose_prep_stream(c->st, c->side, &c->prep)) != hipSuccess) {
       c->prep = nullptr;
       rc = fail(SFC_EHIP, "hipStreamCreate", e); goto bad;
     }

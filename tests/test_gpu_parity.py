@@ -1196,7 +1196,7 @@ def test_batches_of_a_cache_that_serves_lookups(n, bags, C, index_kind):
 
 @pytest.mark.parametrize("lookahead", [1, 2])
 def test_pipelined_caches_of_one_stream_in_turn(lookahead):
-    # they share the stream of their prepares; one of them is closed on the way and another one created
+    # one of them is closed on the way and another one created
     V, D, n = 40_000, 8, 20_000
     sizes = [n, 3000, 12_000, n, 7000, 16_000, n, 2000]
 
