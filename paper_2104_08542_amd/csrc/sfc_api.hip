@@ -167,6 +167,7 @@ struct StepCtx {
   bool told = false;                  // ev_prepared was completed by the grouping pass's own dispatch
   bool grouping_due = false;          // lookahead 0: the grouping pass goes out with sfc_fetch_misses
   bool ungrouped = false;             // prepared without its grouping (see group_now)
+  bool by_vid = false;                // ... and pos_slot is not there either
   SortGeom sg{};                      // shape of the step's counting and grouping passes
   bool joined = false;                // the main stream is behind the side-stream launch of the step's copies
   // pipelined mode: the second launch of the Host copies, due on the main stream behind the
@@ -578,10 +579,18 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
 // resident, 49 / 42.  One step that is grouped late costs its prepare's saving and two launches more.
 constexpr int kServing = 64;
 
+// Is the row of every position of an ungrouped batch written down before the gather?  The gather of bags reads positions
+// again and again ahead of its rows, where another level costs more than a pass over the positions (beside the copies,
+// where these have the side stream); the one-hot gather reads each once.  us a pass, through the virtual id / written down:
+// 53e3 bags of 1 to 10 ids, dim 128, 65.3 / 60.0, 400e3 281 / 227, 400e3 of 1 to 20, dim 32, 234 / 214, 852e3 of dim 16 222 / 215,
+// 556e3 of 1 to 8 of dim 80 over a cache of 3090 rows 488 / 448 (grouped 475), 20e3 of 1 to 5 40.4 / 41.8; one-hot 50e3 of dim 32 34.5 / 39.4,
+// 639e3 of dim 16 64.2 / 68.1, 2.56e6 of dim 32 169 / 177.
+bool rows_by_position(const StepCtx* x) { return x->d_offsets && x->n_ids >= (int64_t)1 << 17; }
+
 int group_now(sfc_cache* c, StepCtx* x) {
   c->served = 0;
   if (!x->ungrouped) return SFC_OK;
-  x->ungrouped = false;
+  x->ungrouped = x->by_vid = false;
   hipStream_t s = c->st;                        // (lookahead 0: the prepares run here as well)
   const int n = (int)x->n_ids;
   const SortGeom& sg = x->sg;
@@ -909,7 +918,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   x->n_ids = n_ids; x->n_bags = n_bags; x->d_offsets = d_offsets;
   x->d_unique = d_unique_ids; x->d_inverse = d_inverse; x->d_slot = d_slot; x->d_miss = d_miss_vids;
   c->last_prepared = (int)(x - c->ctx);
-  x->ungrouped = c->nctx == 1 && !small && n_ids > 0 && c->served >= kServing && !capturing(s);
+  x->by_vid = x->ungrouped = c->nctx == 1 && !small && n_ids > 0 && c->served >= kServing && !capturing(s);
 
   EventPair ep{};
   int rc;
@@ -1021,6 +1030,11 @@ int sfc_fetch_misses(sfc_cache* c) {
   }
   int rc;
   // (on the main stream the grouping pass of a small batch goes out with the copies)
+  if (x->ungrouped && rows_by_position(x)) {
+    hipLaunchKernelGGL(k_pos_rows, dim3((unsigned)((x->n_ids + 1023) / 1024)), dim3(256), 0, c->st, (const int*)x->d_inverse,
+                       (const int*)x->d_slot, (int)x->n_ids, (int)c->C, x->boff, x->pos_slot);
+    x->by_vid = false;
+  }
   const bool with_copies = on_main && x->n_ids > 0 && x->sg.shift == 10 && !prof_on(c, P_PREPARE);
   if (x->grouping_due && !with_copies && (rc = group_positions(c, x, true))) return rc;
   x->joined = on_main;
@@ -1047,19 +1061,19 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
     if (total >= kWarmMinChunks)
       LAUNCH_TIMED_X(c, P_LOOKUP, true, true, k_warm_rows, dim3(grid_for(x->n_ids * c->d4, 2048, kWarmGrid)),
                      dim3(256), s, (const int*)x->d_slot, (const float4*)c->cw, c->d4, (int)c->C, x->boff,
-                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, x->ungrouped ? 0 : (int)(x->n_ids / 4));
-    const int* const row_of_pos = x->ungrouped ? x->d_inverse : x->pos_slot;
+                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, x->by_vid ? 0 : (int)(x->n_ids / 4));
+    const int* const row_of_pos = x->by_vid ? x->d_inverse : x->pos_slot;
     if (!x->d_offsets) {
       const int d4 = c->d4, sh = (d4 & (d4 - 1)) == 0 ? __builtin_ctz(d4) : -1;
       const int bpb = lookup_rows_per_block(d4);
-      auto kern = x->ungrouped ? k_lookup_onehot<true> : k_lookup_onehot<false>;
+      auto kern = x->by_vid ? k_lookup_onehot<true> : k_lookup_onehot<false>;
       LAUNCH_TIMED(c, P_LOOKUP, true, kern, dim3((unsigned)((x->n_bags + bpb - 1) / bpb)), dim3(256), s, row_of_pos,
                    (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, d4, sh, bpb, (const int*)x->d_slot, (int)c->C,
                    x->boff);
     } else {
       const int G = 64 / c->d4 > 0 ? 64 / c->d4 : 1;          // bags per wavefront
       const int64_t per_block = 4 * (int64_t)G;
-      auto kern = x->ungrouped ? k_lookup_bags<true> : k_lookup_bags<false>;
+      auto kern = x->by_vid ? k_lookup_bags<true> : k_lookup_bags<false>;
       LAUNCH_TIMED(c, P_LOOKUP, true, kern, dim3((unsigned)((x->n_bags + per_block - 1) / per_block)), dim3(256), s,
                    x->d_offsets, row_of_pos, (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, c->d4, G, x->n_ids,
                    (const int*)x->d_slot, (int)c->C, x->boff);

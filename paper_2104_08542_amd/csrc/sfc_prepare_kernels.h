@@ -1216,6 +1216,21 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   }
 }
 
+// Row per position of a batch that is not grouped (see rows_by_position in the host code).
+__global__ __launch_bounds__(256) void k_pos_rows(const int* __restrict__ inverse, const int* __restrict__ slot, int n, int C,
+                                                   int boff, int* __restrict__ pos_slot) {
+  constexpr int kPer = 4;
+  const int base = blockIdx.x * 256 * kPer + (int)threadIdx.x;
+  int v[kPer], s[kPer];
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) v[j] = base + j * 256 < n ? inverse[base + j * 256] : -1;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j) s[j] = v[j] >= 0 ? slot[v[j]] : -1;
+#pragma unroll
+  for (int j = 0; j < kPer; ++j)
+    if (v[j] >= 0) pos_slot[base + j * 256] = s[j] >= C ? s[j] + boff : s[j];
+}
+
 // The grouping of a batch that was prepared without it, when its gradient comes all the same: positions counted and
 // ranked, sums and bags, starts of the groups; the grouping pass follows.
 template <int kPer, int kT>

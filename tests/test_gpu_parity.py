@@ -1143,7 +1143,8 @@ def test_what_is_recorded_writes_victims_back(n):
 
 
 @pytest.mark.parametrize("n,bags,C,index_kind", [(6145, 0, 20_000, 0), (7000, 1500, 20_000, 2), (9001, 0, 9000, 1),
-                                                 (30_000, 4000, 12_000, 1), (270_000, 40_000, 20_000, 0)])
+                                                 (30_000, 4000, 12_000, 1), (270_000, 40_000, 20_000, 0),
+                                                 ((1 << 17) - 1, 30_000, 9000, 0), (1 << 17, 30_000, 9000, 0)])
 def test_batches_of_a_cache_that_serves_lookups(n, bags, C, index_kind):
     # 64 steps given up in a row: later batches are prepared without their grouping (ids through the virtual id to the
     # slot in the gather, with and without evictions and bypass rows); a gradient has the step grouped after all
