@@ -574,7 +574,7 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
 // sfc_backward_update) has its step grouped first (group_now), and the following ones are grouped by their prepares again.
 // (Not after the first step that is given up: programs look at a few batches before they train.  Not while the
 // stream is captured: what is recorded may be launched at any time.)  us a pass looked up and given up, every row
-// resident, grouped / not: 53e3 bags of 1 to 10 ids, dim 128, 81.3 / 68.7; 852e3 of dim 16 316 / 217; 400e3 of 1 to 20 of dim 32 297 / 229;
+// resident, grouped / not: 53e3 bags of 1 to 10 ids, dim 128, 81.3 / 60.0; 852e3 of dim 16 316 / 215; 400e3 of 1 to 20 of dim 32 298 / 214;
 // one-hot 8e3 of dim 16 37 / 32, 639e3 of dim 16 88 / 65.5, 2.56e6 of dim 32 233 / 172; 53e3 ids in bags, hashed, a third
 // resident, 49 / 42.  One step that is grouped late costs its prepare's saving and two launches more.
 constexpr int kServing = 64;
