@@ -230,6 +230,7 @@ struct sfc_cache {
   bool updated_once = false;                    // an update has been enqueued: resident rows may differ from the Host table's
   int last_prepared = -1;                       // context of the most recent sfc_prepare
   int served = 0;                               // steps given up since a gradient came last, up to kServing
+  bool recorded = false;                        // every batch is grouped by its prepare (see note_recording)
   // profiling
   int prof = 0;                                 // 0 off, 1 step calls, 2 also the kernels inside them
   std::vector<EventPair> pending[P_N], spare;
@@ -320,7 +321,9 @@ int prof_events(sfc_cache* c, EventPair* ep) {
 // (what is recorded into a graph is a launch and an event of their own)
 bool capturing(hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  return hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();                      // (no answer is not an error of the call that asks)
+  return true;
 }
 
 int prof_end(sfc_cache* c, int which, hipStream_t s, EventPair* ep) {
@@ -573,7 +576,7 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
 // gather then goes from a position by its virtual id to the slot.  A gradient that comes all the same (sfc_segment_sum,
 // sfc_backward_update) has its step grouped first (group_now), and the following ones are grouped by their prepares again.
 // (Not after the first step that is given up: programs look at a few batches before they train.  Not while the
-// stream is captured: what is recorded may be launched at any time.)  us a pass looked up and given up, every row
+// stream is captured, and not once a call that reads what a prepare leaves has been recorded: note_recording.)  us a pass looked up and given up, every row
 // resident, grouped / not: 53e3 bags of 1 to 10 ids, dim 128, 81.3 / 60.0; 852e3 of dim 16 316 / 215; 400e3 of 1 to 20 of dim 32 298 / 214;
 // one-hot 8e3 of dim 16 37 / 32, 639e3 of dim 16 88 / 65.5, 2.56e6 of dim 32 233 / 172; 53e3 ids in bags, hashed, a third
 // resident, 49 / 42.  One step that is grouped late costs its prepare's saving and two launches more.
@@ -587,7 +590,16 @@ constexpr int kServing = 64;
 // 639e3 of dim 16 64.2 / 68.1, 2.56e6 of dim 32 169 / 177.
 bool rows_by_position(const StepCtx* x) { return x->d_offsets && x->n_ids >= (int64_t)1 << 17; }
 
+// Called by what reads the rows of the positions or their groups.  If it is being recorded, its graph may be launched behind
+// any later prepare and reads the same arrays then; the host sees neither that nor that the steps it gives up have had a
+// gradient.  So all further batches are grouped by their prepares.  (Those of the one-block prepare are in any case, and what is recorded with
+// one of them fits no larger batch: the numbers of ids and bags are part of it.)
+void note_recording(sfc_cache* c, const StepCtx* x) {
+  if (c->nctx == 1 && !c->recorded && x->sg.bins > 0 && capturing(c->st)) c->recorded = true;
+}
+
 int group_now(sfc_cache* c, StepCtx* x) {
+  note_recording(c, x);
   c->served = 0;
   if (!x->ungrouped) return SFC_OK;
   x->ungrouped = x->by_vid = false;
@@ -918,7 +930,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   x->n_ids = n_ids; x->n_bags = n_bags; x->d_offsets = d_offsets;
   x->d_unique = d_unique_ids; x->d_inverse = d_inverse; x->d_slot = d_slot; x->d_miss = d_miss_vids;
   c->last_prepared = (int)(x - c->ctx);
-  x->by_vid = x->ungrouped = c->nctx == 1 && !small && n_ids > 0 && c->served >= kServing && !capturing(s);
+  x->by_vid = x->ungrouped = c->nctx == 1 && !small && n_ids > 0 && c->served >= kServing && !c->recorded && !capturing(s);
 
   EventPair ep{};
   int rc;
@@ -1053,6 +1065,7 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
   if ((uintptr_t)d_out & 15) return fail(SFC_EINVAL, "output must be 16-byte aligned");
   int rc;
   if ((rc = rows_ready(c, x))) return rc;
+  note_recording(c, x);
   hipStream_t s = c->st;
   const int64_t total = x->n_bags * c->d4;
   if (total > 0) {

@@ -1195,6 +1195,75 @@ def test_batches_of_a_cache_that_serves_lookups(n, bags, C, index_kind):
     p.finish(); p.close()
 
 
+class Recorded:
+    """The library calls of `calls`, recorded from stream s into a graph."""
+
+    def __init__(self, s, calls):
+        self.hip, vp = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p
+        self.st, self.graph, self.run = vp(s.cuda_stream), vp(), vp()
+        torch.cuda.synchronize()
+        assert self.hip.hipStreamBeginCapture(self.st, 2) == 0                   # relaxed
+        try:
+            calls()
+        finally:
+            rc = self.hip.hipStreamEndCapture(self.st, ctypes.byref(self.graph))
+        assert rc == 0
+        assert self.hip.hipGraphInstantiate(ctypes.byref(self.run), self.graph, None, None, ctypes.c_size_t(0)) == 0
+
+    def launch(self):
+        assert self.hip.hipGraphLaunch(self.run, self.st) == 0
+
+    def destroy(self):
+        torch.cuda.synchronize()
+        self.hip.hipGraphExecDestroy(self.run); self.hip.hipGraphDestroy(self.graph)
+
+
+def _bag_ends(n, bags, t):
+    ends = np.sort(np.random.default_rng(t).integers(0, n + 1, bags - 1))
+    return torch.from_numpy(np.concatenate([[0], ends, [n]]).astype(np.int64))
+
+
+@pytest.mark.parametrize("call", ["lookup", "sum", "static", "update"])
+@pytest.mark.parametrize("n,bags", [(6145, 0), (9000, 2000), (40_000, 0)])
+def test_recorded_calls_of_a_cache_that_serves_lookups(n, bags, call):
+    # the host does not see what a graph launches: a call that was recorded once, launched behind the prepare and the
+    # fetch of later steps, each of which is given up, finds what it reads there beyond the 64th of them
+    V, D, nb = 12_000, 8, bags or n
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        p = Pair(V, D, C=V, max_ids=n, max_bags=nb, side_stream=False)
+        c, o = p.cache, p.orc
+        d_off = torch.empty(bags + 1, dtype=torch.int64, device=p.dev) if bags else None
+        grad = si.grads(nb, D, 83, 0)
+        d_grad, out = grad.to(p.dev), torch.zeros(n, D, device=p.dev)
+        rec = None
+        for t in range(70):
+            ids, off = si.zipf_ids(n, 1.05, V, 83, t), _bag_ends(n, bags, t) if bags else None
+            if bags:
+                d_off.copy_(off)
+            c.prepare(ids.to(p.dev), d_off); c.fetch_misses()
+            o.prepare(ids.numpy(), None if off is None else off.numpy()); o.fetch_misses()
+            if rec is None:
+                rec = Recorded(s, {"lookup": lambda: c.lookup(out[:nb]), "sum": lambda: c.segment_sum(d_grad, out),
+                                   "static": lambda: p.sfc.sfc_segment_sum_static(c.h, d_grad, out),
+                                   "update": lambda: c.backward_update(d_grad)}[call])
+            out.fill_(-1.0)
+            rec.launch()
+            if call != "update" or t:         # (the recording of the update has ended its step)
+                c.discard()
+            torch.cuda.synchronize()
+            if call == "lookup":
+                assert_close(out[:nb].cpu().numpy(), o.lookup(), "lookup of step %d" % t)
+            else:
+                expect = o.backward_update(grad.numpy(), want_common_grad=True)
+                if call != "update":
+                    assert_close(out[:expect.shape[0]].cpu().numpy(), expect, "common gradient of step %d" % t)
+        rec.destroy()
+        if call == "update":
+            p.finish()
+        p.close()
+
+
 @pytest.mark.parametrize("lookahead", [1, 2])
 def test_pipelined_caches_of_one_stream_in_turn(lookahead):
     # one of them is closed on the way and another one created
