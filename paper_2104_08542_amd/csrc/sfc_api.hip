@@ -505,8 +505,8 @@ int seg_launch(sfc_cache* c, StepCtx* x, const float* d_grad, float* d_common, d
   return SFC_OK;
 }
 
-GroupArgs group_args(const sfc_cache* c, const StepCtx* x) {
-  return GroupArgs{x->ungrouped ? nullptr : c->cnt, c->cnt_rep, c->cur_rep, x->sg.bins, x->sg.nrep, c->tile_cnt, x->grp,
+GroupArgs group_args(const sfc_cache* c, const StepCtx* x, bool grouped) {
+  return GroupArgs{grouped ? c->cnt : nullptr, c->cnt_rep, c->cur_rep, x->sg.bins, x->sg.nrep, c->tile_cnt, x->grp,
                    x->cold_pay};
 }
 
@@ -539,7 +539,7 @@ void plan_and_assign(sfc_cache* c, StepCtx* x) {
                        c->tile_eq, x->victim_slot, x->victim_id, x->ctr, c->dmap, c->index, c->hi);
   }
   const int gv = grid_for(n, kVidTile, kGridCap);
-  hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, x->d_unique, group_args(c, x), c->tile_miss,
+  hipLaunchKernelGGL(k_assign_misses, dim3(gv), dim3(256), 0, s, x->d_unique, group_args(c, x, !x->ungrouped), c->tile_miss,
                      x->victim_slot, x->d_slot, x->d_miss, x->miss_row, x->miss_id, x->boff, c->slot_id,
                      c->stamp, c->index, c->hi, c->dmap, x->t, (int)c->C, c->tile_reuse, x->ctr);
 }
@@ -590,33 +590,46 @@ constexpr int kServing = 64;
 // 639e3 of dim 16 64.2 / 68.1, 2.56e6 of dim 32 169 / 177.
 bool rows_by_position(const StepCtx* x) { return x->d_offsets && x->n_ids >= (int64_t)1 << 17; }
 
-// Called by what reads the rows of the positions or their groups.  If it is being recorded, its graph may be launched behind
+// Called by what reads the rows of the positions or their groups: is it being recorded?  Then its graph may be launched behind
 // any later prepare and reads the same arrays then; the host sees neither that nor that the steps it gives up have had a
 // gradient.  So all further batches are grouped by their prepares.  (Those of the one-block prepare are in any case, and what is recorded with
 // one of them fits no larger batch: the numbers of ids and bags are part of it.)
-void note_recording(sfc_cache* c, const StepCtx* x) {
-  if (c->nctx == 1 && !c->recorded && x->sg.bins > 0 && capturing(c->st)) c->recorded = true;
+bool recording(sfc_cache* c, const StepCtx* x) {
+  if (c->nctx > 1 || x->sg.bins == 0 || (c->recorded && !x->ungrouped) || !capturing(c->st)) return false;
+  return c->recorded = true;
 }
 
+// What is only recorded has not run: the step stays as it is for the calls that follow, which do the same again if they come.
+// And launched behind a later step it does nothing: these kernels go by the number in the step's counters.
 int group_now(sfc_cache* c, StepCtx* x) {
-  note_recording(c, x);
+  const bool later = recording(c, x);
   c->served = 0;
   if (!x->ungrouped) return SFC_OK;
-  x->ungrouped = x->by_vid = false;
+  if (!later) x->ungrouped = x->by_vid = false;
   hipStream_t s = c->st;                        // (lookahead 0: the prepares run here as well)
   const int n = (int)x->n_ids;
   const SortGeom& sg = x->sg;
+  const Ctr* const ctr = x->ctr;
   fill<int>(s, c->cnt, n, 0);
   const RankArgs rank{nullptr, nullptr, n, x->d_inverse, c->cnt, c->cnt_rep, sg.nrep, x->pos_slot, nullptr};
   auto count = sg.shift == 10 ? k_count_late<1, 1024> : sg.shift == 12 ? k_count_late<8, 512> : k_count_late<8, 1024>;
-  hipLaunchKernelGGL(count, dim3(sg.blocks), dim3(sg.shift == 12 ? 512 : 1024), 0, s, rank);
+  hipLaunchKernelGGL(count, dim3(sg.blocks), dim3(sg.shift == 12 ? 512 : 1024), 0, s, rank, ctr, x->t);
   const FoldArgs fo{c->cnt, c->cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, 256, kFoldThreads / 256)};
   const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag, 0};
   hipLaunchKernelGGL(k_fold_late, dim3(fo.folds + (x->d_offsets ? (unsigned)((x->n_bags + 255) / 256) : 0u)), dim3(256), 0, s,
-                     x->ctr, fo, bags);
-  hipLaunchKernelGGL(k_starts_late, dim3(grid_for(n, kVidTile, kGridCap)), dim3(256), 0, s, group_args(c, x),
-                     (const Ctr*)x->ctr);
-  return group_positions(c, x, false);
+                     x->ctr, fo, bags, x->t);
+  hipLaunchKernelGGL(k_starts_late, dim3(grid_for(n, kVidTile, kGridCap)), dim3(256), 0, s, group_args(c, x, true), ctr, x->t);
+  auto scat = sg.shift == 10 ? k_scatter_late<4, 256> : sg.shift == 12 ? k_scatter_late<8, 512> : k_scatter_late<8, 1024>;
+  hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.shift == 10 ? 256 : sg.shift == 12 ? 512 : 1024), 0, s, scatter_args(c, x),
+                     ctr, x->t);
+  return SFC_OK;
+}
+
+// Row of every position of an ungrouped batch (see rows_by_position).
+void launch_pos_rows(sfc_cache* c, const StepCtx* x, bool recorded) {
+  auto kern = recorded ? k_pos_rows<true> : k_pos_rows<false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)((x->n_ids + 1023) / 1024)), dim3(256), 0, c->st, (const int*)x->d_inverse,
+                     (const int*)x->d_slot, (int)x->n_ids, (int)c->C, x->boff, x->pos_slot, (const Ctr*)x->ctr, x->t);
 }
 
 int sync_all(sfc_cache* c) {
@@ -1042,9 +1055,8 @@ int sfc_fetch_misses(sfc_cache* c) {
   }
   int rc;
   // (on the main stream the grouping pass of a small batch goes out with the copies)
-  if (x->ungrouped && rows_by_position(x)) {
-    hipLaunchKernelGGL(k_pos_rows, dim3((unsigned)((x->n_ids + 1023) / 1024)), dim3(256), 0, c->st, (const int*)x->d_inverse,
-                       (const int*)x->d_slot, (int)x->n_ids, (int)c->C, x->boff, x->pos_slot);
+  if (x->ungrouped && rows_by_position(x) && !capturing(c->st)) {
+    launch_pos_rows(c, x, false);
     x->by_vid = false;
   }
   const bool with_copies = on_main && x->n_ids > 0 && x->sg.shift == 10 && !prof_on(c, P_PREPARE);
@@ -1065,7 +1077,11 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
   if ((uintptr_t)d_out & 15) return fail(SFC_EINVAL, "output must be 16-byte aligned");
   int rc;
   if ((rc = rows_ready(c, x))) return rc;
-  note_recording(c, x);
+  bool by_vid = x->by_vid;
+  if (recording(c, x) && by_vid) {              // (a launch behind a later step reads the rows that its prepare has left)
+    launch_pos_rows(c, x, true);
+    by_vid = false;
+  }
   hipStream_t s = c->st;
   const int64_t total = x->n_bags * c->d4;
   if (total > 0) {
@@ -1074,19 +1090,19 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
     if (total >= kWarmMinChunks)
       LAUNCH_TIMED_X(c, P_LOOKUP, true, true, k_warm_rows, dim3(grid_for(x->n_ids * c->d4, 2048, kWarmGrid)),
                      dim3(256), s, (const int*)x->d_slot, (const float4*)c->cw, c->d4, (int)c->C, x->boff,
-                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, x->by_vid ? 0 : (int)(x->n_ids / 4));
-    const int* const row_of_pos = x->by_vid ? x->d_inverse : x->pos_slot;
+                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, by_vid ? 0 : (int)(x->n_ids / 4));
+    const int* const row_of_pos = by_vid ? x->d_inverse : x->pos_slot;
     if (!x->d_offsets) {
       const int d4 = c->d4, sh = (d4 & (d4 - 1)) == 0 ? __builtin_ctz(d4) : -1;
       const int bpb = lookup_rows_per_block(d4);
-      auto kern = x->by_vid ? k_lookup_onehot<true> : k_lookup_onehot<false>;
+      auto kern = by_vid ? k_lookup_onehot<true> : k_lookup_onehot<false>;
       LAUNCH_TIMED(c, P_LOOKUP, true, kern, dim3((unsigned)((x->n_bags + bpb - 1) / bpb)), dim3(256), s, row_of_pos,
                    (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, d4, sh, bpb, (const int*)x->d_slot, (int)c->C,
                    x->boff);
     } else {
       const int G = 64 / c->d4 > 0 ? 64 / c->d4 : 1;          // bags per wavefront
       const int64_t per_block = 4 * (int64_t)G;
-      auto kern = x->by_vid ? k_lookup_bags<true> : k_lookup_bags<false>;
+      auto kern = by_vid ? k_lookup_bags<true> : k_lookup_bags<false>;
       LAUNCH_TIMED(c, P_LOOKUP, true, kern, dim3((unsigned)((x->n_bags + per_block - 1) / per_block)), dim3(256), s,
                    x->d_offsets, row_of_pos, (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, c->d4, G, x->n_ids,
                    (const int*)x->d_slot, (int)c->C, x->boff);

@@ -1216,9 +1216,12 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   }
 }
 
-// Row per position of a batch that is not grouped (see rows_by_position in the host code).
+// Row per position of a batch that is not grouped (see rows_by_position in the host code).  kRecorded, and t here and below: the
+// step; where the counters are another step's, a graph has been launched that was recorded on this one: nothing to do.
+template <bool kRecorded>
 __global__ __launch_bounds__(256) void k_pos_rows(const int* __restrict__ inverse, const int* __restrict__ slot, int n, int C,
-                                                   int boff, int* __restrict__ pos_slot) {
+                                                   int boff, int* __restrict__ pos_slot, const Ctr* ctr, int t) {
+  if (kRecorded && ctr->t != t) return;
   constexpr int kPer = 4;
   const int base = blockIdx.x * 256 * kPer + (int)threadIdx.x;
   int v[kPer], s[kPer];
@@ -1232,19 +1235,22 @@ __global__ __launch_bounds__(256) void k_pos_rows(const int* __restrict__ invers
 }
 
 // The grouping of a batch that was prepared without it, when its gradient comes all the same: positions counted and
-// ranked, sums and bags, starts of the groups; the grouping pass follows.
+// ranked, sums and bags, starts of the groups, the grouping pass.
 template <int kPer, int kT>
-__global__ __launch_bounds__(kT) void k_count_late(const RankArgs a) {
+__global__ __launch_bounds__(kT) void k_count_late(const RankArgs a, const Ctr* ctr, int t) {
   __shared__ int lds[kHotBins];
+  if (ctr->t != t) return;
   count_positions<kPer, kT>(nullptr, nullptr, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, nullptr,
                             (int)blockIdx.x, lds);
 }
-__global__ __launch_bounds__(256) void k_fold_late(Ctr* ctr, const FoldArgs fo, const BagArgs bags) {
+__global__ __launch_bounds__(256) void k_fold_late(Ctr* ctr, const FoldArgs fo, const BagArgs bags, int t) {
   __shared__ int words[256];
+  if (ctr->t != t) return;
   fold_or_bags<256>(fo, bags, ctr, (int)blockIdx.x, words);
 }
-__global__ __launch_bounds__(256) void k_starts_late(const GroupArgs gr, const Ctr* ctr) {
+__global__ __launch_bounds__(256) void k_starts_late(const GroupArgs gr, const Ctr* ctr, int t) {
   __shared__ int smem[20];
+  if (ctr->t != t) return;
   const int U = ctr->U;
   int before = 0, summed = 0;
   for (int tile = blockIdx.x; tile * kVidTile < U; tile += gridDim.x) {
@@ -1257,6 +1263,10 @@ __global__ __launch_bounds__(256) void k_starts_late(const GroupArgs gr, const C
     before += block_sum(more, smem);
     if (v < U) group_start(gr, v, nv, before + off);
   }
+}
+template <int kScatPer, int kT>
+__global__ __launch_bounds__(kT) void k_scatter_late(const ScatterArgs a, const Ctr* ctr, int t) {
+  if (ctr->t == t) scatter_positions<kScatPer, kT>(a, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -1264,6 +1264,80 @@ def test_recorded_calls_of_a_cache_that_serves_lookups(n, bags, call):
         p.close()
 
 
+@pytest.mark.parametrize("call", ["lookup", "sum", "static", "update", "fetch"])
+@pytest.mark.parametrize("n,bags", [(6145, 0), (9000, 2000), (140_000, 9000), (270_000, 0)])
+def test_calls_recorded_on_a_step_that_is_not_grouped(n, bags, call):
+    # a call recorded on a step whose prepare left the grouping out has not run: eager calls before the launch do not
+    # count on it, the launch gives the same, and so do launches behind later steps, whose buffers may be others
+    V, D, nb = 12_000, 8, bags or n
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        p = Pair(V, D, C=V, max_ids=n, max_bags=nb, side_stream=False)
+        c, o = p.cache, p.orc
+        d_off = torch.empty(bags + 1, dtype=torch.int64, device=p.dev) if bags else None
+        grad = si.grads(nb, D, 87, 0)
+        d_grad, out, rows = grad.to(p.dev), torch.zeros(n, D, device=p.dev), torch.zeros(nb, D, device=p.dev)
+
+        def load(t, fetch=True):
+            ids, off = si.zipf_ids(n, 1.05, V, 87, t), _bag_ends(n, bags, t) if bags else None
+            if bags:
+                d_off.copy_(off)
+            c.prepare(ids.to(p.dev), d_off)
+            if fetch:
+                c.fetch_misses()
+            return ids.numpy(), None if off is None else off.numpy()
+
+        for t in range(64):
+            o.prepare(*load(t % 3)); o.fetch_misses()
+            c.discard()
+        o.prepare(*load(64, call != "fetch")); o.fetch_misses()
+        want = o.lookup()
+
+        def everything():
+            c.fetch_misses(); c.lookup(rows); c.segment_sum(d_grad, out)
+
+        rec = Recorded(s, {"lookup": lambda: c.lookup(rows), "sum": lambda: c.segment_sum(d_grad, out),
+                           "static": lambda: p.sfc.sfc_segment_sum_static(c.h, d_grad, out), "fetch": everything,
+                           "update": lambda: c.backward_update(d_grad)}[call])
+        if call == "fetch":                   # (the rows come with the launch)
+            rec.launch()
+        if call != "update":
+            assert_close(c.lookup().cpu().numpy(), want, "lookup before the launch")
+            common = c.segment_sum(d_grad)
+        rec.launch()
+        expect = o.backward_update(grad.numpy(), want_common_grad=True)
+        if call != "update":
+            assert_close(common[:expect.shape[0]].cpu().numpy(), expect, "common gradient before the launch")
+            assert_close(c.lookup().cpu().numpy(), want, "lookup behind the launch")
+            assert_close(c.segment_sum(d_grad)[:expect.shape[0]].cpu().numpy(), expect, "common gradient behind the launch")
+        if call in ("lookup", "fetch"):
+            assert_close(rows.cpu().numpy(), want, "recorded lookup")
+        if call in ("sum", "static", "fetch"):
+            assert_close(out[:expect.shape[0]].cpu().numpy(), expect, "recorded common gradient")
+        if call != "update":
+            c.backward_update(d_grad)
+        was = {}                              # (the earlier steps' buffers stay alive)
+        for t in (65, 66) if call != "fetch" else ():
+            if call != "update":              # (the update reads the caller's buffers)
+                c.bufs, was[t] = [p.sfc.StepBuffers(n, p.dev)], c.bufs
+                c._next = 0
+            o.prepare(*load(t)); o.fetch_misses()
+            want = o.lookup()
+            assert_close(c.lookup().cpu().numpy(), want, "lookup of step %d" % t)
+            out.fill_(-1.0); rows.fill_(-1.0)
+            rec.launch()
+            if call != "update":
+                assert_close(c.lookup().cpu().numpy(), want, "lookup of step %d, behind the launch" % t)
+            expect = o.backward_update(grad.numpy(), want_common_grad=True)
+            if call == "lookup":
+                assert_close(rows.cpu().numpy(), want, "recorded lookup of step %d" % t)
+            elif call != "update":
+                assert_close(out[:expect.shape[0]].cpu().numpy(), expect, "recorded common gradient of step %d" % t)
+            c.discard() if call == "update" else c.backward_update(d_grad)
+        rec.destroy()
+        p.finish(); p.close()
+
+
 @pytest.mark.parametrize("lookahead", [1, 2])
 def test_pipelined_caches_of_one_stream_in_turn(lookahead):
     # one of them is closed on the way and another one created
