@@ -307,7 +307,10 @@ int sfc_cache_state(sfc_cache* c, int64_t* h_slot_id, int32_t* h_stamp, float* h
  * (several kernels each) are bracketed by hipEvents on the stream they run on, so their times
  * include the launch latencies between the events (with lookahead >= 1 the prepare's events sit on
  * the library's stream.  With lookahead 0 the prepare's last kernel, the grouping,
- * is launched by sfc_fetch_misses; its time is added to the prepare's).  sfc_lookup is one kernel,
+ * is launched by sfc_fetch_misses; its time is added to the prepare's, and so is that of what a cache that serves
+ * lookups launches there, or with the gradient that comes all the same (see sfc_discard; sfc_segment_sum_static creates no
+ * events, so what it launches for this is in no entry).  The grouping of a step whose few copies run on `stream` goes out
+ * in one kernel with them when device timing is off, in one of its own when it is on).  sfc_lookup is one kernel,
  * or two from 32 MB of output on (the batch's rows are read into the memory-side cache, then
  * gathered): the start and end of each are recorded by the dispatch itself, i.e. the time is the
  * sum of the kernels' own durations as a profiler's kernel trace shows them.  level 2: also, the

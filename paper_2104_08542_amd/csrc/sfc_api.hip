@@ -601,12 +601,18 @@ bool recording(sfc_cache* c, const StepCtx* x) {
 
 // What is only recorded has not run: the step stays as it is for the calls that follow, which do the same again if they come.
 // And launched behind a later step it does nothing: these kernels go by the number in the step's counters.
-int group_now(sfc_cache* c, StepCtx* x) {
+// timed: its time is added to the prepare's (not where no events may be created, and not what is only recorded).
+int group_now(sfc_cache* c, StepCtx* x, bool timed) {
   const bool later = recording(c, x);
   c->served = 0;
   if (!x->ungrouped) return SFC_OK;
   if (!later) x->ungrouped = x->by_vid = false;
   hipStream_t s = c->st;                        // (lookahead 0: the prepares run here as well)
+  EventPair ep{};
+  int rc;
+  timed = timed && !later;
+  if (timed && (rc = prof_begin(c, P_PREPARE, s, &ep))) return rc;
+  ep.extra = true;
   const int n = (int)x->n_ids;
   const SortGeom& sg = x->sg;
   const Ctr* const ctr = x->ctr;
@@ -622,7 +628,7 @@ int group_now(sfc_cache* c, StepCtx* x) {
   auto scat = sg.shift == 10 ? k_scatter_late<4, 256> : sg.shift == 12 ? k_scatter_late<8, 512> : k_scatter_late<8, 1024>;
   hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.shift == 10 ? 256 : sg.shift == 12 ? 512 : 1024), 0, s, scatter_args(c, x),
                      ctr, x->t);
-  return SFC_OK;
+  return timed ? prof_end(c, P_PREPARE, s, &ep) : SFC_OK;
 }
 
 // Row of every position of an ungrouped batch (see rows_by_position).
@@ -1056,7 +1062,11 @@ int sfc_fetch_misses(sfc_cache* c) {
   int rc;
   // (on the main stream the grouping pass of a small batch goes out with the copies)
   if (x->ungrouped && rows_by_position(x) && !capturing(c->st)) {
+    EventPair ep{};
+    if ((rc = prof_begin(c, P_PREPARE, c->st, &ep))) return rc;
+    ep.extra = true;
     launch_pos_rows(c, x, false);
+    if ((rc = prof_end(c, P_PREPARE, c->st, &ep))) return rc;
     x->by_vid = false;
   }
   const bool with_copies = on_main && x->n_ids > 0 && x->sg.shift == 10 && !prof_on(c, P_PREPARE);
@@ -1120,7 +1130,7 @@ int sfc_segment_sum(sfc_cache* c, const float* d_grad, float* d_common_grad) {
   if ((x->n_bags > 0 && !d_grad) || !d_common_grad) return fail(SFC_EINVAL, "null buffer");
   if (((uintptr_t)d_grad | (uintptr_t)d_common_grad) & 15) return fail(SFC_EINVAL, "buffers must be 16-byte aligned");
   int rc;
-  if ((rc = rows_ready(c, x)) || (rc = group_now(c, x))) return rc;
+  if ((rc = rows_ready(c, x)) || (rc = group_now(c, x, true))) return rc;
   if ((rc = seg_launch(c, x, d_grad, d_common_grad, c->bp, c->bp_vid, true, false, nullptr))) return rc;
   HIPCHK(hipGetLastError());
   return SFC_OK;
@@ -1158,7 +1168,7 @@ int sfc_segment_sum_static(sfc_cache* c, const float* d_grad, float* d_common_gr
   // could create profiling events
   if (x->main_pending)
     return fail(SFC_ESTATE, "the step's rows are still due on the main stream: call sfc_lookup first");
-  if ((rc = join_copies(c, x)) || (rc = group_now(c, x))) return rc;
+  if ((rc = join_copies(c, x)) || (rc = group_now(c, x, false))) return rc;
   // every slot that k_seg_finish reads is written by k_seg_stream in the same call: nothing to clear
   double* bp = (double*)base;
   int* bp_vid = (int*)((unsigned char*)base + sums);
@@ -1175,7 +1185,7 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad) {
   if (x->n_bags > 0 && !d_grad) return fail(SFC_EINVAL, "null gradient");
   if ((uintptr_t)d_grad & 15) return fail(SFC_EINVAL, "gradient must be 16-byte aligned");
   int rc;
-  if ((rc = rows_ready(c, x)) || (rc = group_now(c, x))) return rc;
+  if ((rc = rows_ready(c, x)) || (rc = group_now(c, x, true))) return rc;
   c->updated_once = true;
   hipStream_t s = c->st;
   EventPair ep{};

@@ -1338,6 +1338,43 @@ def test_calls_recorded_on_a_step_that_is_not_grouped(n, bags, call):
         p.finish(); p.close()
 
 
+@pytest.mark.parametrize("call", ["sum", "static", "update"])
+@pytest.mark.parametrize("n,bags", [(7000, 0), (9000, 2000), (1 << 17, 30_000)])
+def test_time_of_what_a_serving_cache_launches_later(n, bags, call):
+    # device timing: the rows of the positions (bags from 2^17 ids on) and a grouping that is made up for are added to the
+    # prepare's time and are no calls of their own; the sum that creates no events is timed nowhere.  A batch after the
+    # gradient is grouped by its prepare: nothing to make up for.
+    V, D, nb = 12_000, 8, bags or n
+    p = Pair(V, D, C=V, max_ids=n, max_bags=nb, side_stream=False)
+    c = p.cache
+    off = _bag_ends(n, bags, 0).to(p.dev) if bags else None
+    ids, grad = si.zipf_ids(n, 1.05, V, 88, 0).to(p.dev), si.grads(nb, D, 88, 0).to(p.dev)
+    for t in range(64):
+        c.prepare(ids, off); c.fetch_misses(); c.discard()
+    p.sfc.sfc_profile_enable(c.h, 1)
+    prepare = lambda: p.sfc.sfc_profile_read(c.h)["prepare"]
+
+    def gradient():
+        if call == "update":
+            c.backward_update(grad)
+        else:
+            (c.segment_sum if call == "sum" else lambda g: p.sfc.sfc_segment_sum_static(c.h, g, out))(grad)
+            c.discard()
+
+    out = torch.zeros(n, D, device=p.dev)
+    for late in (True, False):
+        c.prepare(ids, off)
+        ms, calls = prepare()
+        assert ms > 0 and calls == 1
+        c.fetch_misses()
+        ms, calls = prepare()
+        assert calls == 0 and (ms > 0) == (not late or n >= 1 << 17), ms
+        gradient()
+        ms, calls = prepare()
+        assert calls == 0 and (ms > 0) == (late and call != "static"), ms
+    p.close()
+
+
 @pytest.mark.parametrize("lookahead", [1, 2])
 def test_pipelined_caches_of_one_stream_in_turn(lookahead):
     # one of them is closed on the way and another one created
