@@ -152,7 +152,10 @@ void sfc_host_free(void* p);
  * Create an empty cache: the per-GPU cache buffer of MixCache (Host-Manager section), a fixed
  * number of row slots in HBM holding the working rows and their optimizer state.  The manager
  * state (id -> slot index, per-slot recency stamp) lives in HBM too.  Allocates all device
- * memory the later calls use.
+ * memory the later calls use.  With lookahead > 0 (and SFC_POLICY_LRU_BATCH) the stream of the prepares
+ * is chosen here among a few, by whether it runs beside `stream` and side_stream at this moment:
+ * kernels that do nothing for up to 60 us each are run on them, about a millisecond in all.  A
+ * side_stream that has work or is being captured is left alone.
  */
 int sfc_cache_create(const sfc_config* cfg, sfc_cache** out);
 void sfc_cache_destroy(sfc_cache* c);

@@ -75,6 +75,14 @@ int static_scratch(int device, void** out) {
   return SFC_OK;
 }
 
+// Is stream s being captured?
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();                      // (no answer is not an error of the call that asks)
+  return true;
+}
+
 // The stream of a pipelined cache's prepares.  HIP puts the streams of a process on four hardware queues, and what stands
 // behind a step's Host copies in a queue waits for hundreds of microseconds: with the prepares in the queue of the main or the
 // side stream a step takes half as long again.  No call tells a stream's queue, so a few candidates are tried when the cache
@@ -114,8 +122,8 @@ hipError_t choose_prep_stream(hipStream_t main, hipStream_t side, hipStream_t* o
     hipLaunchKernelGGL(k_hold, dim3(1), dim3(64), 0, main, 0LL);          // its code is loaded
     e = hipStreamSynchronize(main);
   }
-  // (a side stream that the caller has given work is left alone)
-  const bool ask_side = e == hipSuccess && hipStreamQuery(side) == hipSuccess;
+  // (a side stream that the caller has given work or is recording is left alone; asking whether it has work would end the recording)
+  const bool ask_side = e == hipSuccess && !capturing(side) && hipStreamQuery(side) == hipSuccess;
   (void)hipGetLastError();
   while (e == hipSuccess && n < kPrepTries && most < 3) {
     if ((e = hipStreamCreateWithFlags(&s[n], hipStreamNonBlocking)) != hipSuccess) break;
@@ -313,19 +321,12 @@ int prof_events(sfc_cache* c, EventPair* ep) {
 
 // Launches a kernel; with `tells` the dispatch itself completes the event.  A record behind the launch is a
 // packet of its own: 6.6 us from launch to launch on the GPU against 4.0, and 1.1 us of host time.
+// (What is recorded into a graph is a launch and an event of their own.)
 #define LAUNCH_THEN(tells, event, kernel, grid, block, s, ...)                                   \
   do {                                                                                           \
     if (tells) hipExtLaunchKernelGGL(kernel, grid, block, 0, s, nullptr, event, 0, __VA_ARGS__); \
     else hipLaunchKernelGGL(kernel, grid, block, 0, s, __VA_ARGS__);                             \
   } while (0)
-// (what is recorded into a graph is a launch and an event of their own)
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
-  (void)hipGetLastError();                      // (no answer is not an error of the call that asks)
-  return true;
-}
-
 int prof_end(sfc_cache* c, int which, hipStream_t s, EventPair* ep) {
   if (!prof_on(c, which)) return SFC_OK;
   HIPCHK(hipEventRecord(ep->b, s));

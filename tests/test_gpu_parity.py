@@ -1375,6 +1375,48 @@ def test_time_of_what_a_serving_cache_launches_later(n, bags, call):
     p.close()
 
 
+@pytest.mark.parametrize("side", ["idle", "busy", "recorded"])
+def test_creation_leaves_a_side_stream_with_work_alone(side):
+    # the prepare stream is chosen by trying streams beside the caller's two: what the caller has the side stream do or record
+    # goes on as if the cache were not being created, and the cache works
+    import paper_2104_08542_amd as sfc
+    hip, vp = ctypes.CDLL("libamdhip64.so"), ctypes.c_void_p
+    V, D, n = 3000, 8, 500
+    p = Pair(V, D, C=1000, max_ids=n, lookahead=1)
+    p.cache.close()
+    s, x = torch.cuda.Stream(), torch.zeros(64, device="cuda:0")
+    torch.cuda.synchronize()
+    real = torch.cuda.Stream
+    graph, run = vp(), vp()
+    if side == "recorded":
+        assert hip.hipStreamBeginCapture(vp(s.cuda_stream), 2) == 0           # relaxed
+    if side != "idle":
+        with torch.cuda.stream(s):
+            if side == "busy":
+                torch.cuda._sleep(20_000_000)
+            x.add_(1.0)
+    try:
+        torch.cuda.Stream = lambda *a, **k: real(*a, **k) if k else s      # (the cache's own side stream)
+        p.cache = sfc.Cache(p.table, 1000, n, lookahead=1)
+    finally:
+        torch.cuda.Stream = real
+        if side == "recorded":
+            rc = hip.hipStreamEndCapture(vp(s.cuda_stream), ctypes.byref(graph))
+    assert p.cache.side is s
+    if side == "recorded":
+        assert rc == 0
+        assert hip.hipGraphInstantiate(ctypes.byref(run), graph, None, None, ctypes.c_size_t(0)) == 0
+        for k in range(3):
+            assert hip.hipGraphLaunch(run, vp(s.cuda_stream)) == 0
+    torch.cuda.synchronize()
+    assert x.unique().tolist() == [{"idle": 0.0, "busy": 1.0, "recorded": 3.0}[side]]
+    batches = [(si.zipf_ids(m, 1.05, V, 91, t), si.grads(m, D, 91, t), None) for t, m in enumerate((n, 40, n, n, 3, n))]
+    p.run_pipelined(batches, False)
+    if side == "recorded":
+        hip.hipGraphExecDestroy(run); hip.hipGraphDestroy(graph)
+    p.close()
+
+
 @pytest.mark.parametrize("lookahead", [1, 2])
 def test_pipelined_caches_of_one_stream_in_turn(lookahead):
     # one of them is closed on the way and another one created
