@@ -261,7 +261,7 @@ int sfc_backward_update(sfc_cache* c, const float* d_grad);
  * Gives up the oldest step that has been fetched and not updated (a batch that was only looked
  * up, e.g. for inference): its step context becomes free, its rows stay in the cache unchanged.
  * With lookahead 0 a cache that has given up 64 steps in a row prepares its batches without what only
- * gradients need, until one comes: that call then makes up for it first.  (Not once sfc_lookup, a segment sum or
+ * gradients need, until one comes: that call then makes up for it first.  (Not once a segment sum or
  * sfc_backward_update has been recorded into a HIP graph on this cache: the graph may be launched behind
  * any later prepare.)
  * SFC_ESTATE if there is no such step or its rows are still on their way.

@@ -173,9 +173,8 @@ struct StepCtx {
   bool discarded = false;             // freed by sfc_discard: the step's copies may still be running
   bool copies_on_main = false;        // this step's copies run on the main stream
   bool told = false;                  // ev_prepared was completed by the grouping pass's own dispatch
-  bool grouping_due = false;          // lookahead 0: the grouping pass goes out with sfc_fetch_misses
+  bool grouping_due = false;          // lookahead 0: the grouping pass goes out with sfc_fetch_misses (ungrouped: the rows of the positions)
   bool ungrouped = false;             // prepared without its grouping (see group_now)
-  bool by_vid = false;                // ... and pos_slot is not there either
   SortGeom sg{};                      // shape of the step's counting and grouping passes
   bool joined = false;                // the main stream is behind the side-stream launch of the step's copies
   // pipelined mode: the second launch of the Host copies, due on the main stream behind the
@@ -218,6 +217,7 @@ struct sfc_cache {
   int* cur_rep = nullptr;                       // [kHotRep, kHotBins] group cursors of the lowest virtual ids, one per copy
   int* n_unique = nullptr;                      // unique ids of the step whose unique passes ran last
   int* pos2bag = nullptr;                       // [max_ids] multi-hot: bag of each position
+  int64_t* bag_ends = nullptr;                  // [max_bags + 1] lookahead 0: the offsets of an ungrouped step
   int* tile_cnt = nullptr;                      // [max_ids / kVidTile + 1]
   int* tile_reuse = nullptr;                    // [max_ids / kVidTile + 1] deleted index entries reused per tile
   int* n_invalid = nullptr;                     // out-of-range positions of the step being prepared
@@ -238,7 +238,7 @@ struct sfc_cache {
   bool updated_once = false;                    // an update has been enqueued: resident rows may differ from the Host table's
   int last_prepared = -1;                       // context of the most recent sfc_prepare
   int served = 0;                               // steps given up since a gradient came last, up to kServing
-  bool recorded = false;                        // every batch is grouped by its prepare (see note_recording)
+  bool recorded = false;                        // every batch is grouped by its prepare (see recording)
   // profiling
   int prof = 0;                                 // 0 off, 1 step calls, 2 also the kernels inside them
   std::vector<EventPair> pending[P_N], spare;
@@ -430,6 +430,10 @@ ScatterArgs scatter_args(const sfc_cache* c, const StepCtx* x) {
                      x->sg.bins, x->sg.shift, x->sg.nrep, x->perm64, x->d_slot, x->pos_slot, (int)c->C, x->boff, (int)x->n_bags};
 }
 
+RowsArgs rows_args(const sfc_cache* c, const StepCtx* x) {
+  return RowsArgs{x->d_inverse, x->d_slot, (int)x->n_ids, (int)c->C, x->boff, x->pos_slot};
+}
+
 // One launch of the Host<->cache copies of a step on stream s (see k_swap_rows for the two
 // launches of pipelined mode).
 int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
@@ -453,7 +457,11 @@ int launch_swap(sfc_cache* c, StepCtx* x, hipStream_t s, int main_variant) {
   const bool tells = !main_variant && s != c->st;
   const SwapArgs args{x->miss_row, x->miss_id, x->victim_id, (float4*)c->cw, (float4*)c->ca, c->host, c->d4, c->s4,
                       (const Ctr*)x->ctr, x->bypass_from, main_variant, staged_at, write_back ? 1 : 0};
-  if (x->grouping_due) {                      // (copies on the main stream: see sfc_fetch_misses)
+  if (x->grouping_due && x->ungrouped) {      // (copies on the main stream: see sfc_fetch_misses)
+    x->grouping_due = false;
+    hipLaunchKernelGGL(k_swap_pos_rows, dim3(blocks + (unsigned)((x->n_ids + 1023) / 1024)), dim3(256), 0, s, args, blocks,
+                       rows_args(c, x));
+  } else if (x->grouping_due) {
     x->grouping_due = false;
     hipLaunchKernelGGL(k_swap_scatter, dim3(blocks + x->sg.blocks), dim3(256), 0, s, args, blocks, scatter_args(c, x));
   } else {
@@ -528,7 +536,7 @@ void plan_and_assign(sfc_cache* c, StepCtx* x) {
   const bool beside_plan = !evicts || c->nctx == 1 || n < kBesidePlanMax;
   const int ft = beside_plan ? 1024 : 256;
   const FoldArgs fo{c->cnt, c->cnt_rep, sg.bins, sg.nrep, c->tile_cnt, x->ungrouped ? 0 : grid_for(n, ft, kFoldThreads / ft)};
-  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, x->ungrouped ? nullptr : c->pos2bag, 1};
+  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag, x->ungrouped ? c->bag_ends : nullptr, 1};
   const int riders = fo.folds + (n > 0 && x->d_offsets ? (int)((x->n_bags + ft - 1) / ft) : 0);
   hipLaunchKernelGGL(k_plan, dim3(1 + (beside_plan ? riders : 0)), dim3(1024), 0, s, c->tile_miss, c->age_hist,
                      c->tile_reuse, c->hist, x->t, c->cfg.lookahead, (int)c->C, c->hi, c->dmap ? 1 : 0, x->ctr, fo, bags);
@@ -550,6 +558,7 @@ void plan_and_assign(sfc_cache* c, StepCtx* x) {
 // (12 us) and this pass, beside the copies' first round trips, cost no time of their own.  (Not in the
 // prepare with the event in front of it: the copies come behind what the caller gives the main stream
 // between the two calls.)  Pipelined, the grouping is on the path of the next prepare and stays in its own.
+// A step that is not grouped has the rows of its positions written down in its place.
 int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
   x->grouping_due = false;
   x->told = false;
@@ -561,6 +570,10 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
   int rc;
   if (extra && (rc = prof_begin(c, P_PREPARE, s, &ep))) return rc;
   ep.extra = true;
+  if (x->ungrouped) {
+    hipLaunchKernelGGL(k_pos_rows, dim3((unsigned)((x->n_ids + 1023) / 1024)), dim3(256), 0, s, rows_args(c, x));
+    return extra ? prof_end(c, P_PREPARE, s, &ep) : SFC_OK;
+  }
   auto scat = sg.shift == 10 ? k_scatter<4, 256> : sg.shift == 12 ? k_scatter<8, 512> : k_scatter<8, 1024>;
   const int threads = sg.shift == 10 ? 256 : sg.shift == 12 ? 512 : 1024;
   // pipelined it is the last kernel of the prepare
@@ -573,25 +586,21 @@ int group_positions(sfc_cache* c, StepCtx* x, bool extra) {
 
 // Lookahead 0: a cache that has given up this many steps in a row without a gradient in between serves lookups, and
 // its batches beyond the one-block prepare are prepared without the grouping of their positions, which the backward
-// half alone reads: counts and ranks, sums, bags, starts of the groups and the grouping pass.  The
-// gather then goes from a position by its virtual id to the slot.  A gradient that comes all the same (sfc_segment_sum,
+// half alone reads: counts and ranks, sums, bags, starts of the groups and the grouping pass.  The rows of the positions,
+// for the gather, are written down where the grouping pass would run.  A gradient that comes all the same (sfc_segment_sum,
 // sfc_backward_update) has its step grouped first (group_now), and the following ones are grouped by their prepares again.
-// (Not after the first step that is given up: programs look at a few batches before they train.  Not while the
-// stream is captured, and not once a call that reads what a prepare leaves has been recorded: note_recording.)  us a pass looked up and given up, every row
-// resident, grouped / not: 53e3 bags of 1 to 10 ids, dim 128, 81.3 / 60.0; 852e3 of dim 16 316 / 215; 400e3 of 1 to 20 of dim 32 298 / 214;
-// one-hot 8e3 of dim 16 37 / 32, 639e3 of dim 16 88 / 65.5, 2.56e6 of dim 32 233 / 172; 53e3 ids in bags, hashed, a third
-// resident, 49 / 42.  One step that is grouped late costs its prepare's saving and two launches more.
+// Not while the stream is captured, and not once a gradient has been recorded: see recording.  Not with lookahead > 0: the
+// grouping of one step would then run on the main stream, in scratch that the prepare of a later step is using on its own.
+// us a pass looked up and given up, every row resident, grouped / not, and what the first sum takes longer when its step is grouped
+// late (five launches): one-hot 8e3 ids of dim 16 32 / 29.5, 27; 50e3 of dim 32 38 / 33.5, 23; 639e3 of dim 16 86 / 65, 50;
+// 2.56e6 of dim 32 215 / 161, 86; bags, 293e3 ids of dim 128 72 / 55, 35; 420e3 of dim 32 72 / 52, 38; 895e3 of dim 16 92 / 66, 53; 53e3,
+// hashed, a third resident, 44 / 40, 38.  So a late grouping is paid back by 2 to 12 steps; behind 64, programs that validate on a
+// few batches and train on have none, and one that trains on a single batch after each 65th loses half a microsecond a step.
+// (The one-hot gather through the virtual id to the slot, without the rows written down: 639e3 63.5, 2.56e6 153; but it
+// reads the caller's d_inverse and d_slot later than the grouping pass does.)
 constexpr int kServing = 64;
 
-// Is the row of every position of an ungrouped batch written down before the gather?  The gather of bags reads positions
-// again and again ahead of its rows, where another level costs more than a pass over the positions (beside the copies,
-// where these have the side stream); the one-hot gather reads each once.  us a pass, through the virtual id / written down:
-// 53e3 bags of 1 to 10 ids, dim 128, 65.3 / 60.0, 400e3 281 / 227, 400e3 of 1 to 20, dim 32, 234 / 214, 852e3 of dim 16 222 / 215,
-// 556e3 of 1 to 8 of dim 80 over a cache of 3090 rows 488 / 448 (grouped 475), 20e3 of 1 to 5 40.4 / 41.8; one-hot 50e3 of dim 32 34.5 / 39.4,
-// 639e3 of dim 16 64.2 / 68.1, 2.56e6 of dim 32 169 / 177.
-bool rows_by_position(const StepCtx* x) { return x->d_offsets && x->n_ids >= (int64_t)1 << 17; }
-
-// Called by what reads the rows of the positions or their groups: is it being recorded?  Then its graph may be launched behind
+// Called by what reads the groups of the positions: is it being recorded?  Then its graph may be launched behind
 // any later prepare and reads the same arrays then; the host sees neither that nor that the steps it gives up have had a
 // gradient.  So all further batches are grouped by their prepares.  (Those of the one-block prepare are in any case, and what is recorded with
 // one of them fits no larger batch: the numbers of ids and bags are part of it.)
@@ -607,7 +616,7 @@ int group_now(sfc_cache* c, StepCtx* x, bool timed) {
   const bool later = recording(c, x);
   c->served = 0;
   if (!x->ungrouped) return SFC_OK;
-  if (!later) x->ungrouped = x->by_vid = false;
+  if (!later) x->ungrouped = false;
   hipStream_t s = c->st;                        // (lookahead 0: the prepares run here as well)
   EventPair ep{};
   int rc;
@@ -618,25 +627,21 @@ int group_now(sfc_cache* c, StepCtx* x, bool timed) {
   const SortGeom& sg = x->sg;
   const Ctr* const ctr = x->ctr;
   fill<int>(s, c->cnt, n, 0);
-  const RankArgs rank{nullptr, nullptr, n, x->d_inverse, c->cnt, c->cnt_rep, sg.nrep, x->pos_slot, nullptr};
+  // (all of it from what the prepare has kept: the caller's ids, virtual ids and offsets may be gone; ranks where the
+  // virtual ids of the table entries were)
+  const RankArgs rank{c->hslot, nullptr, n, nullptr, c->cnt, c->cnt_rep, sg.nrep, c->uvid, nullptr};
   auto count = sg.shift == 10 ? k_count_late<1, 1024> : sg.shift == 12 ? k_count_late<8, 512> : k_count_late<8, 1024>;
   hipLaunchKernelGGL(count, dim3(sg.blocks), dim3(sg.shift == 12 ? 512 : 1024), 0, s, rank, ctr, x->t);
   const FoldArgs fo{c->cnt, c->cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, 256, kFoldThreads / 256)};
-  const BagArgs bags{x->d_offsets, (int)x->n_bags, n, c->pos2bag, 0};
+  const BagArgs bags{c->bag_ends, (int)x->n_bags, n, c->pos2bag, nullptr, 0};
   hipLaunchKernelGGL(k_fold_late, dim3(fo.folds + (x->d_offsets ? (unsigned)((x->n_bags + 255) / 256) : 0u)), dim3(256), 0, s,
                      x->ctr, fo, bags, x->t);
   hipLaunchKernelGGL(k_starts_late, dim3(grid_for(n, kVidTile, kGridCap)), dim3(256), 0, s, group_args(c, x, true), ctr, x->t);
   auto scat = sg.shift == 10 ? k_scatter_late<4, 256> : sg.shift == 12 ? k_scatter_late<8, 512> : k_scatter_late<8, 1024>;
-  hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.shift == 10 ? 256 : sg.shift == 12 ? 512 : 1024), 0, s, scatter_args(c, x),
-                     ctr, x->t);
+  ScatterArgs sc = scatter_args(c, x);
+  sc.inverse = c->hslot; sc.rank_slot = c->uvid;
+  hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.shift == 10 ? 256 : sg.shift == 12 ? 512 : 1024), 0, s, sc, ctr, x->t);
   return timed ? prof_end(c, P_PREPARE, s, &ep) : SFC_OK;
-}
-
-// Row of every position of an ungrouped batch (see rows_by_position).
-void launch_pos_rows(sfc_cache* c, const StepCtx* x, bool recorded) {
-  auto kern = recorded ? k_pos_rows<true> : k_pos_rows<false>;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((x->n_ids + 1023) / 1024)), dim3(256), 0, c->st, (const int*)x->d_inverse,
-                     (const int*)x->d_slot, (int)x->n_ids, (int)c->C, x->boff, x->pos_slot, (const Ctr*)x->ctr, x->t);
 }
 
 int sync_all(sfc_cache* c) {
@@ -839,6 +844,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     if ((rc = dalloc(c, &c->cnt, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->n_unique, 1))) goto bad;
     if ((rc = dalloc(c, &c->pos2bag, c->max_ids))) goto bad;
+    if (nctx == 1 && (rc = dalloc(c, &c->bag_ends, c->max_bags + 1))) goto bad;
     if ((rc = dalloc(c, &c->tile_cnt, c->max_ids / kVidTile + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_reuse, c->max_ids / kVidTile + 2))) goto bad;
     if ((rc = dalloc(c, &c->age_hist, (int64_t)kAgeBins))) goto bad;
@@ -950,7 +956,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   x->n_ids = n_ids; x->n_bags = n_bags; x->d_offsets = d_offsets;
   x->d_unique = d_unique_ids; x->d_inverse = d_inverse; x->d_slot = d_slot; x->d_miss = d_miss_vids;
   c->last_prepared = (int)(x - c->ctx);
-  x->by_vid = x->ungrouped = c->nctx == 1 && !small && n_ids > 0 && c->served >= kServing && !c->recorded && !capturing(s);
+  x->ungrouped = c->nctx == 1 && !small && n_ids > 0 && c->served >= kServing && !c->recorded && !capturing(s);
 
   EventPair ep{};
   int rc;
@@ -990,12 +996,15 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   } else if (!small) {
     fill<int>(s, c->n_unique, 1, 0);
   }
-  const RankArgs rank{c->hslot, c->uvid, n, d_inverse, x->ungrouped ? nullptr : c->cnt, c->cnt_rep, sg.nrep, x->pos_slot, c->first};
+  const RankArgs rank{c->hslot, c->uvid, n, d_inverse, c->cnt, c->cnt_rep, sg.nrep, x->pos_slot, c->first};
   const ResolveArgs res{d_unique_ids, c->vid_hslot, c->utab, c->wide ? 1 : 0, c->index, c->hi, c->dmap, c->stamp,
                         c->hist, x->t, d_slot, c->tile_miss, c->age_hist, x->ctr,
                         start_inside ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid};
   auto rank_resolve = sg.shift == 10 ? k_rank_resolve<1, 1024> : sg.shift == 12 ? k_rank_resolve<8, 512>
                                                                               : k_rank_resolve<8, 1024>;
+  if (x->ungrouped)
+    rank_resolve = sg.shift == 10 ? k_rank_resolve<1, 1024, kVidsAlone> : sg.shift == 12 ? k_rank_resolve<8, 512, kVidsAlone>
+                                                                                         : k_rank_resolve<8, 1024, kVidsAlone>;
   const int rt = sg.shift == 12 ? 512 : 1024, nres = small ? 0 : grid_for(n, rt, kResolveThreads / rt);
   const int ncount = small || n == 0 ? 0 : sg.blocks;
   // from here on behind the whole prepare of the previous step: the step's counters start from
@@ -1023,7 +1032,7 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   } else {
     hipLaunchKernelGGL(rank_resolve, dim3(nres + ncount), dim3(rt), 0, s, rank, res, nres);
   }
-  x->grouping_due = !whole && c->nctx == 1 && !x->ungrouped;
+  x->grouping_due = !whole && c->nctx == 1;
   x->told = false;
   if (!whole) {
     plan_and_assign(c, x);
@@ -1062,15 +1071,7 @@ int sfc_fetch_misses(sfc_cache* c) {
   }
   int rc;
   // (on the main stream the grouping pass of a small batch goes out with the copies)
-  if (x->ungrouped && rows_by_position(x) && !capturing(c->st)) {
-    EventPair ep{};
-    if ((rc = prof_begin(c, P_PREPARE, c->st, &ep))) return rc;
-    ep.extra = true;
-    launch_pos_rows(c, x, false);
-    if ((rc = prof_end(c, P_PREPARE, c->st, &ep))) return rc;
-    x->by_vid = false;
-  }
-  const bool with_copies = on_main && x->n_ids > 0 && x->sg.shift == 10 && !prof_on(c, P_PREPARE);
+  const bool with_copies = on_main && x->n_ids > 0 && (x->ungrouped || x->sg.shift == 10) && !prof_on(c, P_PREPARE);
   if (x->grouping_due && !with_copies && (rc = group_positions(c, x, true))) return rc;
   x->joined = on_main;
   if ((rc = launch_swap(c, x, on_main ? c->st : c->side, 0))) return rc;
@@ -1088,11 +1089,6 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
   if ((uintptr_t)d_out & 15) return fail(SFC_EINVAL, "output must be 16-byte aligned");
   int rc;
   if ((rc = rows_ready(c, x))) return rc;
-  bool by_vid = x->by_vid;
-  if (recording(c, x) && by_vid) {              // (a launch behind a later step reads the rows that its prepare has left)
-    launch_pos_rows(c, x, true);
-    by_vid = false;
-  }
   hipStream_t s = c->st;
   const int64_t total = x->n_bags * c->d4;
   if (total > 0) {
@@ -1101,22 +1097,20 @@ int sfc_lookup(sfc_cache* c, float* d_out) {
     if (total >= kWarmMinChunks)
       LAUNCH_TIMED_X(c, P_LOOKUP, true, true, k_warm_rows, dim3(grid_for(x->n_ids * c->d4, 2048, kWarmGrid)),
                      dim3(256), s, (const int*)x->d_slot, (const float4*)c->cw, c->d4, (int)c->C, x->boff,
-                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, by_vid ? 0 : (int)(x->n_ids / 4));
-    const int* const row_of_pos = by_vid ? x->d_inverse : x->pos_slot;
+                     (const Ctr*)x->ctr, c->warm_sink, (const int4*)x->pos_slot, (int)(x->n_ids / 4));
     if (!x->d_offsets) {
       const int d4 = c->d4, sh = (d4 & (d4 - 1)) == 0 ? __builtin_ctz(d4) : -1;
       const int bpb = lookup_rows_per_block(d4);
-      auto kern = by_vid ? k_lookup_onehot<true> : k_lookup_onehot<false>;
-      LAUNCH_TIMED(c, P_LOOKUP, true, kern, dim3((unsigned)((x->n_bags + bpb - 1) / bpb)), dim3(256), s, row_of_pos,
-                   (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, d4, sh, bpb, (const int*)x->d_slot, (int)c->C,
-                   x->boff);
+      LAUNCH_TIMED(c, P_LOOKUP, true, k_lookup_onehot,
+                   dim3((unsigned)((x->n_bags + bpb - 1) / bpb)), dim3(256), s,
+                   (const int*)x->pos_slot, (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, d4, sh, bpb);
     } else {
       const int G = 64 / c->d4 > 0 ? 64 / c->d4 : 1;          // bags per wavefront
       const int64_t per_block = 4 * (int64_t)G;
-      auto kern = by_vid ? k_lookup_bags<true> : k_lookup_bags<false>;
-      LAUNCH_TIMED(c, P_LOOKUP, true, kern, dim3((unsigned)((x->n_bags + per_block - 1) / per_block)), dim3(256), s,
-                   x->d_offsets, row_of_pos, (const float4*)c->cw, (float4*)d_out, (int)x->n_bags, c->d4, G, x->n_ids,
-                   (const int*)x->d_slot, (int)c->C, x->boff);
+      LAUNCH_TIMED(c, P_LOOKUP, true, k_lookup_bags,
+                   dim3((unsigned)((x->n_bags + per_block - 1) / per_block)), dim3(256), s,
+                   x->d_offsets, (const int*)x->pos_slot, (const float4*)c->cw, (float4*)d_out,
+                   (int)x->n_bags, c->d4, G, x->n_ids);
     }
   }
   HIPCHK(hipGetLastError());

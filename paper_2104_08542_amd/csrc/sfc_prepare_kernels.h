@@ -11,6 +11,7 @@
 // sum, nothing else; see the segment-sum kernels for what that means for the results.
 #pragma once
 #include "sfc_device.h"
+#include <type_traits>
 
 namespace sfc {
 
@@ -451,38 +452,44 @@ inline SortGeom small_geom(int64_t n) {
   return g;
 }
 
-// hslot == nullptr: `inverse` is there already (k_count_late).  cnt == nullptr: that is all (see group_now in the host code).
-template <int kPer, int kT>
-__device__ __forceinline__ void count_positions(const int* __restrict__ hslot, const int* __restrict__ uvid, int n,
+// A batch that is not grouped (see group_now in the host code) has its virtual ids alone, which are kept where the table
+// entries were; when it is grouped after all, its positions are counted from there.
+enum { kCountAll, kVidsAlone, kCountLate };
+template <int kPer, int kT, int kWhat>
+__device__ __forceinline__ void count_positions(std::conditional_t<kWhat == kVidsAlone, int, const int>* __restrict__ hslot,
+                                                const int* __restrict__ uvid, int n,
                                                 int* __restrict__ inverse, int* cnt, int* cnt_rep, int nrep,
                                                 int* __restrict__ rank, unsigned* __restrict__ first, int blk,
                                                 int* lh) {
   // the marks of first appearances have been read: all zero again for the next batch
   static_assert(kPer <= 32 && kT * kPer % 32 == 0, "whole words of marks per block");
-  if (hslot && (int)threadIdx.x < kT * kPer / 32 && blk * kT * kPer + (int)threadIdx.x * 32 < n)
+  if (kWhat != kCountLate && (int)threadIdx.x < kT * kPer / 32 && blk * kT * kPer + (int)threadIdx.x * 32 < n)
     first[blk * (kT * kPer / 32) + threadIdx.x] = 0;
-  if (cnt)
+  if (kWhat != kVidsAlone)
     for (int i = threadIdx.x; i < kHotBins; i += kT) lh[i] = 0;
   const int base = blk * kT * kPer;
   int hv[kPer], vv[kPer], rr[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {              // kPer loads in flight per level of indirection
     const int p = base + j * kT + (int)threadIdx.x;
-    hv[j] = p < n ? (hslot ? hslot[p] : inverse[p]) : -1;
+    hv[j] = p < n ? hslot[p] : -1;
   }
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) vv[j] = hslot && hv[j] >= 0 ? uvid[hv[j]] : hv[j];
-  if (hslot) {
+  for (int j = 0; j < kPer; ++j) vv[j] = kWhat != kCountLate && hv[j] >= 0 ? uvid[hv[j]] : hv[j];
+  if constexpr (kWhat == kVidsAlone) {
 #pragma unroll
-    for (int j = 0; j < kPer; ++j)
-      if (vv[j] >= 0) inverse[base + j * kT + (int)threadIdx.x] = vv[j];
+    for (int j = 0; j < kPer; ++j) {
+      const int p = base + j * kT + (int)threadIdx.x;
+      if (vv[j] >= 0) { inverse[p] = vv[j]; hslot[p] = vv[j]; }
+    }
+    return;
   }
-  if (!cnt) return;
   __syncthreads();
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {
     const int v = vv[j];
     if (v >= 0) {
+      if (kWhat == kCountAll) inverse[base + j * kT + (int)threadIdx.x] = v;
       rr[j] = v < kHotBins ? atomicAdd(&lh[v], 1) : atomicAdd(&cnt[v], 1);
     }
   }
@@ -518,10 +525,11 @@ __device__ __forceinline__ void count_positions(const int* __restrict__ hslot, c
 // one that starts at or before it (six steps of a search in LDS).  With a thread per bag every store
 // touched a line of its own: 38 us for 852e3 bags of 1 to 20 ids, 17 this way.  A wavefront that has seen a
 // violation falls back to a loop per bag.
-// starts: a word of LDS per thread, used within the wavefront alone.  pos2bag == nullptr: the check alone; ctr ==
-// nullptr: without the check's tally (it has been made).
+// starts: a word of LDS per thread, used within the wavefront alone.  kept != nullptr: the check alone, and the offsets
+// are kept there; ctr == nullptr: without the check's tally (it has been made).
 __device__ __forceinline__ void bags_of_positions(const int64_t* __restrict__ offsets, int n_bags, int n,
-                                                  int* __restrict__ pos2bag, Ctr* ctr, int blk, int* starts_all) {
+                                                  int* __restrict__ pos2bag, int64_t* __restrict__ kept, Ctr* ctr, int blk,
+                                                  int* starts_all) {
   const int lane = lane_id(), w = (int)(threadIdx.x >> 6);
   int* const starts = starts_all + w * kWave;
   const int b0 = blk * (int)blockDim.x + w * kWave, b = b0 + lane;
@@ -531,6 +539,10 @@ __device__ __forceinline__ void bags_of_positions(const int64_t* __restrict__ of
     const int64_t lo = offsets[b], hi = offsets[b + 1];
     bad = bag_malformed(lo, hi, b, n_bags, n);
     r = bag_range(lo, hi, n);
+    if (kept) {
+      kept[b] = lo;
+      if (b == n_bags - 1) kept[n_bags] = hi;
+    }
   }
   starts[lane] = r.lo;
   const uint64_t m = __ballot(bad);
@@ -539,7 +551,7 @@ __device__ __forceinline__ void bags_of_positions(const int64_t* __restrict__ of
     volatile HostStatus* h = ctr->hstat;
     if (h) h->bad_offsets_step = ctr->t;
   }
-  if (!pos2bag) return;
+  if (kept) return;
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -569,7 +581,7 @@ __device__ __forceinline__ void bags_of_positions(const int64_t* __restrict__ of
 // and its returning atomics here, 22 without, and the counting pass is none the slower for ranking).
 // rank_slot[p] is read as the rank and overwritten with pos_slot[p] = row of slot[inverse[p]] for the
 // forward gather (a bypass slot C + j lives at row C + boff + j: each step in flight has its own
-// bypass region).
+// bypass region).  kRows = false: without that, the rows are there already (k_scatter_late).
 // A block takes the same positions as a block of the counting pass: their places in a hot group lie
 // side by side, and with half the positions per block two XCDs write into the same 128-byte lines
 // (169 against 120 us at 8.9e6 positions in bags).
@@ -577,7 +589,7 @@ struct ScatterArgs {
   const int *inverse, *pos2bag; int n; const int64_t* grp; int* cold_pay; const int* cur_rep; int bins, shift, nrep;
   int64_t* perm64; const int* slot; int* rank_slot; int C, boff, n_bags;
 };
-template <int kScatPer, int kT>
+template <int kScatPer, int kT, bool kRows>
 __device__ __forceinline__ void scatter_positions(const int* __restrict__ inverse, const int* __restrict__ pos2bag, int n,
                                                   const int64_t* __restrict__ grp, int* __restrict__ cold_pay,
                                                   const int* __restrict__ cur_rep, int bins, int shift, int nrep,
@@ -600,7 +612,7 @@ __device__ __forceinline__ void scatter_positions(const int* __restrict__ invers
   for (int j = 0; j < kScatPer; ++j) {
     const int p = base + j * kT;
     if (vv[j] >= 0) {
-      sv[j] = slot[vv[j]];
+      if (kRows) sv[j] = slot[vv[j]];
       gr[j] = vv[j] < bins ? (int64_t)cur_rep[((p >> shift) & (nrep - 1)) * kHotBins + vv[j]] : grp[vv[j]];
     }
   }
@@ -608,7 +620,7 @@ __device__ __forceinline__ void scatter_positions(const int* __restrict__ invers
   for (int j = 0; j < kScatPer; ++j) {
     const int p = base + j * kT;
     if (vv[j] < 0) continue;
-    rank_slot[p] = sv[j] >= C ? sv[j] + boff : sv[j];   // pos_slot: row index for the forward gather
+    if (kRows) rank_slot[p] = sv[j] >= C ? sv[j] + boff : sv[j];   // pos_slot: row index for the forward gather
     int64_t e = ((int64_t)vv[j] << 32) | (uint32_t)pay[j];
     // a cold group's gradient rows also go where the optimizer kernel finds them without
     // walking the grouping: two words per virtual id, filled in the order of the ranks
@@ -619,9 +631,9 @@ __device__ __forceinline__ void scatter_positions(const int* __restrict__ invers
     perm64[(int)gr[j] + rr[j]] = e;
   }
 }
-template <int kScatPer, int kT>
+template <int kScatPer, int kT, bool kRows = true>
 __device__ __forceinline__ void scatter_positions(const ScatterArgs& a, int blk) {
-  scatter_positions<kScatPer, kT>(a.inverse, a.pos2bag, a.n, a.grp, a.cold_pay, a.cur_rep, a.bins, a.shift, a.nrep, a.perm64,
+  scatter_positions<kScatPer, kT, kRows>(a.inverse, a.pos2bag, a.n, a.grp, a.cold_pay, a.cur_rep, a.bins, a.shift, a.nrep, a.perm64,
                                   a.slot, a.rank_slot, a.C, a.boff, a.n_bags, blk);
 }
 template <int kScatPer, int kT>
@@ -800,14 +812,14 @@ __device__ __forceinline__ void resolve_ids(const int64_t* __restrict__ unique_i
 // 1.28e6 uniform ones 26.7 + 60.8 / 77.5, 8.9e6 in bags 146 + 48 / 178: what is saved is start-up and drain, the random
 // accesses of the two add up.
 struct RankArgs {
-  const int* hslot; const int* uvid; int n; int* inverse; int* cnt; int* cnt_rep; int nrep; int* rank; unsigned* first;
+  int* hslot; const int* uvid; int n; int* inverse; int* cnt; int* cnt_rep; int nrep; int* rank; unsigned* first;
 };
 struct ResolveArgs {
   const int64_t* unique_ids; const int* vid_hslot; uint64_t* utab; int wide;
   const IdxEntry* index; uint32_t hi; const int* dmap; int *stamp, *hist; int t;
   int *slot, *tile_miss, *age_hist; Ctr* ctr; const Ctr* prev; const int* n_unique; int* n_invalid;
 };
-template <int kPer, int kT>
+template <int kPer, int kT, int kWhat = kCountAll>
 __global__ __launch_bounds__(kT) void k_rank_resolve(const RankArgs a, const ResolveArgs b, int nres) {
   __shared__ int lds[kHotBins];
   static_assert(kHotBins >= kAgeBins + kT / kWave, "the LDS of the counting blocks holds that of the resolving ones");
@@ -815,7 +827,7 @@ __global__ __launch_bounds__(kT) void k_rank_resolve(const RankArgs a, const Res
     resolve_ids<kT>(b.unique_ids, b.vid_hslot, b.utab, b.wide, b.index, b.hi, b.dmap, b.stamp, b.hist, b.t, b.slot,
                     b.tile_miss, b.age_hist, b.ctr, b.prev, b.n_unique, b.n_invalid, (int)blockIdx.x, nres, lds);
   else
-    count_positions<kPer, kT>(a.hslot, a.uvid, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, a.first,
+    count_positions<kPer, kT, kWhat>(a.hslot, a.uvid, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, a.first,
                               (int)blockIdx.x - nres, lds);
 }
 
@@ -893,13 +905,13 @@ __device__ __forceinline__ void plan_store(const Plan& pl, Ctr& ctr, int f) {
 // wavefronts, so large pipelined batches give them to the launch of the victims' count: see plan_and_assign.
 constexpr int kFoldThreads = 1 << 16;        // of them all, at most
 struct FoldArgs { int* cnt; const int* cnt_rep; int bins, nrep; int* tile_cnt; int folds; };
-struct BagArgs { const int64_t* offsets; int n_bags, n; int* pos2bag; int tally; };
+struct BagArgs { const int64_t* offsets; int n_bags, n; int* pos2bag; int64_t* kept; int tally; };
 
 // words: a word of LDS per thread
 template <int kT>
 __device__ __forceinline__ void fold_or_bags(const FoldArgs& fo, const BagArgs& bags, Ctr* ctr, int blk, int* words) {
   if (blk >= fo.folds) {
-    bags_of_positions(bags.offsets, bags.n_bags, bags.n, bags.pos2bag, bags.tally ? ctr : nullptr, blk - fo.folds, words);
+    bags_of_positions(bags.offsets, bags.n_bags, bags.n, bags.pos2bag, bags.kept, bags.tally ? ctr : nullptr, blk - fo.folds, words);
     return;
   }
   const int U = ctr->U;
@@ -1216,31 +1228,30 @@ __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict
   }
 }
 
-// Row per position of a batch that is not grouped (see rows_by_position in the host code).  kRecorded, and t here and below: the
-// step; where the counters are another step's, a graph has been launched that was recorded on this one: nothing to do.
-template <bool kRecorded>
-__global__ __launch_bounds__(256) void k_pos_rows(const int* __restrict__ inverse, const int* __restrict__ slot, int n, int C,
-                                                   int boff, int* __restrict__ pos_slot, const Ctr* ctr, int t) {
-  if (kRecorded && ctr->t != t) return;
+// Row per position of a batch that is not grouped, for the forward gather; 1024 positions per block.
+struct RowsArgs { const int *inverse, *slot; int n, C, boff; int* pos_slot; };
+__device__ __forceinline__ void rows_of_positions(const RowsArgs& a, int blk) {
   constexpr int kPer = 4;
-  const int base = blockIdx.x * 256 * kPer + (int)threadIdx.x;
+  const int base = blk * 256 * kPer + (int)threadIdx.x;
   int v[kPer], s[kPer];
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) v[j] = base + j * 256 < n ? inverse[base + j * 256] : -1;
+  for (int j = 0; j < kPer; ++j) v[j] = base + j * 256 < a.n ? a.inverse[base + j * 256] : -1;
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) s[j] = v[j] >= 0 ? slot[v[j]] : -1;
+  for (int j = 0; j < kPer; ++j) s[j] = v[j] >= 0 ? a.slot[v[j]] : -1;
 #pragma unroll
   for (int j = 0; j < kPer; ++j)
-    if (v[j] >= 0) pos_slot[base + j * 256] = s[j] >= C ? s[j] + boff : s[j];
+    if (v[j] >= 0) a.pos_slot[base + j * 256] = s[j] >= a.C ? s[j] + a.boff : s[j];
 }
+__global__ __launch_bounds__(256) void k_pos_rows(const RowsArgs a) { rows_of_positions(a, (int)blockIdx.x); }
 
 // The grouping of a batch that was prepared without it, when its gradient comes all the same: positions counted and
-// ranked, sums and bags, starts of the groups, the grouping pass.
+// ranked, sums and bags, starts of the groups, the grouping pass.  t: the step; where the counters are another step's, a
+// graph has been launched that was recorded on this one: nothing to do.
 template <int kPer, int kT>
 __global__ __launch_bounds__(kT) void k_count_late(const RankArgs a, const Ctr* ctr, int t) {
   __shared__ int lds[kHotBins];
   if (ctr->t != t) return;
-  count_positions<kPer, kT>(nullptr, nullptr, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, nullptr,
+  count_positions<kPer, kT, kCountLate>(a.hslot, nullptr, a.n, nullptr, a.cnt, a.cnt_rep, a.nrep, a.rank, nullptr,
                             (int)blockIdx.x, lds);
 }
 __global__ __launch_bounds__(256) void k_fold_late(Ctr* ctr, const FoldArgs fo, const BagArgs bags, int t) {
@@ -1266,7 +1277,7 @@ __global__ __launch_bounds__(256) void k_starts_late(const GroupArgs gr, const C
 }
 template <int kScatPer, int kT>
 __global__ __launch_bounds__(kT) void k_scatter_late(const ScatterArgs a, const Ctr* ctr, int t) {
-  if (ctr->t == t) scatter_positions<kScatPer, kT>(a, (int)blockIdx.x);
+  if (ctr->t == t) scatter_positions<kScatPer, kT, false>(a, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -211,6 +211,12 @@ __global__ __launch_bounds__(256) void k_swap_scatter(const SwapArgs a, int swap
   else scatter_positions<4, 256>(b, (int)blockIdx.x - swap_blocks);
 }
 
+// The same for a batch that is not grouped: the rows of its positions.
+__global__ __launch_bounds__(256) void k_swap_pos_rows(const SwapArgs a, int swap_blocks, const RowsArgs b) {
+  if ((int)blockIdx.x < swap_blocks) swap_rows(a, swap_blocks);
+  else rows_of_positions(b, (int)blockIdx.x - swap_blocks);
+}
+
 __global__ __launch_bounds__(256) void k_flush(const int64_t* __restrict__ slot_id,
                                                 const float4* __restrict__ cw,
                                                 const float4* __restrict__ ca, HostRows h, int d4,
@@ -314,26 +320,15 @@ __device__ __forceinline__ void split_chunk(unsigned ch, int d4, int sh, unsigne
   else { r = ch / (unsigned)d4; c = ch - r * (unsigned)d4; }
 }
 
-// kByVid (a batch that has not been grouped, see group_now in the host code): pos_slot holds the virtual id per position,
-// slot the slot per virtual id.
-template <bool kByVid>
-__device__ __forceinline__ int row_of(int x, const int* __restrict__ slot, int C, int boff) {
-  if (!kByVid) return x;
-  const int s = slot[x];
-  return s >= C ? s + boff : s;
-}
-
-template <bool kByVid>
 __global__ __launch_bounds__(256) void k_lookup_onehot(const int* __restrict__ pos_slot,
                                                         const float4* __restrict__ cw,
                                                         float4* __restrict__ out, int n_bags,
-                                                        int d4, int sh, int bpb, const int* __restrict__ slot, int C,
-                                                        int boff) {
+                                                        int d4, int sh, int bpb) {
   __shared__ int ls[kLookupBags];
   const int b0 = (int)blockIdx.x * bpb;          // bpb <= kLookupBags = block size
   {
     const int b = b0 + (int)threadIdx.x;
-    ls[threadIdx.x] = ((int)threadIdx.x < bpb && b < n_bags) ? row_of<kByVid>(pos_slot[b], slot, C, boff) : -1;
+    ls[threadIdx.x] = ((int)threadIdx.x < bpb && b < n_bags) ? pos_slot[b] : -1;
   }
   __syncthreads();
   int nb = n_bags - b0;
@@ -380,14 +375,11 @@ __global__ __launch_bounds__(256) void k_lookup_onehot(const int* __restrict__ p
 #endif
 constexpr int kBagUnroll = SFC_BAG_UNROLL;
 
-// kByVid: as in k_lookup_onehot; the virtual ids are fetched another kBagUnroll positions ahead.
-template <bool kByVid>
 __global__ __launch_bounds__(256) void k_lookup_bags(const int64_t* __restrict__ offsets,
                                                       const int* __restrict__ pos_slot,
                                                       const float4* __restrict__ cw,
                                                       float4* __restrict__ out, int n_bags,
-                                                      int d4, int G, int64_t n_ids, const int* __restrict__ slot, int C,
-                                                      int boff) {
+                                                      int d4, int G, int64_t n_ids) {
   const int lane = lane_id();
   const int g = lane / d4, c = lane - g * d4;
   const int64_t b = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * G + g;
@@ -396,15 +388,9 @@ __global__ __launch_bounds__(256) void k_lookup_bags(const int64_t* __restrict__
   int q = r.lo;
   const int e = r.hi;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-  int sl[kBagUnroll], sn[kBagUnroll], vn[kBagUnroll];
+  int sl[kBagUnroll], sn[kBagUnroll];
 #pragma unroll
   for (int k = 0; k < kBagUnroll; ++k) sl[k] = q + k < e ? pos_slot[q + k] : -1;
-  if (kByVid) {
-#pragma unroll
-    for (int k = 0; k < kBagUnroll; ++k) vn[k] = q + kBagUnroll + k < e ? pos_slot[q + kBagUnroll + k] : -1;
-#pragma unroll
-    for (int k = 0; k < kBagUnroll; ++k) sl[k] = sl[k] >= 0 ? row_of<kByVid>(sl[k], slot, C, boff) : -1;
-  }
   for (; q < e; q += kBagUnroll) {
     float4 v[kBagUnroll];
 #pragma unroll
@@ -414,10 +400,8 @@ __global__ __launch_bounds__(256) void k_lookup_bags(const int64_t* __restrict__
     }
 #pragma unroll
     for (int k = 0; k < kBagUnroll; ++k) {
-      const int qn = q + (kByVid ? 2 : 1) * kBagUnroll + k;
-      if (kByVid) sn[k] = vn[k] >= 0 ? row_of<kByVid>(vn[k], slot, C, boff) : -1;
-      const int x = qn < e ? pos_slot[qn] : -1;
-      if (kByVid) vn[k] = x; else sn[k] = x;
+      const int qn = q + kBagUnroll + k;
+      sn[k] = qn < e ? pos_slot[qn] : -1;
     }
 #pragma unroll
     for (int k = 0; k < kBagUnroll; ++k) {

@@ -1338,12 +1338,52 @@ def test_calls_recorded_on_a_step_that_is_not_grouped(n, bags, call):
         p.finish(); p.close()
 
 
+@pytest.mark.parametrize("side_stream", [True, False])
+@pytest.mark.parametrize("n,bags", [(6145, 0), (9000, 2000), (140_000, 9000), (270_000, 0)])
+def test_buffers_of_a_step_that_are_used_again(n, bags, side_stream):
+    # behind the fetch the lookup needs the offsets alone, and behind the lookup a gradient the ids and slots: a program
+    # may use the other buffers for something else, also with a cache that serves lookups (64 steps given up in a row)
+    V, D, nb = 12_000, 8, bags or n
+    p = Pair(V, D, C=9000, max_ids=n, max_bags=nb, side_stream=side_stream)
+    c, o = p.cache, p.orc
+    grad = si.grads(nb, D, 89, 0)
+    d_grad = grad.to(p.dev)
+
+    def load(t):
+        ids, off = si.zipf_ids(n, 1.05, V, 89, t), _bag_ends(n, bags, t) if bags else None
+        d_off = None if off is None else off.to(p.dev)
+        b = c.prepare(ids.to(p.dev), d_off); c.fetch_misses()
+        o.prepare(ids.numpy(), None if off is None else off.numpy()); o.fetch_misses()
+        b.inverse.zero_(); b.miss_vids.zero_()
+        return b, d_off
+
+    for t in range(2):
+        for k in range(64 if t else 0):
+            p.step(si.zipf_ids(40, 1.05, V, 90, k).numpy(), np.zeros((40, D), np.float32), update=False, check_state=False)
+        b, _ = load(3 * t)
+        b.slot.zero_(); b.unique_ids.zero_()
+        assert_close(c.lookup().cpu().numpy(), o.lookup(), "lookup")
+        c.discard()
+        for call in ("sum", "update"):
+            b, d_off = load(3 * t + 1 + (call == "update"))
+            want = o.lookup()
+            assert_close(c.lookup().cpu().numpy(), want, "lookup of a step with a gradient")
+            if bags:
+                d_off.zero_()
+            expect = o.backward_update(grad.numpy(), want_common_grad=True)
+            assert_close(c.segment_sum(d_grad)[:expect.shape[0]].cpu().numpy(), expect, "common gradient")
+            c.backward_update(d_grad)
+            for k in range(64 if t else 0):
+                p.step(si.zipf_ids(40, 1.05, V, 90, k).numpy(), np.zeros((40, D), np.float32), update=False, check_state=False)
+    p.finish(); p.close()
+
+
 @pytest.mark.parametrize("call", ["sum", "static", "update"])
 @pytest.mark.parametrize("n,bags", [(7000, 0), (9000, 2000), (1 << 17, 30_000)])
 def test_time_of_what_a_serving_cache_launches_later(n, bags, call):
-    # device timing: the rows of the positions (bags from 2^17 ids on) and a grouping that is made up for are added to the
-    # prepare's time and are no calls of their own; the sum that creates no events is timed nowhere.  A batch after the
-    # gradient is grouped by its prepare: nothing to make up for.
+    # device timing: the rows of the positions and a grouping that is made up for are added to the prepare's time and are
+    # no calls of their own; the sum that creates no events is timed nowhere.  A batch after the gradient is grouped by its
+    # prepare: nothing to make up for.
     V, D, nb = 12_000, 8, bags or n
     p = Pair(V, D, C=V, max_ids=n, max_bags=nb, side_stream=False)
     c = p.cache
@@ -1368,7 +1408,7 @@ def test_time_of_what_a_serving_cache_launches_later(n, bags, call):
         assert ms > 0 and calls == 1
         c.fetch_misses()
         ms, calls = prepare()
-        assert calls == 0 and (ms > 0) == (not late or n >= 1 << 17), ms
+        assert calls == 0 and ms > 0
         gradient()
         ms, calls = prepare()
         assert calls == 0 and (ms > 0) == (late and call != "static"), ms
