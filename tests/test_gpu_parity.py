@@ -439,9 +439,9 @@ def test_host_copies_at_the_limits_of_the_separate_blocks(D, optimizer, C, sizes
 
 
 @pytest.mark.parametrize("lookahead", [1, 3])
-def test_pipelined_batches_on_one_and_on_two_prepare_streams(lookahead):
-    # pipelined, the unique passes take a stream of their own between 2^18 and 2^20 ids only: steps of
-    # either kind follow each other, a one-block batch among them
+def test_pipelined_batches_either_side_of_where_the_passes_change(lookahead):
+    # at 2^18 ids the counting and grouping passes change shape, at 2^20 the sums of the positions go to another launch:
+    # batches on either side follow each other on the one prepare stream, a one-block batch among them
     V, D = 300_000, 4
     sizes = [270_000, 250_000, 300_000, 1_100_000, 280_000, 4000, 265_000, 1_100_000, 262_144, 262_143]
     p = Pair(V, D, C=250_000, max_ids=1_100_000, lookahead=lookahead)
@@ -506,18 +506,18 @@ class _DeletedEntries:
         return level
 
 
-def test_hashed_index_rebuilt_between_prepares_on_one_and_on_two_streams():
-    # the rebuild of a hashed index runs inside the unique passes of one-stream prepares and as kernels of its own
-    # where those passes have a stream to themselves or the batch is prepared by one block (or empty): whenever one
-    # is due, by the rule replayed here, the next batch is of a form that has not had one yet
+def test_hashed_index_rebuilt_between_prepares_of_every_form():
+    # the rebuild of a hashed index runs inside the unique passes (below and from 2^18 ids on) and as kernels of its own
+    # where the batch is prepared by one block (or empty): whenever one is due, by the rule replayed here, the next batch
+    # is of a form that has not had one yet
     V, D, C, max_ids, U = 1_000_000, 4, 150_000, 270_000, 45_000
     table = _DeletedEntries(4 * (C + max_ids))
     orc = Oracle(C, D, np.zeros((V, D), np.float32), np.ones((V, D), np.float32), lookahead=1)
     rng = np.random.default_rng(512)
-    forms = {"one stream": 60_000, "two streams": 265_000, "one block": 5000, "empty": 0}
-    to_do, had, bs = ["two streams", "one stream", "one block", "empty", "two streams"], [], []
+    forms = {"below 2^18": 60_000, "from 2^18": 265_000, "one block": 5000, "empty": 0}
+    to_do, had, bs = ["from 2^18", "below 2^18", "one block", "empty", "from 2^18"], [], []
     while to_do or table.due:
-        form = to_do.pop(0) if table.due else ["one stream", "two streams"][len(bs) % 2]
+        form = to_do.pop(0) if table.due else ["below 2^18", "from 2^18"][len(bs) % 2]
         if table.due:
             had.append(form)
         n = forms[form]
@@ -528,7 +528,7 @@ def test_hashed_index_rebuilt_between_prepares_on_one_and_on_two_streams():
         level = table.step(pr.evict_ids, pr.unique_ids[pr.miss_vids[pr.slot[pr.miss_vids] < C]])
         # (inserts side by side may share out the deleted entries differently)
         assert abs(level - table.size // 8) > table.size // 8 // 50, (len(bs), level, table.size // 8)
-    assert had == ["two streams", "one stream", "one block", "empty", "two streams"]
+    assert had == ["from 2^18", "below 2^18", "one block", "empty", "from 2^18"]
     p = Pair(V, D, C=C, max_ids=max_ids, lookahead=1, index_kind=HASHED)
     p.run_pipelined(bs, False)
     p.close()
@@ -1192,6 +1192,38 @@ def test_batches_of_a_cache_that_serves_lookups(n, bags, C, index_kind):
     expect = p.orc.backward_update(grad, want_common_grad=True)
     assert_close(out[:expect.shape[0]].cpu().numpy(), expect, "common gradient")
     c.backward_update(d_grad)
+    p.finish(); p.close()
+
+
+@pytest.mark.parametrize("n,bags,D", [(270_000, 0, 32), ((1 << 22) + 3, 0, 4), ((1 << 22) + 3, 300_000, 4)])
+def test_large_batches_of_a_cache_that_serves_lookups(n, bags, D):
+    # the late grouping in the shapes of 2^18 and 2^22 ids on, one-hot and in bags, and lookups of 32 MB and more; device
+    # timing tells that the grouping was left out: what makes up for it is added to the prepare's time
+    V, C, nb = 60_000, 30_000, bags or n
+    p = Pair(V, D, C=C, max_ids=n, max_bags=nb)
+    c, o = p.cache, p.orc
+    for k in range(64):
+        p.step(si.zipf_ids(40, 1.05, V, 92, k).numpy(), np.zeros((40, D), np.float32), update=False, check_state=False)
+    grad = si.grads(nb, D, 92, 0)
+    d_grad = grad.to(p.dev)
+    p.sfc.sfc_profile_enable(c.h, 1)
+    for t in range(3):
+        ids, off = si.zipf_ids(n, 1.05, V, 93, t).numpy().copy(), _bag_ends(n, bags, t) if bags else None
+        ids[::997] = V + 5
+        c.prepare(torch.from_numpy(ids).to(p.dev), None if off is None else off.to(p.dev)); c.fetch_misses()
+        pr = o.prepare(ids, None if off is None else off.numpy()); o.fetch_misses()
+        assert np.array_equal(c.inverse[:n].cpu().numpy(), pr.inverse)
+        assert_close(c.lookup().cpu().numpy(), o.lookup(), "lookup of step %d" % t)
+        if t == 0:
+            c.discard()
+            continue
+        p.sfc.sfc_profile_read(c.h)
+        common = c.segment_sum(d_grad)
+        ms, calls = p.sfc.sfc_profile_read(c.h)["prepare"]
+        assert calls == 0 and (ms > 0) == (t == 1), ms
+        expect = o.backward_update(grad.numpy(), want_common_grad=True)
+        assert_close(common[:expect.shape[0]].cpu().numpy(), expect, "common gradient of step %d" % t)
+        c.backward_update(d_grad)
     p.finish(); p.close()
 
 
