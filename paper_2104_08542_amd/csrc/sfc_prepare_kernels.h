@@ -1148,20 +1148,26 @@ __device__ __forceinline__ void publish(HostStatus* h, int lane, int t, int U, i
 struct GroupArgs {
   const int* cnt; int* cnt_rep; int* cur_rep; int bins, nrep; const int* tile_cnt; int64_t* grp; int2* cold_pay;
 };
-// Virtual id v (below U) has nv positions, which start at off: where its group and the copies of a hot bin start.
-__device__ __forceinline__ void group_start(const GroupArgs& g, int v, int nv, int off) {
-  g.grp[v] = ((int64_t)nv << 32) | (uint32_t)off;
-  g.cold_pay[v] = make_int2(-1, -1);            // the grouping pass fills in the cold groups' rows
-  if (v < g.bins) {                             // one group start per copy of a hot bin; copies back to zero
+// Virtual id v (below U) has nv positions, which start at off: where its group and the copies of a hot bin start.  (The
+// arrays as restricted pointers: read through the struct, each copy's count waited for the store of the one before,
+// 11.1 us instead of 8.5 for the assign pass at 65536 x 39 ids.)
+__device__ __forceinline__ void group_start(int* __restrict__ cnt_rep, int* __restrict__ cur_rep, int bins, int nrep,
+                                            int64_t* __restrict__ grp, int2* __restrict__ cold_pay, int v, int nv, int off) {
+  grp[v] = ((int64_t)nv << 32) | (uint32_t)off;
+  cold_pay[v] = make_int2(-1, -1);              // the grouping pass fills in the cold groups' rows
+  if (v < bins) {                               // one group start per copy of a hot bin; copies back to zero
     int at = off;
 #pragma unroll 8
-    for (int r = 0; r < g.nrep; ++r) {
-      const int c = g.cnt_rep[r * kHotBins + v];
-      g.cur_rep[r * kHotBins + v] = at;
+    for (int r = 0; r < nrep; ++r) {
+      const int c = cnt_rep[r * kHotBins + v];
+      cur_rep[r * kHotBins + v] = at;
       at += c;
-      g.cnt_rep[r * kHotBins + v] = 0;
+      cnt_rep[r * kHotBins + v] = 0;
     }
   }
+}
+__device__ __forceinline__ void group_start(const GroupArgs& g, int v, int nv, int off) {
+  group_start(g.cnt_rep, g.cur_rep, g.bins, g.nrep, g.grp, g.cold_pay, v, nv, off);
 }
 
 __global__ __launch_bounds__(256) void k_assign_misses(const int64_t* __restrict__ unique_ids, const GroupArgs gr,
