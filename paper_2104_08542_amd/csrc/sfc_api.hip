@@ -217,7 +217,8 @@ struct sfc_cache {
   int* cur_rep = nullptr;                       // [kHotRep, kHotBins] group cursors of the lowest virtual ids, one per copy
   int* n_unique = nullptr;                      // unique ids of the step whose unique passes ran last
   int* pos2bag = nullptr;                       // [max_ids] multi-hot: bag of each position
-  int64_t* bag_ends = nullptr;                  // [max_bags + 1] lookahead 0: the offsets of an ungrouped step
+  int* vids = nullptr;                          // [max_ids] lookahead 0: virtual id of each position of an ungrouped step
+  int64_t* bag_ends = nullptr;                  // [max_bags + 1] ... and its offsets
   int* tile_cnt = nullptr;                      // [max_ids / kVidTile + 1]
   int* tile_reuse = nullptr;                    // [max_ids / kVidTile + 1] deleted index entries reused per tile
   int* n_invalid = nullptr;                     // out-of-range positions of the step being prepared
@@ -627,9 +628,9 @@ int group_now(sfc_cache* c, StepCtx* x, bool timed) {
   const SortGeom& sg = x->sg;
   const Ctr* const ctr = x->ctr;
   fill<int>(s, c->cnt, n, 0);
-  // (all of it from what the prepare has kept: the caller's ids, virtual ids and offsets may be gone; ranks where the
-  // virtual ids of the table entries were)
-  const RankArgs rank{c->hslot, nullptr, n, nullptr, c->cnt, c->cnt_rep, sg.nrep, c->uvid, nullptr};
+  // (all of it from what the prepare has kept: the caller's virtual ids and offsets may be gone; ranks where the table
+  // entries were)
+  const RankArgs rank{nullptr, nullptr, n, c->vids, c->cnt, c->cnt_rep, sg.nrep, c->hslot, nullptr};
   auto count = sg.shift == 10 ? k_count_late<1, 1024> : sg.shift == 12 ? k_count_late<8, 512> : k_count_late<8, 1024>;
   hipLaunchKernelGGL(count, dim3(sg.blocks), dim3(sg.shift == 12 ? 512 : 1024), 0, s, rank, ctr, x->t);
   const FoldArgs fo{c->cnt, c->cnt_rep, sg.bins, sg.nrep, c->tile_cnt, grid_for(n, 256, kFoldThreads / 256)};
@@ -639,7 +640,7 @@ int group_now(sfc_cache* c, StepCtx* x, bool timed) {
   hipLaunchKernelGGL(k_starts_late, dim3(grid_for(n, kVidTile, kGridCap)), dim3(256), 0, s, group_args(c, x, true), ctr, x->t);
   auto scat = sg.shift == 10 ? k_scatter_late<4, 256> : sg.shift == 12 ? k_scatter_late<8, 512> : k_scatter_late<8, 1024>;
   ScatterArgs sc = scatter_args(c, x);
-  sc.inverse = c->hslot; sc.rank_slot = c->uvid;
+  sc.inverse = c->vids; sc.rank_slot = c->hslot;
   hipLaunchKernelGGL(scat, dim3(sg.blocks), dim3(sg.shift == 10 ? 256 : sg.shift == 12 ? 512 : 1024), 0, s, sc, ctr, x->t);
   return timed ? prof_end(c, P_PREPARE, s, &ep) : SFC_OK;
 }
@@ -844,7 +845,7 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
     if ((rc = dalloc(c, &c->cnt, c->max_ids))) goto bad;
     if ((rc = dalloc(c, &c->n_unique, 1))) goto bad;
     if ((rc = dalloc(c, &c->pos2bag, c->max_ids))) goto bad;
-    if (nctx == 1 && (rc = dalloc(c, &c->bag_ends, c->max_bags + 1))) goto bad;
+    if (nctx == 1 && ((rc = dalloc(c, &c->vids, c->max_ids)) || (rc = dalloc(c, &c->bag_ends, c->max_bags + 1)))) goto bad;
     if ((rc = dalloc(c, &c->tile_cnt, c->max_ids / kVidTile + 2))) goto bad;
     if ((rc = dalloc(c, &c->tile_reuse, c->max_ids / kVidTile + 2))) goto bad;
     if ((rc = dalloc(c, &c->age_hist, (int64_t)kAgeBins))) goto bad;
@@ -996,15 +997,13 @@ int sfc_prepare(sfc_cache* c, const int64_t* d_ids, int64_t n_ids, const int64_t
   } else if (!small) {
     fill<int>(s, c->n_unique, 1, 0);
   }
-  const RankArgs rank{c->hslot, c->uvid, n, d_inverse, c->cnt, c->cnt_rep, sg.nrep, x->pos_slot, c->first};
+  const RankArgs rank{c->hslot, c->uvid, n, d_inverse, x->ungrouped ? nullptr : c->cnt, c->cnt_rep, sg.nrep,
+                      x->ungrouped ? c->vids : x->pos_slot, c->first};
   const ResolveArgs res{d_unique_ids, c->vid_hslot, c->utab, c->wide ? 1 : 0, c->index, c->hi, c->dmap, c->stamp,
                         c->hist, x->t, d_slot, c->tile_miss, c->age_hist, x->ctr,
                         start_inside ? (const Ctr*)prev->ctr : (const Ctr*)nullptr, (const int*)c->n_unique, c->n_invalid};
   auto rank_resolve = sg.shift == 10 ? k_rank_resolve<1, 1024> : sg.shift == 12 ? k_rank_resolve<8, 512>
                                                                               : k_rank_resolve<8, 1024>;
-  if (x->ungrouped)
-    rank_resolve = sg.shift == 10 ? k_rank_resolve<1, 1024, kVidsAlone> : sg.shift == 12 ? k_rank_resolve<8, 512, kVidsAlone>
-                                                                                         : k_rank_resolve<8, 1024, kVidsAlone>;
   const int rt = sg.shift == 12 ? 512 : 1024, nres = small ? 0 : grid_for(n, rt, kResolveThreads / rt);
   const int ncount = small || n == 0 ? 0 : sg.blocks;
   // from here on behind the whole prepare of the previous step: the step's counters start from

@@ -11,7 +11,6 @@
 // sum, nothing else; see the segment-sum kernels for what that means for the results.
 #pragma once
 #include "sfc_device.h"
-#include <type_traits>
 
 namespace sfc {
 
@@ -452,36 +451,38 @@ inline SortGeom small_geom(int64_t n) {
   return g;
 }
 
-// A batch that is not grouped (see group_now in the host code) has its virtual ids alone, which are kept where the table
-// entries were; when it is grouped after all, its positions are counted from there.
-enum { kCountAll, kVidsAlone, kCountLate };
-template <int kPer, int kT, int kWhat>
-__device__ __forceinline__ void count_positions(std::conditional_t<kWhat == kVidsAlone, int, const int>* __restrict__ hslot,
-                                                const int* __restrict__ uvid, int n,
+// cnt == nullptr (a batch that is not grouped, see group_now in the host code): the virtual ids alone, kept in rank as well.
+// hslot == nullptr (k_count_late): they are there already, in `inverse`.  (At run time: as template arguments these made the counting
+// 1.3 us slower at 65536 x 39 positions.)
+template <int kPer, int kT>
+__device__ __forceinline__ void count_positions(const int* __restrict__ hslot, const int* __restrict__ uvid, int n,
                                                 int* __restrict__ inverse, int* cnt, int* cnt_rep, int nrep,
                                                 int* __restrict__ rank, unsigned* __restrict__ first, int blk,
                                                 int* lh) {
   // the marks of first appearances have been read: all zero again for the next batch
   static_assert(kPer <= 32 && kT * kPer % 32 == 0, "whole words of marks per block");
-  if (kWhat != kCountLate && (int)threadIdx.x < kT * kPer / 32 && blk * kT * kPer + (int)threadIdx.x * 32 < n)
+  if (hslot && (int)threadIdx.x < kT * kPer / 32 && blk * kT * kPer + (int)threadIdx.x * 32 < n)
     first[blk * (kT * kPer / 32) + threadIdx.x] = 0;
-  if (kWhat != kVidsAlone)
+  if (cnt)
     for (int i = threadIdx.x; i < kHotBins; i += kT) lh[i] = 0;
   const int base = blk * kT * kPer;
   int hv[kPer], vv[kPer], rr[kPer];
 #pragma unroll
   for (int j = 0; j < kPer; ++j) {              // kPer loads in flight per level of indirection
     const int p = base + j * kT + (int)threadIdx.x;
-    hv[j] = p < n ? hslot[p] : -1;
+    hv[j] = p < n ? (hslot ? hslot[p] : inverse[p]) : -1;
   }
 #pragma unroll
-  for (int j = 0; j < kPer; ++j) vv[j] = kWhat != kCountLate && hv[j] >= 0 ? uvid[hv[j]] : hv[j];
-  if constexpr (kWhat == kVidsAlone) {
+  for (int j = 0; j < kPer; ++j) vv[j] = hslot && hv[j] >= 0 ? uvid[hv[j]] : hv[j];
+  if (hslot) {
 #pragma unroll
-    for (int j = 0; j < kPer; ++j) {
-      const int p = base + j * kT + (int)threadIdx.x;
-      if (vv[j] >= 0) { inverse[p] = vv[j]; hslot[p] = vv[j]; }
-    }
+    for (int j = 0; j < kPer; ++j)
+      if (vv[j] >= 0) inverse[base + j * kT + (int)threadIdx.x] = vv[j];
+  }
+  if (!cnt) {
+#pragma unroll
+    for (int j = 0; j < kPer; ++j)
+      if (vv[j] >= 0) rank[base + j * kT + (int)threadIdx.x] = vv[j];
     return;
   }
   __syncthreads();
@@ -489,7 +490,6 @@ __device__ __forceinline__ void count_positions(std::conditional_t<kWhat == kVid
   for (int j = 0; j < kPer; ++j) {
     const int v = vv[j];
     if (v >= 0) {
-      if (kWhat == kCountAll) inverse[base + j * kT + (int)threadIdx.x] = v;
       rr[j] = v < kHotBins ? atomicAdd(&lh[v], 1) : atomicAdd(&cnt[v], 1);
     }
   }
@@ -812,14 +812,14 @@ __device__ __forceinline__ void resolve_ids(const int64_t* __restrict__ unique_i
 // 1.28e6 uniform ones 26.7 + 60.8 / 77.5, 8.9e6 in bags 146 + 48 / 178: what is saved is start-up and drain, the random
 // accesses of the two add up.
 struct RankArgs {
-  int* hslot; const int* uvid; int n; int* inverse; int* cnt; int* cnt_rep; int nrep; int* rank; unsigned* first;
+  const int* hslot; const int* uvid; int n; int* inverse; int* cnt; int* cnt_rep; int nrep; int* rank; unsigned* first;
 };
 struct ResolveArgs {
   const int64_t* unique_ids; const int* vid_hslot; uint64_t* utab; int wide;
   const IdxEntry* index; uint32_t hi; const int* dmap; int *stamp, *hist; int t;
   int *slot, *tile_miss, *age_hist; Ctr* ctr; const Ctr* prev; const int* n_unique; int* n_invalid;
 };
-template <int kPer, int kT, int kWhat = kCountAll>
+template <int kPer, int kT>
 __global__ __launch_bounds__(kT) void k_rank_resolve(const RankArgs a, const ResolveArgs b, int nres) {
   __shared__ int lds[kHotBins];
   static_assert(kHotBins >= kAgeBins + kT / kWave, "the LDS of the counting blocks holds that of the resolving ones");
@@ -827,7 +827,7 @@ __global__ __launch_bounds__(kT) void k_rank_resolve(const RankArgs a, const Res
     resolve_ids<kT>(b.unique_ids, b.vid_hslot, b.utab, b.wide, b.index, b.hi, b.dmap, b.stamp, b.hist, b.t, b.slot,
                     b.tile_miss, b.age_hist, b.ctr, b.prev, b.n_unique, b.n_invalid, (int)blockIdx.x, nres, lds);
   else
-    count_positions<kPer, kT, kWhat>(a.hslot, a.uvid, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, a.first,
+    count_positions<kPer, kT>(a.hslot, a.uvid, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, a.first,
                               (int)blockIdx.x - nres, lds);
 }
 
@@ -1257,7 +1257,7 @@ template <int kPer, int kT>
 __global__ __launch_bounds__(kT) void k_count_late(const RankArgs a, const Ctr* ctr, int t) {
   __shared__ int lds[kHotBins];
   if (ctr->t != t) return;
-  count_positions<kPer, kT, kCountLate>(a.hslot, nullptr, a.n, nullptr, a.cnt, a.cnt_rep, a.nrep, a.rank, nullptr,
+  count_positions<kPer, kT>(nullptr, nullptr, a.n, a.inverse, a.cnt, a.cnt_rep, a.nrep, a.rank, nullptr,
                             (int)blockIdx.x, lds);
 }
 __global__ __launch_bounds__(256) void k_fold_late(Ctr* ctr, const FoldArgs fo, const BagArgs bags, int t) {
