@@ -87,10 +87,10 @@ bool capturing(hipStream_t s) {
 // behind a step's Host copies in a queue waits for hundreds of microseconds: with the prepares in the queue of the main or the
 // side stream a step takes half as long again.  No call tells a stream's queue, so a few candidates are tried when the cache
 // is created: a kernel that waits for a moment on the one stream, an empty one on the other.  us a step of one cache that
-// is created behind other streams, four times, the first stream that comes / this way: 65536 x 39 ids of dim 32 with lookahead
-// 2 495, 738, 756, 495 / 491, 494, 494, 739 (there the caller's own two streams share a queue), 16384 x 39 of dim 16 458, 461, 319,
-// 353 / 277, 274, 273, 274, 8192 x 26 of dim 128 119, 170, 168, 124 / 116, 116, 117, 117.  (One stream for all caches of a main
-// stream: three caches in turn 456 to 704 us at 65536 x 39, 589 to 655 this way.)
+// is created behind 0 to 3 other streams, the first stream that comes / this way: 65536 x 39 ids of dim 32 with lookahead 2 501, 518,
+// 737, 500 / 495, 498, 736, 496, 8192 x 26 of dim 128 164, 168, 127, 131 / 127, 163, 124, 122.  (In the two slow ones main and side stream
+// share a queue, which this choice cannot change.  It is made once: a stream that is made later may still land in the queue.  One stream for
+// all caches of a main stream: three caches in turn 456 to 704 us at 65536 x 39, 589 to 655 this way.)
 __global__ void k_hold(long long ticks) {
   const long long t0 = wall_clock64();
   for (int i = 0; i < (1 << 16) && wall_clock64() - t0 < ticks; ++i) __builtin_amdgcn_s_sleep(8);
@@ -798,7 +798,8 @@ int sfc_cache_create(const sfc_config* cfg, sfc_cache** out) {
   // of microseconds.  A second stream, for the unique passes of 2^18 to 2^20 ids beside the rest of the previous prepare,
   // against this one, us a step of one cache / of three in turn: 300e3 ids of dim 16 with lookahead 1 135 -> 114 / 137 -> 108, 639e3
   // 335 -> 313 / 347 -> 325, with lookahead 2 272 -> 272 / 346 -> 326, hashed 277 -> 286 / 365 -> 341, 950e3 398 -> 404 / 466 -> 460;
-  // 700e3 in bags of dim 32 145 -> 123 / 128 -> 129.
+  // 700e3 in bags of dim 32 145 -> 123 / 128 -> 129.  With caches of 1e6 rows of 1e7, lookahead 2: 639e3 152 -> 124, hashed 165 -> 125, 950e3
+  // 404 -> 402 (three of four orders of creation; 545 -> 402 in the other).
   c->prep = cfg->lookahead == 0 ? c->st : c->side;
   if (cfg->lookahead >= 1 && cfg->policy != SFC_POLICY_PREFETCH) {
     if ((e = choose_prep_stream(c->st, c->side, &c->prep)) != hipSuccess) {
